@@ -74,3 +74,24 @@ def test_invalid_code_gives_nan_and_argument_errors(ctx):
     with pytest.raises(binding.IdkmError):
         ctx.pack_codes(torch.zeros(4, dtype=torch.int32).cuda(), 2000)
     assert ctx.pack_codes(torch.zeros(0, dtype=torch.int32).cuda(), 4).shape[0] == 0
+
+
+@pytest.mark.parametrize("offset", [0, 1])          # floats past a 16-byte boundary: quads of four floats, or single rows
+@pytest.mark.parametrize("d", [1, 2, 3, 4, 8, 12])
+@pytest.mark.parametrize("m,k", [(1, 2), (3, 1024), (5, 5), (255, 3), (1023, 16), (2_101_251, 1000)])
+def test_unpack_of_every_row_length_and_remainder(ctx, m, k, d, offset):
+    """Bit-exact rows for every split of the output into 16-byte stores: remainders behind the last quad, codes that
+    straddle two and three words (10 bits), grids that go round more than once, codebooks beyond the LDS copy."""
+    if m > 1_000_000 and d > 4:
+        m //= 8
+    rng = np.random.default_rng(m + 7 * k + d)
+    a = rng.integers(0, k, size=m).astype(np.int32)
+    Cb = torch.from_numpy(rng.standard_normal((k, d)).astype(np.float32)).cuda()
+    words = ctx.pack_codes(torch.from_numpy(a).cuda(), k)
+    buf = torch.full((m * d + offset + 1,), 7.0, dtype=torch.float32, device="cuda")
+    st = ctx._lib.idkm_unpack_quantize(ctx._h, words.data_ptr(), m, Cb.data_ptr(), k, d, buf.data_ptr() + 4 * offset,
+                                       torch.cuda.current_stream().cuda_stream)
+    assert st == binding.IDKM_OK
+    got = buf.cpu().numpy()
+    assert np.array_equal(got[offset:-1].reshape(m, d).view(np.uint32), Cb.cpu().numpy()[a].view(np.uint32))
+    assert got[-1] == 7.0 and (offset == 0 or got[0] == 7.0)
