@@ -34,6 +34,10 @@ struct PersistFns {
 };
 // Persistent forward / backward solve for the lane<->vector family; empty if K (D+1) > 32.
 PersistFns persist_kernel(int K, int D, int dist, bool bwd);
+// The same for a codebook of K/2 < k < K codewords in the kernels for K codewords (K in {4,8,16}); teams of one, or
+// with the two-level exchange, only.
+PersistFns persist_kernel_ragged_0(int K, int D, bool bwd);
+PersistFns persist_kernel_ragged_1(int K, int D, bool bwd);
 // The same for a layer that does not fit the chip's LDS: W (and dL/dWq) are read from memory in every pass, no
 // dynamic LDS; single-problem launch form only.
 PersistFns persist_kernel_global(int K, int D, int dist, bool bwd);

@@ -367,6 +367,60 @@ constexpr size_t LANE_BUF1_WORDS = (size_t)2 * PT * 1536;          // k (d+1) <=
 constexpr size_t LANE_BUF2_WORDS = (size_t)2 * (1024 + 512);       // k d + k
 
 
+// The lane<->vector family's part of plan_persistent.
+bool plan_small(idkm_ctx* ctx, bool bwd, PersistPlan* pp, const void* dwq) {
+    const int k = ctx->k, d = ctx->d;
+    const int64_t m = ctx->m;
+    // A codebook whose size is not a power of two runs in the kernels for the next one, the surplus codewords' weights held
+    // at zero: 512,000 scalar weights under three codewords (23 evaluations, 56 (dF/dC)^T passes) take 333 us there and
+    // 3117 in the lane<->codeword kernels, which use 3 of 64 lanes and a 6-step wavefront sum per vector (28.7 us per
+    // evaluation, 42 per pass).  These kernels know the two-level exchange only; without it, and where the tile does not
+    // fit, the lane<->codeword kernels stay.
+    const bool ragged = k >= 3 && k < 16 && !pow2(k);
+    const int K = pow2_at_least(k);
+    if (k < 2 || k > 16 || d > 4 || K * (d + 1) > XLINE || (ragged && !ctx->tree_exchange)) return false;
+    const PersistFns fs = !ragged ? persist_kernel(k, d, ctx->dist, bwd)
+                          : ctx->dist == DIST_L2 ? persist_kernel_ragged_0(K, d, bwd)
+                                                 : persist_kernel_ragged_1(K, d, bwd);
+    pp->fn = fs.one;
+    pp->fn_batch = fs.batch;
+    if (!pp->fn) return false;
+    pp->threads = PT;
+    pp->lane = false;
+    const int64_t chunk = (int64_t)ctx->min_vec_per_thread * PT;
+    int64_t g = (m + chunk - 1) / chunk;  // a few vectors per thread before adding workgroups
+    // up to 16 vectors per thread one workgroup alone is faster (measured: 2.7 us per pass at m = 4096 against 3.7):
+    // it needs no exchange through memory
+    if (m <= (int64_t)16 * PT) g = 1;
+    if (g < 1) g = 1;
+    // (a team of 2 to 7 workgroups would take the one-level exchange; 8 smaller workgroups take the two-level one)
+    if (ctx->tree_exchange && g > 1 && g < DIES) g = DIES;
+    if (g > ctx->num_cu) g = ctx->num_cu;
+    if (g > PT) g = PT;  // a reducer reads one workgroup per thread
+    int64_t per = (m + g - 1) / g;
+    per = (per + 3) / 4 * 4;
+    const size_t lds = (size_t)per * d * sizeof(float) * (bwd ? 2 : 1);
+    pp->grid = (int)((m + per - 1) / per);
+    pp->per = (int)per;
+    pp->lds = lds;
+    if (ragged && (lds > ctx->tile_limit || (pp->grid > 1 && pp->grid < TREE_MIN_G))) return false;
+    if (lds > ctx->tile_limit) {
+        // the layer does not fit on chip: the same solve with W (and dL/dWq) read from memory in every pass.  Not
+        // inside a batched launch (such a layer fills the device on its own), and only from 16-byte aligned tensors.
+        const PersistFns fg = persist_kernel_global(k, d, ctx->dist, bwd);
+        const bool aligned = (reinterpret_cast<uintptr_t>(ctx->W) & 15u) == 0 &&
+                             (!bwd || (dwq && (reinterpret_cast<uintptr_t>(dwq) & 15u) == 0));
+        // Measured on a 16.8 M-weight layer this form is within 5 % of the stream path (forward 28.3 against 29.9 us
+        // per evaluation, (dF/dC)^T pass 41.3 against 39.7): both are bound by the same arithmetic, so the default
+        // keeps the stream path and this one serves callers that ask for the persistent path (one launch per solve).
+        if (!fg.one || ctx->sink || !aligned || ctx->path != IDKM_PATH_PERSISTENT) return false;
+        pp->fn = fg.one;
+        pp->fn_batch = nullptr;
+        pp->lds = 0;
+    }
+    return true;
+}
+
 // Can (m, k, d) run as one persistent launch with `tiles` resident tensors (1: W; 2: W and dL/dWq)?
 // matrix_ok: the matrix-core kernels may serve the call (every pass of both energies has a matrix-core form).
 // dwq: the backward's upstream gradient (a layer too large for LDS is streamed from memory with 16-byte loads, which
@@ -375,6 +429,7 @@ bool plan_persistent(idkm_ctx* ctx, bool bwd, PersistPlan* pp, bool matrix_ok = 
     if (!ctx->coop || ctx->num_cu < 1) return false;
     const int k = ctx->k, d = ctx->d;
     const int64_t m = ctx->m;
+    if (plan_small(ctx, bwd, pp, dwq)) return true;
     if (!(k >= 2 && k <= 16 && pow2(k) && d <= 4)) {
         // lane<->codeword family
         int kpl = (k + 63) / 64, p = 1;
@@ -421,44 +476,7 @@ bool plan_persistent(idkm_ctx* ctx, bool bwd, PersistPlan* pp, bool matrix_ok = 
         pp->lane = true;
         return true;
     }
-    if (k * (d + 1) > XLINE) return false;
-    const PersistFns fs = persist_kernel(k, d, ctx->dist, bwd);
-    pp->fn = fs.one;
-    pp->fn_batch = fs.batch;
-    if (!pp->fn) return false;
-    pp->threads = PT;
-    pp->lane = false;
-    const int64_t chunk = (int64_t)ctx->min_vec_per_thread * PT;
-    int64_t g = (m + chunk - 1) / chunk;  // a few vectors per thread before adding workgroups
-    // up to 16 vectors per thread one workgroup alone is faster (measured: 2.7 us per pass at m = 4096 against 3.7):
-    // it needs no exchange through memory
-    if (m <= (int64_t)16 * PT) g = 1;
-    if (g < 1) g = 1;
-    // (a team of 2 to 7 workgroups would take the one-level exchange; 8 smaller workgroups take the two-level one)
-    if (ctx->tree_exchange && g > 1 && g < DIES) g = DIES;
-    if (g > ctx->num_cu) g = ctx->num_cu;
-    if (g > PT) g = PT;  // a reducer reads one workgroup per thread
-    int64_t per = (m + g - 1) / g;
-    per = (per + 3) / 4 * 4;
-    const size_t lds = (size_t)per * d * sizeof(float) * (bwd ? 2 : 1);
-    pp->grid = (int)((m + per - 1) / per);
-    pp->per = (int)per;
-    pp->lds = lds;
-    if (lds > ctx->tile_limit) {
-        // the layer does not fit on chip: the same solve with W (and dL/dWq) read from memory in every pass.  Not
-        // inside a batched launch (such a layer fills the device on its own), and only from 16-byte aligned tensors.
-        const PersistFns fg = persist_kernel_global(k, d, ctx->dist, bwd);
-        const bool aligned = (reinterpret_cast<uintptr_t>(ctx->W) & 15u) == 0 &&
-                             (!bwd || (dwq && (reinterpret_cast<uintptr_t>(dwq) & 15u) == 0));
-        // Measured on a 16.8 M-weight layer this form is within 5 % of the stream path (forward 28.3 against 29.9 us
-        // per evaluation, (dF/dC)^T pass 41.3 against 39.7): both are bound by the same arithmetic, so the default
-        // keeps the stream path and this one serves callers that ask for the persistent path (one launch per solve).
-        if (!fg.one || ctx->sink || !aligned || ctx->path != IDKM_PATH_PERSISTENT) return false;
-        pp->fn = fg.one;
-        pp->fn_batch = nullptr;
-        pp->lds = 0;
-    }
-    return true;
+    return false;
 }
 
 idkm_status launch_persistent(idkm_ctx* ctx, const PersistPlan& pp, Args& a, PArgs pa, unsigned int exchanges,
@@ -1009,7 +1027,7 @@ idkm_status idkm_backward(idkm_ctx* ctx, const float* dWq, idkm_bwd_mode mode, f
     unsigned int gm_off = 0;
     if (persistent && mode == IDKM_BWD_GMRES) {
         const int kd = ctx->k * ctx->d;
-        persistent = !pp.lane && kd <= 64 &&
+        persistent = !pp.lane && kd <= 64 && (pow2(ctx->k) || ctx->path == IDKM_PATH_AUTO) &&
                      (pp.grid == 1 || (ctx->tree_exchange && !ctx->sink && pp.grid >= TREE_MIN_G));
         if (persistent) {
             size_t& fixed = ctx->static_lds[(const void*)pp.fn];
@@ -1019,7 +1037,8 @@ idkm_status idkm_backward(idkm_ctx* ctx, const float* dWq, idkm_bwd_mode mode, f
                 (void)hipGetLastError();
             }
             gm_off = (unsigned int)((pp.lds + 15) / 16 * 16);
-            const size_t lds = gm_off + gm_state_bytes(kd, gm_basis_length(ctx->gmres_basis, kd));
+            // (the kernel's rows are as long as its padded codebook; the basis has one vector per unknown at most)
+            const size_t lds = gm_off + gm_state_bytes(pow2_at_least(ctx->k) * ctx->d, gm_basis_length(ctx->gmres_basis, kd));
             if (fixed + lds <= LDS_PER_CU)
                 pp.lds = lds;
             else

@@ -1,0 +1,28 @@
+// Persistent kernels of the lane<->vector family for codebooks whose size is not a power of two, energy variant 1.
+#include "dispatch.h"
+#include "persist_small.hpp"
+
+namespace idkm {
+
+template <int K, int D>
+static PersistFns pick(bool bwd) {
+    return bwd ? PersistFns{persist_bwd<K, D, 1, true>, persist_bwd_batch<K, D, 1, true>}
+               : PersistFns{persist_fwd<K, D, 1, true>, persist_fwd_batch<K, D, 1, true>};
+}
+
+PersistFns persist_kernel_ragged_1(int K, int D, bool bwd) {
+    switch (K * 16 + D) {
+        case 4 * 16 + 1: return pick<4, 1>(bwd);
+        case 8 * 16 + 1: return pick<8, 1>(bwd);
+        case 16 * 16 + 1: return pick<16, 1>(bwd);
+        case 4 * 16 + 2: return pick<4, 2>(bwd);
+        case 8 * 16 + 2: return pick<8, 2>(bwd);
+        case 16 * 16 + 2: return pick<16, 2>(bwd);
+        case 4 * 16 + 4: return pick<4, 4>(bwd);
+        case 8 * 16 + 4: return pick<8, 4>(bwd);
+        case 16 * 16 + 4: return pick<16, 4>(bwd);
+    }
+    return PersistFns{};
+}
+
+}  // namespace idkm

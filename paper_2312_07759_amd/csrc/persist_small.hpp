@@ -686,11 +686,11 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 // interleaves wavefronts, and short groups keep the registers low enough for four or five workgroups per compute unit.
 // s_tab: the caller's LDS table of the product forms' per-codeword operands (fwd_dot_tables), or null: then every lane
 // forms them itself in prepare().
-template <int K, int D, int DIST, int PASS, bool SHARED>
+template <int K, int D, int DIST, int PASS, bool SHARED, bool RAG>
 __device__ __forceinline__ void tile_pass(const Args& a, const float* s_w, const float* s_g, int64_t base, int cnt,
                                           const float* s_Cf, const float* s_Hs, const float* s_Ff,
-                                          float (&acc)[SmallItem<K, D, DIST, PASS>::NREG], const float* s_tab = nullptr) {
-    using Item = SmallItem<K, D, DIST, PASS>;
+                                          float (&acc)[SmallItem<K, D, DIST, PASS, RAG>::NREG], const float* s_tab = nullptr) {
+    using Item = SmallItem<K, D, DIST, PASS, RAG>;
     float c[K][D], hs[K][D], ff[K][D + 1];
 #pragma unroll
     for (int j = 0; j < K; ++j)
@@ -888,15 +888,15 @@ __device__ __forceinline__ void tile_pass_global(const Args& a, const float* gw,
 
 // A pass over the workgroup's share of the layer: its LDS tile (w, g: the tile; base, cnt: its place in the layer) or,
 // GLOBALW, its blocks of the tensors in memory (w, g: the whole tensors).
-template <int K, int D, int DIST, int PASS, bool SHARED, bool GLOBALW>
+template <int K, int D, int DIST, int PASS, bool SHARED, bool GLOBALW, bool RAG>
 __device__ __forceinline__ void any_tile_pass(const Args& a, const PArgs& pa, const float* w, const float* g,
                                               int64_t base, int cnt, const float* s_Cf, const float* s_Hs,
-                                              const float* s_Ff, float (&acc)[SmallItem<K, D, DIST, PASS>::NREG],
+                                              const float* s_Ff, float (&acc)[SmallItem<K, D, DIST, PASS, RAG>::NREG],
                                               const float* s_tab = nullptr) {
     if constexpr (GLOBALW)
         tile_pass_global<K, D, DIST, PASS>(a, w, g, pa.wg, pa.G, s_Cf, s_Hs, s_Ff, acc);
     else
-        tile_pass<K, D, DIST, PASS, SHARED>(a, w, g, base, cnt, s_Cf, s_Hs, s_Ff, acc, s_tab);
+        tile_pass<K, D, DIST, PASS, SHARED, RAG>(a, w, g, base, cnt, s_Cf, s_Hs, s_Ff, acc, s_tab);
 }
 
 // Codewords per reducer: as many as fit 8 words of (n_j, s_j) per workgroup.
@@ -946,7 +946,9 @@ __device__ __forceinline__ void bwd_dot_hf(float hfm, float* tab) {
 
 // Forward solve (Alg. 1) and the evaluation at C*, in one launch.
 // GLOBALW: the layer does not fit the chip's LDS; every pass reads the workgroup's share of W from memory.
-template <int K, int D, int DIST, bool SHARED, bool GLOBALW = false>
+// RAG: a codebook of a.k codewords, K/2 < a.k < K, in the kernel for K (see live_weight).  Launched only as a team of one
+// or with the two-level exchange.
+template <int K, int D, int DIST, bool SHARED, bool GLOBALW = false, bool RAG = false>
 __device__ __forceinline__ void persist_fwd_body(const Args& a, const PArgs& pa) {
     constexpr int KD = K * D;
     constexpr int ACCW = D + 1;
@@ -965,7 +967,7 @@ __device__ __forceinline__ void persist_fwd_body(const Args& a, const PArgs& pa)
     // product form of the loop's E-step: its per-codeword operands, kept up to date by wavefront 0
     // (worth it from k d = 32 on: below, what a lane saves at the start of its pass is less than wavefront 0 adds to the
     // path every workgroup waits on: k = 4, d = 2 4.38 -> 4.64 us per evaluation with the table, k = 16, d = 4 8.65 -> 8.39)
-    constexpr bool DOT = SmallItem<K, D, DIST, PASS_FWD>::FWD_DOT && !GLOBALW && K * D >= 32;
+    constexpr bool DOT = SmallItem<K, D, DIST, PASS_FWD, RAG>::FWD_DOT && !GLOBALW && K * D >= 32;
     __shared__ float s_tab[DOT ? KD + K + D : 1];
 
     const int tid = threadIdx.x, wg = pa.wg;
@@ -976,8 +978,10 @@ __device__ __forceinline__ void persist_fwd_body(const Args& a, const PArgs& pa)
     if (!GLOBALW)
         load_tile<PT>(s_tile, a.W + base * D, cnt * D);
     const float* s_w = GLOBALW ? a.W : s_tile;
+    const int k = RAG ? a.k : K, kd = k * D;                              // codewords that exist
+    const int src = (RAG && tid >= kd && tid < KD) ? tid % D : tid;       // (the others follow codeword 0)
     if (tid < KD) {
-        const float c0 = pa.C0[tid];
+        const float c0 = pa.C0[src];
         s_Cd[tid] = (double)c0;
         s_Cf[tid] = c0;
     }
@@ -990,7 +994,7 @@ __device__ __forceinline__ void persist_fwd_body(const Args& a, const PArgs& pa)
         s_res = 0.0;
     }
     if constexpr (DOT) {
-        if (tid < 64) fwd_dot_tables<K, D>(tid < KD ? pa.C0[tid] : 0.f, -a.nscale, s_tab, -2.f * a.nscale);
+        if (tid < 64) fwd_dot_tables<K, D>(tid < KD ? pa.C0[src] : 0.f, -a.nscale, s_tab, -2.f * a.nscale);
     }
     __syncthreads();
     const double tol = pa.tol;
@@ -1006,7 +1010,7 @@ __device__ __forceinline__ void persist_fwd_body(const Args& a, const PArgs& pa)
     double r_cd = 0.0;
     float r_cf = 0.f;
     if (tid < KD) {
-        r_cf = pa.C0[tid];
+        r_cf = pa.C0[src];
         r_cd = (double)r_cf;
     }
     // n, sv: mass of this lane's codeword and the sum of its component (lanes < k d; all 64 lanes of wavefront 0 call)
@@ -1019,7 +1023,7 @@ __device__ __forceinline__ void persist_fwd_body(const Args& a, const PArgs& pa)
             s_Cd[tid] = cnew;
             const float cn = (float)cnew;
             const double df = (double)cn - (double)r_cf;
-            df2 = df * df;
+            df2 = (!RAG || tid < kd) ? df * df : 0.0;
             r_cf = cn;
             s_Cf[tid] = cn;
         }
@@ -1038,7 +1042,7 @@ __device__ __forceinline__ void persist_fwd_body(const Args& a, const PArgs& pa)
     auto update_all = [&](auto tot) {
         double n = 0.0, sv = 0.0;
         if (tid < KD) {
-            const int j = tid / D, rr = tid - j * D;
+            const int j = src / D, rr = src - j * D;
             n = tot(j * ACCW);
             sv = tot(j * ACCW + 1 + rr);
         }
@@ -1048,7 +1052,7 @@ __device__ __forceinline__ void persist_fwd_body(const Args& a, const PArgs& pa)
     float acc[NACC];
     while (!s_done) {
         IDKM_STAMP(0);
-        any_tile_pass<K, D, DIST, PASS_FWD, SHARED, GLOBALW>(a, pa, s_w, nullptr, base, cnt, s_Cf, nullptr, nullptr, acc, DOT ? s_tab : nullptr);
+        any_tile_pass<K, D, DIST, PASS_FWD, SHARED, GLOBALW, RAG>(a, pa, s_w, nullptr, base, cnt, s_Cf, nullptr, nullptr, acc, DOT ? s_tab : nullptr);
         IDKM_STAMP(1);
         ++seq;
         publish_partials<NACC>(pa, seq, acc, xs);
@@ -1069,7 +1073,7 @@ __device__ __forceinline__ void persist_fwd_body(const Args& a, const PArgs& pa)
                     double total;
                     const bool ok = tree8_grid_totals_regs(pa, seq, xs, total);
                     IDKM_STAMP(4);
-                    const int jj = (tid < KD) ? tid / D : 0, rr = (tid < KD) ? tid - jj * D : 0;
+                    const int jj = (tid < KD) ? src / D : 0, rr = (tid < KD) ? src - jj * D : 0;
                     const double n = tree8_total_of(total, jj * ACCW), sv = tree8_total_of(total, jj * ACCW + 1 + rr);
                     if (ok) update_vals(n, sv);
                 }
@@ -1152,7 +1156,7 @@ __device__ __forceinline__ void persist_fwd_body(const Args& a, const PArgs& pa)
     }
 
     // evaluation at C*: outputs, and n*, F* for the backward
-    any_tile_pass<K, D, DIST, PASS_FIN, SHARED, GLOBALW>(a, pa, s_w, nullptr, base, cnt, s_Cf, nullptr, nullptr, acc);
+    any_tile_pass<K, D, DIST, PASS_FIN, SHARED, GLOBALW, RAG>(a, pa, s_w, nullptr, base, cnt, s_Cf, nullptr, nullptr, acc);
     ++seq;
     publish_partials<NACC>(pa, seq, acc, xs);
     if (pa.tree) {
@@ -1170,7 +1174,7 @@ __device__ __forceinline__ void persist_fwd_body(const Args& a, const PArgs& pa)
             if (!tree_grid_totals<NACC>(pa, seq, xs)) return;
         }
         {
-            if (tid < KD) {
+            if (tid < kd) {
                 const int j = tid / D, rr = tid - j * D;
                 const double n = xs.totd[j * ACCW], s = xs.totd[j * ACCW + 1 + rr];
                 const double cst = (double)s_Cf[tid];
@@ -1184,7 +1188,7 @@ __device__ __forceinline__ void persist_fwd_body(const Args& a, const PArgs& pa)
             }
             if (tid == 0) {
                 int empty = 0, bad = 0;
-                for (int j = 0; j < K; ++j) {
+                for (int j = 0; j < k; ++j) {
                     const double n = xs.totd[j * ACCW];
                     if (!(n > 0.0)) empty++;
                     if (!(n >= 0.0)) bad = 1;
@@ -1206,7 +1210,7 @@ __device__ __forceinline__ void persist_fwd_body(const Args& a, const PArgs& pa)
     }
     for (int r = wg; r < R; r += pa.G) {
         if (!reduce_slice<NACC, WPR>(pa, seq, r * WPR, xs)) return;
-        if (tid < KPR * D) {
+        if (tid < KPR * D && (!RAG || r * KPR * D + tid < kd)) {
             const int jl = tid / D, rr = tid - jl * D, j = r * KPR + jl, idx = j * D + rr;
             const double n = xs.tot[jl * ACCW], s = xs.tot[jl * ACCW + 1 + rr];
             const double cst = (double)s_Cf[idx];
@@ -1220,7 +1224,7 @@ __device__ __forceinline__ void persist_fwd_body(const Args& a, const PArgs& pa)
         }
         if (tid == 0) {
             int empty = 0, bad = 0;
-            for (int jl = 0; jl < KPR; ++jl) {
+            for (int jl = 0; jl < KPR && (!RAG || r * KPR + jl < k); ++jl) {
                 const double n = xs.tot[jl * ACCW];
                 if (!(n > 0.0)) empty++;
                 if (!(n >= 0.0)) bad = 1;
@@ -1453,8 +1457,9 @@ __device__ __forceinline__ int gmres_step(const GmView<N>& gm, U u, const double
 }
 
 // Backward (Alg. 2 per-layer steps): v, the averaged fixed-point iteration of
-// Sec. 4.2 for g (skipped for JFB), and dW, in one launch.
-template <int K, int D, int DIST, bool SHARED, bool GLOBALW = false>
+// Sec. 4.2 for g (skipped for JFB), and dW, in one launch.  RAG: as in the forward; the components of v, g and h that
+// belong to no codeword are zero throughout.
+template <int K, int D, int DIST, bool SHARED, bool GLOBALW = false, bool RAG = false>
 __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa) {
     constexpr int KD = K * D;
     constexpr int KPR = (8 / D) > K ? K : (8 / D);  // codewords per reducer: 8 words of D components
@@ -1465,7 +1470,7 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
     // explicit-Jacobian mode (Eq. "grad", "inv" taken literally): offered when its K D (K D + D + 1) sums fit one
     // exchange line
     constexpr int NBJ = KD * KD + KD * D + KD;
-    constexpr bool HAS_DENSE = NBJ <= XDENSE;
+    constexpr bool HAS_DENSE = NBJ <= XDENSE && !RAG;
     extern __shared__ float s_tile[];
     __shared__ XShared<HAS_DENSE ? NBJ : KD> xs;
     __shared__ double s_v[KD], s_g[KD], s_rn[K];  // a reducer's own slice is the live one; s_rn = 1/(tau n)
@@ -1473,17 +1478,19 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
     // product form of the (dF/dC)^T pass: its per-codeword operands (c_j - mu, -s^2 |c_j - mu|^2, mu, h_j . (F*_j - mu) / tau),
     // formed by wavefront 0 -- the first three once per launch, the last whenever h changes -- from k d = 32 on (below,
     // every lane forms them itself at the start of its pass)
-    constexpr bool BTAB = SmallItem<K, D, DIST, PASS_B2>::B2_DOT && !GLOBALW && KD >= 32;
+    constexpr bool BTAB = SmallItem<K, D, DIST, PASS_B2, RAG>::B2_DOT && !GLOBALW && KD >= 32;
     __shared__ float s_tabB[BTAB ? KD + K + D + K : 1];
     __shared__ int s_done, s_iters, s_conv, s_attempt, s_grow, s_halv, s_bad, s_restart;
     __shared__ double s_alpha, s_prev, s_vnorm, s_res;
     // minimal-residual solve (BWD_GMRES): offered to teams in which every workgroup receives the totals; its state lies
     // in the dynamic LDS at pa.gm_off (behind the tiles), only in launches of that mode
     extern __shared__ double s_dyn_d[];
-    GmView<KD> gm;
-    gm.bind(reinterpret_cast<char*>(s_dyn_d) + pa.gm_off, gm_basis_length(pa.gm_basis, KD));
-
     const int tid = threadIdx.x, wg = pa.wg;
+    const int k = RAG ? a.k : K, kd = k * D;                          // codewords that exist
+    const int src = (RAG && tid >= kd && tid < KD) ? tid % D : tid;   // (the others are copies of codeword 0)
+    GmView<KD> gm;
+    gm.bind(reinterpret_cast<char*>(s_dyn_d) + pa.gm_off, gm_basis_length(pa.gm_basis, kd));
+
     const int64_t base = (int64_t)wg * pa.per;
     int cnt = 0;
     if (base < a.m) cnt = (a.m - base < pa.per) ? (int)(a.m - base) : pa.per;
@@ -1495,16 +1502,16 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
         load_tile<PT>(s_tile + (size_t)pa.per * D, a.G + base * D, cnt * D);
     }
     if (tid < KD) {
-        s_Cf[tid] = a.Cf[tid];
-        s_Ff[tid] = a.Ff[tid];
+        s_Cf[tid] = a.Cf[src];
+        s_Ff[tid] = a.Ff[src];
         s_Hs[tid] = 0.f;
         s_Hv[tid] = 0.f;
     }
     float r_fm = 0.f;  // lane j d + r < k d of wavefront 0: F*_jr - mu_r
     if constexpr (BTAB) {
         if (tid < 64) {
-            const float mu = fwd_dot_tables<K, D>(tid < KD ? a.Cf[tid] : 0.f, -a.nscale, s_tabB, 1.f);
-            if (tid < KD) r_fm = a.Ff[tid] - mu;
+            const float mu = fwd_dot_tables<K, D>(tid < KD ? a.Cf[src] : 0.f, -a.nscale, s_tabB, 1.f);
+            if (tid < KD) r_fm = a.Ff[src] - mu;
         }
     }
     // every change of h/tau goes through here (lanes < k d of wavefront 0, all of them together)
@@ -1513,7 +1520,7 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
         if constexpr (BTAB) bwd_dot_hf<K, D>(h * r_fm, s_tabB);
     };
     if (tid < K) {
-        const double n = a.nd[tid];
+        const double n = (!RAG || tid < k) ? a.nd[tid] : 0.0;
         s_rn[tid] = (n > 0.0) ? (double)a.inv_tau / n : 0.0;  // zero for an empty cluster
     }
     const int mode = pa.mode;
@@ -1540,7 +1547,7 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
     if (pa.tree && !tree_handshake(pa, xs)) return;
     unsigned int seq = pa.seq_base;
 
-    float accr[SmallItem<K, D, DIST, PASS_B2>::NREG];            // (the (dF/dC)^T pass may keep more sums in registers than it publishes)
+    float accr[SmallItem<K, D, DIST, PASS_B2, RAG>::NREG];            // (the (dF/dC)^T pass may keep more sums in registers than it publishes)
     float(&acc)[KD] = reinterpret_cast<float(&)[KD]>(accr);
     bool dense_done = false;
     if constexpr (HAS_DENSE) {
@@ -1548,7 +1555,7 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
             // one pass accumulates v and the sums T, U of dF/dC* (layout as in the stream path's tail_bj); workgroup 0
             // adds them over the team, solves (I - dF/dC*)^T g = v by Gauss-Jordan elimination and broadcasts h/tau
             float accj[NBJ];
-            any_tile_pass<K, D, DIST, PASS_BJ, SHARED, GLOBALW>(a, pa, s_w, s_gt, base, cnt, s_Cf, s_Hs, s_Ff, accj);
+            any_tile_pass<K, D, DIST, PASS_BJ, SHARED, GLOBALW, RAG>(a, pa, s_w, s_gt, base, cnt, s_Cf, s_Hs, s_Ff, accj);
             ++seq;
             publish_partials<NBJ>(pa, seq, accj, xs);
             if (wg == 0) {
@@ -1616,7 +1623,7 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
     }
     if (!dense_done) {
     // B1: v = dL/dC* with W fixed; the solve starts at g = v
-    any_tile_pass<K, D, DIST, PASS_B1, SHARED, GLOBALW>(a, pa, s_w, s_gt, base, cnt, s_Cf, s_Hs, s_Ff, acc);
+    any_tile_pass<K, D, DIST, PASS_B1, SHARED, GLOBALW, RAG>(a, pa, s_w, s_gt, base, cnt, s_Cf, s_Hs, s_Ff, acc);
     ++seq;
     publish_partials<KD>(pa, seq, acc, xs);
     if (tree) {
@@ -1721,7 +1728,7 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
     }
     while (!s_done) {
         IDKM_STAMP(0);
-        any_tile_pass<K, D, DIST, PASS_B2, SHARED, GLOBALW>(a, pa, s_w, s_gt, base, cnt, s_Cf, s_Hs, s_Ff, accr, BTAB ? s_tabB : nullptr);
+        any_tile_pass<K, D, DIST, PASS_B2, SHARED, GLOBALW, RAG>(a, pa, s_w, s_gt, base, cnt, s_Cf, s_Hs, s_Ff, accr, BTAB ? s_tabB : nullptr);
         IDKM_STAMP(1);
         ++seq;
         publish_partials<KD>(pa, seq, acc, xs);
@@ -1925,22 +1932,22 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
     }
 
     // B3: dW = direct + (dF/dW)^T g
-    any_tile_pass<K, D, DIST, PASS_B3, SHARED, GLOBALW>(a, pa, s_w, s_gt, base, cnt, s_Cf, s_Hs, s_Ff, reinterpret_cast<float(&)[1]>(acc[0]));
+    any_tile_pass<K, D, DIST, PASS_B3, SHARED, GLOBALW, RAG>(a, pa, s_w, s_gt, base, cnt, s_Cf, s_Hs, s_Ff, reinterpret_cast<float(&)[1]>(acc[0]));
     if (dense_done || tree) {
-        if (wg == 0 && tid < KD) {
+        if (wg == 0 && tid < kd) {
             a.gd[tid] = s_g[tid];
             a.vd[tid] = s_v[tid];
         }
     } else {
         for (int r = wg; r < R; r += pa.G) {
-            if (tid < WPR) {
+            if (tid < WPR && (!RAG || r * WPR + tid < kd)) {
                 const int idx = r * WPR + tid;
                 a.gd[idx] = s_g[idx];
                 a.vd[idx] = s_v[idx];
             }
         }
     }
-    if (wg == 0 && tid < KD) a.Hs[tid] = s_Hs[tid];
+    if (wg == 0 && tid < kd) a.Hs[tid] = s_Hs[tid];
     if (wg == pa.G - 1 && tid == 0) {
         PResult* o = pa.out;
         o->iters = s_iters;
@@ -1955,19 +1962,19 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
 }
 
 // One team per launch: the grid is the team.
-template <int K, int D, int DIST>
+template <int K, int D, int DIST, bool RAG = false>
 __global__ __launch_bounds__(PT) void persist_fwd(const Args a, const PArgs pa_in) {
     PArgs pa = pa_in;
     pa.wg = blockIdx.x;
     pa.G = gridDim.x;
-    persist_fwd_body<K, D, DIST, false>(a, pa);
+    persist_fwd_body<K, D, DIST, false, false, RAG>(a, pa);
 }
-template <int K, int D, int DIST>
+template <int K, int D, int DIST, bool RAG = false>
 __global__ __launch_bounds__(PT) void persist_bwd(const Args a, const PArgs pa_in) {
     PArgs pa = pa_in;
     pa.wg = blockIdx.x;
     pa.G = gridDim.x;
-    persist_bwd_body<K, D, DIST, false>(a, pa);
+    persist_bwd_body<K, D, DIST, false, false, RAG>(a, pa);
 }
 
 // The same for a layer larger than the chip's LDS (W is read from memory in every pass; no dynamic LDS).
@@ -1988,23 +1995,23 @@ __global__ __launch_bounds__(PT) void persist_bwd_global(const Args a, const PAr
 
 // Several independent problems of one shape (the layers of Alg. 2's loops) in one launch: item_of_wg maps a
 // workgroup to its problem; every team runs its own solve and leaves when that solve is over.
-template <int K, int D, int DIST>
+template <int K, int D, int DIST, bool RAG = false>
 __global__ __launch_bounds__(PT) void persist_fwd_batch(const BatchItem* items, const unsigned short* item_of_wg) {
     const BatchItem& it = items[item_of_wg[blockIdx.x]];
     const Args a = it.a;
     PArgs pa = it.p;
     pa.wg = (int)blockIdx.x - it.wg_begin;
     pa.G = it.wg_count;
-    persist_fwd_body<K, D, DIST, true>(a, pa);
+    persist_fwd_body<K, D, DIST, true, false, RAG>(a, pa);
 }
-template <int K, int D, int DIST>
+template <int K, int D, int DIST, bool RAG = false>
 __global__ __launch_bounds__(PT) void persist_bwd_batch(const BatchItem* items, const unsigned short* item_of_wg) {
     const BatchItem& it = items[item_of_wg[blockIdx.x]];
     const Args a = it.a;
     PArgs pa = it.p;
     pa.wg = (int)blockIdx.x - it.wg_begin;
     pa.G = it.wg_count;
-    persist_bwd_body<K, D, DIST, true>(a, pa);
+    persist_bwd_body<K, D, DIST, true, false, RAG>(a, pa);
 }
 
 }  // namespace idkm

@@ -48,8 +48,15 @@ struct VecLoad<4> {
 // per codeword than the general form.  df receives t_j and ri the factor that turns it into d e_j / d w for the squared
 // energy (2/s); for the plain norm only the sign of t_j is used, and t_j = 0 exactly where w = c_j (the two products
 // are rounded on their own).  The reference point keeps layers far from the origin free of cancellation.
-template <int K, int D, int DIST, bool DERIV>
-__device__ __forceinline__ void estep_small(const float (&w)[D], const float (&c)[K][D], float nscale, float escale,
+//
+// RAG: only the first k of the K codewords exist (K/2 < k < K).  The others are copies of codeword 0, so that everything
+// formed from them is finite and no row minimum changes, and their weights are set to zero.
+template <bool RAG, int K>
+__device__ __forceinline__ float live_weight(float p, int j, int k) {
+    return (RAG && j > K / 2 && j >= k) ? 0.f : p;
+}
+template <int K, int D, int DIST, bool DERIV, bool RAG>
+__device__ __forceinline__ void estep_small(const float (&w)[D], const float (&c)[K][D], float nscale, float escale, int k,
                                             float (&a)[K], float (&df)[K][D], float (&ri)[K]) {
     if constexpr (D == 1 && DERIV) {
         const float c0 = c[0][0];
@@ -65,6 +72,7 @@ __device__ __forceinline__ void estep_small(const float (&w)[D], const float (&c
 #pragma unroll
         for (int j = 0; j < K; ++j) {
             a[j] = (DIST == DIST_SQL2) ? fast_exp2(fmaf(-t[j], t[j], qmin)) : fast_exp2(tmin - fabsf(t[j]));
+            a[j] = live_weight<RAG, K>(a[j], j, k);
             S = (j == 0) ? a[0] : S + a[j];
         }
         const float rS = fast_rcp(S);
@@ -110,7 +118,7 @@ __device__ __forceinline__ void estep_small(const float (&w)[D], const float (&c
     float S = 0.f;
 #pragma unroll
     for (int j = 0; j < K; ++j) {
-        a[j] = fast_exp2(u[j] - umax);
+        a[j] = live_weight<RAG, K>(fast_exp2(u[j] - umax), j, k);
         S += a[j];
     }
     const float rS = fast_rcp(S);
@@ -129,7 +137,7 @@ __device__ __forceinline__ float delta_small(const float (&df)[K][D], const floa
 // Everything one pass does for one weight vector i: E-step, then the pass's own
 // accumulation or per-vector output.  acc has K*(D+1) entries for the forward
 // passes ((n_j, s_j) interleaved), K*D for B1/B2, and is unused for B3.
-template <int K, int D, int DIST, int PASS>
+template <int K, int D, int DIST, int PASS, bool RAG = false>
 struct SmallItem {
     static constexpr bool STATS = (PASS == PASS_FWD || PASS == PASS_FIN);
     static constexpr bool BACK = (PASS == PASS_B1 || PASS == PASS_B2 || PASS == PASS_B3 || PASS == PASS_BJ);
@@ -148,7 +156,9 @@ struct SmallItem {
     // finish(), instead of d subtractions per (vector, codeword) pair; 2 d + 6 operations per pair and 10 per vector
     // instead of 5 d + 9 and 2.  prepare() leaves cm in c, h_j.(F*_j - mu) in ff[j][0], mu_r in ff[r][1] and
     // -s^2 |cm_j|^2 in ff[j][D].
-    static constexpr bool B2_DOT = (PASS == PASS_B2 && DIST == DIST_SQL2 && D >= 2 && K >= D);
+    // (Not for RAG: those codebooks came from kernels that take differences, and one codeword far from the data, which
+    // moves mu, costs the products accuracy.)
+    static constexpr bool B2_DOT = (PASS == PASS_B2 && DIST == DIST_SQL2 && D >= 2 && K >= D && !RAG);
     // accumulators a lane keeps in registers; the first NACC of them are the pass's partial sums after finish()
     static constexpr int NREG = NACC + (B2_DOT ? K : 0);
 
@@ -158,7 +168,7 @@ struct SmallItem {
     // codeword (so that layers far from the origin lose nothing to cancellation): prepare() leaves the k products in
     // ff[j][0] and mu_r in ff[r][1] (the other values of F* are not used again) and run() expects them there; d
     // subtractions per vector instead of d per codeword.
-    static constexpr bool FOLD_HF = ((PASS == PASS_B2 || PASS == PASS_B3) && D >= 2 && K * D >= 32) && !B2_DOT;
+    static constexpr bool FOLD_HF = ((PASS == PASS_B2 || PASS == PASS_B3) && D >= 2 && K * D >= 32) && !B2_DOT && !RAG;
 
     // Forward loop, squared energy, d >= 2: the exponent of a weight of the row softmax (Eq. "aterms") is taken as a
     // product.  With s^2 = log2(e)/tau and a reference point mu (the mean codeword; the energy does not change when w
@@ -170,7 +180,7 @@ struct SmallItem {
     // (this pass uses neither h nor F*).  The rounding error of an exponent is a few float32 ulps of
     // s^2 |c - mu| |w - mu|, i.e. of the exponents themselves; the closest-codeword key of the last pass is not formed
     // this way.
-    static constexpr bool FWD_DOT = (PASS == PASS_FWD && DIST == DIST_SQL2 && D >= 2 && K >= D);
+    static constexpr bool FWD_DOT = (PASS == PASS_FWD && DIST == DIST_SQL2 && D >= 2 && K >= D && !RAG);
 
     // Called once per pass by every caller of run(), after it has loaded the tables into registers.
     static __device__ __forceinline__ void prepare(const Args& a, float (&c)[K][D], float (&hs)[K][D], float (&ff)[K][D + 1]) {
@@ -293,7 +303,7 @@ struct SmallItem {
             float p[K], S = 0.f, pq = 0.f;
 #pragma unroll
             for (int j = 0; j < K; ++j) {
-                p[j] = fast_exp2(l[j] - lmax);
+                p[j] = live_weight<RAG, K>(fast_exp2(l[j] - lmax), j, a.k);
                 S = (j == 0) ? p[0] : S + p[j];
                 pq = fmaf(p[j], q[j], pq);
             }
@@ -326,6 +336,7 @@ struct SmallItem {
 #pragma unroll
             for (int j = 0; j < K; ++j) {
                 p[j] = (DIST == DIST_SQL2) ? fast_exp2(fmaf(-t[j], t[j], qmin)) : fast_exp2(tmin - fabsf(t[j]));
+                p[j] = live_weight<RAG, K>(p[j], j, a.k);
                 S = (j == 0) ? p[0] : S + p[j];
                 q[j] = fmaf(hs[j][0], wr, -(hs[j][0] * (ff[j][0] - c0)));  // loop-invariant product
                 pq = fmaf(p[j], q[j], pq);
@@ -366,6 +377,7 @@ struct SmallItem {
 #pragma unroll
             for (int j = 0; j < K; ++j) {
                 p[j] = (DIST == DIST_SQL2) ? fast_exp2(fmaf(-t[j], t[j], qmin)) : fast_exp2(tmin - fabsf(t[j]));
+                p[j] = live_weight<RAG, K>(p[j], j, a.k);
                 S = (j == 0) ? p[0] : S + p[j];
             }
             const float rS = fast_rcp(S);
@@ -395,7 +407,7 @@ struct SmallItem {
             float p[K], S = 0.f;
 #pragma unroll
             for (int j = 0; j < K; ++j) {
-                p[j] = fast_exp2(l[j] - lmax);
+                p[j] = live_weight<RAG, K>(fast_exp2(l[j] - lmax), j, a.k);
                 S = (j == 0) ? p[0] : S + p[j];
             }
             const float rS = fast_rcp(S);
@@ -414,7 +426,7 @@ struct SmallItem {
 #pragma unroll
         for (int r = 0; r < D; ++r) gs[r] = USE_G ? g[r] * a.inv_tau : 0.f;
         float at[K], df[K][D], ri[K];
-        estep_small<K, D, DIST, BACK>(w, c, a.nscale, a.escale, at, df, ri);
+        estep_small<K, D, DIST, BACK, RAG>(w, c, a.nscale, a.escale, a.k, at, df, ri);
 
         if (STATS) {
 #pragma unroll
@@ -438,10 +450,12 @@ struct SmallItem {
             }
             if (a.A_out) {
 #pragma unroll
-                for (int j = 0; j < K; ++j) a.A_out[i * K + j] = at[j];
+                for (int j = 0; j < K; ++j)
+                    if (!RAG || j < a.k) a.A_out[i * (RAG ? a.k : K) + j] = at[j];
             }
             if (a.assign_out) {
-                // closest codeword decided on a float32 key with separately rounded operations
+                // closest codeword decided on a float32 key with separately rounded operations (the copies of codeword 0
+                // behind a ragged codebook never win: their keys are not below codeword 0's)
                 int best = 0;
                 float bk = 0.f;
 #pragma unroll
