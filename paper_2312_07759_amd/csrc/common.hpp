@@ -249,6 +249,25 @@ __device__ __forceinline__ double wave_sum_d_dpp(double x) {
     const int hi = __builtin_amdgcn_readlane(__double2hiint(x), 63);
     return __hiloint2double(hi, lo);
 }
+typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
+// Sum over the four lanes l % 16 + 16 r of a wavefront (one lane of each row of 16), in every lane.
+// v_permlane16_swap exchanges the odd rows of its first operand with the even rows of its second, v_permlane32_swap
+// the upper half of the first with the lower half of the second; adding the two results pairs every lane with its
+// partner, and both partners add the same two numbers (in either order: the same sum).
+__device__ __forceinline__ float cross_row_sum(float x) {
+    u32x2_t s = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+    s = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+}
+__device__ __forceinline__ double cross_row_sum_d(double x) {
+    u32x2_t lo = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(x), (unsigned)__double2loint(x), false, false);
+    u32x2_t hi = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(x), (unsigned)__double2hiint(x), false, false);
+    x = __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+    lo = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(x), (unsigned)__double2loint(x), false, false);
+    hi = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(x), (unsigned)__double2hiint(x), false, false);
+    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
 // Sum of lanes 0 .. N-1 (the other lanes must hold zero), valid in lane 0: only as many butterfly steps as N needs.
 template <int N>
 __device__ __forceinline__ double first_lanes_sum_d_dpp(double x) {

@@ -45,6 +45,10 @@ PersistFns persist_kernel_global(int K, int D, int dist, bool bwd);
 // matrix: prefer the matrix-core forward loop where one exists (d = 4, k <= 256).
 PersistFns persist_lane_kernel(int KPL, int D, int dist, bool bwd, bool matrix);
 
+// Persistent solve in the row <-> vector form: D in {1,2}, 16 KB >= k codewords, KB in {1,2,4,8,16}.
+PersistFns persist_row_kernel_0(int KB, int D, bool bwd);
+PersistFns persist_row_kernel_1(int KB, int D, bool bwd);
+
 // b-bit code stream of the hard assignments and the reconstruction q(W, C) from it (codes.hip).
 void launch_pack_codes(const int32_t* assign, int64_t m, int bits, uint32_t* words, int64_t nwords, hipStream_t s);
 void launch_unpack_quantize(const uint32_t* words, int64_t nwords, int64_t m, int bits, const float* C, int k, int d,

@@ -441,7 +441,17 @@ bool plan_persistent(idkm_ctx* ctx, bool bwd, PersistPlan* pp, bool matrix_ok = 
         if (g > PT) g = PT;
         int64_t per = (m + g - 1) / g;
         per = (per + 3) / 4 * 4;
-        PersistFns fl = persist_lane_kernel(p, d, ctx->dist, bwd, matrix_ok && ctx->use_matrix);
+        // d <= 2 and k <= 256: the row <-> vector kernels (589,824 scalar weights under 64 codewords, 30 evaluations and a
+        // Jacobian-free backward: 671 us against 1260); beyond 256 codewords their tables do not fit the registers
+        const bool row = d <= 2 && k <= 256;
+        PersistFns fl;
+        if (row) {
+            int kb = 1;
+            while (16 * kb < k) kb <<= 1;
+            fl = ctx->dist == DIST_L2 ? persist_row_kernel_0(kb, d, bwd) : persist_row_kernel_1(kb, d, bwd);
+        } else {
+            fl = persist_lane_kernel(p, d, ctx->dist, bwd, matrix_ok && ctx->use_matrix);
+        }
         size_t lds = (size_t)per * d * sizeof(float) * (bwd ? 2 : 1);
         if (fl.matrix) {
             // tile padded by 16 vectors, then one float per vector (dL/dWq is not kept); these kernels hold more
@@ -472,7 +482,7 @@ bool plan_persistent(idkm_ctx* ctx, bool bwd, PersistPlan* pp, bool matrix_ok = 
         pp->grid = (int)((m + per - 1) / per);
         pp->per = (int)per;
         pp->lds = lds;
-        pp->threads = LT;
+        pp->threads = row ? fl.threads : LT;
         pp->lane = true;
         return true;
     }

@@ -18,17 +18,12 @@ static PersistFns pick4(bool bwd, bool matrix) {
     return PersistFns{persist_mfma_fwd<KPL, 1>, persist_mfma_fwd_batch<KPL, 1>, true, MT};
 }
 
-// Offered for KPL*D <= 16 and KPL*(D+1) <= 24 (k <= 512), d <= 4.
+// Offered for KPL*D <= 16 and KPL*(D+1) <= 24 (k <= 512), d <= 4, where the row <-> vector kernels (d <= 2, k <= 256) do not
+// serve the shape.
 PersistFns persist_lane_kernel_1(int KPL, int D, bool bwd, bool matrix) {
     switch (KPL * 16 + D) {
-        case 1 * 16 + 1: return pick<1, 1>(bwd);
-        case 1 * 16 + 2: return pick<1, 2>(bwd);
         case 1 * 16 + 4: return pick4<1>(bwd, matrix);
-        case 2 * 16 + 1: return pick<2, 1>(bwd);
-        case 2 * 16 + 2: return pick<2, 2>(bwd);
         case 2 * 16 + 4: return pick4<2>(bwd, matrix);
-        case 4 * 16 + 1: return pick<4, 1>(bwd);
-        case 4 * 16 + 2: return pick<4, 2>(bwd);
         case 4 * 16 + 4: return pick4<4>(bwd, matrix);
         case 8 * 16 + 1: return pick<8, 1>(bwd);
         case 8 * 16 + 2: return pick<8, 2>(bwd);

@@ -13,6 +13,7 @@
 #include "lane_k.hpp"
 #include "mfma_lane.hpp"
 #include "persist_small.hpp"
+#include "row_k.hpp"
 
 namespace idkm {
 
@@ -21,9 +22,12 @@ constexpr int LWAVES = LT / 64;
 constexpr int MT = 512;           // threads per workgroup of the matrix-core forward kernel (2 wavefronts per SIMD:
                                   // its accumulators and one 16 x 256 tile of weights need ~200 registers per lane)
 
+constexpr int RT = 512;           // threads per workgroup of the row <-> vector kernels
+constexpr int LWORDS = 9;         // words of a codeword per workgroup: d + 1 <= 9
+
 struct LShared {
-    float red[8][PT];     // reducer: one codeword's words of every workgroup (at most PT workgroups)
-    double tot[8];
+    float red[LWORDS][PT];  // reducer: one codeword's words of every workgroup (at most PT workgroups)
+    double tot[LWORDS];
     double wsum[LWAVES];
     double scalar;        // result of block_sum
     int abort;
@@ -96,7 +100,7 @@ __device__ __forceinline__ void publish_lane(const PArgs& pa, unsigned int seq, 
 // Totals over all workgroups of words [first, first+WPR) of every workgroup's hop-1 block into ls.tot.
 template <int WPR>
 __device__ __forceinline__ bool reduce_lane(const PArgs& pa, unsigned int seq, int nacc, int first, LShared& ls) {
-    static_assert(WPR <= 8, "a reducer handles at most 8 words per workgroup");
+    static_assert(WPR <= LWORDS, "words of one codeword");
     const int tid = threadIdx.x;
     const int G = pa.G;
     if (tid < PT) {
@@ -132,7 +136,7 @@ __device__ __forceinline__ bool reduce_lane(const PArgs& pa, unsigned int seq, i
     }
     __syncthreads();
     if (ls.abort) return false;
-    if (tid < PT) {
+    if (tid < 32 * LWORDS) {  // (the only kernels with nine words have 512 threads)
         const int q = tid >> 5, part = tid & 31;
         double s = 0.0;
         if (q < WPR) {
@@ -192,21 +196,37 @@ __device__ __forceinline__ void lane_tile_pass(const Args& a, LaneWave<KPL, D, D
 #define IDKM_LSTAMP(slot)
 #endif
 
-// Forward solve (Alg. 1) and the evaluation at C*.  MFMA: the loop's passes run on the matrix cores (mfma_lane.hpp;
+// Hop-1 store of a pass whose wavefronts left their totals in part[wavefront][nacc]: they add up in wavefront order,
+// float64, as in publish_lane.
+template <int NW>
+__device__ __forceinline__ void publish_parts(const PArgs& pa, unsigned int seq, const float* part, int stride, int nacc) {
+    unsigned long long* dst = pa.buf1 + ((size_t)(seq & 1u) * pa.G + pa.wg) * nacc;
+    for (int idx = threadIdx.x; idx < nacc; idx += NW * 64) {
+        double t = 0.0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) t += (double)part[w * stride + idx];
+        st_word(&dst[idx], pack_f(seq, (float)t));
+    }
+}
+
+// Forward solve (Alg. 1) and the evaluation at C*.  KB > 0: the passes run in the row <-> vector form (row_k.hpp) with
+// NT = RT threads, for up to 16 KB codewords.  MFMA: the loop's passes run on the matrix cores (mfma_lane.hpp;
 // d = 4), with NT = MT threads; the dynamic LDS then holds the tile padded by 16 zero vectors and,
 // behind it, -s^2 |w|^2 of every vector.
-template <int KPL, int D, int DIST, int NT = LT, bool MFMA = false>
+template <int KPL, int D, int DIST, int NT = LT, bool MFMA = false, int KB = 0>
 __device__ __forceinline__ void persist_lane_fwd_body(const Args& a, const PArgs& pa) {
     static_assert(!MFMA || (D == 4 && KPL <= 4), "matrix-core loop: d = 4, k <= 256");
     constexpr int ACCW = D + 1;
     constexpr int NA = KPL * ACCW;
-    constexpr int KDP = 64 * KPL * D;  // padded codebook size
+    constexpr int KMAX = KB > 0 ? 16 * KB : 64 * KPL;
+    constexpr int KDP = KMAX * D;  // padded codebook size
     extern __shared__ float s_tile[];
-    __shared__ double s_acc[64][NA];
+    __shared__ double s_acc[KB > 0 ? 1 : 64][NA];
     __shared__ LShared ls;
     __shared__ double s_Cd[KDP];  // float64 master copy; the reducer's own codewords are the live ones
-    __shared__ float s_Cf[KDP];
-    __shared__ unsigned int s_new[KDP + 64 * KPL];
+    __shared__ __align__(16) float s_Cf[KDP];
+    __shared__ unsigned int s_new[KDP + KMAX];
+    __shared__ float s_rpart[KB > 0 ? NT / 64 : 1][KB > 0 ? KMAX * ACCW : 1];  // row form: totals of the wavefronts
     __shared__ int s_done, s_iters, s_conv, s_bad;
     __shared__ double s_res;
 
@@ -222,6 +242,8 @@ __device__ __forceinline__ void persist_lane_fwd_body(const Args& a, const PArgs
         s_Cd[i] = (double)c0;
         s_Cf[i] = c0;
     }
+    if (KB > 0)
+        for (int i = kd + tid; i < KDP; i += NT) s_Cf[i] = 0.f;
     if (tid == 0) {
         ls.abort = 0;
         s_done = 0;
@@ -293,6 +315,17 @@ __device__ __forceinline__ void persist_lane_fwd_body(const Args& a, const PArgs
             __syncthreads();
             IDKM_LSTAMP(5);
             publish_matrix();
+        } else if constexpr (KB > 0) {
+            {
+                RowWave<KB, D, DIST, PASS_FWD> st;
+                st.init(k, s_Cf, nullptr, nullptr, a.escale);
+                row_tile_pass<KB, D, DIST, PASS_FWD, NT>(a, st, s_tile, nullptr, base, cnt);
+                IDKM_LSTAMP(1);
+                st.collect(s_rpart[tid >> 6]);
+            }
+            __syncthreads();
+            IDKM_LSTAMP(5);
+            publish_parts<NT / 64>(pa, seq, &s_rpart[0][0], KMAX * ACCW, nacc);
         } else {
             LaneWave<KPL, D, DIST, PASS_FWD> st;
             st.init(k, s_Cf, nullptr, nullptr, a.escale);
@@ -363,7 +396,16 @@ __device__ __forceinline__ void persist_lane_fwd_body(const Args& a, const PArgs
                 done_here = true;
             }
         }
-        if (!done_here) {
+        if constexpr (KB > 0) {
+            {
+                RowWave<KB, D, DIST, PASS_FIN> st;
+                st.init(k, s_Cf, nullptr, nullptr, a.escale);
+                row_tile_pass<KB, D, DIST, PASS_FIN, NT>(a, st, s_tile, nullptr, base, cnt);
+                st.collect(s_rpart[tid >> 6]);
+            }
+            __syncthreads();
+            publish_parts<NT / 64>(pa, seq, &s_rpart[0][0], KMAX * ACCW, nacc);
+        } else if (!done_here) {
             LaneWave<KPL, D, DIST, PASS_FIN> st;
             st.init(k, s_Cf, nullptr, nullptr);
             lane_tile_pass<KPL, D, DIST, PASS_FIN, NT>(a, st, s_tile, nullptr, base, cnt);
@@ -432,18 +474,20 @@ __device__ __forceinline__ void persist_lane_fwd_body(const Args& a, const PArgs
 // matrix cores (MfmaB2; d = 4), with NT = MT threads; the dynamic LDS then holds the tile of W padded
 // by 16 zero vectors and -s^2 |w - mu|^2 of every vector, and dL/dWq -- needed by the first and the last pass only --
 // is read from memory.
-template <int KPL, int D, int DIST, int NT = LT, bool MFMA = false>
+template <int KPL, int D, int DIST, int NT = LT, bool MFMA = false, int KB = 0>
 __device__ __forceinline__ void persist_lane_bwd_body(const Args& a, const PArgs& pa) {
     static_assert(!MFMA || (D == 4 && KPL <= 4), "matrix-core pass: d = 4, k <= 256");
     constexpr int NA = KPL * D;
-    constexpr int KDP = 64 * KPL * D;
+    constexpr int KMAX = KB > 0 ? 16 * KB : 64 * KPL;
+    constexpr int KDP = KMAX * D;
     extern __shared__ float s_tile[];
-    __shared__ double s_acc[64][NA];
+    __shared__ double s_acc[KB > 0 ? 1 : 64][NA];
     __shared__ LShared ls;
     __shared__ double s_v[KDP], s_g[KDP];  // the reducer's own codewords are the live ones
-    __shared__ double s_rn[64 * KPL];      // 1/(tau n_j), zero for an empty cluster
+    __shared__ double s_rn[KMAX];          // 1/(tau n_j), zero for an empty cluster
     __shared__ float s_Cf[KDP], s_Hs[KDP], s_Hv[KDP], s_Ff[KDP];
-    __shared__ unsigned int s_new[KDP + 64 * KPL];
+    __shared__ unsigned int s_new[KDP + KMAX];
+    __shared__ float s_rpart[KB > 0 ? NT / 64 : 1][KB > 0 ? KDP : 1];  // row form: totals of the wavefronts
     __shared__ int s_done, s_iters, s_conv, s_attempt, s_grow, s_halv, s_bad, s_restart;
     __shared__ double s_alpha, s_prev, s_vnorm, s_res;
 
@@ -463,6 +507,8 @@ __device__ __forceinline__ void persist_lane_bwd_body(const Args& a, const PArgs
         s_Hs[i] = 0.f;
         s_Hv[i] = 0.f;
     }
+    if (KB > 0)
+        for (int i = kd + tid; i < KDP; i += NT) s_Cf[i] = s_Ff[i] = s_Hs[i] = 0.f;
     for (int j = tid; j < k; j += NT) {
         const double n = a.nd[j];
         s_rn[j] = (n > 0.0) ? (double)a.inv_tau / n : 0.0;
@@ -550,6 +596,15 @@ __device__ __forceinline__ void persist_lane_bwd_body(const Args& a, const PArgs
             }
             __syncthreads();
             publish_matrix();
+        } else if constexpr (KB > 0) {
+            {
+                RowWave<KB, D, DIST, PASS_B1> st;
+                st.init(k, s_Cf, s_Hs, s_Ff, a.escale);
+                row_tile_pass<KB, D, DIST, PASS_B1, NT>(a, st, s_w, s_gt, base, cnt);
+                st.collect(s_rpart[tid >> 6]);
+            }
+            __syncthreads();
+            publish_parts<NT / 64>(pa, seq, &s_rpart[0][0], KDP, kd);
         } else {
             LaneWave<KPL, D, DIST, PASS_B1> st;
             st.init(k, s_Cf, s_Hs, s_Ff, a.escale);
@@ -603,6 +658,15 @@ __device__ __forceinline__ void persist_lane_bwd_body(const Args& a, const PArgs
             }
             __syncthreads();
             publish_matrix();
+        } else if constexpr (KB > 0) {
+            {
+                RowWave<KB, D, DIST, PASS_B2> st;
+                st.init(k, s_Cf, s_Hs, s_Ff, a.escale);
+                row_tile_pass<KB, D, DIST, PASS_B2, NT>(a, st, s_w, s_gt, base, cnt);
+                st.collect(s_rpart[tid >> 6]);
+            }
+            __syncthreads();
+            publish_parts<NT / 64>(pa, seq, &s_rpart[0][0], KDP, kd);
         } else {
             LaneWave<KPL, D, DIST, PASS_B2> st;
             st.init(k, s_Cf, s_Hs, s_Ff, a.escale);
@@ -695,6 +759,10 @@ __device__ __forceinline__ void persist_lane_bwd_body(const Args& a, const PArgs
         MfmaB3<KPL> st;
         st.init(s_tab0, s_fac0, s_hsb, s_hq, s_hc, s_mu);
         mfma_b3_tile_pass<KPL, DIST, NT>(st, s_tile, s_wn, s_gt, a.dW_out + base * D, cnt, a.escale, a.inv_tau, fold);
+    } else if constexpr (KB > 0) {
+        RowWave<KB, D, DIST, PASS_B3> st;
+        st.init(k, s_Cf, s_Hs, s_Ff, a.escale);
+        row_tile_pass<KB, D, DIST, PASS_B3, NT>(a, st, s_w, s_gt, base, cnt);
     } else {
         LaneWave<KPL, D, DIST, PASS_B3> st;
         st.init(k, s_Cf, s_Hs, s_Ff, a.escale);
@@ -793,6 +861,40 @@ __global__ __launch_bounds__(LT) void persist_lane_bwd_batch(const BatchItem* it
     pa.wg = (int)blockIdx.x - it.wg_begin;
     pa.G = it.wg_count;
     persist_lane_bwd_body<KPL, D, DIST>(a, pa);
+}
+
+// The row <-> vector form (d = 1 and 2, up to 16 KB codewords).
+template <int KB, int D, int DIST>
+__global__ __launch_bounds__(RT) void persist_row_fwd(const Args a, const PArgs pa_in) {
+    PArgs pa = pa_in;
+    pa.wg = blockIdx.x;
+    pa.G = gridDim.x;
+    persist_lane_fwd_body<1, D, DIST, RT, false, KB>(a, pa);
+}
+template <int KB, int D, int DIST>
+__global__ __launch_bounds__(RT) void persist_row_fwd_batch(const BatchItem* items, const unsigned short* item_of_wg) {
+    const BatchItem& it = items[item_of_wg[blockIdx.x]];
+    const Args a = it.a;
+    PArgs pa = it.p;
+    pa.wg = (int)blockIdx.x - it.wg_begin;
+    pa.G = it.wg_count;
+    persist_lane_fwd_body<1, D, DIST, RT, false, KB>(a, pa);
+}
+template <int KB, int D, int DIST>
+__global__ __launch_bounds__(RT) void persist_row_bwd(const Args a, const PArgs pa_in) {
+    PArgs pa = pa_in;
+    pa.wg = blockIdx.x;
+    pa.G = gridDim.x;
+    persist_lane_bwd_body<1, D, DIST, RT, false, KB>(a, pa);
+}
+template <int KB, int D, int DIST>
+__global__ __launch_bounds__(RT) void persist_row_bwd_batch(const BatchItem* items, const unsigned short* item_of_wg) {
+    const BatchItem& it = items[item_of_wg[blockIdx.x]];
+    const Args a = it.a;
+    PArgs pa = it.p;
+    pa.wg = (int)blockIdx.x - it.wg_begin;
+    pa.G = it.wg_count;
+    persist_lane_bwd_body<1, D, DIST, RT, false, KB>(a, pa);
 }
 
 }  // namespace idkm

@@ -159,25 +159,6 @@ __device__ __forceinline__ void st_word_die(unsigned long long* p, unsigned long
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
-// Sum over the four lanes l % 16 + 16 r of a wavefront (one lane of each row of 16), in every lane.
-// v_permlane16_swap exchanges the odd rows of its first operand with the even rows of its second, v_permlane32_swap
-// the upper half of the first with the lower half of the second; adding the two results pairs every lane with its
-// partner, and both partners add the same two numbers (in either order: the same sum).
-__device__ __forceinline__ float cross_row_sum(float x) {
-    u32x2_t s = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    x = __uint_as_float(s[0]) + __uint_as_float(s[1]);
-    s = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return __uint_as_float(s[0]) + __uint_as_float(s[1]);
-}
-__device__ __forceinline__ double cross_row_sum_d(double x) {
-    u32x2_t lo = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(x), (unsigned)__double2loint(x), false, false);
-    u32x2_t hi = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(x), (unsigned)__double2hiint(x), false, false);
-    x = __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
-    lo = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(x), (unsigned)__double2loint(x), false, false);
-    hi = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(x), (unsigned)__double2hiint(x), false, false);
-    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
-}
 // Row totals of accumulators [OFF, NACC) into xs.rpart, taken in power-of-two pieces, largest first (80 sums are a
 // piece of 64 and one of 16, not one of 128 padded with zeros: the exchange network costs about three instructions
 // per value it starts with).
