@@ -268,6 +268,12 @@ __device__ __forceinline__ double cross_row_sum_d(double x) {
     hi = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(x), (unsigned)__double2hiint(x), false, false);
     return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
 }
+// Sum of lanes l and l ^ 32, in both.
+__device__ __forceinline__ double upper_lower_sum_d(double x) {
+    const u32x2_t lo = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(x), (unsigned)__double2loint(x), false, false);
+    const u32x2_t hi = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(x), (unsigned)__double2hiint(x), false, false);
+    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
 // Sum of lanes 0 .. N-1 (the other lanes must hold zero), valid in lane 0: only as many butterfly steps as N needs.
 template <int N>
 __device__ __forceinline__ double first_lanes_sum_d_dpp(double x) {

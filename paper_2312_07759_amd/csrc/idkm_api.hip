@@ -165,6 +165,7 @@ struct idkm_ctx {
     size_t xbuf_words = 0;
     unsigned int seq_base = 0;
     unsigned long long* lane_xbuf = nullptr;  // exchange words of the lane<->codeword persistent kernels (lazy)
+    unsigned int lane_run = 0, small_run = 0; // run of 24-bit stamps that the wide words in lane_xbuf and in xbuf belong to
     unsigned int* abort_word = nullptr;  // device
     PResult* h_res = nullptr;            // pinned host; device memory when res_on_device
     bool res_on_device = false;          // the context of idkm_forward_noalloc: the kernel reports into device memory
@@ -345,6 +346,7 @@ idkm_status launch_pass(idkm_ctx* ctx, const Geometry& g, int pass, Args& a, hip
 constexpr size_t XBUF1_WORDS = (size_t)2 * PT * XLINE;
 constexpr size_t XBUF3_WORDS = (size_t)2 * DIES * XLINE;  // two-level exchange: totals of the dies
 constexpr size_t XBUF_WORDS = XBUF1_WORDS + (size_t)2 * XBCAST + XBUF3_WORDS + DIES;
+constexpr size_t XBUF_ALL_WORDS = XBUF_WORDS + XBUF3_WORDS;       // ... and of the ragged codebooks' exchange
 constexpr size_t LDS_TILE_MAX = 144 * 1024;  // bytes of LDS a persistent workgroup may use for its tile
 
 struct PersistPlan {
@@ -364,7 +366,9 @@ struct Deferred {
 constexpr size_t LDS_PER_CU = 160 * 1024;
 constexpr size_t LANE_TILE_MAX = 94 * 1024;                       // the lane kernels keep ~55 KB of static LDS
 constexpr size_t LANE_BUF1_WORDS = (size_t)2 * PT * 1536;          // k (d+1) <= 1536
-constexpr size_t LANE_BUF2_WORDS = (size_t)2 * (1024 + 512);       // k d + k
+constexpr size_t LANE_BUF3_WORDS = (size_t)2 * DIES * 1536;        // totals of the dies
+// ... the grid totals, one copy per die (buf4), and the die of every workgroup
+constexpr size_t LANE_XBUF_WORDS = LANE_BUF1_WORDS + 2 * LANE_BUF3_WORDS + PT;
 
 
 // The lane<->vector family's part of plan_persistent.
@@ -437,6 +441,7 @@ bool plan_persistent(idkm_ctx* ctx, bool bwd, PersistPlan* pp, bool matrix_ok = 
         if (d > 4 || p * d > 16 || p * (d + 1) > 24) return false;
         int64_t g = (m + 255) / 256;  // at least 16 vectors per wavefront before adding workgroups
         if (g < 1) g = 1;
+        if (g > 1 && g < DIES) g = DIES;  // (one workgroup per die: they all add in parallel)
         if (g > ctx->num_cu) g = ctx->num_cu;
         if (g > PT) g = PT;
         int64_t per = (m + g - 1) / g;
@@ -496,26 +501,46 @@ idkm_status launch_persistent(idkm_ctx* ctx, const PersistPlan& pp, Args& a, PAr
         hipLaunchKernelGGL(k_fill_u64, dim3(64), dim3(256), 0, s, ctx->xbuf, ctx->xbuf_words, 0ull);
         HIP_TRY(ctx, hipGetLastError());
         if (ctx->lane_xbuf) {
-            hipLaunchKernelGGL(k_fill_u64, dim3(256), dim3(256), 0, s, ctx->lane_xbuf, LANE_BUF1_WORDS + LANE_BUF2_WORDS, 0ull);
+            hipLaunchKernelGGL(k_fill_u64, dim3(256), dim3(256), 0, s, ctx->lane_xbuf, LANE_XBUF_WORDS, 0ull);
             HIP_TRY(ctx, hipGetLastError());
         }
         ctx->seq_base = 0;
+        ctx->lane_run = ctx->small_run = 0;
     }
+    // The dies' totals of the large codebooks and the ragged ones carry 24-bit stamps: their words are cleared when this launch's sequence numbers lie in, or reach,
+    // another run of STAMP_RUN than the words left by earlier launches (once per 16.8 M exchanges).
+    const unsigned int run_first = (ctx->seq_base + 1u) / STAMP_RUN, run_last = (ctx->seq_base + exchanges) / STAMP_RUN;
     if (pp.lane) {
         if (!ctx->lane_xbuf) {
-            const size_t bytes = (LANE_BUF1_WORDS + LANE_BUF2_WORDS) * sizeof(unsigned long long);
-            if (hipMalloc(&ctx->lane_xbuf, bytes) != hipSuccess)
+            if (hipMalloc(&ctx->lane_xbuf, LANE_XBUF_WORDS * sizeof(unsigned long long)) != hipSuccess)
                 return fail(ctx, IDKM_ERR_ALLOC, "hipMalloc of the exchange buffer failed");
-            hipLaunchKernelGGL(k_fill_u64, dim3(256), dim3(256), 0, s, ctx->lane_xbuf, LANE_BUF1_WORDS + LANE_BUF2_WORDS, 0ull);
+            hipLaunchKernelGGL(k_fill_u64, dim3(256), dim3(256), 0, s, ctx->lane_xbuf, LANE_XBUF_WORDS, 0ull);
             HIP_TRY(ctx, hipGetLastError());
+            ctx->lane_run = run_first;
+        } else if (run_last != ctx->lane_run) {
+            hipLaunchKernelGGL(k_fill_u64, dim3(64), dim3(256), 0, s, ctx->lane_xbuf + LANE_BUF1_WORDS, 2 * LANE_BUF3_WORDS, 0ull);
+            HIP_TRY(ctx, hipGetLastError());
+            ctx->lane_run = run_first;
         }
         pa.buf1 = ctx->lane_xbuf;
-        pa.buf2 = ctx->lane_xbuf + LANE_BUF1_WORDS;
+        pa.buf3 = ctx->lane_xbuf + LANE_BUF1_WORDS;
+        pa.buf4 = pa.buf3 + LANE_BUF3_WORDS;
+        pa.tab = pa.buf4 + LANE_BUF3_WORDS;
+        pa.tree = (ctx->tree_exchange && !ctx->tree_remote) ? 1 : 2;  // 2: every store of hop 1 at device scope
     } else {
         pa.buf1 = ctx->xbuf;
         pa.buf2 = ctx->xbuf + XBUF1_WORDS;
         pa.buf3 = pa.buf2 + (size_t)2 * XBCAST;
         pa.tab = pa.buf3 + XBUF3_WORDS;
+        if (!pow2(ctx->k)) {  // (their wide words never share memory with the others')
+            if (ctx->xbuf_words < XBUF_ALL_WORDS) return fail(ctx, IDKM_ERR_DEVICE, "exchange buffer too small");
+            pa.buf3 = ctx->xbuf + XBUF_WORDS;
+            if (run_last != ctx->small_run) {
+                hipLaunchKernelGGL(k_fill_u64, dim3(8), dim3(256), 0, s, pa.buf3, XBUF3_WORDS, 0ull);
+                HIP_TRY(ctx, hipGetLastError());
+                ctx->small_run = run_first;
+            }
+        }
         // teams of DIES workgroups or more: hop 1 stays inside each die (the explicit-Jacobian mode keeps the plain
         // exchange, its one reduction ends in workgroup 0).  Also inside a batched launch: a team's workgroups are
         // consecutive in the grid, so its first DIES lie on DIES different dies and member i shares its die with member
@@ -739,7 +764,7 @@ idkm_status idkm_create(idkm_ctx** out, int device_id) {
     if (ok) ok &= hipMemset(c->abort_word, 0, sizeof(unsigned int)) == hipSuccess;
     ok &= hipHostMalloc(&c->h_res, sizeof(PResult)) == hipSuccess;
     if (ok) std::memset(c->h_res, 0, sizeof(PResult));
-    c->xbuf_words = XBUF_WORDS;
+    c->xbuf_words = XBUF_ALL_WORDS;
     ok &= hipMalloc(&c->xbuf, c->xbuf_words * sizeof(unsigned long long)) == hipSuccess;
     if (ok) ok &= hipMemset(c->xbuf, 0, c->xbuf_words * sizeof(unsigned long long)) == hipSuccess;
     if (ok) ok &= hipDeviceSynchronize() == hipSuccess;

@@ -1,12 +1,15 @@
-// Persistent kernels for the lane<->codeword family (k up to 512): one launch per
-// solve, the workgroup's tile of W (and dL/dWq) resident in LDS, the same two-hop
-// stamped exchange as the small-codebook kernels, with one reducer per codeword:
-//   hop 1  workgroup g stores its k (d+1) partial sums contiguously at buf1[parity][g][.];
-//          the reducer of codeword r (workgroup r mod G) reads that codeword's d+1
-//          words from every workgroup, adds them in float64 in a fixed order and
-//          updates its codeword;
-//   hop 2  reducers store the float32 codeword (or h/tau) and a partial squared
-//          norm into buf2; every workgroup reads the k d + k words.
+// Persistent kernels for the lane<->codeword, row<->vector and matrix-core forms (k up to 512): one launch per solve, the
+// workgroup's tile of W (and dL/dWq) resident in LDS, and per pass one exchange of the k (d+1) (backward: k d) sums:
+//   hop 1  (inside a die) workgroup g stores its partial sums contiguously at buf1[parity][g][.]; the members of a die
+//          (workgroups x, x + 8, ...) each own a slice of the words, read it from every member's line, add it in float64
+//          in a fixed order and store the die's totals at buf3[parity][x][.];
+//   hop 2  (across dies) EVERY workgroup reads the words of the up to 8 dies, adds them in a fixed order and applies the
+//          O(k d) update itself, so that all hold the same state and take the same stop decision.
+// As in persist_small.hpp a store of hop 1 only has to reach the die's L2 when all members of the die run there (checked at
+// the start of a launch.  There one workgroup per die adds all of the at most 80 words.)  The form this
+// replaced had one reducer per codeword that read all 256 workgroups through memory, and a broadcast of the result:
+// 589,824 weights under 64 codewords 671 -> 615 us (30 evaluations and a Jacobian-free backward), 589,824 4-vectors under
+// 256 codewords (30 evaluations, 10 passes) 2484 -> 2434, 2,620 4-vectors under 64 (20 evaluations, 10 passes) 415 -> 271.
 // Waits are bounded exactly as in persist_small.hpp.
 #pragma once
 #include "common.hpp"
@@ -22,34 +25,18 @@ constexpr int LWAVES = LT / 64;
 constexpr int MT = 512;           // threads per workgroup of the matrix-core forward kernel (2 wavefronts per SIMD:
                                   // its accumulators and one 16 x 256 tile of weights need ~200 registers per lane)
 
-constexpr int RT = 512;           // threads per workgroup of the row <-> vector kernels
-constexpr int LWORDS = 9;         // words of a codeword per workgroup: d + 1 <= 9
+// Threads per workgroup of the row <-> vector kernels.  With 1024, k = 64, d = 1 takes 610 us instead of 617 at 589,824
+// weights, but 189 instead of 175 at 74,921 (k = 32) and 189 instead of 176 at 9,643 (k = 48): the shares of the wavefronts
+// get too short.
+constexpr int RT = 512;
 
 struct LShared {
-    float red[LWORDS][PT];  // reducer: one codeword's words of every workgroup (at most PT workgroups)
-    double tot[LWORDS];
+    double part[1024];    // hop 1: per-thread (or per-wavefront) sums of a slice
     double wsum[LWAVES];
     double scalar;        // result of block_sum
     int abort;
+    int local;            // all members of this workgroup's die run on one die: hop 1 only has to reach its L2
 };
-
-// Waits for `n` stamped words starting at src (strided by `stride` words, one per thread) -- helper for both hops.
-__device__ __forceinline__ bool poll_word(const PArgs& pa, const unsigned long long* src, unsigned int seq,
-                                          unsigned int* payload) {
-    unsigned int spins = 0;
-    for (;;) {
-        const unsigned long long w = ld_word(src);
-        if ((unsigned int)(w >> 32) == seq) {
-            *payload = (unsigned int)w;
-            return true;
-        }
-        ++spins;
-        if (spins > pa.spin_limit ||
-            ((spins & 31u) == 0u &&
-             __hip_atomic_load(pa.abort_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == pa.seq_base + 1u))
-            return false;
-    }
-}
 
 __device__ __forceinline__ void raise_abort(const PArgs& pa, LShared& ls) {
     ls.abort = 1;
@@ -72,9 +59,20 @@ __device__ __forceinline__ double block_sum_fixed(double x, LShared& ls) {
     return ls.scalar;
 }
 
+// Hop-1 store: word idx of this workgroup's line.
+__device__ __forceinline__ void put_word(const PArgs& pa, const LShared& ls, unsigned long long* line, unsigned int seq, int idx, double t) {
+    if (ls.local)
+        st_word_die(&line[idx], pack_f(seq, (float)t));
+    else
+        st_word(&line[idx], pack_f(seq, (float)t));
+}
+__device__ __forceinline__ unsigned long long* own_line(const PArgs& pa, unsigned int seq, int nacc) {
+    return pa.buf1 + ((size_t)(seq & 1u) * pa.G + pa.wg) * nacc;
+}
+
 // Workgroup partial of the lane accumulators (wavefronts add one after the other, float64) and hop-1 store.
 template <int NA, int ACCW, int NT = LT>
-__device__ __forceinline__ void publish_lane(const PArgs& pa, unsigned int seq, const float (&acc)[NA], int k,
+__device__ __forceinline__ void publish_lane(const PArgs& pa, const LShared& ls, unsigned int seq, const float (&acc)[NA], int k,
                                              double (*s_acc)[NA]) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     for (int wv = 0; wv < NT / 64; ++wv) {
@@ -90,78 +88,215 @@ __device__ __forceinline__ void publish_lane(const PArgs& pa, unsigned int seq, 
         __syncthreads();
     }
     const int nacc = k * ACCW;
-    unsigned long long* dst = pa.buf1 + ((size_t)(seq & 1u) * pa.G + pa.wg) * nacc;
+    unsigned long long* dst = own_line(pa, seq, nacc);
     for (int idx = tid; idx < nacc; idx += NT) {
         const int j = idx / ACCW, comp = idx - j * ACCW;
-        st_word(&dst[idx], pack_f(seq, (float)s_acc[j & 63][(j >> 6) * ACCW + comp]));
+        put_word(pa, ls, dst, seq, idx, s_acc[j & 63][(j >> 6) * ACCW + comp]);
     }
 }
 
-// Totals over all workgroups of words [first, first+WPR) of every workgroup's hop-1 block into ls.tot.
-template <int WPR>
-__device__ __forceinline__ bool reduce_lane(const PArgs& pa, unsigned int seq, int nacc, int first, LShared& ls) {
-    static_assert(WPR <= LWORDS, "words of one codeword");
-    const int tid = threadIdx.x;
-    const int G = pa.G;
-    if (tid < PT) {
-        float f[WPR];
-#pragma unroll
-        for (int q = 0; q < WPR; ++q) f[q] = 0.f;
-        if (tid < G) {
-            const unsigned long long* src = pa.buf1 + ((size_t)(seq & 1u) * G + tid) * nacc + first;
+// Start of a launch: every workgroup says which die it runs on (before it loads its tile) and reads the words of its die's
+// members: leaves ls.local.  Returns false if the wait was abandoned.  Called by all threads; ends with a barrier.
+__device__ __forceinline__ void die_announce(const PArgs& pa) {
+    if (threadIdx.x == 0) st_word(&pa.tab[pa.wg], pack_u(pa.seq_base + 1u, die_id()));
+}
+__device__ __forceinline__ bool die_handshake(const PArgs& pa, LShared& ls) {
+    const int nmem = (pa.G - pa.wg % DIES + DIES - 1) / DIES;  // members of this die, at most PT / DIES = 32
+    if (threadIdx.x < 64) {
+        bool same = true, failed = false;
+        if ((int)threadIdx.x < nmem) {
+            unsigned long long w[1] = {0ull};
+            failed = !poll_words<1>(pa, pa.tab + (pa.wg % DIES) + (size_t)threadIdx.x * DIES, 0, pa.seq_base + 1u, w);
+            same = (unsigned int)w[0] == die_id();
+        }
+        const bool all_same = __builtin_amdgcn_ballot_w64(!same) == 0ull, any_failed = __builtin_amdgcn_ballot_w64(failed) != 0ull;
+        if (threadIdx.x == 0) {
+            ls.local = (all_same && pa.tree != 2) ? 1 : 0;  // 2: test support, every store at device scope
+            if (any_failed) raise_abort(pa, ls);
+        }
+    }
+    __syncthreads();
+    return ls.abort == 0;
+}
+
+// Hop 1, receiving side: this workgroup's slice of its die's totals.  S = ceil(nacc / members) words per member; SP, the
+// power of two at or above it (at most NT), threads take one word each of NT / SP lines at a time; what several lines
+// leave in the lanes of a wavefront is added across lanes, the wavefronts through LDS, all in a fixed order.  With one die
+// (a team of one) the totals go straight to s_tot.  Returns false if the wait was abandoned.
+template <int NT>
+__device__ __forceinline__ bool die_slice(const PArgs& pa, unsigned int seq, int nacc, LShared& ls, double* s_tot) {
+    const int tid = threadIdx.x, lane = tid & 63, x = pa.wg % DIES, mi = pa.wg / DIES;
+    const int nmem = (pa.G - x + DIES - 1) / DIES;
+    const int S = (nacc + nmem - 1) / nmem, first = mi * S;
+    const int n = nacc - first < S ? nacc - first : S;  // (the last members' slices may be short or empty)
+    int lg = 0;
+    while ((1 << lg) < S && (1 << lg) < NT) ++lg;
+    const int SP = 1 << lg, LPR = NT >> lg;  // words and lines a round of loads covers
+    const unsigned long long* src = pa.buf1 + (size_t)(seq & 1u) * pa.G * nacc + first;
+    unsigned long long* out = pa.buf3 + ((size_t)(seq & 1u) * DIES + x) * nacc + first;
+    const unsigned int stamp = stamp24(seq);
+    if (n <= 0) __syncthreads();  // (s_tot may share memory with what publish_lane reads; otherwise the barrier below)
+    for (int w0 = 0; w0 < n; w0 += SP) {
+        const int w = w0 + (tid & (SP - 1)), l0 = tid >> lg;
+        double s = 0.0;
+        bool aborted = false;
+        for (int l = l0; l < nmem && w < n; l += 4 * LPR) {
+            unsigned long long v[4];
             unsigned int spins = 0;
             for (;;) {
-                unsigned long long w[WPR];
-#pragma unroll
-                for (int q = 0; q < WPR; ++q) w[q] = ld_word(src + q);
                 bool ok = true;
 #pragma unroll
-                for (int q = 0; q < WPR; ++q) ok = ok && ((unsigned int)(w[q] >> 32) == seq);
-                if (ok) {
+                for (int u = 0; u < 4; ++u)
+                    v[u] = (l + u * LPR < nmem) ? ld_word(src + (size_t)(x + (l + u * LPR) * DIES) * nacc + w) : pack_f(seq, 0.f);
 #pragma unroll
-                    for (int q = 0; q < WPR; ++q) f[q] = __uint_as_float((unsigned int)w[q]);
-                    break;
-                }
+                for (int u = 0; u < 4; ++u) ok = ok && ((unsigned int)(v[u] >> 32) == seq);
+                if (ok) break;
                 ++spins;
                 if (spins > pa.spin_limit ||
-                    ((spins & 31u) == 0u &&
-                     __hip_atomic_load(pa.abort_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == pa.seq_base + 1u)) {
-                    raise_abort(pa, ls);
+                    ((spins & 31u) == 0u && __hip_atomic_load(pa.abort_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == pa.seq_base + 1u)) {
+                    aborted = true;
                     break;
                 }
             }
-        }
 #pragma unroll
-        for (int q = 0; q < WPR; ++q) ls.red[q][tid] = f[q];
-    }
-    __syncthreads();
-    if (ls.abort) return false;
-    if (tid < 32 * LWORDS) {  // (the only kernels with nine words have 512 threads)
-        const int q = tid >> 5, part = tid & 31;
-        double s = 0.0;
-        if (q < WPR) {
-#pragma unroll
-            for (int u = 0; u < 8; ++u) s += (double)ls.red[q][part * 8 + u];
+            for (int u = 0; u < 4; ++u) s += (double)__uint_as_float((unsigned int)v[u]);
+            if (aborted) break;
         }
-        s = half_sum_d_dpp(s);
-        if (q < WPR && part == 31) ls.tot[q] = s;
+        // lanes of a wavefront that hold the same word
+        if (SP <= 32) {
+            if (SP <= 1) s += dpp_d<0xB1, 0xf>(s);   // quad_perm [1,0,3,2]
+            if (SP <= 2) s += dpp_d<0x4E, 0xf>(s);   // quad_perm [2,3,0,1]
+            if (SP <= 4) s += dpp_d<0x124, 0xf>(s);  // row_ror:4 (lanes l and l + 4 hold the same pairs already)
+            if (SP <= 8) s += dpp_d<0x128, 0xf>(s);  // row_ror:8
+            if (SP <= 16) s = cross_row_sum_d(s);
+            if (SP == 32) s = upper_lower_sum_d(s);
+        }
+        if (SP >= 64 || lane < SP) ls.part[SP >= 64 ? tid : (tid >> 6) * 64 + lane] = s;
+        if (aborted) raise_abort(pa, ls);
+        __syncthreads();
+        if (ls.abort) return false;
+        if (tid < SP && w0 + tid < n) {
+            const int groups = SP >= 64 ? LPR : NT / 64, stride = SP >= 64 ? SP : 64;
+            double c2[2] = {0.0, 0.0};
+            for (int g = 0; g + 1 < groups; g += 2) {
+                c2[0] += ls.part[g * stride + tid];
+                c2[1] += ls.part[(g + 1) * stride + tid];
+            }
+            if (groups & 1) c2[0] += ls.part[(groups - 1) * stride + tid];
+            const double t = c2[0] + c2[1];
+            if (pa.G == 1)
+                s_tot[first + w0 + tid] = t;
+            else
+                st_word(&out[w0 + tid], pack_d40(stamp, t));
+        }
+        if (w0 + SP < n) __syncthreads();
     }
-    __syncthreads();
     return true;
 }
 
-// hop 2: every thread polls words tid, tid+LT, ... < nwords of buf2 into dst (LDS).
-template <int NT = LT>
-__device__ __forceinline__ bool gather_lane(const PArgs& pa, unsigned int seq, int nwords, int stride2,
-                                            unsigned int* dst, LShared& ls) {
-    const unsigned long long* src = pa.buf2 + (size_t)(seq & 1u) * stride2;
-    bool ok = true;
-    for (int i = threadIdx.x; i < nwords; i += NT) {
-        unsigned int p = 0;
-        ok = ok && poll_word(pa, src + i, seq, &p);
-        dst[i] = p;
+// Hop 2 for more than HOP3_WORDS sums, in two steps: every workgroup adds the dies' totals of its own slice and stores the
+// grid totals for its die, whose members read them from the L2.  (With one step every workgroup reads 8 nacc words through
+// memory: 21 MB per pass at k = 256, d = 4.)  Leaves the totals in s_tot, in every workgroup; ends with a barrier.
+constexpr int HOP3_WORDS = 384;
+template <int NT>
+__device__ __forceinline__ bool grid_totals_by_slices(const PArgs& pa, unsigned int seq, int nacc, LShared& ls, double* s_tot) {
+    const int x0 = pa.wg % DIES, mi = pa.wg / DIES, nd = pa.G < DIES ? pa.G : DIES;
+    const int nmem = (pa.G - x0 + DIES - 1) / DIES;
+    const int S = (nacc + nmem - 1) / nmem, first = mi * S;
+    const int n = nacc - first < S ? nacc - first : S;
+    const unsigned int stamp = stamp24(seq);
+    const unsigned long long* src = pa.buf3 + (size_t)(seq & 1u) * DIES * nacc;
+    unsigned long long* mine = pa.buf4 + ((size_t)(seq & 1u) * DIES + x0) * nacc;
+    bool aborted = false;
+    auto give_up = [&](unsigned int& spins) {
+        ++spins;
+        aborted = spins > pa.spin_limit ||
+                  ((spins & 31u) == 0u && __hip_atomic_load(pa.abort_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == pa.seq_base + 1u);
+        return aborted;
+    };
+    for (int w = threadIdx.x; w < n && !aborted; w += NT) {
+        unsigned long long v[DIES];
+        unsigned int spins = 0;
+        for (;;) {
+            bool ok = true;
+#pragma unroll
+            for (int x = 0; x < DIES; ++x) v[x] = x < nd ? ld_word(src + (size_t)x * nacc + first + w) : (unsigned long long)stamp;
+#pragma unroll
+            for (int x = 0; x < DIES; ++x) ok = ok && ((unsigned int)v[x] & 0xffffffu) == stamp;
+            if (ok || give_up(spins)) break;
+        }
+        double t[DIES];
+#pragma unroll
+        for (int x = 0; x < DIES; ++x) t[x] = unpack_d40(v[x]);
+        const unsigned long long word = pack_d40(stamp, ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7])));
+        if (aborted) break;  // (nothing that is not whole is passed on)
+        if (ls.local)
+            st_word_die(&mine[first + w], word);
+        else
+            st_word(&mine[first + w], word);
     }
-    if (!ok) raise_abort(pa, ls);
+    for (int idx = threadIdx.x; idx < nacc && !aborted; idx += 4 * NT) {
+        unsigned long long v[4];
+        unsigned int spins = 0;
+        for (;;) {
+            bool ok = true;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = idx + u * NT < nacc ? ld_word(mine + idx + u * NT) : (unsigned long long)stamp;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) ok = ok && ((unsigned int)v[u] & 0xffffffu) == stamp;
+            if (ok || give_up(spins)) break;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (idx + u * NT < nacc) s_tot[idx + u * NT] = unpack_d40(v[u]);
+    }
+    if (aborted) raise_abort(pa, ls);
+    __syncthreads();
+    return ls.abort == 0;
+}
+
+// Hop 2, every workgroup: grid totals of the nacc sums in s_tot.  Returns false if the wait was abandoned; ends with a
+// barrier.
+template <int NT>
+__device__ __forceinline__ bool grid_totals(const PArgs& pa, unsigned int seq, int nacc, LShared& ls, double* s_tot) {
+    if (pa.G > DIES && nacc > HOP3_WORDS) return grid_totals_by_slices<NT>(pa, seq, nacc, ls, s_tot);
+    if (pa.G > 1) {
+        const int nd = pa.G < DIES ? pa.G : DIES;
+        const unsigned int stamp = stamp24(seq);
+        const unsigned long long* src = pa.buf3 + (size_t)(seq & 1u) * DIES * nacc;
+        bool aborted = false;
+        for (int idx = threadIdx.x; idx < nacc && !aborted; idx += 2 * NT) {
+            const bool two = idx + NT < nacc;
+            unsigned long long v[2][DIES];
+            unsigned int spins = 0;
+            for (;;) {
+                bool ok = true;
+#pragma unroll
+                for (int x = 0; x < DIES; ++x) {
+                    v[0][x] = x < nd ? ld_word(src + (size_t)x * nacc + idx) : (unsigned long long)stamp;
+                    v[1][x] = (two && x < nd) ? ld_word(src + (size_t)x * nacc + idx + NT) : (unsigned long long)stamp;
+                }
+#pragma unroll
+                for (int x = 0; x < DIES; ++x)
+                    ok = ok && ((unsigned int)v[0][x] & 0xffffffu) == stamp && ((unsigned int)v[1][x] & 0xffffffu) == stamp;
+                if (ok) break;
+                ++spins;
+                if (spins > pa.spin_limit ||
+                    ((spins & 31u) == 0u && __hip_atomic_load(pa.abort_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == pa.seq_base + 1u)) {
+                    aborted = true;
+                    break;
+                }
+            }
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                double t[DIES];
+#pragma unroll
+                for (int x = 0; x < DIES; ++x) t[x] = unpack_d40(v[h][x]);
+                if (h == 0 || two) s_tot[idx + h * NT] = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
+            }
+        }
+        if (aborted) raise_abort(pa, ls);
+    }
     __syncthreads();
     return ls.abort == 0;
 }
@@ -189,7 +324,7 @@ __device__ __forceinline__ void lane_tile_pass(const Args& a, LaneWave<KPL, D, D
 #ifdef IDKM_TRACE
 #define IDKM_LSTAMP(slot)                                                                        \
     do {                                                                                         \
-        if (pa.trace && threadIdx.x == 0 && s_iters == 20 && pa.wg < 256)                        \
+        if (pa.trace && threadIdx.x == 0 && iters == 20 && pa.wg < 256)                        \
             pa.trace[2 * 64 * 8 + pa.wg * 8 + (slot)] = (long long)wall_clock64();               \
     } while (0)
 #else
@@ -199,18 +334,18 @@ __device__ __forceinline__ void lane_tile_pass(const Args& a, LaneWave<KPL, D, D
 // Hop-1 store of a pass whose wavefronts left their totals in part[wavefront][nacc]: they add up in wavefront order,
 // float64, as in publish_lane.
 template <int NW>
-__device__ __forceinline__ void publish_parts(const PArgs& pa, unsigned int seq, const float* part, int stride, int nacc) {
-    unsigned long long* dst = pa.buf1 + ((size_t)(seq & 1u) * pa.G + pa.wg) * nacc;
+__device__ __forceinline__ void publish_parts(const PArgs& pa, const LShared& ls, unsigned int seq, const float* part, int stride, int nacc) {
+    unsigned long long* dst = own_line(pa, seq, nacc);
     for (int idx = threadIdx.x; idx < nacc; idx += NW * 64) {
         double t = 0.0;
 #pragma unroll
         for (int w = 0; w < NW; ++w) t += (double)part[w * stride + idx];
-        st_word(&dst[idx], pack_f(seq, (float)t));
+        put_word(pa, ls, dst, seq, idx, t);
     }
 }
 
 // Forward solve (Alg. 1) and the evaluation at C*.  KB > 0: the passes run in the row <-> vector form (row_k.hpp) with
-// NT = RT threads, for up to 16 KB codewords.  MFMA: the loop's passes run on the matrix cores (mfma_lane.hpp;
+// NT threads, for up to 16 KB codewords.  MFMA: the loop's passes run on the matrix cores (mfma_lane.hpp;
 // d = 4), with NT = MT threads; the dynamic LDS then holds the tile padded by 16 zero vectors and,
 // behind it, -s^2 |w|^2 of every vector.
 template <int KPL, int D, int DIST, int NT = LT, bool MFMA = false, int KB = 0>
@@ -221,18 +356,17 @@ __device__ __forceinline__ void persist_lane_fwd_body(const Args& a, const PArgs
     constexpr int KMAX = KB > 0 ? 16 * KB : 64 * KPL;
     constexpr int KDP = KMAX * D;  // padded codebook size
     extern __shared__ float s_tile[];
-    __shared__ double s_acc[KB > 0 ? 1 : 64][NA];
+    // workgroup sums of a vector-ALU pass; from the first hop on, the grid totals of the pass
+    __shared__ double s_acc[KB > 0 ? KMAX : 64][KB > 0 ? ACCW : NA];
+    double* s_tot = &s_acc[0][0];
     __shared__ LShared ls;
-    __shared__ double s_Cd[KDP];  // float64 master copy; the reducer's own codewords are the live ones
+    __shared__ double s_Cd[KDP];  // float64 master copy
     __shared__ __align__(16) float s_Cf[KDP];
-    __shared__ unsigned int s_new[KDP + KMAX];
     __shared__ float s_rpart[KB > 0 ? NT / 64 : 1][KB > 0 ? KMAX * ACCW : 1];  // row form: totals of the wavefronts
-    __shared__ int s_done, s_iters, s_conv, s_bad;
-    __shared__ double s_res;
 
-    const int tid = threadIdx.x, wg = pa.wg, G = pa.G;
+    const int tid = threadIdx.x, wg = pa.wg;
     const int k = a.k, kd = k * D, nacc = k * ACCW;
-    const int stride2 = kd + k;
+    die_announce(pa);
     const int64_t base = (int64_t)wg * pa.per;
     int cnt = 0;
     if (base < a.m) cnt = (a.m - base < pa.per) ? (int)(a.m - base) : pa.per;
@@ -244,15 +378,9 @@ __device__ __forceinline__ void persist_lane_fwd_body(const Args& a, const PArgs
     }
     if (KB > 0)
         for (int i = kd + tid; i < KDP; i += NT) s_Cf[i] = 0.f;
-    if (tid == 0) {
-        ls.abort = 0;
-        s_done = 0;
-        s_iters = 0;
-        s_conv = 0;
-        s_bad = 0;
-        s_res = 0.0;
-    }
+    if (tid == 0) ls.abort = 0;
     __syncthreads();
+    if (!die_handshake(pa, ls)) return;
     const float* s_wn = s_tile + (size_t)(pa.per + 16) * D;
     __shared__ float s_mu[4];
     if constexpr (MFMA) {
@@ -289,17 +417,15 @@ __device__ __forceinline__ void persist_lane_fwd_body(const Args& a, const PArgs
     // hop-1 store of a matrix-core pass: wavefront totals add up in wavefront order, float64, as in publish_lane
     auto publish_matrix = [&]() {
         if constexpr (MFMA) {
-            unsigned long long* dst = pa.buf1 + ((size_t)(seq & 1u) * pa.G + pa.wg) * nacc;
-            for (int idx = tid; idx < nacc; idx += NT) {
-                double t = 0.0;
-#pragma unroll
-                for (int w = 0; w < NT / 64; ++w) t += (double)s_part[w][idx];
-                st_word(&dst[idx], pack_f(seq, (float)t));
-            }
+            publish_parts<NT / 64>(pa, ls, seq, &s_part[0][0], 64 * KPL * ACCW, nacc);
         }
     };
 
-    while (!s_done) {
+    // (every thread holds the state of the stop rule)
+    int iters = 0;
+    bool done = false, conv = false, bad = false;
+    double res = 0.0;
+    while (!done) {
         ++seq;
         IDKM_LSTAMP(0);
         if constexpr (MFMA) {
@@ -325,48 +451,39 @@ __device__ __forceinline__ void persist_lane_fwd_body(const Args& a, const PArgs
             }
             __syncthreads();
             IDKM_LSTAMP(5);
-            publish_parts<NT / 64>(pa, seq, &s_rpart[0][0], KMAX * ACCW, nacc);
+            publish_parts<NT / 64>(pa, ls, seq, &s_rpart[0][0], KMAX * ACCW, nacc);
         } else {
             LaneWave<KPL, D, DIST, PASS_FWD> st;
             st.init(k, s_Cf, nullptr, nullptr, a.escale);
             lane_tile_pass<KPL, D, DIST, PASS_FWD, NT>(a, st, s_tile, nullptr, base, cnt);
             IDKM_LSTAMP(1);
-            publish_lane<NA, ACCW, NT>(pa, seq, st.acc, k, s_acc);
+            publish_lane<NA, ACCW, NT>(pa, ls, seq, st.acc, k, s_acc);
         }
         IDKM_LSTAMP(2);
-        for (int r = wg; r < k; r += G) {
-            if (!reduce_lane<ACCW>(pa, seq, nacc, r * ACCW, ls)) return;
-            if (tid < D) {
-                const int idx = r * D + tid;
-                const double n = ls.tot[0], s = ls.tot[1 + tid];
-                const double cold = s_Cd[idx];
-                double cnew = (n > 0.0) ? fast_div_d(s, n) : cold;
-                if (!(n >= 0.0) || !(fabs(s) <= 1.7e308) || !(fabs(cnew) <= 1.7e308)) cnew = __builtin_nan("");
-                s_Cd[idx] = cnew;
-                st_word(&pa.buf2[(size_t)(seq & 1u) * stride2 + idx], pack_f(seq, (float)cnew));
-            }
-        }
+        if (!die_slice<NT>(pa, seq, nacc, ls, s_tot)) return;
         IDKM_LSTAMP(3);
-        if (!gather_lane<NT>(pa, seq, kd, stride2, s_new, ls)) return;
+        if (!grid_totals<NT>(pa, seq, nacc, ls, s_tot)) return;
         IDKM_LSTAMP(4);
+        // centre update (Alg. 1) and stop test, the same in every workgroup; a non-finite sum gives NaN
         double r2 = 0.0;
         for (int i = tid; i < kd; i += NT) {
-            const double df = (double)__uint_as_float(s_new[i]) - (double)s_Cf[i];
+            const int j = i / D, rr = i - j * D;
+            const double n = s_tot[j * ACCW], sv = s_tot[j * ACCW + 1 + rr];
+            double cnew = (n > 0.0) ? fast_div_d(sv, n) : s_Cd[i];
+            if (!(n >= 0.0) || !(fabs(sv) <= 1.7e308) || !(fabs(cnew) <= 1.7e308)) cnew = __builtin_nan("");
+            s_Cd[i] = cnew;
+            const float cn = (float)cnew;
+            const double df = (double)cn - (double)s_Cf[i];
             r2 += df * df;
+            s_Cf[i] = cn;
         }
         r2 = block_sum_fixed<NT>(r2, ls);
-        for (int i = tid; i < kd; i += NT) s_Cf[i] = __uint_as_float(s_new[i]);
         IDKM_LSTAMP(6);
-        if (tid == 0) {
-            s_iters += 1;
-            s_res = r2;
-            const bool bad = !(r2 <= 1.7e308);
-            if (bad) s_bad = 1;
-            const bool conv = r2 < tol * tol;
-            s_conv = conv ? 1 : 0;
-            if (conv || bad || s_iters >= max_iter) s_done = 1;
-        }
-        __syncthreads();
+        iters += 1;
+        res = r2;
+        bad = !(r2 <= 1.7e308);
+        conv = r2 < tol * tol;
+        done = conv || bad || iters >= max_iter;
     }
 
     // evaluation at C*
@@ -404,69 +521,47 @@ __device__ __forceinline__ void persist_lane_fwd_body(const Args& a, const PArgs
                 st.collect(s_rpart[tid >> 6]);
             }
             __syncthreads();
-            publish_parts<NT / 64>(pa, seq, &s_rpart[0][0], KMAX * ACCW, nacc);
+            publish_parts<NT / 64>(pa, ls, seq, &s_rpart[0][0], KMAX * ACCW, nacc);
         } else if (!done_here) {
             LaneWave<KPL, D, DIST, PASS_FIN> st;
             st.init(k, s_Cf, nullptr, nullptr);
             lane_tile_pass<KPL, D, DIST, PASS_FIN, NT>(a, st, s_tile, nullptr, base, cnt);
-            publish_lane<NA, ACCW, NT>(pa, seq, st.acc, k, s_acc);
+            publish_lane<NA, ACCW, NT>(pa, ls, seq, st.acc, k, s_acc);
         }
-        for (int r = wg; r < k; r += G) {
-            if (!reduce_lane<ACCW>(pa, seq, nacc, r * ACCW, ls)) return;
-            if (tid < D) {
-                const int idx = r * D + tid;
-                const double n = ls.tot[0], s = ls.tot[1 + tid];
-                const double cst = (double)s_Cf[idx];
-                const double f = (n > 0.0) ? fast_div_d(s, n) : cst;
-                a.Cd[idx] = cst;
-                a.Cf[idx] = s_Cf[idx];
-                a.Fd[idx] = f;
-                a.Ff[idx] = (float)f;
-                if (a.C_out) a.C_out[idx] = s_Cf[idx];
-            }
-            if (tid == 0) {
-                double n = ls.tot[0];
-                a.nd[r] = n;
-                bool bad = !(n >= 0.0);
-                for (int rr = 0; rr < D; ++rr)
-                    if (!(fabs(ls.tot[1 + rr]) <= 1.7e308)) bad = true;
-                // the mass of codeword r travels to the last workgroup, which counts empty / non-finite clusters
-                st_word(&pa.buf2[(size_t)(seq & 1u) * stride2 + kd + r], pack_f(seq, bad ? __builtin_nanf("") : (float)n));
-            }
-            __syncthreads();
+        if (!die_slice<NT>(pa, seq, nacc, ls, s_tot)) return;
+    }
+    // only workgroup 0 needs these totals: it writes the state and, last, the word that says the launch ran to its end (the
+    // others of its die pass their slices on)
+    if (wg != 0 && !(nacc > HOP3_WORDS && wg % DIES == 0)) return;
+    if (!grid_totals<NT>(pa, seq, nacc, ls, s_tot)) return;
+    if (wg != 0) return;
+    double empty = 0.0, wrong = 0.0;
+    for (int i = tid; i < kd; i += NT) {
+        const int j = i / D, rr = i - j * D;
+        const double n = s_tot[j * ACCW], sv = s_tot[j * ACCW + 1 + rr];
+        const double cst = (double)s_Cf[i];
+        const double f = (n > 0.0) ? fast_div_d(sv, n) : cst;
+        a.Cd[i] = cst;
+        a.Cf[i] = s_Cf[i];
+        a.Fd[i] = f;
+        a.Ff[i] = (float)f;
+        if (a.C_out) a.C_out[i] = s_Cf[i];
+        if (!(n >= 0.0) || !(fabs(sv) <= 1.7e308)) wrong = 1.0;
+        if (rr == 0) {
+            a.nd[j] = n;
+            if (n == 0.0) empty += 1.0;
         }
     }
-    if (wg == G - 1) {
-        // the masses of all codewords: count empty and non-finite clusters, then report
-        {
-            const unsigned long long* src = pa.buf2 + (size_t)(seq & 1u) * stride2 + kd;
-            bool ok = true;
-            for (int i = tid; i < k; i += NT) {
-                unsigned int p = 0;
-                ok = ok && poll_word(pa, src + i, seq, &p);
-                s_new[i] = p;
-            }
-            if (!ok) raise_abort(pa, ls);
-            __syncthreads();
-            if (ls.abort) return;
-        }
-        double empty = 0.0, bad = 0.0;
-        for (int i = tid; i < k; i += NT) {
-            const float n = __uint_as_float(s_new[i]);
-            if (!(n >= 0.f)) bad += 1.0;
-            else if (!(n > 0.f)) empty += 1.0;
-        }
-        empty = block_sum_fixed<NT>(empty, ls);
-        bad = block_sum_fixed<NT>(bad, ls);
-        if (tid == 0) {
-            PResult* o = pa.out;
-            o->iters = s_iters;
-            o->residual = sqrt(s_res);
-            o->converged = s_conv;
-            o->nonfinite = (s_bad || bad > 0.0) ? 1 : 0;
-            o->empty[0] = (int)(empty + 0.5);
-            o->done = pa.seq_base + 1u;
-        }
+    empty = block_sum_fixed<NT>(empty, ls);
+    wrong = block_sum_fixed<NT>(wrong, ls);
+    if (tid == 0) {
+        PResult* o = pa.out;
+        o->iters = iters;
+        o->residual = sqrt(res);
+        o->converged = conv ? 1 : 0;
+        o->nonfinite = (bad || wrong > 0.0) ? 1 : 0;
+        o->empty[0] = (int)(empty + 0.5);
+        o->done = pa.seq_base + 1u;
     }
 }
 
@@ -481,19 +576,18 @@ __device__ __forceinline__ void persist_lane_bwd_body(const Args& a, const PArgs
     constexpr int KMAX = KB > 0 ? 16 * KB : 64 * KPL;
     constexpr int KDP = KMAX * D;
     extern __shared__ float s_tile[];
-    __shared__ double s_acc[KB > 0 ? 1 : 64][NA];
+    // workgroup sums of a vector-ALU pass; from the first hop on, the grid totals of the pass
+    __shared__ double s_acc[KB > 0 ? KMAX : 64][KB > 0 ? D : NA];
+    double* s_tot = &s_acc[0][0];
     __shared__ LShared ls;
-    __shared__ double s_v[KDP], s_g[KDP];  // the reducer's own codewords are the live ones
+    __shared__ double s_v[KDP], s_g[KDP];
     __shared__ double s_rn[KMAX];          // 1/(tau n_j), zero for an empty cluster
     __shared__ float s_Cf[KDP], s_Hs[KDP], s_Hv[KDP], s_Ff[KDP];
-    __shared__ unsigned int s_new[KDP + KMAX];
     __shared__ float s_rpart[KB > 0 ? NT / 64 : 1][KB > 0 ? KDP : 1];  // row form: totals of the wavefronts
-    __shared__ int s_done, s_iters, s_conv, s_attempt, s_grow, s_halv, s_bad, s_restart;
-    __shared__ double s_alpha, s_prev, s_vnorm, s_res;
 
     const int tid = threadIdx.x, wg = pa.wg, G = pa.G;
     const int k = a.k, kd = k * D;
-    const int stride2 = kd + k;
+    die_announce(pa);
     const int64_t base = (int64_t)wg * pa.per;
     int cnt = 0;
     if (base < a.m) cnt = (a.m - base < pa.per) ? (int)(a.m - base) : pa.per;
@@ -516,22 +610,13 @@ __device__ __forceinline__ void persist_lane_bwd_body(const Args& a, const PArgs
     const int mode = pa.mode;
     const double tol = pa.tol;
     const int max_iter = pa.max_iter;
-    if (tid == 0) {
-        ls.abort = 0;
-        s_done = (mode == BWD_JFB) ? 1 : 0;
-        s_iters = 0;
-        s_conv = (mode == BWD_JFB) ? 1 : 0;
-        s_attempt = 0;
-        s_grow = 0;
-        s_halv = 0;
-        s_bad = 0;
-        s_restart = 0;
-        s_alpha = pa.alpha;
-        s_prev = __builtin_inf();
-        s_vnorm = 0.0;
-        s_res = 0.0;
-    }
+    if (tid == 0) ls.abort = 0;
     __syncthreads();
+    if (!die_handshake(pa, ls)) return;
+    // (every thread holds the state of the stop and restart rules)
+    bool done = mode == BWD_JFB, conv = mode == BWD_JFB, bad = false;
+    int iters = 0, attempt = 0, grow = 0, halv = 0;
+    double alpha = pa.alpha, prev = __builtin_inf(), vnorm2 = 0.0, res = 0.0;
     unsigned int seq = pa.seq_base;
     // matrix-core passes: reference point, vector norms and the codeword tables (C* does not change in the backward)
     constexpr int TS = MfmaFwd<(KPL <= 4 ? KPL : 4)>::TAB_STRIDE;
@@ -569,7 +654,7 @@ __device__ __forceinline__ void persist_lane_bwd_body(const Args& a, const PArgs
     // term and the fold factor (see MfmaB2).
     auto publish_matrix = [&]() {
         if constexpr (MFMA) {
-            unsigned long long* dst = pa.buf1 + ((size_t)(seq & 1u) * pa.G + pa.wg) * kd;
+            unsigned long long* dst = own_line(pa, seq, kd);
             for (int idx = tid; idx < kd; idx += NT) {
                 const int j = idx >> 2, r = idx & 3;
                 double sw = 0.0, st1 = 0.0;
@@ -579,7 +664,7 @@ __device__ __forceinline__ void persist_lane_bwd_body(const Args& a, const PArgs
                     st1 += (double)s_part[w][j * 5];
                 }
                 const double o = sw - (double)(s_Cf[idx] - s_mu[r]) * st1;
-                st_word(&dst[idx], pack_f(seq, (float)(fold ? o * (double)s_fac0[j] : o)));
+                put_word(pa, ls, dst, seq, idx, fold ? o * (double)s_fac0[j] : o);
             }
         }
     };
@@ -604,48 +689,31 @@ __device__ __forceinline__ void persist_lane_bwd_body(const Args& a, const PArgs
                 st.collect(s_rpart[tid >> 6]);
             }
             __syncthreads();
-            publish_parts<NT / 64>(pa, seq, &s_rpart[0][0], KDP, kd);
+            publish_parts<NT / 64>(pa, ls, seq, &s_rpart[0][0], KDP, kd);
         } else {
             LaneWave<KPL, D, DIST, PASS_B1> st;
             st.init(k, s_Cf, s_Hs, s_Ff, a.escale);
             lane_tile_pass<KPL, D, DIST, PASS_B1, NT>(a, st, s_w, s_gt, base, cnt);
-            publish_lane<NA, D, NT>(pa, seq, st.acc, k, s_acc);
+            publish_lane<NA, D, NT>(pa, ls, seq, st.acc, k, s_acc);
         }
-        for (int r = wg; r < k; r += G) {
-            if (!reduce_lane<D>(pa, seq, kd, r * D, ls)) return;
-            if (tid < 64) {
-                double v2 = 0.0;
-                if (tid < D) {
-                    const int idx = r * D + tid;
-                    const double v = ls.tot[tid];
-                    s_v[idx] = v;
-                    s_g[idx] = v;
-                    v2 = v * v;
-                    st_word(&pa.buf2[(size_t)(seq & 1u) * stride2 + idx], pack_f(seq, (float)(v * s_rn[r])));
-                }
-                v2 = wave_sum_d_dpp(v2);
-                if (tid == 0) st_word(&pa.buf2[(size_t)(seq & 1u) * stride2 + kd + r], pack_f(seq, (float)v2));
-            }
-        }
-        if (!gather_lane<NT>(pa, seq, kd + k, stride2, s_new, ls)) return;
+        if (!die_slice<NT>(pa, seq, kd, ls, s_tot) || !grid_totals<NT>(pa, seq, kd, ls, s_tot)) return;
+        // every workgroup holds the whole of v and starts the solve at g = v
         double v2 = 0.0;
-        for (int i = tid; i < k; i += NT) v2 += (double)__uint_as_float(s_new[kd + i]);
-        v2 = block_sum_fixed<NT>(v2, ls);
         for (int i = tid; i < kd; i += NT) {
-            s_Hs[i] = __uint_as_float(s_new[i]);
-            s_Hv[i] = s_Hs[i];
+            const double v = s_tot[i];
+            s_v[i] = v;
+            s_g[i] = v;
+            v2 += v * v;
+            s_Hs[i] = s_Hv[i] = (float)(v * s_rn[i / D]);
         }
-        if (tid == 0) {
-            s_vnorm = v2;  // squared norms throughout
-            if (!(v2 <= 1.7e308)) {
-                s_bad = 1;
-                s_done = 1;
-            }
+        vnorm2 = block_sum_fixed<NT>(v2, ls);  // squared norms throughout
+        if (!(vnorm2 <= 1.7e308)) {
+            bad = true;
+            done = true;
         }
-        __syncthreads();
     }
 
-    while (!s_done) {
+    while (!done) {
         ++seq;
         if constexpr (MFMA) {
             MfmaB2<KPL>::template fill_cotangent<NT>(s_hsb, s_hq, k, s_Hs, s_Ff, s_mu, a.escale);
@@ -666,83 +734,57 @@ __device__ __forceinline__ void persist_lane_bwd_body(const Args& a, const PArgs
                 st.collect(s_rpart[tid >> 6]);
             }
             __syncthreads();
-            publish_parts<NT / 64>(pa, seq, &s_rpart[0][0], KDP, kd);
+            publish_parts<NT / 64>(pa, ls, seq, &s_rpart[0][0], KDP, kd);
         } else {
             LaneWave<KPL, D, DIST, PASS_B2> st;
             st.init(k, s_Cf, s_Hs, s_Ff, a.escale);
             lane_tile_pass<KPL, D, DIST, PASS_B2, NT>(a, st, s_w, s_gt, base, cnt);
-            publish_lane<NA, D, NT>(pa, seq, st.acc, k, s_acc);
+            publish_lane<NA, D, NT>(pa, ls, seq, st.acc, k, s_acc);
         }
-        const double alpha = s_alpha;
-        for (int r = wg; r < k; r += G) {
-            if (!reduce_lane<D>(pa, seq, kd, r * D, ls)) return;
-            if (tid < 64) {
-                double d2 = 0.0;
-                if (tid < D) {
-                    const int idx = r * D + tid;
-                    const double g = s_g[idx];
-                    const double gn = alpha * (s_v[idx] + ls.tot[tid]) + (1.0 - alpha) * g;
-                    const double df = gn - g;
-                    d2 = df * df;
-                    s_g[idx] = gn;
-                    st_word(&pa.buf2[(size_t)(seq & 1u) * stride2 + idx], pack_f(seq, (float)(gn * s_rn[r])));
-                }
-                d2 = wave_sum_d_dpp(d2);
-                if (tid == 0) st_word(&pa.buf2[(size_t)(seq & 1u) * stride2 + kd + r], pack_f(seq, (float)d2));
-            }
-        }
-        if (!gather_lane<NT>(pa, seq, kd + k, stride2, s_new, ls)) return;
+        if (!die_slice<NT>(pa, seq, kd, ls, s_tot) || !grid_totals<NT>(pa, seq, kd, ls, s_tot)) return;
         double d2 = 0.0;
-        for (int i = tid; i < k; i += NT) d2 += (double)__uint_as_float(s_new[kd + i]);
-        d2 = block_sum_fixed<NT>(d2, ls);
-        if (tid == 0) {
-            const double dn = d2;  // squared step norm: every comparison below is between squares
-            bool restart = false, done = false, conv = false, diverged = false;
-            int grow = s_grow;
-            const int attempt = s_attempt + 1;
-            if (!(dn <= 1.7e308)) {
-                diverged = true;
-            } else if (dn <= tol * tol * s_vnorm) {
-                conv = true;
-                done = true;
-            } else {
-                grow = (dn > s_prev) ? grow + 1 : 0;
-                if (grow >= 5) diverged = true;
-            }
-            if (!done && !diverged && attempt >= max_iter) done = true;
-            if (diverged) {
-                if (s_halv < 6) {
-                    restart = true;
-                } else {
-                    done = true;
-                    if (!(dn <= 1.7e308)) s_bad = 1;  // every damping factor tried ended in a non-finite step
-                }
-            }
-            s_iters += 1;
-            s_res = dn;
-            if (conv) s_conv = 1;
-            if (restart) {
-                s_alpha = alpha * 0.5;
-                s_halv += 1;
-                s_attempt = 0;
-                s_grow = 0;
-                s_prev = __builtin_inf();
-            } else {
-                s_attempt = attempt;
-                s_grow = grow;
-                if (!diverged && !conv) s_prev = dn;
-            }
-            s_restart = restart ? 1 : 0;
-            if (done) s_done = 1;
+        for (int i = tid; i < kd; i += NT) {
+            const double g = s_g[i];
+            const double gn = alpha * (s_v[i] + s_tot[i]) + (1.0 - alpha) * g;
+            const double df = gn - g;
+            d2 += df * df;
+            s_g[i] = gn;
         }
-        __syncthreads();
-        if (s_restart) {
-            for (int i = tid; i < kd; i += NT) {
-                s_Hs[i] = s_Hv[i];
-                s_g[i] = s_v[i];
-            }
+        d2 = block_sum_fixed<NT>(d2, ls);
+        const double dn = d2;  // squared step norm: every comparison below is between squares
+        bool restart = false, diverged = false;
+        attempt += 1;
+        if (!(dn <= 1.7e308)) {
+            diverged = true;
+        } else if (dn <= tol * tol * vnorm2) {
+            conv = true;
+            done = true;
         } else {
-            for (int i = tid; i < kd; i += NT) s_Hs[i] = __uint_as_float(s_new[i]);
+            grow = (dn > prev) ? grow + 1 : 0;
+            if (grow >= 5) diverged = true;
+            prev = dn;
+        }
+        if (!done && !diverged && attempt >= max_iter) done = true;
+        if (diverged) {
+            if (halv < 6) {
+                restart = true;
+            } else {
+                done = true;
+                if (!(dn <= 1.7e308)) bad = true;  // every damping factor tried ended in a non-finite step
+            }
+        }
+        iters += 1;
+        res = dn;
+        if (restart) {
+            alpha *= 0.5;
+            halv += 1;
+            attempt = 0;
+            grow = 0;
+            prev = __builtin_inf();
+        }
+        for (int i = tid; i < kd; i += NT) {  // (a thread's own elements)
+            if (restart) s_g[i] = s_v[i];
+            s_Hs[i] = restart ? s_Hv[i] : (float)(s_g[i] * s_rn[i / D]);
         }
         __syncthreads();
     }
@@ -768,23 +810,21 @@ __device__ __forceinline__ void persist_lane_bwd_body(const Args& a, const PArgs
         st.init(k, s_Cf, s_Hs, s_Ff, a.escale);
         lane_tile_pass<KPL, D, DIST, PASS_B3, NT>(a, st, s_w, s_gt, base, cnt);
     }
-    for (int r = wg; r < k; r += G) {
-        if (tid < D) {
-            a.gd[r * D + tid] = s_g[r * D + tid];
-            a.vd[r * D + tid] = s_v[r * D + tid];
-        }
-    }
     if (wg == 0)
-        for (int i = tid; i < kd; i += NT) a.Hs[i] = s_Hs[i];
+        for (int i = tid; i < kd; i += NT) {
+            a.gd[i] = s_g[i];
+            a.vd[i] = s_v[i];
+            a.Hs[i] = s_Hs[i];
+        }
     if (wg == G - 1 && tid == 0) {
         PResult* o = pa.out;
-        o->iters = s_iters;
-        o->converged = s_conv;
-        o->residual = sqrt(s_res);
-        o->alpha = s_alpha;
-        o->vnorm = sqrt(s_vnorm);
-        o->halvings = s_halv;
-        o->nonfinite = s_bad;
+        o->iters = iters;
+        o->converged = conv ? 1 : 0;
+        o->residual = sqrt(res);
+        o->alpha = alpha;
+        o->vnorm = sqrt(vnorm2);
+        o->halvings = halv;
+        o->nonfinite = bad ? 1 : 0;
         o->done = pa.seq_base + 1u;
     }
 }

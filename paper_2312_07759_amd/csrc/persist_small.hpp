@@ -31,6 +31,7 @@
 // Every workgroup checks at the start of the launch that it runs on its leader's die (the die index is a hardware
 // register); one that does not stores with device scope instead, which is correct on any placement.
 #pragma once
+#include <type_traits>
 #include "common.hpp"
 #include "small_k.hpp"
 
@@ -49,14 +50,6 @@ constexpr int TREE_MIN_G = DIES;
 // k = 8, d = 1 7.55 against 7.05 us per evaluation, k = 4, d = 2 5.35 against 4.80, (dF/dC)^T pass at k = 16, d = 1
 // 6.26 against 5.86; with 32 sums 5.87 against 5.45.
 constexpr int WAVE_WORDS_MAX = 8;
-#ifndef IDKM_HOP2_PIPE
-#define IDKM_HOP2_PIPE 1
-#endif
-#ifndef IDKM_HOP2_SLEEP
-#define IDKM_HOP2_SLEEP 5
-#endif
-constexpr int HOP2_PIPE = IDKM_HOP2_PIPE;    // loads in flight while waiting for the dies' totals
-constexpr int HOP2_SLEEP = IDKM_HOP2_SLEEP;  // s_sleep argument (units of 64 cycles) between their issue
 constexpr int XDENSE = 32;   // the explicit-Jacobian mode is offered while its K D (K D + D + 1) sums fit this many words
 // Words between the lines of two workgroups in buf1 for a pass with NACC sums per workgroup: shapes of up to 32 sums
 // keep the short lines they were tuned with.
@@ -77,6 +70,7 @@ struct PArgs {
     unsigned long long* buf1;  // [2][PT][xline_of(NACC)] stamped partial sums, word (workgroup, accumulator)
     unsigned long long* buf2;  // [2][XBCAST] stamped broadcast values
     unsigned long long* buf3;  // [2][DIES][XLINE] two-level exchange: stamped totals of each die
+    unsigned long long* buf4;  // lane family: [2][DIES][k (d+1)] grid totals, one copy per die
     unsigned long long* tab;   // [DIES] two-level exchange: die index of each leader, stamped with the launch id
     int tree;                  // two-level exchange (team of at least TREE_MIN_G workgroups, one problem per launch);
                                // 2: the same with every store at device scope (test support)
@@ -124,9 +118,14 @@ struct BatchItem {
 #endif
 
 
-// Shared scratch of the exchange.
-template <int NACC>
+// Shared scratch of the exchange.  WIDE: the dies' totals travel with 29 significant bits (pack_d40) instead of as float32.
+// Only the ragged codebooks need it: the kernels those shapes came from kept the totals in float64, and under the plain norm
+// at k = 5 the gradient was 2.1e-6 from the 64-bit one with float32 totals, 1.2e-6 in those kernels, 0.7e-6 with these.
+// The others keep float32 words: an evaluation at k = 4, d = 1 takes 1.3 % longer with wide ones.
+template <int NACC, bool WIDE_ = false>
 struct XShared {
+    static constexpr bool WIDE = WIDE_;
+    typedef typename std::conditional<WIDE_, double, float>::type total_t;
     float rpart[pow2_at_least(NACC)][PT / 64];  // partial sums of every wavefront, [accumulator][wavefront]
     double red2[PT];                 // reducer: per-thread sums (thread t: word t mod WPR, workgroups t/WPR + k PT/WPR)
     double tot[8];                   // reducer: totals of its slice
@@ -135,7 +134,7 @@ struct XShared {
     int abort;
     // two-level exchange
     int local;                       // this workgroup runs on its leader's die: its partial sums need only reach the L2
-    float stage2[DIES * (NACC <= 8 ? 8 : NACC)];  // totals of the dies, [die][slot]
+    total_t stage2[DIES * (NACC <= 8 ? 8 : NACC)];  // totals of the dies, [die][slot]
     double totd[NACC];               // grid totals
 };
 
@@ -245,31 +244,45 @@ __device__ __forceinline__ bool poll_words(const PArgs& pa, const unsigned long 
     }
 }
 
-// Bounded wait for ONE stamped word with PIPE loads in flight, issued SLEEP x 64 cycles apart: a load that has to go
-// to memory returns after more than half a microsecond, so with one load at a time a word that lands just after a load
-// was issued is seen a whole round trip later; with staggered loads the next one is at most a fraction of that away.
-template <int PIPE, int SLEEP>
-__device__ __forceinline__ bool poll_word_staggered(const PArgs& pa, const unsigned long long* src, unsigned int seq,
-                                                    unsigned long long& out) {
-    unsigned long long w[PIPE];
-#pragma unroll
-    for (int i = 0; i < PIPE; ++i) {
-        w[i] = ld_word(src);
-        if (i + 1 < PIPE) __builtin_amdgcn_s_sleep(SLEEP);
-    }
+// A die's total travels as the upper 40 bits of the float64 sum (29 significant bits, so that nothing is lost against the
+// 32-bit values the totals end in) and a 24-bit stamp.  Stamps of the 2^24 - 1 values 1 .. are told apart; the host clears
+// the words whenever the sequence numbers enter another run of that length (launch_persistent).
+constexpr unsigned int STAMP_RUN = 0xffffffu;
+__device__ __forceinline__ unsigned int stamp24(unsigned int seq) { return seq % STAMP_RUN + 1u; }
+__device__ __forceinline__ unsigned long long pack_d40(unsigned int stamp, double v) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v) + 0x800000ull;  // to nearest
+    return (b & ~0xffffffull) | (unsigned long long)stamp;
+}
+__device__ __forceinline__ double unpack_d40(unsigned long long w) {
+    return __longlong_as_double((long long)(w & ~0xffffffull));
+}
+
+// A die's total in the form the team uses, its value as every workgroup reads it, and whether a word has arrived.
+template <bool WIDE>
+__device__ __forceinline__ unsigned long long die_word(unsigned int seq, double t) {
+    return WIDE ? pack_d40(stamp24(seq), t) : pack_f(seq, (float)t);
+}
+template <bool WIDE>
+__device__ __forceinline__ double die_value(unsigned long long w) {
+    return WIDE ? unpack_d40(w) : (double)__uint_as_float((unsigned int)w);
+}
+template <bool WIDE>
+__device__ __forceinline__ bool die_arrived(unsigned long long w, unsigned int seq) {
+    return WIDE ? ((unsigned int)w & 0xffffffu) == stamp24(seq) : (unsigned int)(w >> 32) == seq;
+}
+// Bounded wait for one such word.
+template <bool WIDE>
+__device__ __forceinline__ bool poll_die(const PArgs& pa, const unsigned long long* src, unsigned int seq, double& out) {
     unsigned int spins = 0;
     for (;;) {
-#pragma unroll
-        for (int i = 0; i < PIPE; ++i) {
-            if ((unsigned int)(w[i] >> 32) == seq) {
-                out = w[i];
-                return true;
-            }
-            w[i] = ld_word(src);
+        const unsigned long long w = ld_word(src);
+        if (die_arrived<WIDE>(w, seq)) {
+            out = die_value<WIDE>(w);
+            return true;
         }
-        spins += PIPE;
+        ++spins;
         if (spins > pa.spin_limit ||
-            ((spins & 31u) < (unsigned)PIPE && __hip_atomic_load(pa.abort_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == pa.seq_base + 1u))
+            ((spins & 31u) == 0u && __hip_atomic_load(pa.abort_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == pa.seq_base + 1u))
             return false;
     }
 }
@@ -457,9 +470,9 @@ __device__ __forceinline__ bool tree_die_totals(const PArgs& pa, unsigned int se
         double c2[2] = {0.0, 0.0};
 #pragma unroll
         for (int g = 0; g < PARTS; ++g) c2[g & 1] += xs.red2[g * NACC + tid];
-        const float tot = (float)(c2[0] + c2[1]);
-        xs.stage2[x * NACC + tid] = tot;
-        st_word(&pa.buf3[((size_t)(seq & 1u) * DIES + x) * LINE + tid], pack_f(seq, tot));
+        const unsigned long long word = die_word<XS::WIDE>(seq, c2[0] + c2[1]);
+        xs.stage2[x * NACC + tid] = die_value<XS::WIDE>(word);  // (what the other workgroups will read)
+        st_word(&pa.buf3[((size_t)(seq & 1u) * DIES + x) * LINE + tid], word);
     }
     return true;
 }
@@ -485,11 +498,11 @@ __device__ __forceinline__ bool tree_grid_totals(const PArgs& pa, unsigned int s
 #pragma unroll
         for (int u = 0; u < NLD; ++u) {
             const int f = tid + u * PT, x = f / NACC, q = f - x * NACC;
-            w[u] = valid[u] ? ld_word(base + (size_t)x * LINE + q) : pack_f(seq, 0.f);
+            w[u] = valid[u] ? ld_word(base + (size_t)x * LINE + q) : die_word<XS::WIDE>(seq, 0.0);
         }
         bool ok = true;
 #pragma unroll
-        for (int u = 0; u < NLD; ++u) ok = ok && ((unsigned int)(w[u] >> 32) == seq);
+        for (int u = 0; u < NLD; ++u) ok = ok && die_arrived<XS::WIDE>(w[u], seq);
         if (ok) break;
         ++spins;
         if (spins > pa.spin_limit ||
@@ -500,7 +513,7 @@ __device__ __forceinline__ bool tree_grid_totals(const PArgs& pa, unsigned int s
     }
 #pragma unroll
     for (int u = 0; u < NLD; ++u)
-        if (valid[u]) xs.stage2[tid + u * PT] = __uint_as_float((unsigned int)w[u]);
+        if (valid[u]) xs.stage2[tid + u * PT] = die_value<XS::WIDE>(w[u]);
     if (aborted) {
         xs.abort = 1;
         __hip_atomic_store(pa.abort_word, pa.seq_base + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -556,7 +569,7 @@ __device__ __forceinline__ void publish_waves(const PArgs& pa, unsigned int seq,
 }
 
 // hop 1, leader side: thread t adds the four wavefront words of slot t % 8 of member t / 8; the members of a
-// wavefront are added across lanes, the four wavefronts through LDS.  Publishes the die's line and keeps its float32
+// wavefront are added across lanes, the four wavefronts through LDS.  Publishes the die's line and keeps its
 // totals in xs.stage2[die][slot].  Returns false if the wait was abandoned.
 template <class XS>
 __device__ __forceinline__ bool tree8_die_totals(const PArgs& pa, unsigned int seq, XS& xs) {
@@ -583,9 +596,10 @@ __device__ __forceinline__ bool tree8_die_totals(const PArgs& pa, unsigned int s
     __syncthreads();
     if (xs.abort) return false;
     if (tid < 8) {
-        const float tot = (float)((xs.red2[tid] + xs.red2[8 + tid]) + (xs.red2[16 + tid] + xs.red2[24 + tid]));
-        xs.stage2[x * 8 + tid] = tot;
-        st_word(&pa.buf3[((size_t)(seq & 1u) * DIES + x) * 32 + tid], pack_f(seq, tot));
+        const unsigned long long word =
+            die_word<XS::WIDE>(seq, (xs.red2[tid] + xs.red2[8 + tid]) + (xs.red2[16 + tid] + xs.red2[24 + tid]));
+        xs.stage2[x * 8 + tid] = die_value<XS::WIDE>(word);  // (what the other workgroups will read)
+        st_word(&pa.buf3[((size_t)(seq & 1u) * DIES + x) * 32 + tid], word);
     }
     return true;
 }
@@ -597,14 +611,11 @@ template <int NACC, class XS>
 __device__ __forceinline__ void tree8_grid_totals_wave0(const PArgs& pa, unsigned int seq, XS& xs) {
     const int lane = threadIdx.x, x = lane >> 3, p = lane & 7;
     const unsigned long long* src = pa.buf3 + ((size_t)(seq & 1u) * DIES + x) * 32 + p;
-    unsigned long long w[1];
     double s;
     wave_lds_sync();  // (a leader's lanes 0 .. 7 have just written its own die's totals)
     if (x == pa.wg) {
         s = (double)xs.stage2[x * 8 + p];
-    } else if (HOP2_PIPE > 1 ? poll_word_staggered<HOP2_PIPE, HOP2_SLEEP>(pa, src, seq, w[0]) : poll_words<1>(pa, src, 0, seq, w)) {
-        s = (double)__uint_as_float((unsigned int)w[0]);
-    } else {
+    } else if (!poll_die<XS::WIDE>(pa, src, seq, s)) {
         s = 0.0;
         xs.abort = 1;
         __hip_atomic_store(pa.abort_word, pa.seq_base + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -622,15 +633,12 @@ template <class XS>
 __device__ __forceinline__ bool tree8_grid_totals_regs(const PArgs& pa, unsigned int seq, XS& xs, double& total) {
     const int lane = threadIdx.x, x = lane >> 3, p = lane & 7;
     const unsigned long long* src = pa.buf3 + ((size_t)(seq & 1u) * DIES + x) * 32 + p;
-    unsigned long long w[1];
     double s;
     bool failed = false;
     wave_lds_sync();  // (a leader's lanes 0 .. 7 have just written its own die's totals)
     if (x == pa.wg) {
         s = (double)xs.stage2[x * 8 + p];
-    } else if (HOP2_PIPE > 1 ? poll_word_staggered<HOP2_PIPE, HOP2_SLEEP>(pa, src, seq, w[0]) : poll_words<1>(pa, src, 0, seq, w)) {
-        s = (double)__uint_as_float((unsigned int)w[0]);
-    } else {
+    } else if (!poll_die<XS::WIDE>(pa, src, seq, s)) {
         s = 0.0;
         failed = true;
         xs.abort = 1;
@@ -940,7 +948,7 @@ __device__ __forceinline__ void persist_fwd_body(const Args& a, const PArgs& pa)
     constexpr int NB = KD;                     // broadcast words: the new codebook
     static_assert(NACC <= XLINE && NB <= XBCAST && KD <= 64 && PT / 16 == 16, "shape does not fit the exchange layout");
     extern __shared__ float s_tile[];
-    __shared__ XShared<NACC> xs;
+    __shared__ XShared<NACC, RAG> xs;
     __shared__ double s_Cd[KD];  // float64 master copy (a reducer's own slice is the live one)
     __shared__ float s_Cf[KD];
     __shared__ int s_done, s_iters, s_conv, s_bad;
@@ -1453,7 +1461,7 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
     constexpr int NBJ = KD * KD + KD * D + KD;
     constexpr bool HAS_DENSE = NBJ <= XDENSE && !RAG;
     extern __shared__ float s_tile[];
-    __shared__ XShared<HAS_DENSE ? NBJ : KD> xs;
+    __shared__ XShared<HAS_DENSE ? NBJ : KD, RAG> xs;
     __shared__ double s_v[KD], s_g[KD], s_rn[K];  // a reducer's own slice is the live one; s_rn = 1/(tau n)
     __shared__ float s_Cf[KD], s_Hs[KD], s_Hv[KD], s_Ff[KD];
     // product form of the (dF/dC)^T pass: its per-codeword operands (c_j - mu, -s^2 |c_j - mu|^2, mu, h_j . (F*_j - mu) / tau),

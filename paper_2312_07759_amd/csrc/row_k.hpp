@@ -123,7 +123,8 @@ struct RowWave {
     }
 
     // Vectors v0 .. v0 + STEP - 1 of the tile s_w (dL/dWq: s_g); those at or beyond vend contribute nothing and are not
-    // read.  base: index of the tile's first vector in the layer.
+    // read (FULL: there are none).  base: index of the tile's first vector in the layer.
+    template <bool FULL>
     __device__ __forceinline__ void step(const Args& a, const float* s_w, const float* s_g, int64_t base, int v0, int vend) {
         const int j0 = threadIdx.x & 15, vb = v0 + V * ((threadIdx.x & 63) >> 4);
         const float inf = __builtin_inff();
@@ -132,7 +133,7 @@ struct RowWave {
         float w[V][D], g[V][D], live[V];
 #pragma unroll
         for (int i = 0; i < V; ++i) {
-            const bool on = vb + i < vend;
+            const bool on = FULL || vb + i < vend;
             live[i] = on ? 1.f : 0.f;
             const int v = on ? vb + i : v0;  // (vector v0 exists)
 #pragma unroll
@@ -515,7 +516,9 @@ template <int KB, int D, int DIST, int PASS, int NT>
 __device__ __forceinline__ void row_tile_pass(const Args& a, RowWave<KB, D, DIST, PASS>& st, const float* s_w,
                                               const float* s_g, int64_t base, int cnt) {
     constexpr int STEP = RowWave<KB, D, DIST, PASS>::STEP;
-    for (int v0 = (threadIdx.x >> 6) * STEP; v0 < cnt; v0 += (NT / 64) * STEP) st.step(a, s_w, s_g, base, v0, cnt);
+    int v0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * STEP;
+    for (; v0 + STEP <= cnt; v0 += (NT / 64) * STEP) st.template step<true>(a, s_w, s_g, base, v0, cnt);
+    if (v0 < cnt) st.template step<false>(a, s_w, s_g, base, v0, cnt);
 }
 
 }  // namespace idkm

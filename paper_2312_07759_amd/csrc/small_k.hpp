@@ -63,7 +63,9 @@ __device__ __forceinline__ void estep_small(const float (&w)[D], const float (&c
         const float wr = w[0] - c0;
         float t[K];
 #pragma unroll
-        for (int j = 0; j < K; ++j) t[j] = scaled_minus_unfused(wr, escale, (c[j][0] - c0) * escale);  // (c_j - c_0) s is loop-invariant
+        for (int j = 0; j < K; ++j)
+            t[j] = RAG ? (w[0] - c[j][0]) * escale  // (these codebooks came from kernels that take the difference first)
+                       : scaled_minus_unfused(wr, escale, (c[j][0] - c0) * escale);  // (c_j - c_0) s is loop-invariant
         float tmin = fabsf(t[0]);
 #pragma unroll
         for (int j = 1; j < K; ++j) tmin = fminf(tmin, fabsf(t[j]));
@@ -326,7 +328,8 @@ struct SmallItem {
             const float wr = w[0] - c0;
             float t[K];
 #pragma unroll
-            for (int j = 0; j < K; ++j) t[j] = scaled_minus_unfused(wr, sc, (c[j][0] - c0) * sc);  // loop-invariant product
+            for (int j = 0; j < K; ++j)
+                t[j] = RAG ? (w[0] - c[j][0]) * sc : scaled_minus_unfused(wr, sc, (c[j][0] - c0) * sc);  // loop-invariant product
             float tmin = fabsf(t[0]);
 #pragma unroll
             for (int j = 1; j < K; ++j) tmin = fminf(tmin, fabsf(t[j]));
@@ -338,7 +341,7 @@ struct SmallItem {
                 p[j] = (DIST == DIST_SQL2) ? fast_exp2(fmaf(-t[j], t[j], qmin)) : fast_exp2(tmin - fabsf(t[j]));
                 p[j] = live_weight<RAG, K>(p[j], j, a.k);
                 S = (j == 0) ? p[0] : S + p[j];
-                q[j] = fmaf(hs[j][0], wr, -(hs[j][0] * (ff[j][0] - c0)));  // loop-invariant product
+                q[j] = RAG ? hs[j][0] * (w[0] - ff[j][0]) : fmaf(hs[j][0], wr, -(hs[j][0] * (ff[j][0] - c0)));  // loop-invariant product
                 pq = fmaf(p[j], q[j], pq);
             }
             const float rS = fast_rcp(S);

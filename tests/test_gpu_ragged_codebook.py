@@ -124,3 +124,24 @@ def test_batched_ragged_layers_share_launches_and_explicit_path_keeps_its_limits
             ctx.backward(dev(G), binding.BWD_GMRES)
     finally:
         ctx.set_path(binding.PATH_AUTO)
+
+
+def test_wide_totals_do_not_meet_the_words_of_other_solves(ctx):
+    """One context alternates between k = 3, 4 and 7, and its sequence numbers cross the point where the 24-bit stamps of the
+    ragged codebooks' exchange start over: the same bits every time."""
+    probs = {k: _problem(30_011, 1, k, seed=k) for k in (3, 4, 7)}
+    d = {k: (dev(W), dev(C0), dev(G)) for k, (W, C0, G) in probs.items()}
+    c = binding.Context(0)
+
+    def solve(k):
+        f = c.forward(d[k][0], d[k][1], 0.2, 0.0, 9, wl.DIST_SQL2)
+        b = c.backward(d[k][2], binding.BWD_IMPLICIT, tol=0.0, max_iter=5)
+        assert f["info"].path == binding.PATH_PERSISTENT
+        return f["C"].clone(), b["dW"].clone()
+
+    first = {k: solve(k) for k in (3, 4, 7)}
+    for _ in range(3):
+        c.advance_sequence((1 << 24) - 100)     # (10 + 36 numbers a solve)
+        for k in (3, 7, 4, 3, 4, 7):
+            assert all(torch.equal(x, y) for x, y in zip(first[k], solve(k)))
+    c.close()

@@ -65,3 +65,35 @@ def test_block_counts_and_ragged_shares(ctx, k, d, m, dist):
         assert rel(bj["dW"].cpu().numpy(), ctx.backward(Gd, binding.BWD_JFB)["dW"].cpu().numpy()) < 2e-4
     finally:
         ctx.set_path(binding.PATH_AUTO)
+
+
+@pytest.mark.parametrize("m,d,k", [(20_003, 1, 40), (5_001, 4, 256), (40_001, 2, 300), (2_100, 1, 17)])
+@pytest.mark.parametrize("setting", ["0", "2"])
+def test_exchange_of_the_large_codebook_kernels(m, d, k, setting, monkeypatch):
+    """The forms of the first hop (through the die's L2, or every store at device scope) give the same bits; results do not
+    change where the 24-bit stamps of the dies' totals start over, nor after solves of other shapes in between."""
+    W, C0, G = wl.random_problem(m, d, k, seed=k, std=0.5, spread=1.5)
+    Wd, Cd, Gd = dev(W), dev(C0), dev(G)
+
+    def solve(c):
+        f = c.forward(Wd, Cd, 0.3, 0.0, 10, wl.DIST_SQL2)
+        b = c.backward(Gd, binding.BWD_IMPLICIT, tol=0.0, max_iter=6)
+        assert f["info"].path == binding.PATH_PERSISTENT
+        return f["C"].clone(), f["Wq"].clone(), b["dW"].clone()
+
+    c = binding.Context(0)
+    first = solve(c)
+    monkeypatch.setenv("IDKM_TREE", setting)
+    other = binding.Context(0)
+    monkeypatch.delenv("IDKM_TREE")
+    assert all(torch.equal(x, y) for x, y in zip(first, solve(other)))
+    other.close()
+    ref = orc.soft_kmeans(W.astype(np.float32), C0.astype(np.float32), 0.3, 0.0, 10, wl.DIST_SQL2)
+    assert rel(first[0].cpu().numpy(), ref["C"]) < TOL_VAL
+    W2, C2, _ = wl.random_problem(9_001, 1, 20, seed=1, std=0.5, spread=1.5)
+    for _ in range(2):
+        c.advance_sequence((1 << 24) - 70)      # every solve here takes 54 numbers: the next one crosses
+        for _ in range(3):
+            assert all(torch.equal(x, y) for x, y in zip(first, solve(c)))
+            c.forward(dev(W2), dev(C2), 0.3, 0.0, 7, wl.DIST_SQL2)
+    c.close()
