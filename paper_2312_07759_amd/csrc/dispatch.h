@@ -18,7 +18,6 @@ int mfma_lane_threads(int KPL, int dist, int pass);  // workgroup size that kern
 
 // Lane<->codeword family, stream path: reduction of the per-workgroup partials and the O(k d) tail of a pass.
 KernelFn lane_tail_kernel(int pass);
-KernelFn lane_tail_wide_kernel();  // PASS_B2 tail for 1024 threads
 void launch_reduce_rows(const Args& a, int nacc, int nwg, int pass, hipStream_t s);
 
 struct PArgs;
@@ -45,7 +44,11 @@ PersistFns persist_kernel_global(int K, int D, int dist, bool bwd);
 // matrix: prefer the matrix-core forward loop where one exists (d = 4, k <= 256).
 PersistFns persist_lane_kernel(int KPL, int D, int dist, bool bwd, bool matrix);
 
-// Persistent solve in the row <-> vector form: D in {1,2}, 16 KB >= k codewords, KB in {1,2,4,8,16}.
+// Stream path's passes in the row <-> vector form: D in {1,2,8}, 16 KB >= k codewords, KB in {1,2,4,8,16}; launched with
+// RST threads and vec_per_wg D floats of dynamic LDS (twice that for PASS_B1 and PASS_B3).
+KernelFn row_kernel_0(int KB, int D, int pass);
+KernelFn row_kernel_1(int KB, int D, int pass);
+// Persistent solve in the row <-> vector form, the same shapes (D = 8: forward only).
 PersistFns persist_row_kernel_0(int KB, int D, bool bwd);
 PersistFns persist_row_kernel_1(int KB, int D, bool bwd);
 

@@ -20,6 +20,7 @@
 #include "persist_lane.hpp"
 
 namespace idkm {
+
 KernelFn small_kernel_0(int, int, int);
 KernelFn small_kernel_1(int, int, int);
 KernelFn lane_kernel_0(int, int, int);
@@ -141,7 +142,6 @@ struct idkm_ctx {
     Ctrl* h_ctrl = nullptr;  // pinned host mirror
     unsigned int* tickets = nullptr;  // arrival counters of the stream path, zero between launches
     unsigned int stream_launches = 0; // upper bound of Ctrl::launch_seq
-    bool wide_tail = false;           // lane family, GMRES with k d >= 512: the pass tail runs with 1024 threads
     int gmres_basis = 64;             // basis length of IDKM_BWD_GMRES before a restart (idkm_set_gmres_basis, <= GM_RMAX)
     double *Cd = nullptr, *nd = nullptr, *Fd = nullptr, *gd = nullptr, *vd = nullptr, *ud = nullptr;
     float *Cf = nullptr, *Ff = nullptr, *Hs = nullptr;
@@ -178,6 +178,7 @@ struct idkm_ctx {
     hipStream_t pending_stream = nullptr;
     std::vector<Deferred>* sink = nullptr;  // set by a batched call: persistent launches are handed over, not issued
     std::map<const void*, std::pair<size_t, int>> checked;  // kernel -> (largest LDS size set, blocks per CU at that size)
+    std::map<const void*, size_t> row_lds;                  // kernel -> dynamic LDS limit set so far (row <-> vector passes)
     std::map<const void*, size_t> static_lds;               // bytes of static LDS of the kernels whose dynamic LDS is sized against it
     unsigned int spin_limit = 1u << 20;
     bool use_matrix = true;           // d = 4, 17 <= k <= 256: matrix-core kernels where they exist
@@ -217,6 +218,7 @@ struct Geometry {
     bool matrix = false;
     int nwg_m = 0;
     int64_t vec_per_wg_m = 0;
+    int kb = 0;  // > 0: the row <-> vector passes (d in {1, 2, 8}, k <= 256), 16 kb codewords
 };
 
 bool pow2(int x) { return x > 0 && (x & (x - 1)) == 0; }
@@ -243,6 +245,18 @@ idkm_status plan(idkm_ctx* ctx, int64_t m, int k, int d, Geometry* g) {
         if (vpw < 1) vpw = 1;
         if (vpw > 512) vpw = (m + 8191) / 8192 > 512 ? (m + 8191) / 8192 : 512;
         g->vec_per_wg = vpw * (WG / 64);
+        if (d != 4 && k <= 256) {
+            // row <-> vector passes: one workgroup per compute unit and round, of at least a step for each wavefront (so
+            // that few partial sums are left to reduce), its tiles at most 36 KB each
+            g->kb = 1;
+            while (16 * g->kb < k) g->kb <<= 1;
+            int64_t v = (m + ctx->num_cu - 1) / (ctx->num_cu > 0 ? ctx->num_cu : 1);
+            if (v < 64) v = 64;
+            v = (v + 15) / 16 * 16;
+            const int64_t most = 9216 / d;
+            if (v > most) v = most;
+            g->vec_per_wg = v;
+        }
     }
     int64_t nwg = (m + g->vec_per_wg - 1) / g->vec_per_wg;
     if (nwg > 0x3fffffff) return fail(ctx, IDKM_ERR_UNSUPPORTED, "m too large");
@@ -311,7 +325,9 @@ Args base_args(idkm_ctx* ctx) {
 }
 
 idkm_status launch_pass(idkm_ctx* ctx, const Geometry& g, int pass, Args& a, hipStream_t s) {
-    KernelFn fn = g.small ? small_kernel(ctx->k, ctx->d, ctx->dist, pass) : lane_kernel(g.kpl, ctx->d, ctx->dist, pass);
+    KernelFn fn = g.small ? small_kernel(ctx->k, ctx->d, ctx->dist, pass)
+                  : g.kb  ? (ctx->dist == DIST_L2 ? row_kernel_0(g.kb, ctx->d, pass) : row_kernel_1(g.kb, ctx->d, pass))
+                          : lane_kernel(g.kpl, ctx->d, ctx->dist, pass);
     KernelFn fn_m = g.matrix ? mfma_lane_kernel(g.kpl, ctx->dist, pass) : nullptr;
     if (!fn && !fn_m) return fail(ctx, IDKM_ERR_UNSUPPORTED, "no kernel for this (k, d)");
     const int nwg = fn_m ? g.nwg_m : g.nwg;
@@ -326,7 +342,15 @@ idkm_status launch_pass(idkm_ctx* ctx, const Geometry& g, int pass, Args& a, hip
     }
     if (fn_m)
         hipLaunchKernelGGL(fn_m, dim3(nwg), dim3(mfma_lane_threads(g.kpl, ctx->dist, pass)), (size_t)(a.vec_per_wg + 16) * 20, s, a);
-    else
+    else if (g.kb) {
+        const size_t lds = (size_t)a.vec_per_wg * ctx->d * sizeof(float) * (pass == PASS_B1 || pass == PASS_B3 ? 2 : 1);
+        size_t& set = ctx->row_lds[(const void*)fn];
+        if (set < lds) {
+            HIP_TRY(ctx, hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+            set = lds;
+        }
+        hipLaunchKernelGGL(fn, dim3(nwg), dim3(RST), lds, s, a);
+    } else
         hipLaunchKernelGGL(fn, dim3(nwg), dim3(WG), 0, s, a);
     HIP_TRY(ctx, hipGetLastError());
     if (!g.small && pass != PASS_B3) {
@@ -334,10 +358,7 @@ idkm_status launch_pass(idkm_ctx* ctx, const Geometry& g, int pass, Args& a, hip
         const int nacc = ctx->k * ((pass == PASS_FWD || pass == PASS_FIN) ? ctx->d + 1 : ctx->d);
         launch_reduce_rows(a, nacc, nwg, pass, s);
         HIP_TRY(ctx, hipGetLastError());
-        if (pass == PASS_B2 && ctx->wide_tail)
-            hipLaunchKernelGGL(lane_tail_wide_kernel(), dim3(1), dim3(1024), 0, s, a);
-        else
-            hipLaunchKernelGGL(lane_tail_kernel(pass), dim3(1), dim3(WG), 0, s, a);
+        hipLaunchKernelGGL(lane_tail_kernel(pass), dim3(1), dim3(ctx->k * ctx->d >= 512 ? 1024 : WG), 0, s, a);
         HIP_TRY(ctx, hipGetLastError());
     }
     return IDKM_OK;
@@ -365,8 +386,9 @@ struct Deferred {
 };
 constexpr size_t LDS_PER_CU = 160 * 1024;
 constexpr size_t LANE_TILE_MAX = 94 * 1024;                       // the lane kernels keep ~55 KB of static LDS
-constexpr size_t LANE_BUF1_WORDS = (size_t)2 * PT * 1536;          // k (d+1) <= 1536
-constexpr size_t LANE_BUF3_WORDS = (size_t)2 * DIES * 1536;        // totals of the dies
+constexpr size_t LANE_NACC = 2304;                                  // k (d+1) at most: k = 256, d = 8
+constexpr size_t LANE_BUF1_WORDS = (size_t)2 * PT * LANE_NACC;
+constexpr size_t LANE_BUF3_WORDS = (size_t)2 * DIES * LANE_NACC;   // totals of the dies
 // ... the grid totals, one copy per die (buf4), and the die of every workgroup
 constexpr size_t LANE_XBUF_WORDS = LANE_BUF1_WORDS + 2 * LANE_BUF3_WORDS + PT;
 
@@ -438,7 +460,11 @@ bool plan_persistent(idkm_ctx* ctx, bool bwd, PersistPlan* pp, bool matrix_ok = 
         // lane<->codeword family
         int kpl = (k + 63) / 64, p = 1;
         while (p < kpl) p <<= 1;
-        if (d > 4 || p * d > 16 || p * (d + 1) > 24) return false;
+        // d = 8: the forward solve of layers of more than 4096 vectors, under IDKM_PATH_AUTO (the explicit persistent path is
+        // not offered for d > 4, and smaller layers stay on the stream path that idkm_info reports for them): 294,912
+        // 8-vectors under 256 codewords, 20 evaluations and a Jacobian-free backward, 2051 us against 2954 there
+        const bool row8 = d == 8 && k <= 256 && !bwd && m > 4096 && ctx->path == IDKM_PATH_AUTO;
+        if (!row8 && (d > 4 || p * d > 16 || p * (d + 1) > 24)) return false;
         int64_t g = (m + 255) / 256;  // at least 16 vectors per wavefront before adding workgroups
         if (g < 1) g = 1;
         if (g > 1 && g < DIES) g = DIES;  // (one workgroup per die: they all add in parallel)
@@ -448,7 +474,7 @@ bool plan_persistent(idkm_ctx* ctx, bool bwd, PersistPlan* pp, bool matrix_ok = 
         per = (per + 3) / 4 * 4;
         // d <= 2 and k <= 256: the row <-> vector kernels (589,824 scalar weights under 64 codewords, 30 evaluations and a
         // Jacobian-free backward: 671 us against 1260); beyond 256 codewords their tables do not fit the registers
-        const bool row = d <= 2 && k <= 256;
+        const bool row = row8 || (d <= 2 && k <= 256);
         PersistFns fl;
         if (row) {
             int kb = 1;
@@ -483,7 +509,17 @@ bool plan_persistent(idkm_ctx* ctx, bool bwd, PersistPlan* pp, bool matrix_ok = 
         pp->fn = fl.one;
         pp->fn_batch = fl.batch;
         if (!pp->fn) return false;
-        if (lds > LANE_TILE_MAX) return false;
+        size_t most = LANE_TILE_MAX;
+        if (row8) {
+            size_t& fixed = ctx->static_lds[(const void*)pp->fn];
+            if (fixed == 0) {
+                hipFuncAttributes at;
+                fixed = (hipFuncGetAttributes(&at, (const void*)pp->fn) == hipSuccess) ? at.sharedSizeBytes : LDS_PER_CU;
+                (void)hipGetLastError();
+            }
+            most = std::min(most, LDS_PER_CU - std::min(fixed, LDS_PER_CU));
+        }
+        if (lds > most) return false;
         pp->grid = (int)((m + per - 1) / per);
         pp->per = (int)per;
         pp->lds = lds;
@@ -1116,9 +1152,7 @@ idkm_status idkm_backward(idkm_ctx* ctx, const float* dWq, idkm_bwd_mode mode, f
         st = run_until_done(ctx, g, PASS_B2, a, s, (int64_t)max_iter * 7, [](const Ctrl& c) { return c.b_done != 0; });
         if (st != IDKM_OK) return st;
     } else if (mode == IDKM_BWD_GMRES) {
-        ctx->wide_tail = !g.small && ctx->k * ctx->d >= 512;
         st = run_until_done(ctx, g, PASS_B2, a, s, (int64_t)max_iter + 2, [](const Ctrl& c) { return c.b_done != 0; });
-        ctx->wide_tail = false;
         if (st != IDKM_OK) return st;
     }
     st = launch_pass(ctx, g, PASS_B3, a, s);

@@ -7,6 +7,8 @@ namespace idkm {
 template <int KPL, int D>
 static KernelFn pick(int pass) {
     if (KPL * (D + 1) > 80) return nullptr;
+    if constexpr (KPL <= 4 && D != 4) return nullptr;  // (the row <-> vector passes serve these)
+    else
     switch (pass) {
         case PASS_FWD: return lane_pass<KPL, D, 0, PASS_FWD>;
         case PASS_FIN: return lane_pass<KPL, D, 0, PASS_FIN>;
@@ -50,10 +52,8 @@ KernelFn lane_tail_kernel(int pass) {
     return nullptr;
 }
 
-KernelFn lane_tail_wide_kernel() { return lane_tail_b2_wide<0>; }
-
 void launch_reduce_rows(const Args& a, int nacc, int nwg, int pass, hipStream_t s) {
-    hipLaunchKernelGGL(reduce_rows<0>, dim3((nacc + 63) / 64), dim3(WG), 0, s, a, nacc, nwg, pass);
+    hipLaunchKernelGGL(reduce_rows<0>, dim3((nacc + 63) / 64), dim3(RRT), 0, s, a, nacc, nwg, pass);
 }
 
 }  // namespace idkm

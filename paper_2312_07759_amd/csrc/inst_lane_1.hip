@@ -7,6 +7,8 @@ namespace idkm {
 template <int KPL, int D>
 static KernelFn pick(int pass) {
     if (KPL * (D + 1) > 80) return nullptr;
+    if constexpr (KPL <= 4 && D != 4) return nullptr;  // (the row <-> vector passes serve these)
+    else
     switch (pass) {
         case PASS_FWD: return lane_pass<KPL, D, 1, PASS_FWD>;
         case PASS_FIN: return lane_pass<KPL, D, 1, PASS_FIN>;

@@ -1,0 +1,40 @@
+// Instantiations of the stream path's row <-> vector passes for energy variant 1.
+#include "dispatch.h"
+#include "row_k.hpp"
+
+namespace idkm {
+
+template <int KB, int D>
+static KernelFn pick(int pass) {
+    switch (pass) {
+        case PASS_FWD: return row_pass<KB, D, 1, PASS_FWD>;
+        case PASS_FIN: return row_pass<KB, D, 1, PASS_FIN>;
+        case PASS_B1: return row_pass<KB, D, 1, PASS_B1>;
+        case PASS_B2: return row_pass<KB, D, 1, PASS_B2>;
+        case PASS_B3: return row_pass<KB, D, 1, PASS_B3>;
+    }
+    return nullptr;
+}
+
+template <int KB>
+static KernelFn pick_d(int D, int pass) {
+    switch (D) {
+        case 1: return pick<KB, 1>(pass);
+        case 2: return pick<KB, 2>(pass);
+        case 8: return pick<KB, 8>(pass);
+    }
+    return nullptr;
+}
+
+KernelFn row_kernel_1(int KB, int D, int pass) {
+    switch (KB) {
+        case 1: return pick_d<1>(D, pass);
+        case 2: return pick_d<2>(D, pass);
+        case 4: return pick_d<4>(D, pass);
+        case 8: return pick_d<8>(D, pass);
+        case 16: return pick_d<16>(D, pass);
+    }
+    return nullptr;
+}
+
+}  // namespace idkm

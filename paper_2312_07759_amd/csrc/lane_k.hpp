@@ -405,50 +405,56 @@ __global__ __launch_bounds__(WG) void lane_pass(const Args a) {
     }
 }
 
-// tot[acc] = sum over workgroups of partials[wg][acc], fixed order.  One workgroup per 64 accumulators; the four
-// wavefronts take interleaved quarters of the workgroups with eight loads in flight each.
+// tot[acc] = sum over workgroups of partials[wg][acc], fixed order.  One workgroup per 64 accumulators; its 16 wavefronts
+// take the workgroups in turn with eight loads in flight each.  Bound by the latency of those loads: few workgroups run
+// here (k (d+1) / 64), so each needs many wavefronts (2304 sums of 1024 workgroups took 14 us with four).
+constexpr int RRT = 1024;
 template <int UNUSED>  // a template only so that the header can be included by several translation units
-__global__ __launch_bounds__(WG) void reduce_rows(const Args a, int nacc, int nwg, int pass) {
+__global__ __launch_bounds__(RRT) void reduce_rows(const Args a, int nacc, int nwg, int pass) {
     if (pass == PASS_FWD && a.ctrl->done) return;
     if (pass == PASS_B2 && a.ctrl->b_done) return;
-    __shared__ double s_q[WG / 64][64];
+    constexpr int NW = RRT / 64;
+    __shared__ double s_q[NW][64];
     const int lane = threadIdx.x & 63, part = threadIdx.x >> 6;
     const int acc = blockIdx.x * 64 + lane;
     double s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     if (acc < nacc) {
         const double* __restrict__ p = a.partials + acc;
         int wg = part;
-        for (; wg + 7 * 4 < nwg; wg += 8 * 4) {
+        for (; wg + 7 * NW < nwg; wg += 8 * NW) {
             double x[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) x[u] = p[(size_t)(wg + 4 * u) * nacc];
+            for (int u = 0; u < 8; ++u) x[u] = p[(size_t)(wg + NW * u) * nacc];
 #pragma unroll
             for (int u = 0; u < 8; ++u) s[u] += x[u];
         }
-        for (; wg < nwg; wg += 4) s[0] += p[(size_t)wg * nacc];
+        for (; wg < nwg; wg += NW) s[0] += p[(size_t)wg * nacc];
     }
     s_q[part][lane] = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
     __syncthreads();
-    if (part == 0 && acc < nacc) a.tot[acc] = (s_q[0][lane] + s_q[1][lane]) + (s_q[2][lane] + s_q[3][lane]);
+    if (part == 0 && acc < nacc) {
+        double t[NW];
+#pragma unroll
+        for (int w = 0; w < NW; ++w) t[w] = s_q[w][lane];
+#pragma unroll
+        for (int h = NW / 2; h >= 1; h /= 2)
+#pragma unroll
+            for (int w = 0; w < h; ++w) t[w] += t[w + h];
+        a.tot[acc] = t[0];
+    }
 }
 
-// The O(k d) update and stop logic of a pass whose totals are already in a.tot (single workgroup).
+// The O(k d) update and stop logic of a pass whose totals are already in a.tot (single workgroup; 1024 threads from
+// k d = 512 on, where its loops over the state -- and, for the minimal-residual solve, over the Krylov basis -- are what
+// it spends its time on).
 template <int PASS>
-__global__ __launch_bounds__(WG) void lane_tail(const Args a) {
+__global__ __launch_bounds__(1024) void lane_tail(const Args a) {
     if (PASS == PASS_FWD && a.ctrl->done) return;
     if (PASS == PASS_B2 && a.ctrl->b_done) return;
     if (PASS == PASS_FWD) tail_forward(a, a.tot);
     if (PASS == PASS_FIN) tail_final(a, a.tot);
     if (PASS == PASS_B1) tail_b1(a, a.tot);
     if (PASS == PASS_B2) tail_b2(a, a.tot);
-}
-
-// The same tail with 16 wavefronts, for the minimal-residual solve at large k d: its inner products and vector
-// updates over the Krylov basis are spread over the threads of this one workgroup.
-template <int UNUSED>
-__global__ __launch_bounds__(1024) void lane_tail_b2_wide(const Args a) {
-    if (a.ctrl->b_done) return;
-    tail_b2(a, a.tot);
 }
 
 }  // namespace idkm

@@ -6,7 +6,7 @@
 //   hop 2  (across dies) EVERY workgroup reads the words of the up to 8 dies, adds them in a fixed order and applies the
 //          O(k d) update itself, so that all hold the same state and take the same stop decision.
 // As in persist_small.hpp a store of hop 1 only has to reach the die's L2 when all members of the die run there (checked at
-// the start of a launch.  There one workgroup per die adds all of the at most 80 words.)  The form this
+// the start of a launch).  There one workgroup per die adds all of the at most 80 words.  The form this
 // replaced had one reducer per codeword that read all 256 workgroups through memory, and a broadcast of the result:
 // 589,824 weights under 64 codewords 671 -> 615 us (30 evaluations and a Jacobian-free backward), 589,824 4-vectors under
 // 256 codewords (30 evaluations, 10 passes) 2484 -> 2434, 2,620 4-vectors under 64 (20 evaluations, 10 passes) 415 -> 271.
@@ -360,7 +360,6 @@ __device__ __forceinline__ void persist_lane_fwd_body(const Args& a, const PArgs
     __shared__ double s_acc[KB > 0 ? KMAX : 64][KB > 0 ? ACCW : NA];
     double* s_tot = &s_acc[0][0];
     __shared__ LShared ls;
-    __shared__ double s_Cd[KDP];  // float64 master copy
     __shared__ __align__(16) float s_Cf[KDP];
     __shared__ float s_rpart[KB > 0 ? NT / 64 : 1][KB > 0 ? KMAX * ACCW : 1];  // row form: totals of the wavefronts
 
@@ -373,7 +372,6 @@ __device__ __forceinline__ void persist_lane_fwd_body(const Args& a, const PArgs
     load_tile<NT>(s_tile, a.W + base * D, cnt * D);
     for (int i = tid; i < kd; i += NT) {
         const float c0 = pa.C0[i];
-        s_Cd[i] = (double)c0;
         s_Cf[i] = c0;
     }
     if (KB > 0)
@@ -469,9 +467,8 @@ __device__ __forceinline__ void persist_lane_fwd_body(const Args& a, const PArgs
         for (int i = tid; i < kd; i += NT) {
             const int j = i / D, rr = i - j * D;
             const double n = s_tot[j * ACCW], sv = s_tot[j * ACCW + 1 + rr];
-            double cnew = (n > 0.0) ? fast_div_d(sv, n) : s_Cd[i];
+            double cnew = (n > 0.0) ? fast_div_d(sv, n) : (double)s_Cf[i];
             if (!(n >= 0.0) || !(fabs(sv) <= 1.7e308) || !(fabs(cnew) <= 1.7e308)) cnew = __builtin_nan("");
-            s_Cd[i] = cnew;
             const float cn = (float)cnew;
             const double df = (double)cn - (double)s_Cf[i];
             r2 += df * df;
@@ -903,7 +900,7 @@ __global__ __launch_bounds__(LT) void persist_lane_bwd_batch(const BatchItem* it
     persist_lane_bwd_body<KPL, D, DIST>(a, pa);
 }
 
-// The row <-> vector form (d = 1 and 2, up to 16 KB codewords).
+// The row <-> vector form (d = 1 and 2, and the forward solve for d = 8; up to 16 KB codewords).
 template <int KB, int D, int DIST>
 __global__ __launch_bounds__(RT) void persist_row_fwd(const Args a, const PArgs pa_in) {
     PArgs pa = pa_in;

@@ -1,4 +1,4 @@
-// Row <-> vector kernels for codebooks of up to 256 codewords with d = 1 and 2: a row of 16 lanes works on V vectors at
+// Row <-> vector kernels for codebooks of up to 256 codewords with d = 1, 2 and 8: a row of 16 lanes works on V vectors at
 // a time, lane l of the row owning codewords l, l + 16, ...  (KB of them).  The softmax sums of a vector run over a lane's
 // registers and then over the 16 lanes (four DPP additions for each of the V vectors, their chains side by side), and the
 // M-step sums stay in the lane's registers until the end of the pass, where the four rows of a wavefront are added.
@@ -19,6 +19,7 @@ namespace idkm {
 // Values per lane that a step may keep live (256 registers at two wavefronts per SIMD; at 160 the forward loop at k = 256,
 // d = 2 spilled 46 registers).
 constexpr int ROW_BUDGET = 150;
+constexpr int ROW_BUDGET_8 = 226;  // d = 8 (the sums alone are 144 at k = 256; nothing else is kept)
 
 template <int KB, int D, int DIST, int PASS>
 struct RowWave {
@@ -36,7 +37,8 @@ struct RowWave {
     static constexpr int NSTATE = BACK ? ((DIST == DIST_L2 && D > 1) ? 3 : 2) : 1;  // values per (vector, codeword) pair
     static constexpr int KEPT = NA + (REGS ? KB * D * (USE_H ? 3 : 1) : 2 * D);
     static constexpr int cost(int v) { return KEPT + v * (KB * NSTATE + D * (USE_G ? 3 : 2)); }
-    static constexpr int V = (D <= 4 && cost(4) <= ROW_BUDGET) ? 4 : (cost(2) <= ROW_BUDGET ? 2 : 1);  // vectors of a row per step
+    static constexpr int BUDGET = D == 8 ? ROW_BUDGET_8 : ROW_BUDGET;
+    static constexpr int V = (D <= 4 && cost(4) <= BUDGET) ? 4 : (cost(2) <= BUDGET ? 2 : 1);  // vectors of a row per step
     static constexpr int STEP = 4 * V;                                                      // vectors of a wavefront per step
 
     float rc[REGS ? KB : 1][D], rh[(REGS && USE_H) ? KB : 1][D], rf[(REGS && USE_H) ? KB : 1][D];
@@ -80,6 +82,10 @@ struct RowWave {
         }
 #pragma unroll
         for (int q = 0; q < NA; ++q) acc[q] = 0.f;
+    }
+    // d = 8: operands read in an earlier phase of a step are read again, not kept (they would spill).
+    static __device__ __forceinline__ void next_phase() {
+        if (!REGS) asm volatile("" ::: "memory");
     }
     // Operands of codeword j0 + 16 b (in the coordinates of the pass).
     __device__ __forceinline__ void table_row(const float* t, int b, float (&x)[D]) const {
@@ -129,7 +135,7 @@ struct RowWave {
         const int j0 = threadIdx.x & 15, vb = v0 + V * ((threadIdx.x & 63) >> 4);
         const float inf = __builtin_inff();
         const float escale = a.escale;
-        if (!REGS) asm volatile("" ::: "memory");  // (the tables are read anew in every step)
+        next_phase();
         float w[V][D], g[V][D], live[V];
 #pragma unroll
         for (int i = 0; i < V; ++i) {
@@ -214,6 +220,7 @@ struct RowWave {
         }
         if constexpr (PASS == PASS_FIN) {
             if (a.Wq_out) {
+                next_phase();
                 float s[V][D];
 #pragma unroll
                 for (int i = 0; i < V; ++i)
@@ -239,6 +246,7 @@ struct RowWave {
             }
             if (a.assign_out) {
                 // closest codeword on a float32 key with separately rounded operations; lowest index on ties
+                next_phase();
                 float best[V];
                 int cand[V];
 #pragma unroll
@@ -275,6 +283,7 @@ struct RowWave {
             }
         }
         if constexpr (BACK) {
+            next_phase();
             float q[KB][V], qb[V];
 #pragma unroll
             for (int i = 0; i < V; ++i) qb[i] = 0.f;
@@ -300,6 +309,7 @@ struct RowWave {
             }
 #pragma unroll
             for (int i = 0; i < V; ++i) qb[i] = row16_sum(qb[i]);
+            next_phase();
             float out[V][D];
 #pragma unroll
             for (int i = 0; i < V; ++i)
@@ -378,6 +388,7 @@ struct RowWave {
             shift = __builtin_amdgcn_ballot_w64(smin < 7.9e-31f) != 0ull;  // below 2^-100
         }
         if (shift) {
+            next_phase();
             float emin[V];
 #pragma unroll
             for (int i = 0; i < V; ++i) emin[i] = inf_();
@@ -426,6 +437,7 @@ struct RowWave {
                 }
         } else {
             // delta = 2 (w - c) = (2/s) t: the factor 2/(s S) joins the row's scalar
+            next_phase();
             float q[KB][V], qb[V];
 #pragma unroll
             for (int i = 0; i < V; ++i) qb[i] = 0.f;
@@ -455,6 +467,7 @@ struct RowWave {
                     qb[i] = fmaf(p[b][i], s, qb[i]);
                 }
             }
+            next_phase();
             float f[V];
 #pragma unroll
             for (int i = 0; i < V; ++i) {
@@ -519,6 +532,51 @@ __device__ __forceinline__ void row_tile_pass(const Args& a, RowWave<KB, D, DIST
     int v0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * STEP;
     for (; v0 + STEP <= cnt; v0 += (NT / 64) * STEP) st.template step<true>(a, s_w, s_g, base, v0, cnt);
     if (v0 < cnt) st.template step<false>(a, s_w, s_g, base, v0, cnt);
+}
+
+// Stream path: one launch per pass.  Every workgroup copies its chunk of W (and dL/dWq) into LDS and leaves its sums in
+// a.partials[workgroup][.] (float64) for reduce_rows and lane_tail.  Dynamic LDS: vec_per_wg vectors, twice that for the
+// passes that read dL/dWq.
+constexpr int RST = 512;
+template <int KB, int D, int DIST, int PASS>
+__global__ __launch_bounds__(RST) void row_pass(const Args a) {
+    using RW = RowWave<KB, D, DIST, PASS>;
+    if (PASS == PASS_FWD && a.ctrl->done) return;
+    if (PASS == PASS_B2 && a.ctrl->b_done) return;
+    constexpr int KDP = 16 * KB * D;
+    extern __shared__ __align__(16) float s_tile[];
+    __shared__ __align__(16) float s_Cf[KDP];
+    __shared__ __align__(16) float s_Hs[RW::USE_H ? KDP : 1], s_Ff[RW::USE_H ? KDP : 1];
+    __shared__ float s_part[PASS == PASS_B3 ? 1 : RST / 64][PASS == PASS_B3 ? 1 : 16 * KB * RW::ACCW];
+    const int tid = threadIdx.x, k = a.k, kd = k * D, per = (int)a.vec_per_wg;
+    const int64_t base = (int64_t)blockIdx.x * per;
+    int cnt = 0;
+    if (base < a.m) cnt = (a.m - base < per) ? (int)(a.m - base) : per;
+    load_tile<RST>(s_tile, a.W + base * D, cnt * D);
+    float* s_g = s_tile + (size_t)per * D;
+    if (RW::USE_G) load_tile<RST>(s_g, a.G + base * D, cnt * D);
+    for (int i = tid; i < KDP; i += RST) {
+        s_Cf[i] = i < kd ? a.Cf[i] : 0.f;
+        if (RW::USE_H) {
+            s_Hs[i] = i < kd ? a.Hs[i] : 0.f;
+            s_Ff[i] = i < kd ? a.Ff[i] : 0.f;
+        }
+    }
+    __syncthreads();
+    RW st;
+    st.init(k, s_Cf, s_Hs, s_Ff, a.escale);
+    row_tile_pass<KB, D, DIST, PASS, RST>(a, st, s_tile, s_g, base, cnt);
+    if constexpr (PASS != PASS_B3) {
+        st.collect(s_part[tid >> 6]);
+        __syncthreads();
+        const int nacc = k * RW::ACCW;
+        for (int idx = tid; idx < nacc; idx += RST) {
+            double t = 0.0;
+#pragma unroll
+            for (int w = 0; w < RST / 64; ++w) t += (double)s_part[w][idx];
+            a.partials[(size_t)blockIdx.x * nacc + idx] = t;
+        }
+    }
 }
 
 }  // namespace idkm

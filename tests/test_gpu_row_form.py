@@ -1,5 +1,5 @@
-"""Row <-> vector kernels (17 <= k <= 256 and k = 1, d = 1 and 2, persistent path): every block count and its edges, shares
-that end inside a step, rows that underflow, against the float64 oracle and the stream path's lane <-> codeword kernels."""
+"""Row <-> vector kernels (k = 1 and 17 <= k <= 256 for d = 1 and 2; every k <= 256 for d = 8; both paths): every block count
+and its edges, shares that end inside a step, rows that underflow, against the float64 oracle."""
 import numpy as np
 import pytest
 import torch
@@ -97,3 +97,45 @@ def test_exchange_of_the_large_codebook_kernels(m, d, k, setting, monkeypatch):
             assert all(torch.equal(x, y) for x, y in zip(first, solve(c)))
             c.forward(dev(W2), dev(C2), 0.3, 0.0, 7, wl.DIST_SQL2)
     c.close()
+
+
+@pytest.mark.parametrize("dist", [wl.DIST_L2, wl.DIST_SQL2])
+@pytest.mark.parametrize("k,m", [(1, 4_097), (3, 9_001), (16, 4_100), (17, 20_011), (64, 5_003), (65, 1_300), (128, 6_001), (129, 70_001),
+                                 (256, 4_096), (256, 40_003)])
+def test_8_vectors_on_the_default_and_the_stream_path(ctx, k, m, dist):
+    """d = 8: above 4096 vectors the default path solves the forward in one launch, everything else stays on the stream path
+    and the explicit persistent path stays refused."""
+    d = 8
+    W, C0, G = wl.random_problem(m, d, k, seed=k + m, std=0.5, spread=1.5)
+    C0 = C0 + 0.01 * np.random.default_rng(k).standard_normal(C0.shape)
+    W[::311] += 30.0
+    W, C0, G = W.astype(np.float32), C0.astype(np.float32), G.astype(np.float32)
+    Wd, Cd, Gd = dev(W), dev(C0), dev(G)
+    tau, iters = 0.4, 5
+    ref = orc.soft_kmeans(W, C0, tau, 0.0, iters, dist)
+    for path in (binding.PATH_AUTO, binding.PATH_STREAM):
+        ctx.set_path(path)
+        try:
+            f = ctx.forward(Wd, Cd, tau, 0.0, iters, dist, want_A=True, want_assign=True)
+            want = binding.PATH_PERSISTENT if path == binding.PATH_AUTO and m > 4096 else binding.PATH_STREAM
+            assert f["info"].path == want and f["info"].iters == iters
+            Cg = f["C"].cpu().numpy()
+            assert rel(Cg, ref["C"]) < TOL_VAL
+            assert rel(f["A"].cpu().numpy(), orc.attention(W, Cg, tau, dist)) < TOL_VAL
+            assert rel(f["Wq"].cpu().numpy(), orc.soft_quantize(W, Cg, tau, dist)) < TOL_VAL
+            assert np.array_equal(f["assign"].cpu().numpy(), orc.hard_assign_f32(W, Cg))
+            bj = ctx.backward(Gd, binding.BWD_JFB)
+            rj = orc.backward(W, Cg, tau, dist, G, "jfb")
+            assert bj["info"].path == binding.PATH_STREAM
+            assert rel(bj["dW"].cpu().numpy(), rj["dW"]) < TOL_GRAD and rel(ctx.get_cotangents(k, d)[0], rj["v"]) < TOL_GRAD
+            bi = ctx.backward(Gd, binding.BWD_IMPLICIT, tol=0.0, max_iter=4, alpha=0.5)
+            ri = orc.backward(W, Cg, tau, dist, G, "implicit", tol=0.0, max_iter=4, alpha=0.5)
+            assert rel(bi["dW"].cpu().numpy(), ri["dW"]) < TOL_GRAD
+        finally:
+            ctx.set_path(binding.PATH_AUTO)
+    ctx.set_path(binding.PATH_PERSISTENT)
+    try:
+        with pytest.raises(binding.IdkmError):
+            ctx.forward(Wd, Cd, tau, 0.0, iters, dist)
+    finally:
+        ctx.set_path(binding.PATH_AUTO)
