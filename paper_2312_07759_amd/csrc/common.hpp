@@ -340,6 +340,31 @@ __device__ __forceinline__ float fast_rcp(float x) { return __builtin_amdgcn_rcp
 __device__ __forceinline__ float fast_sqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
 __device__ __forceinline__ float fast_rsq(float x) { return __builtin_amdgcn_rsqf(x); }
 
+// Wavefronts that share a SIMD and have equal shares of a pass: the hardware issues the oldest first, so without more one
+// runs ahead and the rest of the other's share runs alone, with nothing to fill its latencies (at k = 64, d = 1 the first
+// wavefront of a workgroup was done after 7.5 of the 12.5 us a pass took).  The issue priority therefore falls with each
+// quarter of the share that is done: whoever is behind goes first.  Which wavefront does what, and so the order of every
+// sum, stays the same.  Row <-> vector passes: 615 -> 598 us at k = 64, d = 1, 2051 -> 2024 at k = 256, d = 8.  Not for the
+// matrix-core passes, whose wavefronts fill each other's gaps better out of step (2434 -> 2760 us at k = 256, d = 4).
+struct PassPriority {
+    int left, quarter, level = 3;
+    __device__ __forceinline__ explicit PassPriority(int steps) {
+        quarter = __builtin_amdgcn_readfirstlane(steps + 3) >> 2;
+        left = quarter;
+        __builtin_amdgcn_s_setprio(3);
+    }
+    __device__ __forceinline__ void step_done() {
+        if (--left == 0) {
+            left = quarter;
+            --level;
+            if (level == 2) __builtin_amdgcn_s_setprio(2);
+            else if (level == 1) __builtin_amdgcn_s_setprio(1);
+            else __builtin_amdgcn_s_setprio(0);
+        }
+    }
+    __device__ __forceinline__ ~PassPriority() { __builtin_amdgcn_s_setprio(0); }
+};
+
 // ---------------------------------------------------------------- stamped words
 
 // Values that cross workgroups travel as 64-bit words {sequence number, 32-bit payload} written and read with

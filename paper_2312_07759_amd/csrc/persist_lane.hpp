@@ -3,8 +3,9 @@
 //   hop 1  (inside a die) workgroup g stores its partial sums contiguously at buf1[parity][g][.]; the members of a die
 //          (workgroups x, x + 8, ...) each own a slice of the words, read it from every member's line, add it in float64
 //          in a fixed order and store the die's totals at buf3[parity][x][.];
-//   hop 2  (across dies) EVERY workgroup reads the words of the up to 8 dies, adds them in a fixed order and applies the
-//          O(k d) update itself, so that all hold the same state and take the same stop decision.
+//   hop 2  (across dies) every member adds the 8 dies' totals of its slice, in a fixed order, and stores the grid totals at
+//          buf4[parity][x][.], where its die reads them; EVERY workgroup applies the O(k d) update itself, so that all
+//          hold the same state and take the same stop decision.
 // As in persist_small.hpp a store of hop 1 only has to reach the die's L2 when all members of the die run there (checked at
 // the start of a launch).  There one workgroup per die adds all of the at most 80 words.  The form this
 // replaced had one reducer per codeword that read all 256 workgroups through memory, and a broadcast of the result:
@@ -194,10 +195,10 @@ __device__ __forceinline__ bool die_slice(const PArgs& pa, unsigned int seq, int
     return true;
 }
 
-// Hop 2 for more than HOP3_WORDS sums, in two steps: every workgroup adds the dies' totals of its own slice and stores the
-// grid totals for its die, whose members read them from the L2.  (With one step every workgroup reads 8 nacc words through
-// memory: 21 MB per pass at k = 256, d = 4.)  Leaves the totals in s_tot, in every workgroup; ends with a barrier.
-constexpr int HOP3_WORDS = 384;
+// Hop 2 where dies have several members, in two steps: every workgroup adds the dies' totals of its own slice and stores the
+// grid totals for its die, whose members read them from the L2.  (With one step every workgroup polls 8 nacc words through
+// memory, and those polls hold up the stores they wait for: k = 64, d = 1 598 us against 562 with two steps.)  Leaves the
+// totals in s_tot, in every workgroup; ends with a barrier.
 template <int NT>
 __device__ __forceinline__ bool grid_totals_by_slices(const PArgs& pa, unsigned int seq, int nacc, LShared& ls, double* s_tot) {
     const int x0 = pa.wg % DIES, mi = pa.wg / DIES, nd = pa.G < DIES ? pa.G : DIES;
@@ -259,7 +260,7 @@ __device__ __forceinline__ bool grid_totals_by_slices(const PArgs& pa, unsigned 
 // barrier.
 template <int NT>
 __device__ __forceinline__ bool grid_totals(const PArgs& pa, unsigned int seq, int nacc, LShared& ls, double* s_tot) {
-    if (pa.G > DIES && nacc > HOP3_WORDS) return grid_totals_by_slices<NT>(pa, seq, nacc, ls, s_tot);
+    if (pa.G > DIES) return grid_totals_by_slices<NT>(pa, seq, nacc, ls, s_tot);
     if (pa.G > 1) {
         const int nd = pa.G < DIES ? pa.G : DIES;
         const unsigned int stamp = stamp24(seq);
@@ -362,6 +363,7 @@ __device__ __forceinline__ void persist_lane_fwd_body(const Args& a, const PArgs
     __shared__ LShared ls;
     __shared__ __align__(16) float s_Cf[KDP];
     __shared__ float s_rpart[KB > 0 ? NT / 64 : 1][KB > 0 ? KMAX * ACCW : 1];  // row form: totals of the wavefronts
+    __shared__ __align__(16) float s_rtab[KB > 0 ? RowWave<(KB > 0 ? KB : 1), D, DIST, PASS_FWD>::TAB : 1];
 
     const int tid = threadIdx.x, wg = pa.wg;
     const int k = a.k, kd = k * D, nacc = k * ACCW;
@@ -441,8 +443,13 @@ __device__ __forceinline__ void persist_lane_fwd_body(const Args& a, const PArgs
             publish_matrix();
         } else if constexpr (KB > 0) {
             {
-                RowWave<KB, D, DIST, PASS_FWD> st;
-                st.init(k, s_Cf, nullptr, nullptr, a.escale);
+                using RW = RowWave<KB, D, DIST, PASS_FWD>;
+                if (RW::TAB > 1) {
+                    RW::template fill_table<NT>(s_rtab, k, s_Cf, nullptr, nullptr, a.escale);
+                    __syncthreads();
+                }
+                RW st;
+                st.init(k, RW::TAB > 1 ? s_rtab : s_Cf, nullptr, nullptr, a.escale);
                 row_tile_pass<KB, D, DIST, PASS_FWD, NT>(a, st, s_tile, nullptr, base, cnt);
                 IDKM_LSTAMP(1);
                 st.collect(s_rpart[tid >> 6]);
@@ -529,7 +536,7 @@ __device__ __forceinline__ void persist_lane_fwd_body(const Args& a, const PArgs
     }
     // only workgroup 0 needs these totals: it writes the state and, last, the word that says the launch ran to its end (the
     // others of its die pass their slices on)
-    if (wg != 0 && !(nacc > HOP3_WORDS && wg % DIES == 0)) return;
+    if (wg % DIES != 0) return;
     if (!grid_totals<NT>(pa, seq, nacc, ls, s_tot)) return;
     if (wg != 0) return;
     double empty = 0.0, wrong = 0.0;

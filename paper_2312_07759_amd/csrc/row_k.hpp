@@ -46,7 +46,30 @@ struct RowWave {
     float acc[NA];
     int k;
 
-    // Cf, Hs, Ff: tables in LDS, [16 KB][D], zero from row k on (16-byte aligned for d = 8).
+    // d = 8, scaled passes: the operands of the codewords in the coordinates of the pass, formed once per pass by the whole
+    // workgroup (in every step they cost as much again as the energies): tab[j][.] = s c_j, 1e18 where no codeword is; the
+    // (dF/dC)^T pass also h_j / s behind them, then h_j . F_j.  TAB floats of LDS; the caller's barrier follows.
+    static constexpr int TAB = (!REGS && SCALED) ? 16 * KB * (USE_H ? 2 * D + 1 : D) : 1;
+    template <int NT>
+    static __device__ __forceinline__ void fill_table(float* tab, int k, const float* Cf, const float* Hs, const float* Ff, float escale) {
+        if constexpr (!REGS && SCALED) {
+            const float inv = 1.0f / escale;
+            for (int i = threadIdx.x; i < 16 * KB * D; i += NT) {
+                tab[i] = i < k * D ? Cf[i] * escale : 1e18f;
+                if (USE_H) tab[16 * KB * D + i] = Hs[i] * inv;
+            }
+            if (USE_H)
+                for (int j = threadIdx.x; j < 16 * KB; j += NT) {
+                    float hf = 0.f;
+#pragma unroll
+                    for (int r = 0; r < D; ++r) hf = fmaf(Hs[j * D + r], Ff[j * D + r], hf);
+                    tab[32 * KB * D + j] = hf;
+                }
+        }
+    }
+
+    // Cf, Hs, Ff: tables in LDS, [16 KB][D], zero from row k on (16-byte aligned for d = 8); scaled passes at d = 8: Cf is the
+    // table above and the others are not read.
     __device__ __forceinline__ void init(int k_, const float* Cf, const float* Hs, const float* Ff, float escale) {
         const int j0 = threadIdx.x & 15;
         k = k_;
@@ -104,11 +127,6 @@ struct RowWave {
             for (int r = 0; r < D; ++r) c[r] = rc[b][r];
         } else {
             table_row(tc, b, c);
-            const bool valid = (int)(threadIdx.x & 15) + 16 * b < k;
-            if (SCALED) {
-#pragma unroll
-                for (int r = 0; r < D; ++r) c[r] = valid ? c[r] * escale : 1e18f;
-            }
         }
     }
     __device__ __forceinline__ void cotangent(int b, float (&h)[D]) const {
@@ -322,19 +340,17 @@ struct RowWave {
                 if (PASS == PASS_B3) cotangent(b, h);
 #pragma unroll
                 for (int i = 0; i < V; ++i) {
-                    const float th = p[b][i] * (q[b][i] - qb[i]);
+                    // a_ij (q_ij - q_i) times the factor of w - c in d e / d w (2, or 1 / ||w - c||)
+                    float th = p[b][i] * (q[b][i] - qb[i]);
+                    if (DIST == DIST_SQL2) th *= 2.f;
+                    if (DIST == DIST_L2 && D > 1) th *= ri[(DIST == DIST_L2 && D > 1) ? b : 0][i];
+                    const float pt = PASS == PASS_B3 ? p[b][i] * a.tau : 0.f;
 #pragma unroll
                     for (int r = 0; r < D; ++r) {
                         const float df = w[i][r] - c[r];
-                        float dl;
-                        if (DIST == DIST_SQL2)
-                            dl = 2.f * df;
-                        else if (D == 1)
-                            dl = (df > 0.f) ? 1.f : ((df < 0.f) ? -1.f : 0.f);
-                        else
-                            dl = df * ri[(DIST == DIST_L2 && D > 1) ? b : 0][i];
+                        const float dl = (DIST == DIST_L2 && D == 1) ? ((df > 0.f) ? 1.f : ((df < 0.f) ? -1.f : 0.f)) : df;
                         if (PASS == PASS_B3) {
-                            out[i][r] = fmaf(p[b][i], h[r] * a.tau, out[i][r]);
+                            out[i][r] = fmaf(pt, h[r], out[i][r]);
                             out[i][r] = fmaf(-th, dl, out[i][r]);
                         } else {
                             float t = acc[b * ACCW + r];
@@ -448,15 +464,8 @@ struct RowWave {
                     cotangent(b, h);
                     hf = rf[b][0];
                 } else {
-                    float f[D];
-                    cotangent(b, h);
-                    image(b, f);
-                    hf = 0.f;
-#pragma unroll
-                    for (int r = 0; r < D; ++r) {
-                        hf = fmaf(h[r], f[r], hf);
-                        h[r] *= inv;
-                    }
+                    table_row(tc + 16 * KB * D, b, h);
+                    hf = tc[32 * KB * D + (threadIdx.x & 15) + 16 * b];
                 }
 #pragma unroll
                 for (int i = 0; i < V; ++i) {
@@ -530,7 +539,11 @@ __device__ __forceinline__ void row_tile_pass(const Args& a, RowWave<KB, D, DIST
                                               const float* s_g, int64_t base, int cnt) {
     constexpr int STEP = RowWave<KB, D, DIST, PASS>::STEP;
     int v0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * STEP;
-    for (; v0 + STEP <= cnt; v0 += (NT / 64) * STEP) st.template step<true>(a, s_w, s_g, base, v0, cnt);
+    PassPriority prio((cnt - v0 + (NT / 64) * STEP - 1) / ((NT / 64) * STEP));
+    for (; v0 + STEP <= cnt; v0 += (NT / 64) * STEP) {
+        st.template step<true>(a, s_w, s_g, base, v0, cnt);
+        prio.step_done();
+    }
     if (v0 < cnt) st.template step<false>(a, s_w, s_g, base, v0, cnt);
 }
 
@@ -547,6 +560,7 @@ __global__ __launch_bounds__(RST) void row_pass(const Args a) {
     extern __shared__ __align__(16) float s_tile[];
     __shared__ __align__(16) float s_Cf[KDP];
     __shared__ __align__(16) float s_Hs[RW::USE_H ? KDP : 1], s_Ff[RW::USE_H ? KDP : 1];
+    __shared__ __align__(16) float s_rtab[RW::TAB];
     __shared__ float s_part[PASS == PASS_B3 ? 1 : RST / 64][PASS == PASS_B3 ? 1 : 16 * KB * RW::ACCW];
     const int tid = threadIdx.x, k = a.k, kd = k * D, per = (int)a.vec_per_wg;
     const int64_t base = (int64_t)blockIdx.x * per;
@@ -563,8 +577,12 @@ __global__ __launch_bounds__(RST) void row_pass(const Args a) {
         }
     }
     __syncthreads();
+    if (RW::TAB > 1) {
+        RW::template fill_table<RST>(s_rtab, k, s_Cf, s_Hs, s_Ff, a.escale);
+        __syncthreads();
+    }
     RW st;
-    st.init(k, s_Cf, s_Hs, s_Ff, a.escale);
+    st.init(k, RW::TAB > 1 ? s_rtab : s_Cf, s_Hs, s_Ff, a.escale);
     row_tile_pass<KB, D, DIST, PASS, RST>(a, st, s_tile, s_g, base, cnt);
     if constexpr (PASS != PASS_B3) {
         st.collect(s_part[tid >> 6]);
