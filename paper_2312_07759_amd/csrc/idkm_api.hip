@@ -428,7 +428,7 @@ bool plan_small(idkm_ctx* ctx, bool bwd, PersistPlan* pp, const void* dwq) {
     const size_t lds = (size_t)per * d * sizeof(float) * (bwd ? 2 : 1);
     pp->grid = (int)((m + per - 1) / per);
     pp->per = (int)per;
-    pp->lds = lds;
+    pp->lds = ctx->sink ? (size_t)per * d * sizeof(float) : lds;  // (a batched backward keeps dL/dWq in memory)
     if (ragged && (lds > ctx->tile_limit || (pp->grid > 1 && pp->grid < TREE_MIN_G))) return false;
     if (lds > ctx->tile_limit) {
         // the layer does not fit on chip: the same solve with W (and dL/dWq) read from memory in every pass.  Not
@@ -1337,6 +1337,8 @@ idkm_status batch_launch(idkm_batch* b, hipStream_t s) {
     std::vector<Deferred>& q = b->deferred;
     b->launches = 0;
     if (q.empty()) return IDKM_OK;
+    // largest tiles first: a launch reserves the LDS of its largest tile for every workgroup, so layers of a size belong together
+    std::stable_sort(q.begin(), q.end(), [](const Deferred& x, const Deferred& y) { return x.pp.lds > y.pp.lds; });
     std::vector<char> taken(q.size(), 0);
     size_t item_off = 0, map_off = 0;
     for (size_t first = 0; first < q.size(); ++first) {
