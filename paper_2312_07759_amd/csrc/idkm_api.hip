@@ -394,7 +394,7 @@ constexpr size_t LANE_XBUF_WORDS = LANE_BUF1_WORDS + 2 * LANE_BUF3_WORDS + PT;
 
 
 // The lane<->vector family's part of plan_persistent.
-bool plan_small(idkm_ctx* ctx, bool bwd, PersistPlan* pp, const void* dwq) {
+bool plan_small(idkm_ctx* ctx, bool bwd, PersistPlan* pp, const void* dwq, int mode) {
     const int k = ctx->k, d = ctx->d;
     const int64_t m = ctx->m;
     // A codebook whose size is not a power of two runs in the kernels for the next one, the surplus codewords' weights held
@@ -415,9 +415,26 @@ bool plan_small(idkm_ctx* ctx, bool bwd, PersistPlan* pp, const void* dwq) {
     pp->lane = false;
     const int64_t chunk = (int64_t)ctx->min_vec_per_thread * PT;
     int64_t g = (m + chunk - 1) / chunk;  // a few vectors per thread before adding workgroups
-    // up to 16 vectors per thread one workgroup alone is faster (measured: 2.7 us per pass at m = 4096 against 3.7):
-    // it needs no exchange through memory
-    if (m <= (int64_t)16 * PT) g = 1;
+    // Up to 16 vectors per thread one workgroup alone needs no exchange through memory (2.0 to 5.5 us a pass in a team of
+    // eight whatever m is), but walks through all vectors itself.  Where the lines lie (us per evaluation, one workgroup
+    // against eight; m = 1024 / 1800 / 4096, plain norm): k = 4, d = 1 1.1 / 1.6 / 1.9 against 2.2; k = 8, d = 1 1.4 / 2.7 /
+    // 2.8 against 2.5; k = 16, d = 1 2.0 / 3.7 / 4.8 against 2.8; k = 8, d = 4 2.6 / 6.2 / 6.6 against 3.4; k = 16, d = 4
+    // 4.4 / 8.7 / 11.8 against 4.5.  (dF/dC)^T passes: k = 4, d = 1 1.6 / 2.4 / 2.9 against 2.5; k = 16, d = 1 2.9 / 4.8 /
+    // 7.2 against 3.2; k = 16, d = 4 6.9 / 12.0 / 19.1 against 5.8.  Batched launches hide the exchange behind other layers
+    // and keep one workgroup, as do the modes that are solved in one place.
+    if (m <= (int64_t)16 * PT) {
+        const int64_t v = (m + PT - 1) / PT;
+        const int kd = K * d;
+        int from = 99;  // vectors per thread from which the team of eight is faster
+        if (bwd)
+            from = kd >= 64 ? 4 : kd >= 16 ? 5 : (kd >= 8 && K > 2) ? 8 : kd >= 4 ? 12 : 99;
+        else if (K >= 8)
+            from = kd >= 32 ? 5 : kd >= 16 ? 6 : 8;
+        else if (kd >= 16)
+            from = 12;
+        const bool one = ctx->sink || !ctx->tree_exchange || mode == IDKM_BWD_DENSE || mode == IDKM_BWD_GMRES;
+        g = (!one && v >= from) ? DIES : 1;
+    }
     if (g < 1) g = 1;
     // (a team of 2 to 7 workgroups would take the one-level exchange; 8 smaller workgroups take the two-level one)
     if (ctx->tree_exchange && g > 1 && g < DIES) g = DIES;
@@ -451,11 +468,12 @@ bool plan_small(idkm_ctx* ctx, bool bwd, PersistPlan* pp, const void* dwq) {
 // matrix_ok: the matrix-core kernels may serve the call (every pass of both energies has a matrix-core form).
 // dwq: the backward's upstream gradient (a layer too large for LDS is streamed from memory with 16-byte loads, which
 // W and dL/dWq must allow).
-bool plan_persistent(idkm_ctx* ctx, bool bwd, PersistPlan* pp, bool matrix_ok = true, const void* dwq = nullptr) {
+// mode: the backward's (BWD_JFB where there is none).
+bool plan_persistent(idkm_ctx* ctx, bool bwd, PersistPlan* pp, bool matrix_ok = true, const void* dwq = nullptr, int mode = IDKM_BWD_JFB) {
     if (!ctx->coop || ctx->num_cu < 1) return false;
     const int k = ctx->k, d = ctx->d;
     const int64_t m = ctx->m;
-    if (plan_small(ctx, bwd, pp, dwq)) return true;
+    if (plan_small(ctx, bwd, pp, dwq, mode)) return true;
     if (!(k >= 2 && k <= 16 && pow2(k) && d <= 4)) {
         // lane<->codeword family
         int kpl = (k + 63) / 64, p = 1;
@@ -1041,7 +1059,7 @@ idkm_status idkm_backward(idkm_ctx* ctx, const float* dWq, idkm_bwd_mode mode, f
         // when the K D (K D + D + 1) sums fit one exchange line the persistent kernel does it in one launch
         // (and batched calls can share that launch between layers)
         PersistPlan ppd;
-        if (kd * kd + kd * ctx->d + kd <= XDENSE && ctx->path != IDKM_PATH_STREAM && plan_persistent(ctx, true, &ppd, true, dWq)) {
+        if (kd * kd + kd * ctx->d + kd <= XDENSE && ctx->path != IDKM_PATH_STREAM && plan_persistent(ctx, true, &ppd, true, dWq, (int)mode)) {
             PArgs pa;
             std::memset(&pa, 0, sizeof(pa));
             pa.tol = 0.0;
@@ -1090,7 +1108,7 @@ idkm_status idkm_backward(idkm_ctx* ctx, const float* dWq, idkm_bwd_mode mode, f
     }
 
     PersistPlan pp;
-    bool persistent = ctx->path != IDKM_PATH_STREAM && plan_persistent(ctx, true, &pp, true, dWq);
+    bool persistent = ctx->path != IDKM_PATH_STREAM && plan_persistent(ctx, true, &pp, true, dWq, (int)mode);
     // The minimal-residual solve keeps O(k d R) state.  Inside the persistent kernel every workgroup holds all of it
     // (in LDS, behind its tiles), which takes a team where every workgroup receives the grid totals (one workgroup, or
     // the two-level exchange of a full-device team), k d <= 64 and room for the state beside the tiles; everything

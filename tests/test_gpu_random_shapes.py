@@ -135,3 +135,26 @@ def test_full_device_teams_on_the_persistent_path(ctx, k, d, m, tau, seed, dist)
         gg = ctx.get_cotangents(k, d)[1]
         res = rj["v"] + orc.vjp_F(Cg, W, tau, dist, gg)[0] - gg
         assert np.linalg.norm(res) < TOL_GRAD * np.linalg.norm(rj["v"]), (bg["info"], np.linalg.norm(res), np.linalg.norm(rj["v"]))
+
+
+# layers of up to 16 vectors per thread on both sides of the line between one workgroup and a team of eight
+@pytest.mark.parametrize("dist", [wl.DIST_L2, wl.DIST_SQL2])
+@pytest.mark.parametrize("k,d,m", [(4, 1, 2_816), (4, 1, 2_817), (8, 1, 1_792), (8, 1, 1_793), (16, 1, 1_281), (16, 4, 769), (16, 4, 1_025),
+                                   (4, 4, 4_096), (2, 2, 2_817), (7, 2, 1_281), (8, 4, 1_024), (16, 2, 4_095)])
+def test_small_layers_around_the_first_team(ctx, k, d, m, dist):
+    W, C0, G = wl.random_problem(m, d, k, seed=m + k, std=0.5, spread=1.5)
+    C0 = (C0 + 0.01 * np.random.default_rng(k).standard_normal(C0.shape)).astype(np.float32)
+    W, G = W.astype(np.float32), G.astype(np.float32)
+    Wd, Cd, Gd = dev(W), dev(C0), dev(G)
+    ref = orc.soft_kmeans(W, C0, 0.15, 0.0, 10, dist)
+    out = ctx.forward(Wd, Cd, 0.15, 0.0, 10, dist, want_assign=True)
+    Cg = out["C"].cpu().numpy()
+    assert out["info"].path == binding.PATH_PERSISTENT and rel(Cg, ref["C"]) < TOL_VAL
+    assert rel(out["Wq"].cpu().numpy(), orc.soft_quantize(W, Cg, 0.15, dist)) < TOL_VAL
+    assert np.array_equal(out["assign"].cpu().numpy(), orc.hard_assign_f32(W, Cg))
+    for name, mode, kw in (("jfb", binding.BWD_JFB, {}), ("implicit", binding.BWD_IMPLICIT, dict(tol=0.0, max_iter=6))):
+        b = ctx.backward(Gd, mode, **kw)
+        assert b["info"].path == binding.PATH_PERSISTENT
+        assert rel(b["dW"].cpu().numpy(), orc.backward(W, Cg, 0.15, dist, G, name, tol=0.0, max_iter=6)["dW"]) < TOL_GRAD
+    b = ctx.backward(Gd, binding.BWD_GMRES, tol=1e-5, max_iter=200)
+    assert b["info"].path == binding.PATH_PERSISTENT
