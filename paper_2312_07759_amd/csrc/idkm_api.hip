@@ -666,7 +666,7 @@ idkm_status finish_persistent(idkm_ctx* ctx, idkm_info* info) {
         HIP_TRY(ctx, hipMemcpyAsync(&ctx->res_copy, ctx->h_res, sizeof(PResult), hipMemcpyDeviceToHost, ctx->pending_stream));
     HIP_TRY(ctx, hipStreamSynchronize(ctx->pending_stream));
     const PResult& c = ctx->res_on_device ? ctx->res_copy : *ctx->h_res;
-    if (c.done != ctx->pending_id) return fail(ctx, IDKM_ERR_DEVICE, "a grid-wide wait hit its limit");
+    if (c.done != ctx->pending_id || c.aborted == ctx->pending_id) return fail(ctx, IDKM_ERR_DEVICE, "a grid-wide wait hit its limit");
     if (kind == 1) {
         for (int r = 0; r < c.nred && r < 16; ++r)
             if (c.fin[r] != ctx->pending_id) return fail(ctx, IDKM_ERR_DEVICE, "a grid-wide wait hit its limit");

@@ -41,7 +41,7 @@ struct LShared {
 
 __device__ __forceinline__ void raise_abort(const PArgs& pa, LShared& ls) {
     ls.abort = 1;
-    __hip_atomic_store(pa.abort_word, pa.seq_base + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    raise_abort(pa);
 }
 
 // Sum of one float64 per thread over the workgroup, fixed order, returned to every thread.

@@ -63,7 +63,7 @@ struct PResult {
     int empty[16], bad[16];  // per reducer, from the evaluation at C*
     int nred;                // forward: reducers that report in fin[] (0: the workgroup that wrote `done` wrote everything)
     unsigned int fin[16];    // forward: == launch id once reducer r has written its slice of the state
-    int pad_;
+    unsigned int aborted;    // == launch id once any workgroup has given up a wait, whatever the others went on to do
 };
 
 struct PArgs {
@@ -117,6 +117,14 @@ struct BatchItem {
 #define IDKM_SUB(slot) do { } while (0)
 #endif
 
+
+// A bounded wait has expired: tells the other workgroups to leave, and the host.  (The host cannot go by `done` alone: in
+// the last exchange the workgroup that writes it may already hold all its words while another one waits in vain, and
+// leaves without its share of the output.)
+__device__ __forceinline__ void raise_abort(const PArgs& pa) {
+    __hip_atomic_store(pa.abort_word, pa.seq_base + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&pa.out->aborted, pa.seq_base + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 
 // Shared scratch of the exchange.  WIDE: the dies' totals travel with 29 significant bits (pack_d40) instead of as float32.
 // Only the ragged codebooks need it: the kernels those shapes came from kept the totals in float64, and under the plain norm
@@ -336,7 +344,7 @@ __device__ __forceinline__ bool reduce_slice(const PArgs& pa, unsigned int seq, 
     xs.red2[tid] = s;
     if (aborted) {
         xs.abort = 1;
-        __hip_atomic_store(pa.abort_word, pa.seq_base + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        raise_abort(pa);
     }
     __syncthreads();
 #ifdef IDKM_TRACE
@@ -379,7 +387,7 @@ __device__ __forceinline__ bool gather_bcast(const PArgs& pa, unsigned int seq, 
     }
     if (aborted) {
         xs.abort = 1;
-        __hip_atomic_store(pa.abort_word, pa.seq_base + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        raise_abort(pa);
     }
     __syncthreads();
     return xs.abort == 0;
@@ -404,7 +412,7 @@ __device__ __forceinline__ bool tree_handshake(const PArgs& pa, XS& xs) {
                 local = ((unsigned int)w[0] == mine) ? 1 : 0;
             } else {
                 xs.abort = 1;
-                __hip_atomic_store(pa.abort_word, pa.seq_base + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                raise_abort(pa);
             }
         }
         if (pa.tree == 2) local = 0;  // test support: behave as if no workgroup ran on its leader's die
@@ -462,7 +470,7 @@ __device__ __forceinline__ bool tree_die_totals(const PArgs& pa, unsigned int se
     }
     if (aborted) {
         xs.abort = 1;
-        __hip_atomic_store(pa.abort_word, pa.seq_base + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        raise_abort(pa);
     }
     __syncthreads();
     if (xs.abort) return false;
@@ -516,7 +524,7 @@ __device__ __forceinline__ bool tree_grid_totals(const PArgs& pa, unsigned int s
         if (valid[u]) xs.stage2[tid + u * PT] = die_value<XS::WIDE>(w[u]);
     if (aborted) {
         xs.abort = 1;
-        __hip_atomic_store(pa.abort_word, pa.seq_base + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        raise_abort(pa);
     }
     __syncthreads();
     if (xs.abort) return false;
@@ -591,7 +599,7 @@ __device__ __forceinline__ bool tree8_die_totals(const PArgs& pa, unsigned int s
     if ((tid & 63) < 8) xs.red2[(tid >> 6) * 8 + p] = s;
     if (aborted) {
         xs.abort = 1;
-        __hip_atomic_store(pa.abort_word, pa.seq_base + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        raise_abort(pa);
     }
     __syncthreads();
     if (xs.abort) return false;
@@ -618,7 +626,7 @@ __device__ __forceinline__ void tree8_grid_totals_wave0(const PArgs& pa, unsigne
     } else if (!poll_die<XS::WIDE>(pa, src, seq, s)) {
         s = 0.0;
         xs.abort = 1;
-        __hip_atomic_store(pa.abort_word, pa.seq_base + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        raise_abort(pa);
     }
     s = sum_over_lane_bits_3_to_5(s);
     if (lane < 8 && slot_acc(p) < NACC) xs.totd[slot_acc(p)] = s;
@@ -642,7 +650,7 @@ __device__ __forceinline__ bool tree8_grid_totals_regs(const PArgs& pa, unsigned
         s = 0.0;
         failed = true;
         xs.abort = 1;
-        __hip_atomic_store(pa.abort_word, pa.seq_base + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        raise_abort(pa);
     }
     total = sum_over_lane_bits_3_to_5(s);
     return __builtin_amdgcn_ballot_w64(failed) == 0ull;
@@ -1117,7 +1125,7 @@ __device__ __forceinline__ void persist_fwd_body(const Args& a, const PArgs& pa)
             }
             if (aborted) {
                 xs.abort = 1;
-                __hip_atomic_store(pa.abort_word, pa.seq_base + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                raise_abort(pa);
             }
             IDKM_SUB(9);
             const double r2 = first_lanes_sum_d_dpp<KD>(df2);  // lanes >= KD hold zero; lane 0 decides
