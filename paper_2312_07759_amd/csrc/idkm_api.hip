@@ -165,7 +165,7 @@ struct idkm_ctx {
     size_t xbuf_words = 0;
     unsigned int seq_base = 0;
     unsigned long long* lane_xbuf = nullptr;  // exchange words of the lane<->codeword persistent kernels (lazy)
-    unsigned int lane_run = 0, small_run = 0; // run of 24-bit stamps that the wide words in lane_xbuf and in xbuf belong to
+    size_t lane_words = 0;                    // ... of this size
     unsigned int* abort_word = nullptr;  // device
     PResult* h_res = nullptr;            // pinned host; device memory when res_on_device
     bool res_on_device = false;          // the context of idkm_forward_noalloc: the kernel reports into device memory
@@ -367,7 +367,8 @@ idkm_status launch_pass(idkm_ctx* ctx, const Geometry& g, int pass, Args& a, hip
 constexpr size_t XBUF1_WORDS = (size_t)2 * PT * XLINE;
 constexpr size_t XBUF3_WORDS = (size_t)2 * DIES * XLINE;  // two-level exchange: totals of the dies
 constexpr size_t XBUF_WORDS = XBUF1_WORDS + (size_t)2 * XBCAST + XBUF3_WORDS + DIES;
-constexpr size_t XBUF_ALL_WORDS = XBUF_WORDS + XBUF3_WORDS;       // ... and of the ragged codebooks' exchange
+// ... and the lines of the ragged codebooks, whose sums take two words (see SumWords)
+constexpr size_t XBUF_ALL_WORDS = XBUF_WORDS + 2 * (XBUF1_WORDS + XBUF3_WORDS);
 constexpr size_t LDS_TILE_MAX = 144 * 1024;  // bytes of LDS a persistent workgroup may use for its tile
 
 struct PersistPlan {
@@ -386,12 +387,15 @@ struct Deferred {
 };
 constexpr size_t LDS_PER_CU = 160 * 1024;
 constexpr size_t LANE_TILE_MAX = 94 * 1024;                       // the lane kernels keep ~55 KB of static LDS
-constexpr size_t LANE_NACC = 2304;                                  // k (d+1) at most: k = 256, d = 8
-constexpr size_t LANE_BUF1_WORDS = (size_t)2 * PT * LANE_NACC;
-constexpr size_t LANE_BUF3_WORDS = (size_t)2 * DIES * LANE_NACC;   // totals of the dies
-// ... the grid totals, one copy per die (buf4), and the die of every workgroup
-constexpr size_t LANE_XBUF_WORDS = LANE_BUF1_WORDS + 2 * LANE_BUF3_WORDS + PT;
-
+// Exchange words of the large-codebook kernels: a line per workgroup (buf1), the totals of the dies (buf3) and the grid totals,
+// a copy per die (buf4), in two words a sum, and the die of every workgroup.  Most sums k (d + 1) of a pass, and words of
+// a workgroup's line: d <= 4 1536 and as many; d = 8 (k <= 256) 2304 and twice that (float64 sums).
+struct LaneBuf {
+    size_t line, buf3;
+    explicit LaneBuf(int d) : line(d == 8 ? 4608 : 1536), buf3((size_t)2 * DIES * 2 * (d == 8 ? 2304 : 1536)) {}
+    size_t buf1() const { return (size_t)2 * PT * line; }
+    size_t words() const { return buf1() + 2 * buf3 + PT; }
+};
 
 // The lane<->vector family's part of plan_persistent.
 bool plan_small(idkm_ctx* ctx, bool bwd, PersistPlan* pp, const void* dwq, int mode) {
@@ -555,45 +559,39 @@ idkm_status launch_persistent(idkm_ctx* ctx, const PersistPlan& pp, Args& a, PAr
         hipLaunchKernelGGL(k_fill_u64, dim3(64), dim3(256), 0, s, ctx->xbuf, ctx->xbuf_words, 0ull);
         HIP_TRY(ctx, hipGetLastError());
         if (ctx->lane_xbuf) {
-            hipLaunchKernelGGL(k_fill_u64, dim3(256), dim3(256), 0, s, ctx->lane_xbuf, LANE_XBUF_WORDS, 0ull);
+            hipLaunchKernelGGL(k_fill_u64, dim3(256), dim3(256), 0, s, ctx->lane_xbuf, ctx->lane_words, 0ull);
             HIP_TRY(ctx, hipGetLastError());
         }
         ctx->seq_base = 0;
-        ctx->lane_run = ctx->small_run = 0;
     }
-    // The dies' totals of the large codebooks and the ragged ones carry 24-bit stamps: their words are cleared when this launch's sequence numbers lie in, or reach,
-    // another run of STAMP_RUN than the words left by earlier launches (once per 16.8 M exchanges).
-    const unsigned int run_first = (ctx->seq_base + 1u) / STAMP_RUN, run_last = (ctx->seq_base + exchanges) / STAMP_RUN;
     if (pp.lane) {
-        if (!ctx->lane_xbuf) {
-            if (hipMalloc(&ctx->lane_xbuf, LANE_XBUF_WORDS * sizeof(unsigned long long)) != hipSuccess)
+        const LaneBuf lb(ctx->d);
+        if (ctx->lane_words < lb.words()) {
+            if (ctx->lane_xbuf) (void)hipFree(ctx->lane_xbuf);  // (waits for what still runs)
+            ctx->lane_xbuf = nullptr;
+            ctx->lane_words = 0;
+            if (hipMalloc(&ctx->lane_xbuf, lb.words() * sizeof(unsigned long long)) != hipSuccess) {
+                (void)hipGetLastError();
                 return fail(ctx, IDKM_ERR_ALLOC, "hipMalloc of the exchange buffer failed");
-            hipLaunchKernelGGL(k_fill_u64, dim3(256), dim3(256), 0, s, ctx->lane_xbuf, LANE_XBUF_WORDS, 0ull);
+            }
+            ctx->lane_words = lb.words();
+            hipLaunchKernelGGL(k_fill_u64, dim3(256), dim3(256), 0, s, ctx->lane_xbuf, ctx->lane_words, 0ull);
             HIP_TRY(ctx, hipGetLastError());
-            ctx->lane_run = run_first;
-        } else if (run_last != ctx->lane_run) {
-            hipLaunchKernelGGL(k_fill_u64, dim3(64), dim3(256), 0, s, ctx->lane_xbuf + LANE_BUF1_WORDS, 2 * LANE_BUF3_WORDS, 0ull);
-            HIP_TRY(ctx, hipGetLastError());
-            ctx->lane_run = run_first;
         }
         pa.buf1 = ctx->lane_xbuf;
-        pa.buf3 = ctx->lane_xbuf + LANE_BUF1_WORDS;
-        pa.buf4 = pa.buf3 + LANE_BUF3_WORDS;
-        pa.tab = pa.buf4 + LANE_BUF3_WORDS;
+        pa.buf3 = ctx->lane_xbuf + lb.buf1();
+        pa.buf4 = pa.buf3 + lb.buf3;
+        pa.tab = pa.buf4 + lb.buf3;
         pa.tree = (ctx->tree_exchange && !ctx->tree_remote) ? 1 : 2;  // 2: every store of hop 1 at device scope
     } else {
         pa.buf1 = ctx->xbuf;
         pa.buf2 = ctx->xbuf + XBUF1_WORDS;
         pa.buf3 = pa.buf2 + (size_t)2 * XBCAST;
         pa.tab = pa.buf3 + XBUF3_WORDS;
-        if (!pow2(ctx->k)) {  // (their wide words never share memory with the others')
+        if (!pow2(ctx->k)) {
             if (ctx->xbuf_words < XBUF_ALL_WORDS) return fail(ctx, IDKM_ERR_DEVICE, "exchange buffer too small");
-            pa.buf3 = ctx->xbuf + XBUF_WORDS;
-            if (run_last != ctx->small_run) {
-                hipLaunchKernelGGL(k_fill_u64, dim3(8), dim3(256), 0, s, pa.buf3, XBUF3_WORDS, 0ull);
-                HIP_TRY(ctx, hipGetLastError());
-                ctx->small_run = run_first;
-            }
+            pa.buf1 = ctx->xbuf + XBUF_WORDS;
+            pa.buf3 = pa.buf1 + 2 * XBUF1_WORDS;
         }
         // teams of DIES workgroups or more: hop 1 stays inside each die (the explicit-Jacobian mode keeps the plain
         // exchange, its one reduction ends in workgroup 0).  Also inside a batched launch: a team's workgroups are

@@ -60,15 +60,15 @@ __device__ __forceinline__ double block_sum_fixed(double x, LShared& ls) {
     return ls.scalar;
 }
 
-// Hop-1 store: word idx of this workgroup's line.
-__device__ __forceinline__ void put_word(const PArgs& pa, const LShared& ls, unsigned long long* line, unsigned int seq, int idx, double t) {
-    if (ls.local)
-        st_word_die(&line[idx], pack_f(seq, (float)t));
-    else
-        st_word(&line[idx], pack_f(seq, (float)t));
+// Hop-1 store: sum idx of this workgroup's line.  WIDE as in SumWords: the workgroups' sums of d = 8 travel as float64 (its
+// solves on the stream path hand them on in that form), the others as float32; the totals are float64 from there on.
+template <bool WIDE>
+__device__ __forceinline__ void put_sum(const LShared& ls, unsigned long long* line, int nacc, unsigned int seq, int idx, double t) {
+    st_sum<WIDE>(&line[idx], nacc, seq, t, ls.local != 0);
 }
+template <bool WIDE>
 __device__ __forceinline__ unsigned long long* own_line(const PArgs& pa, unsigned int seq, int nacc) {
-    return pa.buf1 + ((size_t)(seq & 1u) * pa.G + pa.wg) * nacc;
+    return pa.buf1 + ((size_t)(seq & 1u) * pa.G + pa.wg) * nacc * SumWords<WIDE>::N;
 }
 
 // Workgroup partial of the lane accumulators (wavefronts add one after the other, float64) and hop-1 store.
@@ -89,10 +89,10 @@ __device__ __forceinline__ void publish_lane(const PArgs& pa, const LShared& ls,
         __syncthreads();
     }
     const int nacc = k * ACCW;
-    unsigned long long* dst = own_line(pa, seq, nacc);
+    unsigned long long* dst = own_line<false>(pa, seq, nacc);
     for (int idx = tid; idx < nacc; idx += NT) {
         const int j = idx / ACCW, comp = idx - j * ACCW;
-        put_word(pa, ls, dst, seq, idx, s_acc[j & 63][(j >> 6) * ACCW + comp]);
+        put_sum<false>(ls, dst, nacc, seq, idx, s_acc[j & 63][(j >> 6) * ACCW + comp]);
     }
 }
 
@@ -120,11 +120,15 @@ __device__ __forceinline__ bool die_handshake(const PArgs& pa, LShared& ls) {
     return ls.abort == 0;
 }
 
+// Words of the dies' and the grid's totals: the halves of a sum lie next to each other, the lower one first.
+__device__ __forceinline__ unsigned long long half_word(unsigned int seq, double t, int half) {
+    return pack_u(seq, (unsigned int)(half ? __double2hiint(t) : __double2loint(t)));
+}
 // Hop 1, receiving side: this workgroup's slice of its die's totals.  S = ceil(nacc / members) words per member; SP, the
 // power of two at or above it (at most NT), threads take one word each of NT / SP lines at a time; what several lines
 // leave in the lanes of a wavefront is added across lanes, the wavefronts through LDS, all in a fixed order.  With one die
 // (a team of one) the totals go straight to s_tot.  Returns false if the wait was abandoned.
-template <int NT>
+template <int NT, bool WIDE = false>
 __device__ __forceinline__ bool die_slice(const PArgs& pa, unsigned int seq, int nacc, LShared& ls, double* s_tot) {
     const int tid = threadIdx.x, lane = tid & 63, x = pa.wg % DIES, mi = pa.wg / DIES;
     const int nmem = (pa.G - x + DIES - 1) / DIES;
@@ -133,24 +137,29 @@ __device__ __forceinline__ bool die_slice(const PArgs& pa, unsigned int seq, int
     int lg = 0;
     while ((1 << lg) < S && (1 << lg) < NT) ++lg;
     const int SP = 1 << lg, LPR = NT >> lg;  // words and lines a round of loads covers
-    const unsigned long long* src = pa.buf1 + (size_t)(seq & 1u) * pa.G * nacc + first;
-    unsigned long long* out = pa.buf3 + ((size_t)(seq & 1u) * DIES + x) * nacc + first;
-    const unsigned int stamp = stamp24(seq);
+    constexpr int UNR = WIDE ? 8 : 4;        // lines in flight
+    using Word = SumWords<WIDE>;
+    const unsigned long long* src = pa.buf1 + (size_t)(seq & 1u) * pa.G * nacc * Word::N + first;
+    unsigned long long* out = pa.buf3 + ((size_t)(seq & 1u) * DIES + x) * nacc * 2 + 2 * first;
     if (n <= 0) __syncthreads();  // (s_tot may share memory with what publish_lane reads; otherwise the barrier below)
     for (int w0 = 0; w0 < n; w0 += SP) {
         const int w = w0 + (tid & (SP - 1)), l0 = tid >> lg;
         double s = 0.0;
         bool aborted = false;
-        for (int l = l0; l < nmem && w < n; l += 4 * LPR) {
-            unsigned long long v[4];
+        for (int l = l0; l < nmem && w < n; l += UNR * LPR) {
+            Word v[UNR];
             unsigned int spins = 0;
             for (;;) {
                 bool ok = true;
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    v[u] = (l + u * LPR < nmem) ? ld_word(src + (size_t)(x + (l + u * LPR) * DIES) * nacc + w) : pack_f(seq, 0.f);
+                for (int u = 0; u < UNR; ++u) {
+                    if (l + u * LPR < nmem)
+                        v[u].load(src + (size_t)(x + (l + u * LPR) * DIES) * nacc * Word::N + w, nacc);
+                    else
+                        v[u].zero(seq);
+                }
 #pragma unroll
-                for (int u = 0; u < 4; ++u) ok = ok && ((unsigned int)(v[u] >> 32) == seq);
+                for (int u = 0; u < UNR; ++u) ok = ok && v[u].arrived(seq);
                 if (ok) break;
                 ++spins;
                 if (spins > pa.spin_limit ||
@@ -160,7 +169,7 @@ __device__ __forceinline__ bool die_slice(const PArgs& pa, unsigned int seq, int
                 }
             }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) s += (double)__uint_as_float((unsigned int)v[u]);
+            for (int u = 0; u < UNR; ++u) s += v[u].value();
             if (aborted) break;
         }
         // lanes of a wavefront that hold the same word
@@ -176,125 +185,170 @@ __device__ __forceinline__ bool die_slice(const PArgs& pa, unsigned int seq, int
         if (aborted) raise_abort(pa, ls);
         __syncthreads();
         if (ls.abort) return false;
-        if (tid < SP && w0 + tid < n) {
+        // (two lanes a sum, one for each word: a slice leaves in one run of stores)
+        const int live = n - w0 < SP ? n - w0 : SP;
+        for (int h = tid; h < 2 * live; h += NT) {
+            const int q = h >> 1;
             const int groups = SP >= 64 ? LPR : NT / 64, stride = SP >= 64 ? SP : 64;
             double c2[2] = {0.0, 0.0};
             for (int g = 0; g + 1 < groups; g += 2) {
-                c2[0] += ls.part[g * stride + tid];
-                c2[1] += ls.part[(g + 1) * stride + tid];
+                c2[0] += ls.part[g * stride + q];
+                c2[1] += ls.part[(g + 1) * stride + q];
             }
-            if (groups & 1) c2[0] += ls.part[(groups - 1) * stride + tid];
+            if (groups & 1) c2[0] += ls.part[(groups - 1) * stride + q];
             const double t = c2[0] + c2[1];
             if (pa.G == 1)
-                s_tot[first + w0 + tid] = t;
+                s_tot[first + w0 + q] = t;  // (both lanes the same value)
             else
-                st_word(&out[w0 + tid], pack_d40(stamp, t));
+                st_word(&out[2 * w0 + h], half_word(seq, t, h & 1));
         }
         if (w0 + SP < n) __syncthreads();
     }
     return true;
 }
 
+// Sum of nd dies' totals of one word pair, for a pair of lanes: each waits for its half from every die (src, src + line, ...)
+// and gets the other from its neighbour.  Both return the sum, or false if the wait of either was abandoned.
+__device__ __forceinline__ bool dies_sum(const PArgs& pa, const unsigned long long* src, int line, int nd, unsigned int seq, double& out) {
+    unsigned long long v[DIES];
+    unsigned int spins = 0;
+    int failed = 0;
+    for (;;) {
+        bool ok = true;
+#pragma unroll
+        for (int x = 0; x < DIES; ++x) v[x] = x < nd ? ld_word(src + (size_t)x * line) : pack_u(seq, 0u);
+#pragma unroll
+        for (int x = 0; x < DIES; ++x) ok = ok && (unsigned int)(v[x] >> 32) == seq;
+        if (ok) break;
+        ++spins;
+        if (spins > pa.spin_limit ||
+            ((spins & 31u) == 0u && __hip_atomic_load(pa.abort_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == pa.seq_base + 1u)) {
+            failed = 1;
+            break;
+        }
+    }
+    failed |= dpp_i<0xB1, 0xf>(0, failed);  // quad_perm [1,0,3,2]
+    double t[DIES];
+#pragma unroll
+    for (int x = 0; x < DIES; ++x) {
+        const int own = (int)(unsigned int)v[x], other = dpp_i<0xB1, 0xf>(0, own);
+        t[x] = (threadIdx.x & 1) ? __hiloint2double(own, other) : __hiloint2double(other, own);
+    }
+    out = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
+    return !failed;
+}
+
 // Hop 2 where dies have several members, in two steps: every workgroup adds the dies' totals of its own slice and stores the
 // grid totals for its die, whose members read them from the L2.  (With one step every workgroup polls 8 nacc words through
 // memory, and those polls hold up the stores they wait for: k = 64, d = 1 598 us against 562 with two steps.)  Leaves the
 // totals in s_tot, in every workgroup; ends with a barrier.
-template <int NT>
+template <int NT, int MAXACC, int MAXRND>
 __device__ __forceinline__ bool grid_totals_by_slices(const PArgs& pa, unsigned int seq, int nacc, LShared& ls, double* s_tot) {
-    const int x0 = pa.wg % DIES, mi = pa.wg / DIES, nd = pa.G < DIES ? pa.G : DIES;
+    const int x0 = pa.wg % DIES, mi = pa.wg / DIES;
     const int nmem = (pa.G - x0 + DIES - 1) / DIES;
     const int S = (nacc + nmem - 1) / nmem, first = mi * S;
     const int n = nacc - first < S ? nacc - first : S;
-    const unsigned int stamp = stamp24(seq);
-    const unsigned long long* src = pa.buf3 + (size_t)(seq & 1u) * DIES * nacc;
-    unsigned long long* mine = pa.buf4 + ((size_t)(seq & 1u) * DIES + x0) * nacc;
+    const unsigned long long* src = pa.buf3 + (size_t)(seq & 1u) * DIES * nacc * 2 + 2 * first;
+    unsigned long long* mine = pa.buf4 + ((size_t)(seq & 1u) * DIES + x0) * nacc * 2;
     bool aborted = false;
     auto give_up = [&](unsigned int& spins) {
         ++spins;
-        aborted = spins > pa.spin_limit ||
-                  ((spins & 31u) == 0u && __hip_atomic_load(pa.abort_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == pa.seq_base + 1u);
-        return aborted;
+        return spins > pa.spin_limit ||
+               ((spins & 31u) == 0u && __hip_atomic_load(pa.abort_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == pa.seq_base + 1u);
     };
-    for (int w = threadIdx.x; w < n && !aborted; w += NT) {
-        unsigned long long v[DIES];
-        unsigned int spins = 0;
-        for (;;) {
-            bool ok = true;
-#pragma unroll
-            for (int x = 0; x < DIES; ++x) v[x] = x < nd ? ld_word(src + (size_t)x * nacc + first + w) : (unsigned long long)stamp;
-#pragma unroll
-            for (int x = 0; x < DIES; ++x) ok = ok && ((unsigned int)v[x] & 0xffffffu) == stamp;
-            if (ok || give_up(spins)) break;
-        }
-        double t[DIES];
-#pragma unroll
-        for (int x = 0; x < DIES; ++x) t[x] = unpack_d40(v[x]);
-        const unsigned long long word = pack_d40(stamp, ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7])));
-        if (aborted) break;  // (nothing that is not whole is passed on)
+    auto pass_on = [&](int h, double t) {
+        const unsigned long long word = half_word(seq, t, h & 1);
         if (ls.local)
-            st_word_die(&mine[first + w], word);
+            st_word_die(&mine[2 * first + h], word);
         else
-            st_word(&mine[first + w], word);
+            st_word(&mine[2 * first + h], word);
+    };
+    // A full device's slices: a row of 16 lanes takes a sum, lane 2 x + h waits for half h of die x's total, and the dies are
+    // added across lanes; RND sums of a lane in flight.  Few members have long slices: two lanes a sum.  (232,121 weights,
+    // k = 64, 20 evaluations and 10 passes: 394 us with rows, 405 with pairs; 95,909 8-vectors, k = 128, 20 evaluations: 481
+    // and 494; the matrix-core kernel at k = 256, with two sums in flight, 2500 and 2473: MAXRND = 1 there.)
+    constexpr int ROWS = NT / 16, RND = (MAXACC + (PT / DIES) * ROWS - 1) / ((PT / DIES) * ROWS);
+    if (RND <= MAXRND && n <= ROWS * RND) {
+        const int half = threadIdx.x & 1, x = (threadIdx.x >> 1) & (DIES - 1), w0 = threadIdx.x >> 4;
+        unsigned long long v[RND];
+        unsigned int spins = 0;
+        if (w0 < n) {
+            for (;;) {
+                bool ok = true;
+#pragma unroll
+                for (int u = 0; u < RND; ++u)
+                    v[u] = w0 + u * ROWS < n ? ld_word(src + (size_t)x * 2 * nacc + 2 * (w0 + u * ROWS) + half) : pack_u(seq, 0u);
+#pragma unroll
+                for (int u = 0; u < RND; ++u) ok = ok && (unsigned int)(v[u] >> 32) == seq;
+                if (ok) break;
+                if (give_up(spins)) {
+                    aborted = true;
+                    break;
+                }
+            }
+            aborted = __builtin_amdgcn_ballot_w64(aborted) != 0ull;  // (nothing that is not whole is passed on)
+        }
+        if (w0 < n && !aborted) {
+#pragma unroll
+            for (int u = 0; u < RND; ++u) {
+                if (w0 + u * ROWS >= n) break;
+                const int own = (int)(unsigned int)v[u], other = dpp_i<0xB1, 0xf>(0, own);  // quad_perm [1,0,3,2]
+                double t = half ? __hiloint2double(own, other) : __hiloint2double(other, own);
+                t += dpp_d<0x4E, 0xf>(t);   // quad_perm [2,3,0,1]: dies x and x ^ 1
+                t += dpp_d<0x141, 0xf>(t);  // row_half_mirror: the other quad
+                t += dpp_d<0x140, 0xf>(t);  // row_mirror: the other half of the row
+                if (x == 0) pass_on(2 * (w0 + u * ROWS) + half, t);
+            }
+        }
+    } else {
+        for (int h = threadIdx.x; h < 2 * n && !aborted; h += NT) {
+            double t;
+            aborted = !dies_sum(pa, src + h, 2 * nacc, DIES, seq, t);
+            if (aborted) break;
+            pass_on(h, t);
+        }
     }
-    for (int idx = threadIdx.x; idx < nacc && !aborted; idx += 4 * NT) {
-        unsigned long long v[4];
+    // (the words lie as the halves of s_tot do)
+    typedef unsigned int __attribute__((may_alias)) half_t;
+    half_t* tot = reinterpret_cast<half_t*>(s_tot);
+    constexpr int GW = (2 * MAXACC + NT - 1) / NT;  // words of a thread, all in flight
+    if ((int)threadIdx.x < 2 * nacc && !aborted) {
+        const int idx = threadIdx.x;
+        unsigned long long v[GW];
         unsigned int spins = 0;
         for (;;) {
             bool ok = true;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) v[u] = idx + u * NT < nacc ? ld_word(mine + idx + u * NT) : (unsigned long long)stamp;
+            for (int u = 0; u < GW; ++u) v[u] = idx + u * NT < 2 * nacc ? ld_word(mine + idx + u * NT) : pack_u(seq, 0u);
 #pragma unroll
-            for (int u = 0; u < 4; ++u) ok = ok && ((unsigned int)v[u] & 0xffffffu) == stamp;
-            if (ok || give_up(spins)) break;
+            for (int u = 0; u < GW; ++u) ok = ok && (unsigned int)(v[u] >> 32) == seq;
+            if (ok) break;
+            if (give_up(spins)) {
+                aborted = true;
+                break;
+            }
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (idx + u * NT < nacc) s_tot[idx + u * NT] = unpack_d40(v[u]);
+        for (int u = 0; u < GW; ++u)
+            if (idx + u * NT < 2 * nacc) tot[idx + u * NT] = (unsigned int)v[u];
     }
     if (aborted) raise_abort(pa, ls);
     __syncthreads();
     return ls.abort == 0;
 }
 
-// Hop 2, every workgroup: grid totals of the nacc sums in s_tot.  Returns false if the wait was abandoned; ends with a
+// Hop 2, every workgroup: grid totals of the nacc <= MAXACC sums in s_tot.  Returns false if the wait was abandoned; ends with a
 // barrier.
-template <int NT>
+template <int NT, int MAXACC, int MAXRND>
 __device__ __forceinline__ bool grid_totals(const PArgs& pa, unsigned int seq, int nacc, LShared& ls, double* s_tot) {
-    if (pa.G > DIES) return grid_totals_by_slices<NT>(pa, seq, nacc, ls, s_tot);
-    if (pa.G > 1) {
-        const int nd = pa.G < DIES ? pa.G : DIES;
-        const unsigned int stamp = stamp24(seq);
-        const unsigned long long* src = pa.buf3 + (size_t)(seq & 1u) * DIES * nacc;
+    if (pa.G > DIES) return grid_totals_by_slices<NT, MAXACC, MAXRND>(pa, seq, nacc, ls, s_tot);
+    if (pa.G > 1) {  // one workgroup per die
+        const unsigned long long* src = pa.buf3 + (size_t)(seq & 1u) * DIES * nacc * 2;
         bool aborted = false;
-        for (int idx = threadIdx.x; idx < nacc && !aborted; idx += 2 * NT) {
-            const bool two = idx + NT < nacc;
-            unsigned long long v[2][DIES];
-            unsigned int spins = 0;
-            for (;;) {
-                bool ok = true;
-#pragma unroll
-                for (int x = 0; x < DIES; ++x) {
-                    v[0][x] = x < nd ? ld_word(src + (size_t)x * nacc + idx) : (unsigned long long)stamp;
-                    v[1][x] = (two && x < nd) ? ld_word(src + (size_t)x * nacc + idx + NT) : (unsigned long long)stamp;
-                }
-#pragma unroll
-                for (int x = 0; x < DIES; ++x)
-                    ok = ok && ((unsigned int)v[0][x] & 0xffffffu) == stamp && ((unsigned int)v[1][x] & 0xffffffu) == stamp;
-                if (ok) break;
-                ++spins;
-                if (spins > pa.spin_limit ||
-                    ((spins & 31u) == 0u && __hip_atomic_load(pa.abort_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == pa.seq_base + 1u)) {
-                    aborted = true;
-                    break;
-                }
-            }
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                double t[DIES];
-#pragma unroll
-                for (int x = 0; x < DIES; ++x) t[x] = unpack_d40(v[h][x]);
-                if (h == 0 || two) s_tot[idx + h * NT] = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
-            }
+        for (int h = threadIdx.x; h < 2 * nacc && !aborted; h += NT) {
+            double t;
+            aborted = !dies_sum(pa, src + h, 2 * nacc, pa.G, seq, t);
+            if (!(h & 1)) s_tot[h >> 1] = t;
         }
         if (aborted) raise_abort(pa, ls);
     }
@@ -334,14 +388,14 @@ __device__ __forceinline__ void lane_tile_pass(const Args& a, LaneWave<KPL, D, D
 
 // Hop-1 store of a pass whose wavefronts left their totals in part[wavefront][nacc]: they add up in wavefront order,
 // float64, as in publish_lane.
-template <int NW>
+template <int NW, bool WIDE = false>
 __device__ __forceinline__ void publish_parts(const PArgs& pa, const LShared& ls, unsigned int seq, const float* part, int stride, int nacc) {
-    unsigned long long* dst = own_line(pa, seq, nacc);
+    unsigned long long* dst = own_line<WIDE>(pa, seq, nacc);
     for (int idx = threadIdx.x; idx < nacc; idx += NW * 64) {
         double t = 0.0;
 #pragma unroll
         for (int w = 0; w < NW; ++w) t += (double)part[w * stride + idx];
-        put_word(pa, ls, dst, seq, idx, t);
+        put_sum<WIDE>(ls, dst, nacc, seq, idx, t);
     }
 }
 
@@ -356,6 +410,7 @@ __device__ __forceinline__ void persist_lane_fwd_body(const Args& a, const PArgs
     constexpr int NA = KPL * ACCW;
     constexpr int KMAX = KB > 0 ? 16 * KB : 64 * KPL;
     constexpr int KDP = KMAX * D;  // padded codebook size
+    constexpr bool WIDE1 = D == 8;
     extern __shared__ float s_tile[];
     // workgroup sums of a vector-ALU pass; from the first hop on, the grid totals of the pass
     __shared__ double s_acc[KB > 0 ? KMAX : 64][KB > 0 ? ACCW : NA];
@@ -456,7 +511,7 @@ __device__ __forceinline__ void persist_lane_fwd_body(const Args& a, const PArgs
             }
             __syncthreads();
             IDKM_LSTAMP(5);
-            publish_parts<NT / 64>(pa, ls, seq, &s_rpart[0][0], KMAX * ACCW, nacc);
+            publish_parts<NT / 64, WIDE1>(pa, ls, seq, &s_rpart[0][0], KMAX * ACCW, nacc);
         } else {
             LaneWave<KPL, D, DIST, PASS_FWD> st;
             st.init(k, s_Cf, nullptr, nullptr, a.escale);
@@ -465,9 +520,9 @@ __device__ __forceinline__ void persist_lane_fwd_body(const Args& a, const PArgs
             publish_lane<NA, ACCW, NT>(pa, ls, seq, st.acc, k, s_acc);
         }
         IDKM_LSTAMP(2);
-        if (!die_slice<NT>(pa, seq, nacc, ls, s_tot)) return;
+        if (!die_slice<NT, WIDE1>(pa, seq, nacc, ls, s_tot)) return;
         IDKM_LSTAMP(3);
-        if (!grid_totals<NT>(pa, seq, nacc, ls, s_tot)) return;
+        if (!grid_totals<NT, KMAX * ACCW, KB ? 3 : 1>(pa, seq, nacc, ls, s_tot)) return;
         IDKM_LSTAMP(4);
         // centre update (Alg. 1) and stop test, the same in every workgroup; a non-finite sum gives NaN
         double r2 = 0.0;
@@ -525,19 +580,19 @@ __device__ __forceinline__ void persist_lane_fwd_body(const Args& a, const PArgs
                 st.collect(s_rpart[tid >> 6]);
             }
             __syncthreads();
-            publish_parts<NT / 64>(pa, ls, seq, &s_rpart[0][0], KMAX * ACCW, nacc);
+            publish_parts<NT / 64, WIDE1>(pa, ls, seq, &s_rpart[0][0], KMAX * ACCW, nacc);
         } else if (!done_here) {
             LaneWave<KPL, D, DIST, PASS_FIN> st;
             st.init(k, s_Cf, nullptr, nullptr);
             lane_tile_pass<KPL, D, DIST, PASS_FIN, NT>(a, st, s_tile, nullptr, base, cnt);
             publish_lane<NA, ACCW, NT>(pa, ls, seq, st.acc, k, s_acc);
         }
-        if (!die_slice<NT>(pa, seq, nacc, ls, s_tot)) return;
+        if (!die_slice<NT, WIDE1>(pa, seq, nacc, ls, s_tot)) return;
     }
     // only workgroup 0 needs these totals: it writes the state and, last, the word that says the launch ran to its end (the
     // others of its die pass their slices on)
     if (wg % DIES != 0) return;
-    if (!grid_totals<NT>(pa, seq, nacc, ls, s_tot)) return;
+    if (!grid_totals<NT, KMAX * ACCW, KB ? 3 : 1>(pa, seq, nacc, ls, s_tot)) return;
     if (wg != 0) return;
     double empty = 0.0, wrong = 0.0;
     for (int i = tid; i < kd; i += NT) {
@@ -658,7 +713,7 @@ __device__ __forceinline__ void persist_lane_bwd_body(const Args& a, const PArgs
     // term and the fold factor (see MfmaB2).
     auto publish_matrix = [&]() {
         if constexpr (MFMA) {
-            unsigned long long* dst = own_line(pa, seq, kd);
+            unsigned long long* dst = own_line<false>(pa, seq, kd);
             for (int idx = tid; idx < kd; idx += NT) {
                 const int j = idx >> 2, r = idx & 3;
                 double sw = 0.0, st1 = 0.0;
@@ -668,7 +723,7 @@ __device__ __forceinline__ void persist_lane_bwd_body(const Args& a, const PArgs
                     st1 += (double)s_part[w][j * 5];
                 }
                 const double o = sw - (double)(s_Cf[idx] - s_mu[r]) * st1;
-                put_word(pa, ls, dst, seq, idx, fold ? o * (double)s_fac0[j] : o);
+                put_sum<false>(ls, dst, kd, seq, idx, fold ? o * (double)s_fac0[j] : o);
             }
         }
     };
@@ -700,7 +755,7 @@ __device__ __forceinline__ void persist_lane_bwd_body(const Args& a, const PArgs
             lane_tile_pass<KPL, D, DIST, PASS_B1, NT>(a, st, s_w, s_gt, base, cnt);
             publish_lane<NA, D, NT>(pa, ls, seq, st.acc, k, s_acc);
         }
-        if (!die_slice<NT>(pa, seq, kd, ls, s_tot) || !grid_totals<NT>(pa, seq, kd, ls, s_tot)) return;
+        if (!die_slice<NT>(pa, seq, kd, ls, s_tot) || !grid_totals<NT, KDP, KB ? 3 : 1>(pa, seq, kd, ls, s_tot)) return;
         // every workgroup holds the whole of v and starts the solve at g = v
         double v2 = 0.0;
         for (int i = tid; i < kd; i += NT) {
@@ -745,7 +800,7 @@ __device__ __forceinline__ void persist_lane_bwd_body(const Args& a, const PArgs
             lane_tile_pass<KPL, D, DIST, PASS_B2, NT>(a, st, s_w, s_gt, base, cnt);
             publish_lane<NA, D, NT>(pa, ls, seq, st.acc, k, s_acc);
         }
-        if (!die_slice<NT>(pa, seq, kd, ls, s_tot) || !grid_totals<NT>(pa, seq, kd, ls, s_tot)) return;
+        if (!die_slice<NT>(pa, seq, kd, ls, s_tot) || !grid_totals<NT, KDP, KB ? 3 : 1>(pa, seq, kd, ls, s_tot)) return;
         double d2 = 0.0;
         for (int i = tid; i < kd; i += NT) {
             const double g = s_g[i];

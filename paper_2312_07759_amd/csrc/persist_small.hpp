@@ -67,10 +67,11 @@ struct PResult {
 };
 
 struct PArgs {
-    unsigned long long* buf1;  // [2][PT][xline_of(NACC)] stamped partial sums, word (workgroup, accumulator)
+    unsigned long long* buf1;  // [2][PT][xline_of(NACC)] stamped partial sums, word (workgroup, accumulator); twice as long where
+                               // sums take two words (SumWords), buf3 too
     unsigned long long* buf2;  // [2][XBCAST] stamped broadcast values
     unsigned long long* buf3;  // [2][DIES][XLINE] two-level exchange: stamped totals of each die
-    unsigned long long* buf4;  // lane family: [2][DIES][k (d+1)] grid totals, one copy per die
+    unsigned long long* buf4;  // lane family: [2][DIES][2 k (d+1)] grid totals, one copy per die
     unsigned long long* tab;   // [DIES] two-level exchange: die index of each leader, stamped with the launch id
     int tree;                  // two-level exchange (team of at least TREE_MIN_G workgroups, one problem per launch);
                                // 2: the same with every store at device scope (test support)
@@ -126,9 +127,10 @@ __device__ __forceinline__ void raise_abort(const PArgs& pa) {
     __hip_atomic_store(&pa.out->aborted, pa.seq_base + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// Shared scratch of the exchange.  WIDE: the dies' totals travel with 29 significant bits (pack_d40) instead of as float32.
-// Only the ragged codebooks need it: the kernels those shapes came from kept the totals in float64, and under the plain norm
-// at k = 5 the gradient was 2.1e-6 from the 64-bit one with float32 totals, 1.2e-6 in those kernels, 0.7e-6 with these.
+// Shared scratch of the exchange.  WIDE: what wavefronts have added up travels as float64 (two words a sum) instead of as
+// float32.  Only the ragged codebooks need it: the kernels those shapes came from kept the totals in float64 -- their Krylov
+// solve the workgroups' sums as well -- and under the plain norm at k = 5 the gradient was 2.1e-6 from the 64-bit one with
+// float32 totals, 1.2e-6 in those kernels, 0.7e-6 with float64 ones.
 // The others keep float32 words: an evaluation at k = 4, d = 1 takes 1.3 % longer with wide ones.
 template <int NACC, bool WIDE_ = false>
 struct XShared {
@@ -138,7 +140,7 @@ struct XShared {
     double red2[PT];                 // reducer: per-thread sums (thread t: word t mod WPR, workgroups t/WPR + k PT/WPR)
     double tot[8];                   // reducer: totals of its slice
     unsigned int bc[XBCAST];         // payloads of the broadcast words
-    float own[XLINE];                // this workgroup's own partial sums (read back directly by a team of one)
+    total_t own[XLINE];              // this workgroup's own partial sums (read back directly by a team of one)
     int abort;
     // two-level exchange
     int local;                       // this workgroup runs on its leader's die: its partial sums need only reach the L2
@@ -164,6 +166,53 @@ __device__ __forceinline__ unsigned int die_id() {
 // A stamped word that only a workgroup of the same die will read: it has to reach the die's L2, not memory.
 __device__ __forceinline__ void st_word_die(unsigned long long* p, unsigned long long v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// A sum on its way between workgroups: one stamped word that carries it as float32 or, WIDE, two words that carry the halves
+// of the float64 value (each with its own stamp: a reader may see one before the other).  The lower halves of a line lie
+// together and the upper ones `gap` words behind them, so that a wavefront's store or load is one run of words for each.
+template <bool WIDE>
+struct SumWords {
+    static constexpr int N = WIDE ? 2 : 1;
+    unsigned long long w[N];
+    __device__ __forceinline__ void load(const unsigned long long* p, int gap) {
+        w[0] = ld_word(p);
+        if (WIDE) w[N - 1] = ld_word(p + gap);
+    }
+    __device__ __forceinline__ void zero(unsigned int seq) {
+#pragma unroll
+        for (int h = 0; h < N; ++h) w[h] = pack_u(seq, 0u);
+    }
+    __device__ __forceinline__ bool arrived(unsigned int seq) const {
+        bool ok = (unsigned int)(w[0] >> 32) == seq;
+        if (WIDE) ok = ok && (unsigned int)(w[N - 1] >> 32) == seq;
+        return ok;
+    }
+    __device__ __forceinline__ double value() const {
+        if constexpr (WIDE)
+            return __hiloint2double((int)(unsigned int)w[1], (int)(unsigned int)w[0]);
+        else
+            return (double)__uint_as_float((unsigned int)w[0]);
+    }
+};
+// die: only workgroups of this die read it.
+template <bool WIDE>
+__device__ __forceinline__ void st_sum(unsigned long long* p, int gap, unsigned int seq, double t, bool die) {
+    if constexpr (WIDE) {
+        const unsigned long long lo = pack_u(seq, (unsigned int)__double2loint(t)), hi = pack_u(seq, (unsigned int)__double2hiint(t));
+        if (die) {
+            st_word_die(p, lo);
+            st_word_die(p + gap, hi);
+        } else {
+            st_word(p, lo);
+            st_word(p + gap, hi);
+        }
+    } else {
+        if (die)
+            st_word_die(p, pack_f(seq, (float)t));
+        else
+            st_word(p, pack_f(seq, (float)t));
+    }
 }
 
 // Row totals of accumulators [OFF, NACC) into xs.rpart, taken in power-of-two pieces, largest first (80 sums are a
@@ -216,8 +265,13 @@ __device__ __forceinline__ void publish_partials(const PArgs& pa, unsigned int s
         // the four wavefronts in float64, a fixed order
         const double s = ((double)xs.rpart[tid][0] + (double)xs.rpart[tid][1]) +
                          ((double)xs.rpart[tid][2] + (double)xs.rpart[tid][3]);
-        xs.own[tid] = (float)s;
+        xs.own[tid] = (typename XS::total_t)s;
         // a workgroup's words lie together: one store transaction per workgroup and pass
+        if constexpr (XS::WIDE) {  // (a leader reads its own sums from xs.own, a team of one too)
+            if (pa.tree && pa.wg >= DIES)
+                st_sum<true>(&pa.buf1[((size_t)(seq & 1u) * PT + pa.wg) * xline_of(NACC) * 2 + tid], xline_of(NACC), seq, s, xs.local != 0);
+            return;
+        }
         unsigned long long* dst = &pa.buf1[((size_t)(seq & 1u) * PT + pa.wg) * xline_of(NACC) + tid];
         if (!pa.tree)
             st_word(dst, pack_f(seq, (float)s));
@@ -252,47 +306,19 @@ __device__ __forceinline__ bool poll_words(const PArgs& pa, const unsigned long 
     }
 }
 
-// A die's total travels as the upper 40 bits of the float64 sum (29 significant bits, so that nothing is lost against the
-// 32-bit values the totals end in) and a 24-bit stamp.  Stamps of the 2^24 - 1 values 1 .. are told apart; the host clears
-// the words whenever the sequence numbers enter another run of that length (launch_persistent).
-constexpr unsigned int STAMP_RUN = 0xffffffu;
-__device__ __forceinline__ unsigned int stamp24(unsigned int seq) { return seq % STAMP_RUN + 1u; }
-__device__ __forceinline__ unsigned long long pack_d40(unsigned int stamp, double v) {
-    const unsigned long long b = (unsigned long long)__double_as_longlong(v) + 0x800000ull;  // to nearest
-    return (b & ~0xffffffull) | (unsigned long long)stamp;
-}
-__device__ __forceinline__ double unpack_d40(unsigned long long w) {
-    return __longlong_as_double((long long)(w & ~0xffffffull));
-}
-
-// A die's total in the form the team uses, its value as every workgroup reads it, and whether a word has arrived.
+// Bounded wait for one sum.
 template <bool WIDE>
-__device__ __forceinline__ unsigned long long die_word(unsigned int seq, double t) {
-    return WIDE ? pack_d40(stamp24(seq), t) : pack_f(seq, (float)t);
-}
-template <bool WIDE>
-__device__ __forceinline__ double die_value(unsigned long long w) {
-    return WIDE ? unpack_d40(w) : (double)__uint_as_float((unsigned int)w);
-}
-template <bool WIDE>
-__device__ __forceinline__ bool die_arrived(unsigned long long w, unsigned int seq) {
-    return WIDE ? ((unsigned int)w & 0xffffffu) == stamp24(seq) : (unsigned int)(w >> 32) == seq;
-}
-// Bounded wait for one such word.
-template <bool WIDE>
-__device__ __forceinline__ bool poll_die(const PArgs& pa, const unsigned long long* src, unsigned int seq, double& out) {
-    unsigned int spins = 0;
-    for (;;) {
-        const unsigned long long w = ld_word(src);
-        if (die_arrived<WIDE>(w, seq)) {
-            out = die_value<WIDE>(w);
-            return true;
-        }
-        ++spins;
-        if (spins > pa.spin_limit ||
-            ((spins & 31u) == 0u && __hip_atomic_load(pa.abort_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == pa.seq_base + 1u))
-            return false;
+__device__ __forceinline__ bool poll_sum(const PArgs& pa, const unsigned long long* src, int gap, unsigned int seq, double& out) {
+    if constexpr (WIDE) {
+        unsigned long long w[2];
+        if (!poll_words<2>(pa, src, gap, seq, w)) return false;
+        out = SumWords<true>{{w[0], w[1]}}.value();
+    } else {
+        unsigned long long w[1];
+        if (!poll_words<1>(pa, src, 0, seq, w)) return false;
+        out = (double)__uint_as_float((unsigned int)w[0]);
     }
+    return true;
 }
 
 // hop 1, reducer side: totals over all workgroups of words [first, first+WPR) into xs.tot (float64, fixed order).
@@ -429,7 +455,8 @@ __device__ __forceinline__ bool tree_handshake(const PArgs& pa, XS& xs) {
 // abandoned (uniform over the workgroup).
 template <int NACC, class XS>
 __device__ __forceinline__ bool tree_die_totals(const PArgs& pa, unsigned int seq, XS& xs) {
-    constexpr int LINE = xline_of(NACC);
+    using Word = SumWords<XS::WIDE>;
+    constexpr int LINE = xline_of(NACC) * Word::N;
     constexpr int PARTS = PT / NACC;                 // member groups
     constexpr int MPT = (32 + PARTS - 1) / PARTS;    // members per thread
     static_assert(PARTS >= 1, "one thread per accumulator at least");
@@ -437,7 +464,7 @@ __device__ __forceinline__ bool tree_die_totals(const PArgs& pa, unsigned int se
     const bool live = part < PARTS;
     const int nmem = (pa.G - x + DIES - 1) / DIES;  // members of this die, the leader included; <= 32
     const unsigned long long* line0 = pa.buf1 + ((size_t)(seq & 1u) * PT + x) * LINE + q;
-    unsigned long long w[MPT];
+    Word w[MPT];
     bool valid[MPT];
 #pragma unroll
     for (int u = 0; u < MPT; ++u) {
@@ -448,11 +475,15 @@ __device__ __forceinline__ bool tree_die_totals(const PArgs& pa, unsigned int se
     unsigned int spins = 0;
     for (;;) {
 #pragma unroll
-        for (int u = 0; u < MPT; ++u)
-            w[u] = valid[u] ? ld_word(line0 + (size_t)(part + PARTS * u) * DIES * LINE) : pack_f(seq, 0.f);
+        for (int u = 0; u < MPT; ++u) {
+            if (valid[u])
+                w[u].load(line0 + (size_t)(part + PARTS * u) * DIES * LINE, xline_of(NACC));
+            else
+                w[u].zero(seq);
+        }
         bool ok = true;
 #pragma unroll
-        for (int u = 0; u < MPT; ++u) ok = ok && ((unsigned int)(w[u] >> 32) == seq);
+        for (int u = 0; u < MPT; ++u) ok = ok && w[u].arrived(seq);
         if (ok) break;
         ++spins;
         if (spins > pa.spin_limit ||
@@ -465,7 +496,7 @@ __device__ __forceinline__ bool tree_die_totals(const PArgs& pa, unsigned int se
         // (thread q < NACC wrote xs.own[q] itself in publish_partials; members that do not exist carry zeros)
         double c2[2] = {tid < NACC ? (double)xs.own[q] : 0.0, 0.0};
 #pragma unroll
-        for (int u = 0; u < MPT; ++u) c2[u & 1] += (double)__uint_as_float((unsigned int)w[u]);
+        for (int u = 0; u < MPT; ++u) c2[u & 1] += w[u].value();
         xs.red2[part * NACC + q] = c2[0] + c2[1];
     }
     if (aborted) {
@@ -478,9 +509,9 @@ __device__ __forceinline__ bool tree_die_totals(const PArgs& pa, unsigned int se
         double c2[2] = {0.0, 0.0};
 #pragma unroll
         for (int g = 0; g < PARTS; ++g) c2[g & 1] += xs.red2[g * NACC + tid];
-        const unsigned long long word = die_word<XS::WIDE>(seq, c2[0] + c2[1]);
-        xs.stage2[x * NACC + tid] = die_value<XS::WIDE>(word);  // (what the other workgroups will read)
-        st_word(&pa.buf3[((size_t)(seq & 1u) * DIES + x) * LINE + tid], word);
+        const typename XS::total_t tot = (typename XS::total_t)(c2[0] + c2[1]);
+        xs.stage2[x * NACC + tid] = tot;
+        st_sum<XS::WIDE>(&pa.buf3[((size_t)(seq & 1u) * DIES + x) * LINE + tid], xline_of(NACC), seq, tot, false);
     }
     return true;
 }
@@ -489,11 +520,12 @@ __device__ __forceinline__ bool tree_die_totals(const PArgs& pa, unsigned int se
 // totals are left in xs.totd.  Ends with a barrier.  Returns false if the wait was abandoned.
 template <int NACC, class XS>
 __device__ __forceinline__ bool tree_grid_totals(const PArgs& pa, unsigned int seq, XS& xs) {
-    constexpr int LINE = xline_of(NACC);
+    using Word = SumWords<XS::WIDE>;
+    constexpr int LINE = xline_of(NACC) * Word::N;
     constexpr int NLD = (DIES * NACC + PT - 1) / PT;
     const int tid = threadIdx.x;
     const unsigned long long* base = pa.buf3 + (size_t)(seq & 1u) * DIES * LINE;
-    unsigned long long w[NLD];
+    Word w[NLD];
     bool valid[NLD];
 #pragma unroll
     for (int u = 0; u < NLD; ++u) {
@@ -506,11 +538,14 @@ __device__ __forceinline__ bool tree_grid_totals(const PArgs& pa, unsigned int s
 #pragma unroll
         for (int u = 0; u < NLD; ++u) {
             const int f = tid + u * PT, x = f / NACC, q = f - x * NACC;
-            w[u] = valid[u] ? ld_word(base + (size_t)x * LINE + q) : die_word<XS::WIDE>(seq, 0.0);
+            if (valid[u])
+                w[u].load(base + (size_t)x * LINE + q, xline_of(NACC));
+            else
+                w[u].zero(seq);
         }
         bool ok = true;
 #pragma unroll
-        for (int u = 0; u < NLD; ++u) ok = ok && die_arrived<XS::WIDE>(w[u], seq);
+        for (int u = 0; u < NLD; ++u) ok = ok && w[u].arrived(seq);
         if (ok) break;
         ++spins;
         if (spins > pa.spin_limit ||
@@ -521,7 +556,7 @@ __device__ __forceinline__ bool tree_grid_totals(const PArgs& pa, unsigned int s
     }
 #pragma unroll
     for (int u = 0; u < NLD; ++u)
-        if (valid[u]) xs.stage2[tid + u * PT] = die_value<XS::WIDE>(w[u]);
+        if (valid[u]) xs.stage2[tid + u * PT] = (typename XS::total_t)w[u].value();
     if (aborted) {
         xs.abort = 1;
         raise_abort(pa);
@@ -603,11 +638,16 @@ __device__ __forceinline__ bool tree8_die_totals(const PArgs& pa, unsigned int s
     }
     __syncthreads();
     if (xs.abort) return false;
-    if (tid < 8) {
-        const unsigned long long word =
-            die_word<XS::WIDE>(seq, (xs.red2[tid] + xs.red2[8 + tid]) + (xs.red2[16 + tid] + xs.red2[24 + tid]));
-        xs.stage2[x * 8 + tid] = die_value<XS::WIDE>(word);  // (what the other workgroups will read)
-        st_word(&pa.buf3[((size_t)(seq & 1u) * DIES + x) * 32 + tid], word);
+    if (tid < 8 * SumWords<XS::WIDE>::N) {
+        const typename XS::total_t tot = (typename XS::total_t)((xs.red2[p] + xs.red2[8 + p]) + (xs.red2[16 + p] + xs.red2[24 + p]));
+        unsigned long long* dst = &pa.buf3[((size_t)(seq & 1u) * DIES + x) * 32 + tid];
+        if constexpr (XS::WIDE) {  // (lanes 8 .. 15 store the upper halves)
+            if (tid < 8) xs.stage2[x * 8 + tid] = tot;
+            st_word(dst, pack_u(seq, (unsigned int)(tid < 8 ? __double2loint(tot) : __double2hiint(tot))));
+        } else {
+            xs.stage2[x * 8 + tid] = tot;
+            st_word(dst, pack_f(seq, tot));
+        }
     }
     return true;
 }
@@ -623,7 +663,7 @@ __device__ __forceinline__ void tree8_grid_totals_wave0(const PArgs& pa, unsigne
     wave_lds_sync();  // (a leader's lanes 0 .. 7 have just written its own die's totals)
     if (x == pa.wg) {
         s = (double)xs.stage2[x * 8 + p];
-    } else if (!poll_die<XS::WIDE>(pa, src, seq, s)) {
+    } else if (!poll_sum<XS::WIDE>(pa, src, 8, seq, s)) {
         s = 0.0;
         xs.abort = 1;
         raise_abort(pa);
@@ -646,7 +686,7 @@ __device__ __forceinline__ bool tree8_grid_totals_regs(const PArgs& pa, unsigned
     wave_lds_sync();  // (a leader's lanes 0 .. 7 have just written its own die's totals)
     if (x == pa.wg) {
         s = (double)xs.stage2[x * 8 + p];
-    } else if (!poll_die<XS::WIDE>(pa, src, seq, s)) {
+    } else if (!poll_sum<XS::WIDE>(pa, src, 8, seq, s)) {
         s = 0.0;
         failed = true;
         xs.abort = 1;

@@ -127,21 +127,28 @@ def test_batched_ragged_layers_share_launches_and_explicit_path_keeps_its_limits
 
 
 def test_wide_totals_do_not_meet_the_words_of_other_solves(ctx):
-    """One context alternates between k = 3, 4 and 7, and its sequence numbers cross the point where the 24-bit stamps of the
-    ragged codebooks' exchange start over: the same bits every time."""
+    """One context alternates between k = 3, 4 and 7: the same bits every time.  So too where the sequence numbers start over
+    and every word of the exchange is left from a solve of other data that had the same numbers."""
     probs = {k: _problem(30_011, 1, k, seed=k) for k in (3, 4, 7)}
     d = {k: (dev(W), dev(C0), dev(G)) for k, (W, C0, G) in probs.items()}
     c = binding.Context(0)
 
-    def solve(k):
-        f = c.forward(d[k][0], d[k][1], 0.2, 0.0, 9, wl.DIST_SQL2)
-        b = c.backward(d[k][2], binding.BWD_IMPLICIT, tol=0.0, max_iter=5)
+    def solve(k, ctx):
+        f = ctx.forward(d[k][0], d[k][1], 0.2, 0.0, 30, wl.DIST_SQL2)
+        b = ctx.backward(d[k][2], binding.BWD_IMPLICIT, tol=0.0, max_iter=5)
         assert f["info"].path == binding.PATH_PERSISTENT
         return f["C"].clone(), b["dW"].clone()
 
-    first = {k: solve(k) for k in (3, 4, 7)}
-    for _ in range(3):
-        c.advance_sequence((1 << 24) - 100)     # (10 + 36 numbers a solve)
-        for k in (3, 7, 4, 3, 4, 7):
-            assert all(torch.equal(x, y) for x, y in zip(first[k], solve(k)))
+    first = {k: solve(k, c) for k in (3, 4, 7)}
+    for k in (3, 7, 4, 3, 4, 7):
+        assert all(torch.equal(x, y) for x, y in zip(first[k], solve(k, c)))
     c.close()
+    for k in (3, 7):
+        c = binding.Context(0)
+        W, C0, G = _problem(30_011, 1, k, seed=50 + k)
+        c.forward(dev(W), dev(C0), 0.2, 0.0, 30, wl.DIST_SQL2)      # numbers 1 .. 31
+        c.backward(dev(G), binding.BWD_IMPLICIT, tol=0.0, max_iter=5)
+        c.advance_sequence(0xFFFFFFFF)                              # fewer than 31 are left: the next launch starts at 1 again
+        for j in (k, 4, 7, 3):
+            assert all(torch.equal(x, y) for x, y in zip(first[j], solve(j, c)))
+        c.close()

@@ -71,7 +71,8 @@ def test_block_counts_and_ragged_shares(ctx, k, d, m, dist):
 @pytest.mark.parametrize("setting", ["0", "2"])
 def test_exchange_of_the_large_codebook_kernels(m, d, k, setting, monkeypatch):
     """The forms of the first hop (through the die's L2, or every store at device scope) give the same bits; results do not
-    change where the 24-bit stamps of the dies' totals start over, nor after solves of other shapes in between."""
+    change after solves of other shapes in between, nor where the sequence numbers start over and every word of the
+    exchange is left from a solve of other data that had the same numbers."""
     W, C0, G = wl.random_problem(m, d, k, seed=k, std=0.5, spread=1.5)
     Wd, Cd, Gd = dev(W), dev(C0), dev(G)
 
@@ -91,12 +92,35 @@ def test_exchange_of_the_large_codebook_kernels(m, d, k, setting, monkeypatch):
     ref = orc.soft_kmeans(W.astype(np.float32), C0.astype(np.float32), 0.3, 0.0, 10, wl.DIST_SQL2)
     assert rel(first[0].cpu().numpy(), ref["C"]) < TOL_VAL
     W2, C2, _ = wl.random_problem(9_001, 1, 20, seed=1, std=0.5, spread=1.5)
-    for _ in range(2):
-        c.advance_sequence((1 << 24) - 70)      # every solve here takes 54 numbers: the next one crosses
-        for _ in range(3):
-            assert all(torch.equal(x, y) for x, y in zip(first, solve(c)))
-            c.forward(dev(W2), dev(C2), 0.3, 0.0, 7, wl.DIST_SQL2)
+    for _ in range(3):
+        assert all(torch.equal(x, y) for x, y in zip(first, solve(c)))
+        c.forward(dev(W2), dev(C2), 0.3, 0.0, 7, wl.DIST_SQL2)
+    long = c.forward(Wd, Cd, 0.3, 0.0, 30, wl.DIST_SQL2)["C"].clone()
     c.close()
+    c = binding.Context(0)
+    W3, C3, _ = wl.random_problem(m, d, k, seed=k + 1, std=0.5, spread=1.5)
+    c.forward(dev(W3), dev(C3), 0.3, 0.0, 30, wl.DIST_SQL2)      # numbers 1 .. 31
+    c.advance_sequence(0xFFFFFFFF)                               # fewer than 31 are left: the next launch starts at 1 again
+    assert torch.equal(long, c.forward(Wd, Cd, 0.3, 0.0, 30, wl.DIST_SQL2)["C"])
+    assert all(torch.equal(x, y) for x, y in zip(first, solve(c)))
+    c.close()
+
+
+# What wavefronts have added up stays float64: the totals of a large or padded codebook carry more than the 29 bits of a
+# shorter word, and those of a team of one (whose workgroup sums are the totals) more than a float32.  (A sum of n words of
+# 24 bits has about 24 + log2(n) bits and one more for every halving of the smallest word: n is large where there are few components.)
+@pytest.mark.parametrize("k,d,m,bits", [(40, 1, 20_003, 29), (256, 4, 5_001, 29), (300, 2, 20_001, 29), (100, 2, 9_001, 29), (5, 1, 300_007, 29),
+                                        (12, 4, 100_003, 29), (3, 1, 300_007, 29), (13, 2, 700, 24)])
+def test_float64_outputs_hold_float64_sums(ctx, k, d, m, bits):
+    W, C0, G = wl.random_problem(m, d, k, seed=k + m, std=0.5, spread=1.5)
+    f = ctx.forward(dev(W), dev(C0), 0.3, 0.0, 5, wl.DIST_SQL2)
+    modes = [(binding.BWD_JFB, {})] + ([(binding.BWD_GMRES, dict(tol=1e-5, max_iter=100))] if k < 16 else [])
+    for mode, kw in modes:
+        b = ctx.backward(dev(G), mode, **kw)
+        assert f["info"].path == binding.PATH_PERSISTENT and b["info"].path == binding.PATH_PERSISTENT
+        v = ctx.get_cotangents(k, d)[0].reshape(-1)
+        low = v.view(np.uint64) & np.uint64((1 << (53 - bits)) - 1)
+        assert np.mean(low != 0) > 0.5
 
 
 @pytest.mark.parametrize("dist", [wl.DIST_L2, wl.DIST_SQL2])
