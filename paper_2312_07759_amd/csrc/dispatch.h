@@ -45,9 +45,10 @@ PersistFns persist_kernel_global(int K, int D, int dist, bool bwd);
 PersistFns persist_lane_kernel(int KPL, int D, int dist, bool bwd, bool matrix);
 
 // Stream path's passes in the row <-> vector form: D in {1,2,8}, 16 KB >= k codewords, KB in {1,2,4,8,16}; launched with
-// RST threads and vec_per_wg D floats of dynamic LDS (twice that for PASS_B1 and PASS_B3).
-KernelFn row_kernel_0(int KB, int D, int pass);
-KernelFn row_kernel_1(int KB, int D, int pass);
+// RST threads and vec_per_wg D floats of dynamic LDS (twice that for PASS_B1 and PASS_B3).  several: the grid has fewer
+// workgroups than there are tiles of vec_per_wg vectors.
+KernelFn row_kernel_0(int KB, int D, int pass, bool several);
+KernelFn row_kernel_1(int KB, int D, int pass, bool several);
 // Persistent solve in the row <-> vector form, the same shapes (D = 8: forward only).
 PersistFns persist_row_kernel_0(int KB, int D, bool bwd);
 PersistFns persist_row_kernel_1(int KB, int D, bool bwd);

@@ -178,7 +178,7 @@ struct idkm_ctx {
     hipStream_t pending_stream = nullptr;
     std::vector<Deferred>* sink = nullptr;  // set by a batched call: persistent launches are handed over, not issued
     std::map<const void*, std::pair<size_t, int>> checked;  // kernel -> (largest LDS size set, blocks per CU at that size)
-    std::map<const void*, size_t> row_lds;                  // kernel -> dynamic LDS limit set so far (row <-> vector passes)
+    std::map<const void*, bool> row_lds;                    // row <-> vector passes whose dynamic LDS limit has been set
     std::map<const void*, size_t> static_lds;               // bytes of static LDS of the kernels whose dynamic LDS is sized against it
     unsigned int spin_limit = 1u << 20;
     bool use_matrix = true;           // d = 4, 17 <= k <= 256: matrix-core kernels where they exist
@@ -219,6 +219,8 @@ struct Geometry {
     int nwg_m = 0;
     int64_t vec_per_wg_m = 0;
     int kb = 0;  // > 0: the row <-> vector passes (d in {1, 2, 8}, k <= 256), 16 kb codewords
+    int64_t wg_most = 0;  // ... their largest grid
+    bool several = false; // ... and whether it is smaller than the number of tiles
 };
 
 bool pow2(int x) { return x > 0 && (x & (x - 1)) == 0; }
@@ -246,20 +248,29 @@ idkm_status plan(idkm_ctx* ctx, int64_t m, int k, int d, Geometry* g) {
         if (vpw > 512) vpw = (m + 8191) / 8192 > 512 ? (m + 8191) / 8192 : 512;
         g->vec_per_wg = vpw * (WG / 64);
         if (d != 4 && k <= 256) {
-            // row <-> vector passes: one workgroup per compute unit and round, of at least a step for each wavefront (so
-            // that few partial sums are left to reduce), its tiles at most 36 KB each
+            // row <-> vector passes: as many tiles for each compute unit, all of about the same size (at least a step for each
+            // wavefront), and one workgroup a tile until the device is full; from there on a workgroup takes several in turn,
+            // so that the partial sums to reduce, and their workspace, stay bounded (at most 1024 workgroups)
             g->kb = 1;
             while (16 * g->kb < k) g->kb <<= 1;
-            int64_t v = (m + ctx->num_cu - 1) / (ctx->num_cu > 0 ? ctx->num_cu : 1);
+            const int64_t cus = ctx->num_cu > 0 ? ctx->num_cu : 1, most = row_tile_vectors(d);
+            // workgroups of a repeated pass that a compute unit holds: tile, tables and the wavefronts' sums
+            const int64_t lds = most * d * 4 + (int64_t)16 * g->kb * (8 * d + (RST / 64) * 4 * (d + 1));
+            const int64_t resident = std::max<int64_t>(1, std::min<int64_t>(2048 / RST, (int64_t)(160 * 1024) / lds));
+            int64_t tiles = (m + cus * most - 1) / (cus * most);  // of a compute unit
+            if (tiles > resident) tiles = (tiles + resident - 1) / resident * resident;
+            int64_t v = (m + cus * tiles - 1) / (cus * tiles);
             if (v < 64) v = 64;
-            v = (v + 15) / 16 * 16;
-            const int64_t most = 9216 / d;
-            if (v > most) v = most;
-            g->vec_per_wg = v;
+            g->vec_per_wg = (v + 15) / 16 * 16;
+            g->wg_most = cus * resident;
         }
     }
     int64_t nwg = (m + g->vec_per_wg - 1) / g->vec_per_wg;
-    if (nwg > 0x3fffffff) return fail(ctx, IDKM_ERR_UNSUPPORTED, "m too large");
+    if (g->wg_most == 0 && nwg > 0x3fffffff) return fail(ctx, IDKM_ERR_UNSUPPORTED, "m too large");
+    if (g->wg_most > 0 && nwg > g->wg_most) {
+        nwg = g->wg_most;
+        g->several = true;
+    }
     g->nwg = (int)nwg;
     g->matrix = false;
     if (!g->small && d == 4 && g->kpl <= 4 && ctx->use_matrix) {
@@ -326,7 +337,7 @@ Args base_args(idkm_ctx* ctx) {
 
 idkm_status launch_pass(idkm_ctx* ctx, const Geometry& g, int pass, Args& a, hipStream_t s) {
     KernelFn fn = g.small ? small_kernel(ctx->k, ctx->d, ctx->dist, pass)
-                  : g.kb  ? (ctx->dist == DIST_L2 ? row_kernel_0(g.kb, ctx->d, pass) : row_kernel_1(g.kb, ctx->d, pass))
+                  : g.kb  ? (ctx->dist == DIST_L2 ? row_kernel_0(g.kb, ctx->d, pass, g.several) : row_kernel_1(g.kb, ctx->d, pass, g.several))
                           : lane_kernel(g.kpl, ctx->d, ctx->dist, pass);
     KernelFn fn_m = g.matrix ? mfma_lane_kernel(g.kpl, ctx->dist, pass) : nullptr;
     if (!fn && !fn_m) return fail(ctx, IDKM_ERR_UNSUPPORTED, "no kernel for this (k, d)");
@@ -343,11 +354,13 @@ idkm_status launch_pass(idkm_ctx* ctx, const Geometry& g, int pass, Args& a, hip
     if (fn_m)
         hipLaunchKernelGGL(fn_m, dim3(nwg), dim3(mfma_lane_threads(g.kpl, ctx->dist, pass)), (size_t)(a.vec_per_wg + 16) * 20, s, a);
     else if (g.kb) {
-        const size_t lds = (size_t)a.vec_per_wg * ctx->d * sizeof(float) * (pass == PASS_B1 || pass == PASS_B3 ? 2 : 1);
-        size_t& set = ctx->row_lds[(const void*)fn];
-        if (set < lds) {
-            HIP_TRY(ctx, hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-            set = lds;
+        const int tensors = pass == PASS_B1 || pass == PASS_B3 ? 2 : 1;
+        const size_t lds = (size_t)a.vec_per_wg * ctx->d * sizeof(float) * tensors;
+        bool& set = ctx->row_lds[(const void*)fn];
+        if (!set) {  // (the limit is the kernel's, not the context's: always the most that any call needs)
+            HIP_TRY(ctx, hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                             (int)(row_tile_vectors(ctx->d) * ctx->d * sizeof(float) * tensors)));
+            set = true;
         }
         hipLaunchKernelGGL(fn, dim3(nwg), dim3(RST), lds, s, a);
     } else

@@ -507,7 +507,7 @@ __device__ __forceinline__ void persist_lane_fwd_body(const Args& a, const PArgs
                 st.init(k, RW::TAB > 1 ? s_rtab : s_Cf, nullptr, nullptr, a.escale);
                 row_tile_pass<KB, D, DIST, PASS_FWD, NT>(a, st, s_tile, nullptr, base, cnt);
                 IDKM_LSTAMP(1);
-                st.collect(s_rpart[tid >> 6]);
+                st.collect(s_rpart[tid >> 6], tid);
             }
             __syncthreads();
             IDKM_LSTAMP(5);
@@ -577,7 +577,7 @@ __device__ __forceinline__ void persist_lane_fwd_body(const Args& a, const PArgs
                 RowWave<KB, D, DIST, PASS_FIN> st;
                 st.init(k, s_Cf, nullptr, nullptr, a.escale);
                 row_tile_pass<KB, D, DIST, PASS_FIN, NT>(a, st, s_tile, nullptr, base, cnt);
-                st.collect(s_rpart[tid >> 6]);
+                st.collect(s_rpart[tid >> 6], tid);
             }
             __syncthreads();
             publish_parts<NT / 64, WIDE1>(pa, ls, seq, &s_rpart[0][0], KMAX * ACCW, nacc);
@@ -745,7 +745,7 @@ __device__ __forceinline__ void persist_lane_bwd_body(const Args& a, const PArgs
                 RowWave<KB, D, DIST, PASS_B1> st;
                 st.init(k, s_Cf, s_Hs, s_Ff, a.escale);
                 row_tile_pass<KB, D, DIST, PASS_B1, NT>(a, st, s_w, s_gt, base, cnt);
-                st.collect(s_rpart[tid >> 6]);
+                st.collect(s_rpart[tid >> 6], tid);
             }
             __syncthreads();
             publish_parts<NT / 64>(pa, ls, seq, &s_rpart[0][0], KDP, kd);
@@ -790,7 +790,7 @@ __device__ __forceinline__ void persist_lane_bwd_body(const Args& a, const PArgs
                 RowWave<KB, D, DIST, PASS_B2> st;
                 st.init(k, s_Cf, s_Hs, s_Ff, a.escale);
                 row_tile_pass<KB, D, DIST, PASS_B2, NT>(a, st, s_w, s_gt, base, cnt);
-                st.collect(s_rpart[tid >> 6]);
+                st.collect(s_rpart[tid >> 6], tid);
             }
             __syncthreads();
             publish_parts<NT / 64>(pa, ls, seq, &s_rpart[0][0], KDP, kd);

@@ -523,8 +523,8 @@ struct RowWave {
     }
 
     // After the last step: the pass's sums over the wavefront into part[codeword][ACCW] (all 16 KB codewords).
-    __device__ __forceinline__ void collect(float* part) const {
-        const int lane = threadIdx.x & 63, j0 = lane & 15, row = lane >> 4;
+    __device__ __forceinline__ void collect(float* part, int tid) const {
+        const int lane = tid & 63, j0 = lane & 15, row = lane >> 4;
 #pragma unroll
         for (int q = 0; q < NA; ++q) {
             const float s = cross_row_sum(acc[q]);
@@ -547,11 +547,16 @@ __device__ __forceinline__ void row_tile_pass(const Args& a, RowWave<KB, D, DIST
     if (v0 < cnt) st.template step<false>(a, s_w, s_g, base, v0, cnt);
 }
 
-// Stream path: one launch per pass.  Every workgroup copies its chunk of W (and dL/dWq) into LDS and leaves its sums in
-// a.partials[workgroup][.] (float64) for reduce_rows and lane_tail.  Dynamic LDS: vec_per_wg vectors, twice that for the
-// passes that read dL/dWq.
+// Stream path: one launch per pass.  A workgroup takes tiles b, b + grid, ... of vec_per_wg vectors, copies each into LDS
+// (dL/dWq too) and adds the tile's sums to a.partials[workgroup][.] (float64) for reduce_rows and lane_tail.  Dynamic LDS: one
+// tile, two for the passes that read dL/dWq.  SEVERAL = false (d = 8): the grid has a workgroup for every tile; as a loop the
+// passes at k = 256 keep some 15 registers more, and spill them.  36 KB tiles: 294,912 8-vectors, k = 256, 62.2 us an
+// evaluation against 66.4 with 18 KB and 72.5 with 12; 2.4 M 2-vectors, k = 64, 59.4 against 69.4 and 69.0.
 constexpr int RST = 512;
-template <int KB, int D, int DIST, int PASS>
+// Vectors of the largest tile: 36 KB, and for scalars no more than 256 float32 additions to a sum before it is float64 (252
+// vectors of a lane, the four rows of a wavefront).
+constexpr int64_t row_tile_vectors(int d) { return d == 1 ? 252 * (RST / 64) * 4 : 9216 / d; }
+template <int KB, int D, int DIST, int PASS, bool SEVERAL>
 __global__ __launch_bounds__(RST) void row_pass(const Args a) {
     using RW = RowWave<KB, D, DIST, PASS>;
     if (PASS == PASS_FWD && a.ctrl->done) return;
@@ -563,12 +568,7 @@ __global__ __launch_bounds__(RST) void row_pass(const Args a) {
     __shared__ __align__(16) float s_rtab[RW::TAB];
     __shared__ float s_part[PASS == PASS_B3 ? 1 : RST / 64][PASS == PASS_B3 ? 1 : 16 * KB * RW::ACCW];
     const int tid = threadIdx.x, k = a.k, kd = k * D, per = (int)a.vec_per_wg;
-    const int64_t base = (int64_t)blockIdx.x * per;
-    int cnt = 0;
-    if (base < a.m) cnt = (a.m - base < per) ? (int)(a.m - base) : per;
-    load_tile<RST>(s_tile, a.W + base * D, cnt * D);
     float* s_g = s_tile + (size_t)per * D;
-    if (RW::USE_G) load_tile<RST>(s_g, a.G + base * D, cnt * D);
     for (int i = tid; i < KDP; i += RST) {
         s_Cf[i] = i < kd ? a.Cf[i] : 0.f;
         if (RW::USE_H) {
@@ -576,24 +576,43 @@ __global__ __launch_bounds__(RST) void row_pass(const Args a) {
             s_Ff[i] = i < kd ? a.Ff[i] : 0.f;
         }
     }
-    __syncthreads();
     if (RW::TAB > 1) {
+        __syncthreads();
         RW::template fill_table<RST>(s_rtab, k, s_Cf, s_Hs, s_Ff, a.escale);
-        __syncthreads();
     }
-    RW st;
-    st.init(k, RW::TAB > 1 ? s_rtab : s_Cf, s_Hs, s_Ff, a.escale);
-    row_tile_pass<KB, D, DIST, PASS, RST>(a, st, s_tile, s_g, base, cnt);
-    if constexpr (PASS != PASS_B3) {
-        st.collect(s_part[tid >> 6]);
+    auto tile = [&](int64_t t) {
+        int tid = threadIdx.x;
+        if (SEVERAL) asm volatile("" : "+v"(tid));  // (what every tile needs is formed again, not kept over the steps)
+        const int64_t base = t * per;
+        const int cnt = (a.m - base < per) ? (int)(a.m - base) : per;
+        load_tile<RST>(s_tile, a.W + base * D, cnt * D);
+        if (RW::USE_G) load_tile<RST>(s_g, a.G + base * D, cnt * D);
         __syncthreads();
-        const int nacc = k * RW::ACCW;
-        for (int idx = tid; idx < nacc; idx += RST) {
-            double t = 0.0;
+        RW st;
+        st.init(k, RW::TAB > 1 ? s_rtab : s_Cf, s_Hs, s_Ff, a.escale);
+        row_tile_pass<KB, D, DIST, PASS, RST>(a, st, s_tile, s_g, base, cnt);
+        if (SEVERAL) asm volatile("" : "+v"(tid));
+        if constexpr (PASS != PASS_B3) {
+            st.collect(s_part[tid >> 6], tid);
+            __syncthreads();
+            const int nacc = k * RW::ACCW;
+            for (int idx = tid; idx < nacc; idx += RST) {
+                double x = 0.0;
 #pragma unroll
-            for (int w = 0; w < RST / 64; ++w) t += (double)s_part[w][idx];
-            a.partials[(size_t)blockIdx.x * nacc + idx] = t;
+                for (int w = 0; w < RST / 64; ++w) x += (double)s_part[w][idx];
+                double* p = &a.partials[(size_t)blockIdx.x * nacc + idx];
+                *p = (!SEVERAL || t == (int64_t)blockIdx.x) ? x : *p + x;  // (a thread's own sums)
+            }
         }
+    };
+    if constexpr (SEVERAL) {
+        const int64_t tiles = (a.m + per - 1) / per;
+        for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x) {
+            tile(t);
+            if (PASS == PASS_B3) __syncthreads();  // (the other passes: the barrier behind collect)
+        }
+    } else {
+        tile(blockIdx.x);
     }
 }
 

@@ -163,3 +163,39 @@ def test_8_vectors_on_the_default_and_the_stream_path(ctx, k, m, dist):
             ctx.forward(Wd, Cd, tau, 0.0, iters, dist)
     finally:
         ctx.set_path(binding.PATH_AUTO)
+
+
+# more tiles than workgroups (256 compute units; one workgroup each at k d = 512 with 8-vectors, four with scalars), the last
+# tile ragged: the workgroups take several in turn
+@pytest.mark.parametrize("k,d,m", [(64, 8, 600_011), (129, 8, 299_003), (3, 1, 8_300_003)])
+def test_stream_passes_with_more_tiles_than_workgroups(ctx, k, d, m):
+    rng = np.random.default_rng(m)
+    W = (0.5 * rng.standard_normal((m, d))).astype(np.float32)
+    C0 = (W[:k] + 0.01 * rng.standard_normal((k, d))).astype(np.float32)
+    G = rng.standard_normal((m, d)).astype(np.float32)
+    tau, dist = 0.4, wl.DIST_SQL2
+    ctx.set_path(binding.PATH_STREAM)
+    try:
+        f = ctx.forward(dev(W), dev(C0), tau, 0.0, 1, dist, want_assign=True)
+        Cg = f["C"].cpu().numpy()
+        assert rel(Cg, orc.F(C0, W, tau, dist)) < TOL_VAL
+        i = np.r_[0:3_000, m // 2:m // 2 + 3_000, m - 3_000:m]
+        assert rel(f["Wq"].cpu().numpy()[i], orc.soft_quantize(W[i], Cg, tau, dist)) < TOL_VAL
+        assert np.array_equal(f["assign"].cpu().numpy()[i], orc.hard_assign_f32(W[i], Cg))
+        b = ctx.backward(dev(G), binding.BWD_IMPLICIT, tol=0.0, max_iter=2)
+        r = orc.backward(W, Cg, tau, dist, G, "implicit", tol=0.0, max_iter=2)
+        assert rel(ctx.get_cotangents(k, d)[0], r["v"]) < TOL_GRAD
+        assert rel(b["dW"].cpu().numpy(), r["dW"]) < TOL_GRAD
+    finally:
+        ctx.set_path(binding.PATH_AUTO)
+
+
+def test_workspace_of_the_stream_passes_does_not_grow_with_the_layer():
+    m, d, k = 4_200_000, 8, 256
+    W = torch.randn((m, d), device="cuda")
+    c = binding.Context(0)
+    c.set_path(binding.PATH_STREAM)
+    free = torch.cuda.mem_get_info()[0]
+    c.forward(W, W[:k].clone(), 1.0, 0.0, 1, wl.DIST_SQL2, want_Wq=False)
+    assert free - torch.cuda.mem_get_info()[0] < 40 << 20     # (1024 workgroups at the most: 19 MB of sums)
+    c.close()
