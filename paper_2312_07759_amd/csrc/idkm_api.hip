@@ -390,6 +390,7 @@ struct PersistPlan {
     int grid, per, threads;
     bool lane;  // lane<->codeword family: own exchange buffers
     size_t lds;
+    bool small_team = false;  // a team of eight for a layer that one workgroup could hold
 };
 // A persistent solve that a batched call will launch together with others.
 struct Deferred {
@@ -411,7 +412,7 @@ struct LaneBuf {
 };
 
 // The lane<->vector family's part of plan_persistent.
-bool plan_small(idkm_ctx* ctx, bool bwd, PersistPlan* pp, const void* dwq, int mode) {
+bool plan_small(idkm_ctx* ctx, bool bwd, PersistPlan* pp, const void* dwq, int mode, bool alone) {
     const int k = ctx->k, d = ctx->d;
     const int64_t m = ctx->m;
     // A codebook whose size is not a power of two runs in the kernels for the next one, the surplus codewords' weights held
@@ -438,7 +439,8 @@ bool plan_small(idkm_ctx* ctx, bool bwd, PersistPlan* pp, const void* dwq, int m
     // 2.8 against 2.5; k = 16, d = 1 2.0 / 3.7 / 4.8 against 2.8; k = 8, d = 4 2.6 / 6.2 / 6.6 against 3.4; k = 16, d = 4
     // 4.4 / 8.7 / 11.8 against 4.5.  (dF/dC)^T passes: k = 4, d = 1 1.6 / 2.4 / 2.9 against 2.5; k = 16, d = 1 2.9 / 4.8 /
     // 7.2 against 3.2; k = 16, d = 4 6.9 / 12.0 / 19.1 against 5.8.  Batched launches hide the exchange behind other layers
-    // and keep one workgroup, as do the modes that are solved in one place.
+    // and keep one workgroup, as do the modes that are solved in one place, and calls whose result nobody may wait for
+    // (idkm_forward_noalloc).  One workgroup waits for nobody: a team that gave up a wait is solved again by one (`alone`).
     if (m <= (int64_t)16 * PT) {
         const int64_t v = (m + PT - 1) / PT;
         const int kd = K * d;
@@ -449,8 +451,9 @@ bool plan_small(idkm_ctx* ctx, bool bwd, PersistPlan* pp, const void* dwq, int m
             from = kd >= 32 ? 5 : kd >= 16 ? 6 : 8;
         else if (kd >= 16)
             from = 12;
-        const bool one = ctx->sink || !ctx->tree_exchange || mode == IDKM_BWD_DENSE || mode == IDKM_BWD_GMRES;
+        const bool one = alone || ctx->sink || ctx->res_on_device || !ctx->tree_exchange || mode == IDKM_BWD_DENSE || mode == IDKM_BWD_GMRES;
         g = (!one && v >= from) ? DIES : 1;
+        pp->small_team = g > 1;
     }
     if (g < 1) g = 1;
     // (a team of 2 to 7 workgroups would take the one-level exchange; 8 smaller workgroups take the two-level one)
@@ -485,12 +488,15 @@ bool plan_small(idkm_ctx* ctx, bool bwd, PersistPlan* pp, const void* dwq, int m
 // matrix_ok: the matrix-core kernels may serve the call (every pass of both energies has a matrix-core form).
 // dwq: the backward's upstream gradient (a layer too large for LDS is streamed from memory with 16-byte loads, which
 // W and dL/dWq must allow).
-// mode: the backward's (BWD_JFB where there is none).
-bool plan_persistent(idkm_ctx* ctx, bool bwd, PersistPlan* pp, bool matrix_ok = true, const void* dwq = nullptr, int mode = IDKM_BWD_JFB) {
+// mode: the backward's (BWD_JFB where there is none).  alone: small layers in one workgroup.
+bool plan_persistent(idkm_ctx* ctx, bool bwd, PersistPlan* pp, bool matrix_ok = true, const void* dwq = nullptr, int mode = IDKM_BWD_JFB,
+                     bool alone = false) {
+    pp->small_team = false;
     if (!ctx->coop || ctx->num_cu < 1) return false;
     const int k = ctx->k, d = ctx->d;
     const int64_t m = ctx->m;
-    if (plan_small(ctx, bwd, pp, dwq, mode)) return true;
+    if (plan_small(ctx, bwd, pp, dwq, mode, alone)) return true;
+    pp->small_team = false;
     if (!(k >= 2 && k <= 16 && pow2(k) && d <= 4)) {
         // lane<->codeword family
         int kpl = (k + 63) / 64, p = 1;
@@ -972,11 +978,15 @@ idkm_status idkm_forward(idkm_ctx* ctx, const float* W, int64_t m, int32_t d, co
         pa.C0 = C0;
         pa.tol = (double)tol;
         pa.max_iter = (int)max_iter;
-        st = launch_persistent(ctx, pp, a, pa, (unsigned int)max_iter + 1u, s);
-        if (st == IDKM_OK) {
-            ctx->pending_kind = 1;
-            if (ctx->defer_wait) return IDKM_OK;
-            st = finish_persistent(ctx, info);
+        for (bool again = true; again;) {
+            st = launch_persistent(ctx, pp, a, pa, (unsigned int)max_iter + 1u, s);
+            if (st == IDKM_OK) {
+                ctx->pending_kind = 1;
+                if (ctx->defer_wait) return IDKM_OK;
+                st = finish_persistent(ctx, info);
+            }
+            again = st == IDKM_ERR_DEVICE && pp.small_team && plan_persistent(ctx, false, &pp, true, nullptr, IDKM_BWD_JFB, true);
+            if (again) ctx->err.clear();
         }
         // Under IDKM_PATH_AUTO a persistent attempt that could not run to its end -- the grid was not co-resident
         // (other work occupies compute units) or a bounded wait expired -- is answered by the stream path, which
@@ -1161,11 +1171,15 @@ idkm_status idkm_backward(idkm_ctx* ctx, const float* dWq, idkm_bwd_mode mode, f
             pa.alpha = (double)alpha;
             pa.gm_basis = ctx->gmres_basis;
             pa.gm_off = gm_off;
-            st = launch_persistent(ctx, pp, a, pa, (unsigned int)ex, s);
-            if (st == IDKM_OK) {
-                ctx->pending_kind = 2;
-                if (ctx->defer_wait) return IDKM_OK;
-                st = finish_persistent(ctx, info);
+            for (bool again = true; again;) {
+                st = launch_persistent(ctx, pp, a, pa, (unsigned int)ex, s);
+                if (st == IDKM_OK) {
+                    ctx->pending_kind = 2;
+                    if (ctx->defer_wait) return IDKM_OK;
+                    st = finish_persistent(ctx, info);
+                }
+                again = st == IDKM_ERR_DEVICE && pp.small_team && plan_persistent(ctx, true, &pp, true, dWq, (int)mode, true);
+                if (again) ctx->err.clear();
             }
             if (st != IDKM_ERR_DEVICE || ctx->path != IDKM_PATH_AUTO) return st;
             ctx->err.clear();  // as in idkm_forward: the stream path answers instead
