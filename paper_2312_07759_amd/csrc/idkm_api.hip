@@ -5,6 +5,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
+#include <cstddef>
 #include <cstring>
 #include <map>
 #include <mutex>
@@ -166,6 +167,7 @@ struct idkm_ctx {
     unsigned int seq_base = 0;
     unsigned long long* lane_xbuf = nullptr;  // exchange words of the lane<->codeword persistent kernels (lazy)
     size_t lane_words = 0;                    // ... of this size
+    unsigned long long* rag_xbuf = nullptr;   // exchange words of the ragged codebooks' persistent kernels (lazy)
     unsigned int* abort_word = nullptr;  // device
     PResult* h_res = nullptr;            // pinned host; device memory when res_on_device
     bool res_on_device = false;          // the context of idkm_forward_noalloc: the kernel reports into device memory
@@ -208,6 +210,11 @@ idkm_status fail(idkm_ctx* ctx, idkm_status s, const std::string& msg) {
         if (e_ != hipSuccess)                                                                      \
             return fail(ctx, IDKM_ERR_DEVICE, std::string(#expr) + ": " + hipGetErrorString(e_)); \
     } while (0)
+
+// Distance between two 32-bit words (not of one array), in words.
+unsigned long long words_between(const unsigned int* from, const unsigned int* to) {
+    return (unsigned long long)(((intptr_t)reinterpret_cast<uintptr_t>(to) - (intptr_t)reinterpret_cast<uintptr_t>(from)) / 4);
+}
 
 struct Geometry {
     bool small;    // lane<->vector family
@@ -380,8 +387,9 @@ idkm_status launch_pass(idkm_ctx* ctx, const Geometry& g, int pass, Args& a, hip
 constexpr size_t XBUF1_WORDS = (size_t)2 * PT * XLINE;
 constexpr size_t XBUF3_WORDS = (size_t)2 * DIES * XLINE;  // two-level exchange: totals of the dies
 constexpr size_t XBUF_WORDS = XBUF1_WORDS + (size_t)2 * XBCAST + XBUF3_WORDS + DIES;
-// ... and the lines of the ragged codebooks, whose sums take two words (see SumWords)
-constexpr size_t XBUF_ALL_WORDS = XBUF_WORDS + 2 * (XBUF1_WORDS + XBUF3_WORDS);
+// Lines of the ragged codebooks, whose sums take two words (see SumWords).  A buffer of their own: with xbuf three times as
+// large it came to lie elsewhere, and the solves that do not use the rest took 1 to 3 % longer (same code, same bits).
+constexpr size_t RAG_WORDS = 2 * (XBUF1_WORDS + XBUF3_WORDS);
 constexpr size_t LDS_TILE_MAX = 144 * 1024;  // bytes of LDS a persistent workgroup may use for its tile
 
 struct PersistPlan {
@@ -581,6 +589,10 @@ idkm_status launch_persistent(idkm_ctx* ctx, const PersistPlan& pp, Args& a, PAr
             hipLaunchKernelGGL(k_fill_u64, dim3(256), dim3(256), 0, s, ctx->lane_xbuf, ctx->lane_words, 0ull);
             HIP_TRY(ctx, hipGetLastError());
         }
+        if (ctx->rag_xbuf) {
+            hipLaunchKernelGGL(k_fill_u64, dim3(64), dim3(256), 0, s, ctx->rag_xbuf, RAG_WORDS, 0ull);
+            HIP_TRY(ctx, hipGetLastError());
+        }
         ctx->seq_base = 0;
     }
     if (pp.lane) {
@@ -608,8 +620,15 @@ idkm_status launch_persistent(idkm_ctx* ctx, const PersistPlan& pp, Args& a, PAr
         pa.buf3 = pa.buf2 + (size_t)2 * XBCAST;
         pa.tab = pa.buf3 + XBUF3_WORDS;
         if (!pow2(ctx->k)) {
-            if (ctx->xbuf_words < XBUF_ALL_WORDS) return fail(ctx, IDKM_ERR_DEVICE, "exchange buffer too small");
-            pa.buf1 = ctx->xbuf + XBUF_WORDS;
+            if (!ctx->rag_xbuf) {
+                if (hipMalloc(&ctx->rag_xbuf, RAG_WORDS * sizeof(unsigned long long)) != hipSuccess) {
+                    (void)hipGetLastError();
+                    return fail(ctx, IDKM_ERR_ALLOC, "hipMalloc of the exchange buffer failed");
+                }
+                hipLaunchKernelGGL(k_fill_u64, dim3(64), dim3(256), 0, s, ctx->rag_xbuf, RAG_WORDS, 0ull);
+                HIP_TRY(ctx, hipGetLastError());
+            }
+            pa.buf1 = ctx->rag_xbuf;
             pa.buf3 = pa.buf1 + 2 * XBUF1_WORDS;
         }
         // teams of DIES workgroups or more: hop 1 stays inside each die (the explicit-Jacobian mode keeps the plain
@@ -831,11 +850,18 @@ idkm_status idkm_create(idkm_ctx** out, int device_id) {
     }
     ok &= hipMalloc(&c->tickets, TICKET_WORDS * sizeof(unsigned int)) == hipSuccess;
     if (ok) ok &= hipMemset(c->tickets, 0, TICKET_WORDS * sizeof(unsigned int)) == hipSuccess;
-    ok &= hipMalloc(&c->abort_word, sizeof(unsigned int)) == hipSuccess;
-    if (ok) ok &= hipMemset(c->abort_word, 0, sizeof(unsigned int)) == hipSuccess;
+    ok &= hipMalloc(&c->abort_word, 2 * sizeof(unsigned long long)) == hipSuccess;
     ok &= hipHostMalloc(&c->h_res, sizeof(PResult)) == hipSuccess;
-    if (ok) std::memset(c->h_res, 0, sizeof(PResult));
-    c->xbuf_words = XBUF_ALL_WORDS;
+    if (ok) {
+        std::memset(c->h_res, 0, sizeof(PResult));
+        void* res = nullptr;  // as the kernels see it
+        ok &= hipHostGetDevicePointer(&res, c->h_res, 0) == hipSuccess;
+        if (ok) {
+            const unsigned long long words[2] = {0ull, words_between(c->abort_word, &static_cast<PResult*>(res)->aborted)};
+            ok &= hipMemcpy(c->abort_word, words, sizeof(words), hipMemcpyHostToDevice) == hipSuccess;
+        }
+    }
+    c->xbuf_words = XBUF_WORDS;
     ok &= hipMalloc(&c->xbuf, c->xbuf_words * sizeof(unsigned long long)) == hipSuccess;
     if (ok) ok &= hipMemset(c->xbuf, 0, c->xbuf_words * sizeof(unsigned long long)) == hipSuccess;
     if (ok) ok &= hipDeviceSynchronize() == hipSuccess;
@@ -851,7 +877,7 @@ idkm_status idkm_destroy(idkm_ctx* c) {
     if (!c) return IDKM_ERR_INVALID_ARG;
     (void)hipSetDevice(c->device);
     (void)hipDeviceSynchronize();
-    void* dev[] = {c->ctrl, c->Cd, c->Fd, c->gd, c->vd, c->ud, c->nd, c->Cf, c->Ff, c->Hs, c->stage, c->tot, c->partials, c->kry, c->tickets, c->xbuf, c->lane_xbuf, c->abort_word};
+    void* dev[] = {c->ctrl, c->Cd, c->Fd, c->gd, c->vd, c->ud, c->nd, c->Cf, c->Ff, c->Hs, c->stage, c->tot, c->partials, c->kry, c->tickets, c->xbuf, c->lane_xbuf, c->rag_xbuf, c->abort_word};
     for (void* p : dev)
         if (p) (void)hipFree(p);
     if (c->ev0) (void)hipEventDestroy(c->ev0);
@@ -1660,6 +1686,7 @@ struct StaticScratch {
     float Cf[64], Ff[64];
     unsigned int abort_word;
     unsigned int pad_;
+    unsigned long long abort_away;  // way to res.aborted (see PArgs::abort_word)
     PResult res;
 };
 constexpr size_t STATIC_SCRATCH_BYTES = (sizeof(StaticScratch) + 255) / 256 * 256;
@@ -1735,6 +1762,9 @@ idkm_status idkm_forward_noalloc(int device_id, const float* W, int64_t m, int32
         // the stamps start from a cleared array (sequence number 0 is never used); a fill kernel, not a memset
         hipLaunchKernelGGL(k_fill_u64, dim3(64), dim3(256), 0, s, reinterpret_cast<unsigned long long*>(ptr),
                            STATIC_SCRATCH_BYTES / sizeof(unsigned long long), 0ull);
+        hipLaunchKernelGGL(k_fill_u64, dim3(1), dim3(64), 0, s, &sc->abort_away, (size_t)1,
+                           words_between(&sc->abort_word, &sc->res.aborted));
+        static_assert(offsetof(StaticScratch, abort_away) == offsetof(StaticScratch, abort_word) + 8, "the word behind the abort word");
         if (hipGetLastError() != hipSuccess) return bad(IDKM_ERR_DEVICE, "clearing the scratch array failed");
         sd.ready = true;
     }

@@ -71,7 +71,6 @@ struct PArgs {
                                // sums take two words (SumWords), buf3 too
     unsigned long long* buf2;  // [2][XBCAST] stamped broadcast values
     unsigned long long* buf3;  // [2][DIES][XLINE] two-level exchange: stamped totals of each die
-    unsigned long long* buf4;  // lane family: [2][DIES][2 k (d+1)] grid totals, one copy per die
     unsigned long long* tab;   // [DIES] two-level exchange: die index of each leader, stamped with the launch id
     int tree;                  // two-level exchange (team of at least TREE_MIN_G workgroups, one problem per launch);
                                // 2: the same with every store at device scope (test support)
@@ -85,8 +84,11 @@ struct PArgs {
     int max_iter;
     int mode;                  // backward: BWD_IMPLICIT or BWD_JFB
     double alpha;              // backward: damping factor
-    unsigned int* abort_word;  // device word; holds this launch's id once a bounded wait has expired
+    unsigned int* abort_word;  // device word; holds this launch's id once a bounded wait has expired.  8 bytes behind it:
+                               // how many 32-bit words away PResult::aborted lies
     PResult* out;              // pinned host memory
+    unsigned long long* buf4;  // lane family: [2][DIES][2 k (d+1)] grid totals, one copy per die.  (Behind what the small-codebook
+                               // kernels load in groups: between buf3 and tab it cost their passes up to 1 %.)
     int wg, G;                 // this workgroup's index within its team and the team's size; filled in by the kernel
 #ifdef IDKM_TRACE
     long long* trace;          // [2 workgroups][64 passes][8 stamps], then [256 workgroups][8 stamps] of pass 20 (development builds only)
@@ -119,12 +121,15 @@ struct BatchItem {
 #endif
 
 
-// A bounded wait has expired: tells the other workgroups to leave, and the host.  (The host cannot go by `done` alone: in
-// the last exchange the workgroup that writes it may already hold all its words while another one waits in vain, and
-// leaves without its share of the output.)
+// A bounded wait has expired: tells the other workgroups to leave, and the host.  (The host cannot go by `done` alone: in the
+// last exchange of a backward the workgroup that writes it may already hold all its words while another one waits in vain
+// and leaves without its rows of dW.)  Where the host's word lies is said behind the team's word and read only
+// here: as a kernel argument it takes scalar registers from the passes (4,096 weights, k = 4, 80 passes: 289 -> 300 us).  (As
+// a distance, so that the compiler knows a global address and not one that may be in LDS.)
 __device__ __forceinline__ void raise_abort(const PArgs& pa) {
     __hip_atomic_store(pa.abort_word, pa.seq_base + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(&pa.out->aborted, pa.seq_base + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    const long long away = (long long)ld_word(reinterpret_cast<const unsigned long long*>(pa.abort_word) + 1);
+    __hip_atomic_store(pa.abort_word + away, pa.seq_base + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // Shared scratch of the exchange.  WIDE: what wavefronts have added up travels as float64 (two words a sum) instead of as
@@ -313,12 +318,21 @@ __device__ __forceinline__ bool poll_sum(const PArgs& pa, const unsigned long lo
         unsigned long long w[2];
         if (!poll_words<2>(pa, src, gap, seq, w)) return false;
         out = SumWords<true>{{w[0], w[1]}}.value();
+        return true;
     } else {
-        unsigned long long w[1];
-        if (!poll_words<1>(pa, src, 0, seq, w)) return false;
-        out = (double)__uint_as_float((unsigned int)w[0]);
+        unsigned int spins = 0;
+        for (;;) {
+            const unsigned long long w = ld_word(src);
+            if ((unsigned int)(w >> 32) == seq) {
+                out = (double)__uint_as_float((unsigned int)w);
+                return true;
+            }
+            ++spins;
+            if (spins > pa.spin_limit ||
+                ((spins & 31u) == 0u && __hip_atomic_load(pa.abort_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == pa.seq_base + 1u))
+                return false;
+        }
     }
-    return true;
 }
 
 // hop 1, reducer side: totals over all workgroups of words [first, first+WPR) into xs.tot (float64, fixed order).
@@ -638,16 +652,17 @@ __device__ __forceinline__ bool tree8_die_totals(const PArgs& pa, unsigned int s
     }
     __syncthreads();
     if (xs.abort) return false;
-    if (tid < 8 * SumWords<XS::WIDE>::N) {
-        const typename XS::total_t tot = (typename XS::total_t)((xs.red2[p] + xs.red2[8 + p]) + (xs.red2[16 + p] + xs.red2[24 + p]));
-        unsigned long long* dst = &pa.buf3[((size_t)(seq & 1u) * DIES + x) * 32 + tid];
-        if constexpr (XS::WIDE) {  // (lanes 8 .. 15 store the upper halves)
+    if constexpr (XS::WIDE) {
+        if (tid < 16) {  // (lanes 8 .. 15 store the upper halves)
+            const double tot = (xs.red2[p] + xs.red2[8 + p]) + (xs.red2[16 + p] + xs.red2[24 + p]);
             if (tid < 8) xs.stage2[x * 8 + tid] = tot;
-            st_word(dst, pack_u(seq, (unsigned int)(tid < 8 ? __double2loint(tot) : __double2hiint(tot))));
-        } else {
-            xs.stage2[x * 8 + tid] = tot;
-            st_word(dst, pack_f(seq, tot));
+            st_word(&pa.buf3[((size_t)(seq & 1u) * DIES + x) * 32 + tid],
+                    pack_u(seq, (unsigned int)(tid < 8 ? __double2loint(tot) : __double2hiint(tot))));
         }
+    } else if (tid < 8) {
+        const float tot = (float)((xs.red2[tid] + xs.red2[8 + tid]) + (xs.red2[16 + tid] + xs.red2[24 + tid]));
+        xs.stage2[x * 8 + tid] = tot;
+        st_word(&pa.buf3[((size_t)(seq & 1u) * DIES + x) * 32 + tid], pack_f(seq, tot));
     }
     return true;
 }
