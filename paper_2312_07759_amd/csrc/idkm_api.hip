@@ -509,10 +509,13 @@ bool plan_persistent(idkm_ctx* ctx, bool bwd, PersistPlan* pp, bool matrix_ok = 
         // lane<->codeword family
         int kpl = (k + 63) / 64, p = 1;
         while (p < kpl) p <<= 1;
-        // d = 8: the forward solve of layers of more than 4096 vectors, under IDKM_PATH_AUTO (the explicit persistent path is
-        // not offered for d > 4, and smaller layers stay on the stream path that idkm_info reports for them): 294,912
-        // 8-vectors under 256 codewords, 20 evaluations and a Jacobian-free backward, 2051 us against 2954 there
-        const bool row8 = d == 8 && k <= 256 && !bwd && m > 4096 && ctx->path == IDKM_PATH_AUTO;
+        // d = 8: the forward solve alone, under IDKM_PATH_AUTO alone (the explicit persistent path is not offered for d > 4).
+        // 20 evaluations, stream path against this one, us: k = 16 from 300 to 10,000 vectors 280-295 / 135-168, k = 64
+        // 300-334 / 232-284, k = 100 and 128 at 4,097 364-368 / 340-370, at 64,000 520 / 335; beyond 128 codewords a small team's
+        // workgroups wait for longer slices of the totals: k = 160 and 256 at 4,097 468-487 / 593-667, at 10,000 491-513 / 547-579,
+        // at 16,000 534-567 / 535-573, at 24,000 562-599 / 534-558, at 290,000 (k = 256) 1496 / 1370.  Layers of up to 4096 vectors
+        // stay on the stream path, which idkm_info has always reported for them, though up to 128 codewords they would gain.
+        const bool row8 = d == 8 && k <= 256 && !bwd && m > (k <= 128 ? 4096 : 16000) && ctx->path == IDKM_PATH_AUTO;
         if (!row8 && (d > 4 || p * d > 16 || p * (d + 1) > 24)) return false;
         int64_t g = (m + 255) / 256;  // at least 16 vectors per wavefront before adding workgroups
         if (g < 1) g = 1;

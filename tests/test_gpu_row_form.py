@@ -125,10 +125,10 @@ def test_float64_outputs_hold_float64_sums(ctx, k, d, m, bits):
 
 @pytest.mark.parametrize("dist", [wl.DIST_L2, wl.DIST_SQL2])
 @pytest.mark.parametrize("k,m", [(1, 4_097), (3, 9_001), (16, 4_100), (17, 20_011), (64, 5_003), (65, 1_300), (128, 6_001), (129, 70_001),
-                                 (256, 4_096), (256, 40_003)])
+                                 (256, 4_096), (256, 9_001), (256, 40_003)])
 def test_8_vectors_on_the_default_and_the_stream_path(ctx, k, m, dist):
-    """d = 8: above 4096 vectors the default path solves the forward in one launch, everything else stays on the stream path
-    and the explicit persistent path stays refused."""
+    """d = 8: the default path solves the forward in one launch above 4096 vectors (16000 beyond 128 codewords), everything else
+    stays on the stream path and the explicit persistent path stays refused."""
     d = 8
     W, C0, G = wl.random_problem(m, d, k, seed=k + m, std=0.5, spread=1.5)
     C0 = C0 + 0.01 * np.random.default_rng(k).standard_normal(C0.shape)
@@ -141,7 +141,7 @@ def test_8_vectors_on_the_default_and_the_stream_path(ctx, k, m, dist):
         ctx.set_path(path)
         try:
             f = ctx.forward(Wd, Cd, tau, 0.0, iters, dist, want_A=True, want_assign=True)
-            want = binding.PATH_PERSISTENT if path == binding.PATH_AUTO and m > 4096 else binding.PATH_STREAM
+            want = binding.PATH_PERSISTENT if path == binding.PATH_AUTO and m > (4096 if k <= 128 else 16000) else binding.PATH_STREAM
             assert f["info"].path == want and f["info"].iters == iters
             Cg = f["C"].cpu().numpy()
             assert rel(Cg, ref["C"]) < TOL_VAL
