@@ -1,6 +1,6 @@
 """Codebooks of 3 .. 15 codewords whose size is not a power of two: the persistent path runs them in the lane<->vector
 kernels of the next power of two, with the surplus codewords' weights held at zero.  Held to the float64 oracle and to the
-stream path (the lane<->codeword kernels, any k) over team sizes, both energies, all backward modes and batched calls."""
+stream path (d = 1 and 2: the row<->vector passes, d = 4: the lane<->codeword ones) over team sizes, both energies, all backward modes and batched calls."""
 import numpy as np
 import pytest
 import torch
@@ -74,11 +74,19 @@ def test_every_padded_shape_against_the_oracle_and_the_stream_path(ctx, k, d, m,
     # the general path at the same codebook
     ctx.set_path(binding.PATH_STREAM)
     try:
-        s = ctx.forward(Wd, Cd, tau, 0.0, iters, dist)
+        s = ctx.forward(Wd, Cd, tau, 0.0, iters, dist, want_A=True, want_assign=True)
         assert s["info"].path == binding.PATH_STREAM
-        assert rel(f["C"].cpu().numpy(), s["C"].cpu().numpy()) < 1e-5
+        Cs = s["C"].cpu().numpy()
+        assert rel(Cg, Cs) < 1e-5
+        assert rel(s["A"].cpu().numpy(), orc.attention(W, Cs, tau, dist)) < TOL_VAL
+        assert rel(s["Wq"].cpu().numpy(), orc.soft_quantize(W, Cs, tau, dist)) < TOL_VAL
+        assert np.array_equal(s["assign"].cpu().numpy(), orc.hard_assign_f32(W, Cs))
         sj = ctx.backward(Gd, binding.BWD_JFB)
         assert rel(res["jfb"]["dW"].cpu().numpy(), sj["dW"].cpu().numpy()) < 1e-4
+        si = ctx.backward(Gd, binding.BWD_IMPLICIT, tol=0.0, max_iter=8)
+        assert si["info"].path == binding.PATH_STREAM
+        ri = orc.backward(W, Cs, tau, dist, G, "implicit", tol=0.0, max_iter=8)
+        assert rel(ctx.get_cotangents(k, d)[1], ri["g"]) < TOL_GRAD and rel(si["dW"].cpu().numpy(), ri["dW"]) < TOL_GRAD
     finally:
         ctx.set_path(binding.PATH_AUTO)
 
