@@ -55,7 +55,9 @@ typedef enum {
 /* How the device work is scheduled.  Results are identical up to rounding order. */
 typedef enum {
     IDKM_PATH_AUTO = 0,      /* persistent when the problem fits on chip, else stream; also stream when a persistent
-                                attempt could not run to its end (see idkm_set_spin_limit) */
+                                attempt could not run to its end (see idkm_set_spin_limit).  d = 8 (which the explicit
+                                persistent path does not take): idkm_forward is persistent for k <= 128 above 4096 vectors
+                                and for 129 <= k <= 256 above 16000, idkm_backward is stream */
     IDKM_PATH_STREAM = 1,    /* one kernel launch per pass over W */
     IDKM_PATH_PERSISTENT = 2 /* one launch per solve, W held in LDS, one grid-wide exchange per pass */
 } idkm_path;
@@ -91,8 +93,10 @@ idkm_status idkm_set_path(idkm_ctx* ctx, idkm_path path);
  * enable = 0 sends them to the vector-ALU kernels that serve every other shape instead (diagnostics, comparisons);
  * the default is 1.  Takes effect from the next idkm_forward; a backward follows the setting in force at its call. */
 idkm_status idkm_set_matrix_cores(idkm_ctx* ctx, int32_t enable);
-/* Persistent path, k in {2,4,8,16}: a workgroup keeps its share of W (and of dL/dWq in the backward) in LDS when it
- * is at most `bytes` (default and maximum 147456).  A layer with larger shares (more than about 9.4 M weights) is
+/* Persistent path, 2 <= k <= 16, d <= 4: a workgroup keeps its share of W (and of dL/dWq in the backward) in LDS when it
+ * is at most `bytes` (default and maximum 147456).  (A batched backward reads dL/dWq from memory, but the limit is compared
+ * with both shares there too, so that a layer takes the same path alone and in a batch; k not a power of two: a larger layer
+ * goes to the kernels that serve k > 16.)  A layer with larger shares (more than about 9.4 M weights) is
  * served by the stream path under IDKM_PATH_AUTO; under IDKM_PATH_PERSISTENT the same one-launch solve reads W and
  * dL/dWq from memory in every pass (needs both 16-byte aligned, else IDKM_ERR_UNSUPPORTED).  Smaller values of
  * `bytes` send smaller layers that way (test support, comparisons). */
@@ -100,7 +104,9 @@ idkm_status idkm_set_tile_limit(idkm_ctx* ctx, int64_t bytes);
 /* Bound of every device-side wait of the persistent kernels, in polls (default 2^20, about a second).  When a
  * wait expires all workgroups leave the kernel.  Under IDKM_PATH_AUTO the call is then answered by the stream path
  * (a new launch from the host; idkm_info.path says IDKM_PATH_STREAM), and so is a call whose persistent grid would
- * not be resident at once; under an explicit IDKM_PATH_PERSISTENT the call returns IDKM_ERR_DEVICE.  The context
+ * not be resident at once; under an explicit IDKM_PATH_PERSISTENT the call returns IDKM_ERR_DEVICE.  (A layer of at most
+ * 4096 vectors, 2 <= k <= 16, that ran as a team of workgroups is first solved again by one, which waits for nobody, on
+ * either path.)  A call that returns IDKM_OK has written all of its outputs.  The context
  * stays usable either way.  A limit of 0 makes the first unsuccessful poll give up (used to exercise that path). */
 idkm_status idkm_set_spin_limit(idkm_ctx* ctx, uint32_t polls);
 /* Measurement support.  With enable != 0 the library records a HIP event on the caller's stream immediately before

@@ -525,7 +525,8 @@ bool plan_persistent(idkm_ctx* ctx, bool bwd, PersistPlan* pp, bool matrix_ok = 
         int64_t per = (m + g - 1) / g;
         per = (per + 3) / 4 * 4;
         // d <= 2 and k <= 256: the row <-> vector kernels (589,824 scalar weights under 64 codewords, 30 evaluations and a
-        // Jacobian-free backward: 671 us against 1260); beyond 256 codewords their tables do not fit the registers
+        // Jacobian-free backward: 550 us against 1260 in the lane <-> codeword form they replaced, 671 when that was all that
+        // had changed); beyond 256 codewords their tables do not fit the registers
         const bool row = row8 || (d <= 2 && k <= 256);
         PersistFns fl;
         if (row) {
@@ -1186,7 +1187,7 @@ idkm_status idkm_backward(idkm_ctx* ctx, const float* dWq, idkm_bwd_mode mode, f
     }
     if (ctx->path == IDKM_PATH_PERSISTENT && !persistent)
         return fail(ctx, IDKM_ERR_UNSUPPORTED, mode == IDKM_BWD_GMRES
-                        ? "IDKM_BWD_GMRES on the persistent path needs k in {2,4,8,16}, k*d <= 64, a team of one or of at least 8 workgroups and room in LDS for its basis beside the tiles"
+                        ? "IDKM_BWD_GMRES under IDKM_PATH_PERSISTENT needs k in {2,4,8,16} (under IDKM_PATH_AUTO every k in 2 .. 16 may run in one launch), k*d <= 64, a team of one or of at least 8 workgroups and room in LDS for its basis beside the tiles"
                         : "the persistent path needs k <= 512, d <= 4 and the tiles of W and dWq to fit in LDS");
     if (persistent) {
         const uint64_t ex = 1ull + (mode == IDKM_BWD_IMPLICIT ? (uint64_t)max_iter * 7ull

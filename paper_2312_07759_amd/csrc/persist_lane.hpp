@@ -6,11 +6,13 @@
 //   hop 2  (across dies) every member adds the 8 dies' totals of its slice, in a fixed order, and stores the grid totals at
 //          buf4[parity][x][.], where its die reads them; EVERY workgroup applies the O(k d) update itself, so that all
 //          hold the same state and take the same stop decision.
+// Workgroups' sums travel as float32 (d = 8: float64), the dies' and the grid's totals as float64 in two words (SumWords).
 // As in persist_small.hpp a store of hop 1 only has to reach the die's L2 when all members of the die run there (checked at
 // the start of a launch).  There one workgroup per die adds all of the at most 80 words.  The form this
-// replaced had one reducer per codeword that read all 256 workgroups through memory, and a broadcast of the result:
-// 589,824 weights under 64 codewords 671 -> 615 us (30 evaluations and a Jacobian-free backward), 589,824 4-vectors under
-// 256 codewords (30 evaluations, 10 passes) 2484 -> 2434, 2,620 4-vectors under 64 (20 evaluations, 10 passes) 415 -> 271.
+// replaced had one reducer per codeword that read all 256 workgroups through memory, and a broadcast of the result.  Before
+// and now: 589,824 weights under 64 codewords 671 -> 550 us (30 evaluations and a Jacobian-free backward; 598 -> 562 of it from
+// the slices of hop 2), 589,824 4-vectors under 256 codewords (30 evaluations, 10 passes) 2484 -> 2461.  Totals in one word
+// with 29 bits, for comparison: 553 and 2416; 64,000 8-vectors under 256 codewords (20 evaluations) 510 against 577.
 // Waits are bounded exactly as in persist_small.hpp.
 #pragma once
 #include "common.hpp"

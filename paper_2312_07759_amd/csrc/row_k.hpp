@@ -6,8 +6,9 @@
 // Bound by issue on the vector ALU.  The lane <-> codeword form it replaces on these shapes (one vector per wavefront and
 // step) pays a broadcast of the vector and a dependent six-step wavefront sum per vector whatever k is: at k = 64, d = 1
 // about 20 issue slots per (vector, 64 codewords) against 7 slots per pair here plus about 112 / k for the row sums.
-// 589,824 weights, k = 64, d = 1: 30 evaluations and a Jacobian-free backward 1260 -> 671 us; 4 vectors per row and step
-// where they fit the registers.
+// 589,824 weights, k = 64, d = 1, 30 evaluations and a Jacobian-free backward: 1260 -> 671 us by this form alone, 550 with the
+// exchange and the issue priority it has now (71 % of the issue slots of the launch taken; 10.1 slots per pair, row sums and
+// exchange included); 4 vectors per row and step where they fit the registers.
 // Vectors are read from the workgroup's LDS tile (all lanes of a row read the same address).
 #pragma once
 #include "common.hpp"
@@ -19,7 +20,10 @@ namespace idkm {
 // Values per lane that a step may keep live (256 registers at two wavefronts per SIMD; at 160 the forward loop at k = 256,
 // d = 2 spilled 46 registers).
 constexpr int ROW_BUDGET = 150;
-constexpr int ROW_BUDGET_8 = 226;  // d = 8 (the sums alone are 144 at k = 256; nothing else is kept)
+// d = 8: the sums alone are 144 at k = 256, and nothing else is kept.  The forward loop fits (226 registers).  The pass for v and
+// the (dF/dC)^T pass do not at k = 256, with one vector a step either: the compiler brings operands forward from LDS and
+// spills 50 to 137 registers inside the step loop (66 % of the issue slots taken in the pass for v, 179 us at 294,912 vectors).
+constexpr int ROW_BUDGET_8 = 226;
 
 template <int KB, int D, int DIST, int PASS>
 struct RowWave {
