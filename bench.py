@@ -49,6 +49,19 @@ def bwd_lane_ops_per_vector(k: int, d: int, dist: int) -> int:
     return k * (5 * d + 9) + TRANS_COST * trans
 
 
+def operator_lane_ops_per_vector(k: int, d: int, dist: int):
+    """Where (dF/dC)^T is formed once as a matrix (k <= 8; at most 128 sums of v and pair moments), the operations the moments
+    add to the pass for v, per weight vector: the pair's weight, d additions for w - mid and its moments.  None elsewhere."""
+    kk = 2
+    while kk < k:
+        kk *= 2
+    sums = 1 + d + d * (d + 1) // 2 if dist == 1 else 2 * (d + d * d)
+    if d > 4 or k < 2 or kk * d + kk * (kk - 1) // 2 * sums > 128:
+        return None
+    ops = 2 + 3 * d + d * (d + 1) // 2 if dist == 1 else 1 + d + 2 * (2 * d + d * d)
+    return kk * (kk - 1) // 2 * ops
+
+
 def matrix_core_lane_cycles_per_vector(k: int, dist: int) -> int:
     """The same count for the shapes whose forward loop runs on the matrix cores (d = 4, 17 <= k <= 256, persistent
     path): per (vector, codeword) pair 8 float32 multiply-adds on the matrix cores (4 of the energy product, 4 of
@@ -236,9 +249,22 @@ def main() -> int:
     kms = dict(measure.kernel_ms)
     roofline = roofline_of(cfg, dist, fwd_ms, finfo, kms.get("fwd"))
     # the (dF/dC)^T passes of the implicit backward (Eq. "backiter"): the JFB call is the same launch without them
-    # (one pass for v, one for dL/dW), so their time is the difference of the two calls
+    # (one pass for v, one for dL/dW), so their time is the difference of the two calls.  Small codebooks form the operator
+    # in the pass for v and iterate on the matrix: there the whole launch, two passes over W, is what is priced.
     roofline_backward = None
-    if binfo.iters > 0:
+    op_ops = operator_lane_ops_per_vector(cfg.k, cfg.d, dist)
+    if binfo.iters > 0 and op_ops is not None:
+        bops = 2 * bwd_lane_ops_per_vector(cfg.k, cfg.d, dist) + op_ops
+        b_ms = kms.get("bwd") or bwd_ms
+        roofline_backward = {
+            "bound": "alu", "kernel": "implicit backward: one pass for v and the operator (dF/dC)^T, the averaged iteration on the "
+                                      "k d x k d matrix, one pass for dL/dW",
+            "achieved": bops * cfg.m / (b_ms * 1e-3) / 1e12, "peak": PEAK_LANE_OPS / 1e12, "unit": "Tlane-op/s",
+            "frac": bops * cfg.m / (b_ms * 1e-3) / PEAK_LANE_OPS, "lane_ops_per_vector": bops, "passes": 2,
+            "iterations_on_the_matrix": binfo.iters, "implicit_ms": b_ms, "jfb_ms": kms.get("jfb") or jfb_ms,
+            "timed": "kernel launch (library-recorded events)" if kms.get("bwd") else "whole call",
+            "note": "lane-ops per vector = 2 (k (5d+9) + 2 (k+1)) + the pair moments; the iteration itself is a chain of O((k d)^2) steps"}
+    elif binfo.iters > 0:
         bops = bwd_lane_ops_per_vector(cfg.k, cfg.d, dist)
         use_kernel = bool(kms.get("bwd") and kms.get("jfb"))
         b_ms, j_ms = (kms["bwd"], kms["jfb"]) if use_kernel else (bwd_ms, jfb_ms)

@@ -13,6 +13,7 @@ constexpr int PASS_B1 = 2;   // v = dL/dC* with W fixed
 constexpr int PASS_B2 = 3;   // u = (dF/dC)^T g
 constexpr int PASS_B3 = 4;   // dW = direct + (dF/dW)^T g
 constexpr int PASS_BJ = 5;   // v and the explicit Jacobian dF/dC* in one pass, then a direct solve (k d <= 16)
+constexpr int PASS_BP = 6;   // v and the pair moments dF/dC* follows from (see pairs.hpp)
 
 constexpr int DIST_L2 = 0;
 constexpr int DIST_SQL2 = 1;
@@ -969,22 +970,28 @@ __device__ __forceinline__ void tail_bj(const Args& a, const double* tot) {
     }
 }
 
-template <int PASS, int NACC>
-__device__ __forceinline__ void grid_tail(const Args& a, unsigned int seq) {
-    constexpr int nacc = NACC;
-    if (!arrive_last(a.tickets)) return;
+// True in the threads of the workgroup that arrives last, with the NACC totals in s_tot (LDS: the tail that follows reads them
+// without a trip through memory).
+template <int NACC>
+__device__ __forceinline__ bool grid_totals(const Args& a, unsigned int seq, double* s_tot) {
+    if (!arrive_last(a.tickets)) return false;
     if (threadIdx.x <= TSHARDS) a.tickets[threadIdx.x * TSTRIDE] = 0u;  // every workgroup has arrived
     if (threadIdx.x == 0) a.ctrl->launch_seq = seq;
-    // the totals stay in LDS: the tail that follows reads them without a trip through memory
-    __shared__ double s_tot[NACC];
-    if (!reduce_stamped(a, nacc, seq, s_tot)) {
+    if (!reduce_stamped(a, NACC, seq, s_tot)) {
         if (threadIdx.x == 0) {  // ends the host's loops; the call reports a device error
             a.ctrl->abort_flag = 1;
             a.ctrl->done = 1;
             a.ctrl->b_done = 1;
         }
-        return;
+        return false;
     }
+    return true;
+}
+
+template <int PASS, int NACC>
+__device__ __forceinline__ void grid_tail(const Args& a, unsigned int seq) {
+    __shared__ double s_tot[NACC];
+    if (!grid_totals<NACC>(a, seq, s_tot)) return;
     if (PASS == PASS_FWD) tail_forward(a, s_tot);
     if (PASS == PASS_FIN) tail_final(a, s_tot);
     if (PASS == PASS_B1) tail_b1(a, s_tot);

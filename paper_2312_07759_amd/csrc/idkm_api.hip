@@ -1218,9 +1218,23 @@ idkm_status idkm_backward(idkm_ctx* ctx, const float* dWq, idkm_bwd_mode mode, f
     hipLaunchKernelGGL(k_init_backward, dim3(1), dim3(1), 0, s, a, (int)mode, (double)tol, (int)max_iter, (double)alpha,
                        ctx->gmres_basis);
     HIP_TRY(ctx, hipGetLastError());
-    st = launch_pass(ctx, g, PASS_B1, a, s);
+    const bool pairs = mode == IDKM_BWD_IMPLICIT && g.small && pair_shape(ctx->k, ctx->d, ctx->dist) &&
+                       pair_solve_pays(ctx->k, ctx->d, (int)max_iter);
+    if (pairs) {
+        // v and the operator in one pass, whose last workgroup runs the whole iteration (about four workgroups per compute unit:
+        // it adds the sums of all of them)
+        Geometry gp = g;
+        gp.vec_per_wg = (int64_t)WG * std::max<int64_t>(1, (ctx->m + (int64_t)WG * 1024 - 1) / ((int64_t)WG * 1024));
+        gp.nwg = (int)((ctx->m + gp.vec_per_wg - 1) / gp.vec_per_wg);
+        st = ensure_partials(ctx, (size_t)gp.nwg * (size_t)pair_sums(ctx->k, ctx->d, ctx->dist));
+        if (st != IDKM_OK) return st;
+        a.partials = ctx->partials;
+        st = launch_pass(ctx, gp, PASS_BP, a, s);
+    } else {
+        st = launch_pass(ctx, g, PASS_B1, a, s);
+    }
     if (st != IDKM_OK) return st;
-    if (mode == IDKM_BWD_IMPLICIT) {
+    if (mode == IDKM_BWD_IMPLICIT && !pairs) {
         // every attempt (alpha, alpha/2, ...) may use max_iter passes; at most 7 attempts
         st = run_until_done(ctx, g, PASS_B2, a, s, (int64_t)max_iter * 7, [](const Ctrl& c) { return c.b_done != 0; });
         if (st != IDKM_OK) return st;

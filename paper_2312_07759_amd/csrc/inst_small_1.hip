@@ -13,6 +13,15 @@ struct pick_bj<K, D, true> {
     static KernelFn get() { return small_pass<K, D, 1, PASS_BJ>; }
 };
 
+template <int K, int D, bool OK>
+struct pick_bp {
+    static KernelFn get() { return nullptr; }
+};
+template <int K, int D>
+struct pick_bp<K, D, true> {
+    static KernelFn get() { return small_pass<K, D, 1, PASS_BP>; }
+};
+
 template <int K, int D>
 static KernelFn pick(int pass) {
     switch (pass) {
@@ -22,6 +31,7 @@ static KernelFn pick(int pass) {
         case PASS_B2: return small_pass<K, D, 1, PASS_B2>;
         case PASS_B3: return small_pass<K, D, 1, PASS_B3>;
         case PASS_BJ: return pick_bj<K, D, (K * D <= DENSE_MAX_KD)>::get();
+        case PASS_BP: return pick_bp<K, D, pair_shape(K, D, 1)>::get();
     }
     return nullptr;
 }

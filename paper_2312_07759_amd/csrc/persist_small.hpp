@@ -1523,8 +1523,13 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
     // exchange line
     constexpr int NBJ = KD * KD + KD * D + KD;
     constexpr bool HAS_DENSE = NBJ <= XDENSE && !RAG;
+    // the averaged iteration and the Krylov solve on the explicit operator (see pairs.hpp)
+    constexpr bool HAS_PAIRS = pair_shape(K, D, DIST);
+    constexpr int NBP = HAS_PAIRS ? pair_sums(K, D, DIST) : 1;
+    constexpr int NXS = (HAS_DENSE ? NBJ : KD) > NBP ? (HAS_DENSE ? NBJ : KD) : NBP;
     extern __shared__ float s_tile[];
-    __shared__ XShared<HAS_DENSE ? NBJ : KD, RAG> xs;
+    __shared__ XShared<NXS, RAG> xs;
+    __shared__ double s_Fd[HAS_PAIRS ? KD : 1];
     __shared__ double s_v[KD], s_g[KD], s_rn[K];  // a reducer's own slice is the live one; s_rn = 1/(tau n)
     __shared__ float s_Cf[KD], s_Hs[KD], s_Hv[KD], s_Ff[KD];
     // product form of the (dF/dC)^T pass: its per-codeword operands (c_j - mu, -s^2 |c_j - mu|^2, mu, h_j . (F*_j - mu) / tau),
@@ -1560,6 +1565,7 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
     if (tid < KD) {
         s_Cf[tid] = a.Cf[src];
         s_Ff[tid] = a.Ff[src];
+        if (HAS_PAIRS) s_Fd[tid] = a.Fd[src];
         s_Hs[tid] = 0.f;
         s_Hv[tid] = 0.f;
     }
@@ -1677,7 +1683,40 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
             dense_done = true;
         }
     }
-    if (!dense_done) {
+    // (every workgroup has to receive the totals)
+    const bool pairs = HAS_PAIRS && (mode == BWD_IMPLICIT || mode == BWD_GMRES) && (tree || pa.G == 1) &&
+                       pair_solve_pays(K, D, max_iter);
+    double row[HAS_PAIRS ? KD : 1];  // lane j d + r of wavefront 0: its row of (dF/dC)^T
+    if constexpr (HAS_PAIRS) {
+        if (pairs) {
+            float accp[NBP];
+            any_tile_pass<K, D, DIST, PASS_BP, SHARED, GLOBALW, RAG>(a, pa, s_w, s_gt, base, cnt, s_Cf, s_Hs, s_Ff, accp);
+            ++seq;
+            publish_partials<NBP>(pa, seq, accp, xs);
+            if (tree) {
+                if (!tree_totals<NBP>(pa, seq, xs)) return;
+            } else {
+                __syncthreads();
+                if (tid < NBP) xs.totd[tid] = (double)xs.own[tid];
+                __syncthreads();
+            }
+            if (tid < 64) {
+                pair_row<K, D, DIST>([&](int i) { return xs.totd[i]; }, s_Cf, s_Fd, s_rn, a.escale, row);
+                double v2 = 0.0;
+                if (tid < KD) {
+                    const double v = xs.totd[tid];
+                    s_v[tid] = v;
+                    s_g[tid] = v;
+                    v2 = v * v;
+                    xs.bc[tid] = __float_as_uint((float)(v * s_rn[tid / D]));
+                }
+                v2 = first_lanes_sum_d_dpp<KD>(v2);
+                if (tid < R) xs.bc[KD + tid] = (tid == 0) ? __float_as_uint((float)v2) : 0u;
+            }
+            __syncthreads();
+        }
+    }
+    if (!dense_done && !pairs) {
     // B1: v = dL/dC* with W fixed; the solve starts at g = v
     any_tile_pass<K, D, DIST, PASS_B1, SHARED, GLOBALW, RAG>(a, pa, s_w, s_gt, base, cnt, s_Cf, s_Hs, s_Ff, acc);
     ++seq;
@@ -1722,7 +1761,7 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
     }
     }
     }
-    if (!(tree && !dense_done) && !gather_bcast<KD, WPR, KD>(pa, seq, NB, !dense_done, xs)) return;
+    if (!(tree && !dense_done) && !pairs && !gather_bcast<KD, WPR, KD>(pa, seq, NB, !dense_done, xs)) return;
     if (tid < KD) {
         set_h(__uint_as_float(xs.bc[tid]));
         s_Hv[tid] = __uint_as_float(xs.bc[tid]);
@@ -1781,6 +1820,37 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
         r_g = s_g[tid];
         r_v = s_v[tid];
         r_rn = s_rn[tid / D];
+    }
+    if constexpr (HAS_PAIRS) {
+        if (pairs && !s_done) {
+            if (tid < 64) {
+                if (mode == BWD_GMRES) {
+                    const double vn = fast_sqrt_d(vnorm2);
+                    wave_lds_sync();
+                    double hn = tid < KD ? gm.Q[tid] : 0.0;
+                    for (int over = 0; !over;) {
+                        const double u = pair_apply<KD>(row, hn);
+                        over = gmres_step<KD>(gm, [&](int) { return u; }, s_v, s_g, tol, vn, max_iter, s_iters, s_conv, s_bad, s_res, hn);
+                        over = __builtin_amdgcn_readfirstlane(over);
+                    }
+                    r_g = hn;
+                } else {
+                    const AveragedResult o = averaged_iteration<KD, true>(row, r_v, pa.alpha, tol * tol * vnorm2, max_iter, r_g);
+                    if (tid < KD) s_g[tid] = r_g;
+                    if (tid == 0) {
+                        s_iters = o.iters;
+                        s_res = o.step2;
+                        s_alpha = o.alpha;
+                        s_halv = o.halvings;
+                        s_conv = o.converged;
+                        s_bad = o.bad;
+                    }
+                }
+                if (tid < KD) set_h((float)(r_g * r_rn));
+                if (tid == 0) s_done = 1;
+            }
+            __syncthreads();
+        }
     }
     while (!s_done) {
         IDKM_STAMP(0);
@@ -1989,7 +2059,7 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
 
     // B3: dW = direct + (dF/dW)^T g
     any_tile_pass<K, D, DIST, PASS_B3, SHARED, GLOBALW, RAG>(a, pa, s_w, s_gt, base, cnt, s_Cf, s_Hs, s_Ff, reinterpret_cast<float(&)[1]>(acc[0]));
-    if (dense_done || tree) {
+    if (dense_done || tree || pairs) {
         if (wg == 0 && tid < kd) {
             a.gd[tid] = s_g[tid];
             a.vd[tid] = s_v[tid];

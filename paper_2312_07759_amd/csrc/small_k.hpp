@@ -3,6 +3,7 @@
 // of the M-step live in the lane's registers.
 #pragma once
 #include "common.hpp"
+#include "pairs.hpp"
 
 namespace idkm {
 
@@ -142,14 +143,15 @@ __device__ __forceinline__ float delta_small(const float (&df)[K][D], const floa
 template <int K, int D, int DIST, int PASS, bool RAG = false>
 struct SmallItem {
     static constexpr bool STATS = (PASS == PASS_FWD || PASS == PASS_FIN);
-    static constexpr bool BACK = (PASS == PASS_B1 || PASS == PASS_B2 || PASS == PASS_B3 || PASS == PASS_BJ);
-    static constexpr bool USE_G = (PASS == PASS_B1 || PASS == PASS_B3 || PASS == PASS_BJ);
+    static constexpr bool BACK = (PASS == PASS_B1 || PASS == PASS_B2 || PASS == PASS_B3 || PASS == PASS_BJ || PASS == PASS_BP);
+    static constexpr bool USE_G = (PASS == PASS_B1 || PASS == PASS_B3 || PASS == PASS_BJ || PASS == PASS_BP);
     static constexpr bool USE_H = (PASS == PASS_B2 || PASS == PASS_B3);
     static constexpr bool USE_F = USE_H || PASS == PASS_BJ;  // needs F* = F(C*, W)
     static constexpr int ACCW = STATS ? (D + 1) : D;
     static constexpr int KD = K * D;
     // dense backward: T[KD][KD], U[KD][D], V[KD]
-    static constexpr int NACC = (PASS == PASS_B3) ? 1 : (PASS == PASS_BJ ? KD * KD + KD * D + KD : K * ACCW);
+    static constexpr int NACC = (PASS == PASS_B3) ? 1 : PASS == PASS_BJ ? KD * KD + KD * D + KD
+                                                   : PASS == PASS_BP ? pair_sums(K, D, DIST) : K * ACCW;
 
     // (dF/dC)^T pass, squared energy, d >= 2 (the pass an implicit solve repeats): in coordinates relative to the mean
     // codeword mu, wm = w - mu and cm_j = c_j - mu, the exponents of the row are products as in the forward loop
@@ -544,15 +546,91 @@ struct SmallItem {
                         out[r] = fmaf(-th, dl, out[r]);
                     } else {
                         float t = acc[VOFF + j * ACCW + r];
-                        if (PASS == PASS_B1 || PASS == PASS_BJ) t = fmaf(at[j], g[r], t);
+                        if (PASS == PASS_B1 || PASS == PASS_BJ || PASS == PASS_BP) t = fmaf(at[j], g[r], t);
                         acc[VOFF + j * ACCW + r] = fmaf(th, dl, t);
                     }
                 }
+            }
+            if constexpr (PASS == PASS_BP) {
+                constexpr int NM = pair_moments(D, DIST);
+                int b = KD;
+#pragma unroll
+                for (int j = 0; j < K; ++j)
+#pragma unroll
+                    for (int l = j + 1; l < K; ++l, b += NM) {
+                        const float pi = at[j] * at[l];
+                        float u[D];  // twice w - (c_j + c_l)/2 (scalar weights: in scaled coordinates)
+#pragma unroll
+                        for (int r = 0; r < D; ++r) u[r] = df[j][r] + df[l][r];
+                        if constexpr (DIST == DIST_SQL2) {
+                            acc[b] += pi;
+                            int q = b + 1 + D;
+#pragma unroll
+                            for (int r = 0; r < D; ++r) {
+                                const float pu = pi * u[r];
+                                acc[b + 1 + r] += pu;
+#pragma unroll
+                                for (int s2 = r; s2 < D; ++s2, ++q) acc[q] = fmaf(pu, u[s2], acc[q]);
+                            }
+                        } else {
+#pragma unroll
+                            for (int side = 0; side < 2; ++side)
+#pragma unroll
+                                for (int r = 0; r < D; ++r) {
+                                    const float pd = pi * delta_small<K, D, DIST>(df, ri, side ? l : j, r);
+                                    const int q = b + side * (D + D * D);
+                                    acc[q + r] += pd;
+#pragma unroll
+                                    for (int s2 = 0; s2 < D; ++s2) acc[q + D + r * D + s2] = fmaf(pd, u[s2], acc[q + D + r * D + s2]);
+                                }
+                        }
+                    }
             }
             if (PASS == PASS_B3) VecLoad<D>::store(a.dW_out, i, out);
         }
     }
 };
+
+// Tail of PASS_BP on the stream path: the whole averaged iteration, in wavefront 0 of the last workgroup.
+template <int K, int D, int DIST>
+__device__ __forceinline__ void grid_tail_pairs(const Args& a, unsigned int seq) {
+    constexpr int KD = K * D, NACC = pair_sums(K, D, DIST);
+    __shared__ double s_tot[NACC], s_F[KD], s_rn[K];
+    __shared__ float s_c[KD];
+    if (!grid_totals<NACC>(a, seq, s_tot)) return;
+    const int tid = threadIdx.x;
+    if (tid < KD) {
+        s_F[tid] = a.Fd[tid];
+        s_c[tid] = a.Cf[tid];
+    }
+    if (tid < K) s_rn[tid] = (a.nd[tid] > 0.0) ? (double)a.inv_tau / a.nd[tid] : 0.0;
+    __syncthreads();
+    if (tid >= 64) return;
+    Ctrl* c = a.ctrl;
+    double row[KD], g = 0.0;
+    pair_row<K, D, DIST>([&](int i) { return s_tot[i]; }, s_c, s_F, s_rn, a.escale, row);
+    const double v = tid < KD ? s_tot[tid] : 0.0;
+    const double v2 = lane_value_d(first_lanes_sum_d_dpp<KD>(v * v), 0);
+    const bool finite = v2 <= 1.7e308;
+    AveragedResult o = {0, 0, 0, 0, c->b_alpha, 0.0};
+    if (finite)
+        o = averaged_iteration<KD, false>(row, v, c->b_alpha, c->b_tol * c->b_tol * v2, c->b_max_iter, g);
+    if (tid < KD) {
+        a.vd[tid] = v;
+        a.gd[tid] = g;
+        store_h(a, tid, g);
+    }
+    if (tid == 0) {
+        c->b_vnorm = sqrt(v2);
+        c->b_iters = o.iters;
+        c->b_converged = o.converged;
+        c->b_halvings = o.halvings;
+        c->b_alpha = o.alpha;
+        c->b_residual = sqrt(o.step2);
+        c->b_done = 1;
+        if (!finite || o.bad) c->nonfinite = 1;
+    }
+}
 
 template <int K, int D, int DIST, int PASS>
 __global__ __launch_bounds__(WG) void small_pass(const Args a) {
@@ -620,7 +698,10 @@ __global__ __launch_bounds__(WG) void small_pass(const Args a) {
         // row = accumulator, column = workgroup: the reducing workgroup reads 64 consecutive words per load
         st_word(reinterpret_cast<unsigned long long*>(a.partials) + (size_t)q * gridDim.x + blockIdx.x, pack_f(seq, (float)s));
     }
-    grid_tail<PASS, NACC>(a, seq);
+    if constexpr (PASS == PASS_BP)
+        grid_tail_pairs<K, D, DIST>(a, seq);
+    else
+        grid_tail<PASS, NACC>(a, seq);
 }
 
 }  // namespace idkm

@@ -1,0 +1,110 @@
+"""Implicit backward of small codebooks: (dF/dC)^T is formed once, as a k d x k d matrix from the moments of pairs of codewords,
+and the averaged iteration and the Krylov solve run on it.  Held to the float64 oracle and to the pass that applies the
+operator to one vector (idkm_step_JCT)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import idkm_oracle as orc
+from paper_2312_07759_amd import binding
+from paper_2312_07759_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+# One float32 pass against the oracle: an attention weight carries about 3e-6 where it matters (126 ln 2 x 3 ulps at most
+# 2e-5), a moment two weights and one factor (w - mid), sums of m random errors less; three steps of the iteration apply
+# the matrix three times.  4e-5 relative to the largest component that enters.
+TOL_OP = 4e-5
+
+
+def rel(x, ref):
+    x, ref = np.asarray(x, dtype=np.float64), np.asarray(ref, dtype=np.float64)
+    den = np.linalg.norm(ref)
+    return float(np.linalg.norm(x - ref) / (den if den > 0 else 1.0))
+
+
+def dev(x):
+    return torch.as_tensor(np.ascontiguousarray(x), dtype=torch.float32).cuda()
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = binding.Context(0)
+    yield c
+    c.close()
+
+
+# every padded codebook size of the three lane counts; one workgroup, the smallest team of eight, a full device; more vectors
+# than a workgroup's tile divides into
+SHAPES = [(2, 1, 37), (2, 1, 4_097), (2, 2, 70_001), (2, 4, 1_023), (3, 1, 4_099), (3, 2, 9_001), (3, 4, 37), (4, 1, 4_096),
+          (4, 1, 300_007), (4, 2, 8_191), (4, 4, 20_011), (5, 1, 300_001), (6, 1, 2_050), (7, 1, 15), (8, 1, 1_800), (8, 1, 70_003)]
+
+
+@pytest.mark.parametrize("dist", [wl.DIST_L2, wl.DIST_SQL2])
+@pytest.mark.parametrize("k,d,m", SHAPES)
+def test_three_steps_and_the_krylov_solve(ctx, k, d, m, dist):
+    W, C0, G = wl.random_problem(m, d, k, seed=7 * k + d + m, std=0.7, spread=0.7)
+    C0 = C0 + 0.01 * np.random.default_rng(m).standard_normal(C0.shape)
+    W, C0, G = W.astype(np.float32), C0.astype(np.float32), G.astype(np.float32)
+    tau = 0.15 if dist == wl.DIST_SQL2 else 0.3
+    for path in (binding.PATH_AUTO, binding.PATH_STREAM):
+        ctx.set_path(path)
+        try:
+            f = ctx.forward(dev(W), dev(C0), tau, 0.0, 4, dist)
+            C = f["C"].cpu().numpy()
+            for alpha in (1.0, 0.25):
+                b = ctx.backward(dev(G), binding.BWD_IMPLICIT, tol=0.0, max_iter=3, alpha=alpha)
+                assert b["info"].iters == 3 and not b["info"].converged and b["info"].alpha == alpha
+                v, g = ctx.get_cotangents(k, d)
+                ref = orc.backward(W, C, tau, dist, G, "implicit", tol=0.0, max_iter=3, alpha=alpha)
+                assert np.max(np.abs(v - ref["v"])) < TOL_OP * np.max(np.abs(ref["v"]))
+                scale = max(np.max(np.abs(ref["g"])), np.max(np.abs(v)))
+                assert np.max(np.abs(g - ref["g"])) < TOL_OP * scale, np.max(np.abs(g - ref["g"])) / scale
+                assert rel(b["dW"].cpu().numpy(), ref["dW"]) < 1e-4
+            bj = ctx.backward(dev(G), binding.BWD_GMRES, tol=1e-6, max_iter=100)
+            v, g = ctx.get_cotangents(k, d)
+            r = v + orc.vjp_F(C, W, tau, dist, g)[0] - g
+            assert np.linalg.norm(r) < 1e-4 * max(np.linalg.norm(v), np.linalg.norm(g)), bj["info"]
+            # the pass that applies the operator to one vector
+            u = ctx.step_JCT(dev(g)).cpu().numpy()
+            ru = orc.vjp_F(C, W, tau, dist, g)[0]
+            # (its terms are of the size of g; where they nearly cancel, as with five rows, the sum itself is no measure)
+            assert np.max(np.abs(u - ru)) < TOL_OP * max(np.max(np.abs(ru)), np.max(np.abs(g)))
+        finally:
+            ctx.set_path(binding.PATH_AUTO)
+
+
+@pytest.mark.parametrize("k,d", [(3, 1), (4, 1), (4, 2), (8, 1)])
+def test_hard_rows_empty_clusters_and_distant_layers(ctx, k, d):
+    """Nearly hard rows (pair weights of 1e-10 beside exact zeros), a codeword without mass and data at 100 spreads from the
+    origin: nothing cancels against the diagonal, what belongs to the empty cluster stays zero."""
+    m = 9_001
+    W, C0, G = wl.random_problem(m, d, k, seed=3 * k + d, std=0.5, spread=1.5)
+    C0[k - 1] = 5.0e3
+    W, C0, G = (W + 100.0).astype(np.float32), (C0 + 100.0).astype(np.float32), G.astype(np.float32)
+    for tau in (0.3, 0.02):
+        f = ctx.forward(dev(W), dev(C0), tau, 0.0, 3, wl.DIST_SQL2)
+        assert f["info"].empty_clusters == 1
+        C = f["C"].cpu().numpy()
+        b = ctx.backward(dev(G), binding.BWD_IMPLICIT, tol=0.0, max_iter=3)
+        ref = orc.backward(W, C, tau, wl.DIST_SQL2, G, "implicit", tol=0.0, max_iter=3)
+        v, g = ctx.get_cotangents(k, d)
+        assert np.all(g[k - 1] == 0.0) and np.all(np.isfinite(g))
+        assert rel(g, ref["g"]) < 1e-3 and rel(b["dW"].cpu().numpy(), ref["dW"]) < 1e-3
+
+
+@pytest.mark.parametrize("k,seed", [(4, 1), (8, 0)])
+def test_divergence_restarts_with_half_the_step(ctx, k, seed):
+    """An eigenvalue of dF/dC above 3 (a codebook far from its fixed point, plain norm): no damping converges; the steps of every
+    attempt, the six halvings and what the last one ends with are the oracle's."""
+    m, tau = 3_000, 0.05
+    W, C0, G = wl.random_problem(m, 1, k, seed=seed, std=0.3, spread=2.0)
+    C0 = C0 * np.random.default_rng(seed).uniform(0.2, 3.0)
+    W, C0, G = W.astype(np.float32), C0.astype(np.float32), G.astype(np.float32)
+    f = ctx.forward(dev(W), dev(C0), tau, 1e30, 1, wl.DIST_L2)
+    C = f["C"].cpu().numpy()
+    assert np.max(np.linalg.eigvals(orc.jacobian_C(C, W, tau, wl.DIST_L2)).real) > 3.0
+    b = ctx.backward(dev(G), binding.BWD_IMPLICIT, tol=1e-6, max_iter=400)
+    ref = orc.backward(W, C, tau, wl.DIST_L2, G, "implicit", tol=1e-6, max_iter=400)
+    assert not b["info"].converged and b["info"].alpha == ref["alpha"] == 1.0 / 64 and b["info"].iters == ref["iters"]
+    assert rel(ctx.get_cotangents(k, 1)[1], ref["g"]) < 1e-3 and rel(b["dW"].cpu().numpy(), ref["dW"]) < 1e-3
