@@ -366,6 +366,15 @@ struct PassPriority {
     __device__ __forceinline__ ~PassPriority() { __builtin_amdgcn_s_setprio(0); }
 };
 
+// Between LDS accesses of ONE wavefront where a lane reads what another lane wrote: the hardware runs a wavefront's
+// LDS instructions in order, but the compiler reasons per thread (it may forward a thread's own earlier load past
+// another lane's store, or move accesses); this keeps its memory operations in program order.  No instruction issued
+// beyond a wait for the outstanding LDS operations.
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // ---------------------------------------------------------------- stamped words
 
 // Values that cross workgroups travel as 64-bit words {sequence number, 32-bit payload} written and read with

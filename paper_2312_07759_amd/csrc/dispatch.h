@@ -32,7 +32,8 @@ struct PersistFns {
     int threads = 0;
 };
 // Persistent forward / backward solve for the lane<->vector family; empty if K (D+1) > 32.
-PersistFns persist_kernel(int K, int D, int dist, bool bwd);
+PersistFns persist_kernel_0(int K, int D, bool bwd);
+PersistFns persist_kernel_1(int K, int D, bool bwd);
 // The same for a codebook of K/2 < k < K codewords in the kernels for K codewords (K in {4,8,16}); teams of one, or
 // with the two-level exchange, only.
 PersistFns persist_kernel_ragged_0(int K, int D, bool bwd);

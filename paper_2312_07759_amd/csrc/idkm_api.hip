@@ -431,7 +431,7 @@ bool plan_small(idkm_ctx* ctx, bool bwd, PersistPlan* pp, const void* dwq, int m
     const bool ragged = k >= 3 && k < 16 && !pow2(k);
     const int K = pow2_at_least(k);
     if (k < 2 || k > 16 || d > 4 || K * (d + 1) > XLINE || (ragged && !ctx->tree_exchange)) return false;
-    const PersistFns fs = !ragged ? persist_kernel(k, d, ctx->dist, bwd)
+    const PersistFns fs = !ragged ? (ctx->dist == DIST_L2 ? persist_kernel_0(k, d, bwd) : persist_kernel_1(k, d, bwd))
                           : ctx->dist == DIST_L2 ? persist_kernel_ragged_0(K, d, bwd)
                                                  : persist_kernel_ragged_1(K, d, bwd);
     pp->fn = fs.one;

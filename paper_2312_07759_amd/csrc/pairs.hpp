@@ -95,77 +95,155 @@ __device__ __forceinline__ double pair_apply(const double (&row)[N], double g) {
 // until ||g+ - g||^2 <= stop2, at most max_iter steps an attempt; a non-finite step or five growing ones in a row start over
 // with half the step, at most six times -- the steps, counters and stop rule of the passes it replaces.  v, g: lane c < N owns
 // component c (v is zero in the others).  F32: the squared step norm is rounded to float32, like the word that carries it
-// between workgroups elsewhere.
+// between workgroups elsewhere.  s_A: N x N doubles of LDS of this wavefront.
 struct AveragedResult {
     int iters, converged, bad, halvings;
     double alpha, step2;
 };
+
+// Up to four unknowns: 64 steps at a time.  A step is delta_n = A^n delta_0 with A = alpha (dF/dC)^T + (1 - alpha) I, so lane j
+// forms delta_{n+j} from delta_n by the powers A, A^2, A^4, ... its index asks for; the stop rule is evaluated for all of them at
+// once, and g moves by the sum of the steps up to the one that ends the attempt.  One step after the other is a chain of
+// about 350 cycles, 9.6 us for 64 of them; this way 64 take 2 us (2.4 M weights, k = 4, 104 steps: launch 47 -> 28 us).
 template <int N, bool F32>
-__device__ __forceinline__ AveragedResult averaged_iteration(const double (&row)[N], double v, double alpha, double stop2, int max_iter,
-                                                             double& g) {
+__device__ __forceinline__ AveragedResult averaged_iteration_wide(const double (&row)[N], double v, double alpha, double stop2,
+                                                                  int max_iter, double* s_A, double& g) {
+    static_assert(N <= 4, "every lane keeps a power of A");
     AveragedResult o = {0, 0, 0, 0, alpha, 0.0};
     const int lane = threadIdx.x & 63;
-    // up to four unknowns every lane keeps all of them: no value crosses lanes in the chain of a step (104 steps at k = 4)
-    constexpr bool ALL = N <= 4;
-    constexpr int NV = ALL ? N : 1, NR = ALL ? N : 1;
-    double M[NR][N], b[NV], x[NV], v0[NV], J[NR][N];
-    if constexpr (ALL) {
+    double x[N];
+    for (bool again = true; again;) {
+        again = false;
+        double dl[N];  // delta_n, the same in every lane
+        const double d0 = o.alpha * pair_apply<N>(row, v);
 #pragma unroll
         for (int i = 0; i < N; ++i) {
-            v0[i] = lane_value_d(v, i);
-#pragma unroll
-            for (int c = 0; c < N; ++c) J[i][c] = lane_value_d(row[c], i);
+            x[i] = lane_value_d(v, i);
+            dl[i] = lane_value_d(d0, i);
         }
-    } else {
-        v0[0] = v;
+        if (lane < N) {
 #pragma unroll
-        for (int c = 0; c < N; ++c) J[0][c] = row[c];
+            for (int c = 0; c < N; ++c) s_A[lane * N + c] = o.alpha * row[c] + (lane == c ? 1.0 - o.alpha : 0.0);
+        }
+        double prev = __builtin_inf();
+        int grow = 0, left = max_iter;
+        for (;;) {
+            double P[N][N], d[N];
+            wave_lds_sync();  // (and A is read again, not held in registers across the loop)
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                d[i] = dl[i];
+#pragma unroll
+                for (int c = 0; c < N; ++c) P[i][c] = s_A[i * N + c];
+            }
+#pragma nounroll
+            for (int bit = 0; bit < 6; ++bit) {
+                const bool on = (lane >> bit) & 1;
+                double t[N], Q[N][N];
+#pragma unroll
+                for (int i = 0; i < N; ++i) {
+                    t[i] = P[i][0] * d[0];
+#pragma unroll
+                    for (int c = 1; c < N; ++c) t[i] = fma(P[i][c], d[c], t[i]);
+#pragma unroll
+                    for (int c = 0; c < N; ++c) {
+                        Q[i][c] = P[i][0] * P[0][c];
+#pragma unroll
+                        for (int e = 1; e < N; ++e) Q[i][c] = fma(P[i][e], P[e][c], Q[i][c]);
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < N; ++i) {
+                    d[i] = on ? t[i] : d[i];
+#pragma unroll
+                    for (int c = 0; c < N; ++c) P[i][c] = Q[i][c];
+                }
+            }
+            double d2 = 0.0;
+#pragma unroll
+            for (int i = 0; i < N; ++i) d2 = fma(d[i], d[i], d2);
+            if (F32) d2 = (double)(float)d2;
+            const double before = __shfl_up(d2, 1, 64);
+            const bool finite = d2 <= 1.7e308, conv = finite && d2 <= stop2;
+            const bool up = finite && !conv && d2 > (lane == 0 ? prev : before);
+            const unsigned long long mc = __builtin_amdgcn_ballot_w64(conv), mu = __builtin_amdgcn_ballot_w64(up);
+            unsigned long long run = mu;  // steps that end five growing ones in a row; `grow` of them lie before lane 0
+#pragma unroll
+            for (int s = 1; s < 5; ++s) {
+                const int old = grow < s ? grow : s;
+                run &= (mu << s) | (((1ull << old) - 1ull) << (s - old));
+            }
+            const unsigned long long md = run | __builtin_amdgcn_ballot_w64(!finite);
+            const unsigned long long ml = left <= 64 ? 1ull << (left - 1) : 0ull;
+            const unsigned long long any = mc | md | ml;
+            const int e = any ? (int)__builtin_ctzll(any) : 63;  // the last step taken
+            o.iters += e + 1;
+            o.step2 = lane_value_d(d2, e);
+            const bool diverged = (md >> e) & 1ull & (any != 0);
+            if (diverged && o.halvings < 6) {
+                o.alpha *= 0.5;
+                o.halvings += 1;
+                again = true;
+                break;
+            }
+#pragma unroll
+            for (int i = 0; i < N; ++i) x[i] += wave_sum_d_dpp(lane <= e ? d[i] : 0.0);
+            if (any) {
+                o.converged = (mc >> e) & 1ull ? 1 : 0;
+                if (diverged && !(o.step2 <= 1.7e308)) o.bad = 1;  // every damping factor tried ended in a non-finite step
+                break;
+            }
+            left -= 64;
+            prev = o.step2;
+            grow = (int)__builtin_clzll(~mu);
+            wave_lds_sync();
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                double t = 0.0;
+#pragma unroll
+                for (int c = 0; c < N; ++c) t = fma(s_A[i * N + c], lane_value_d(d[c], 63), t);
+                dl[i] = t;
+            }
+        }
     }
+    g = x[0];
+#pragma unroll
+    for (int i = 1; i < N; ++i) g = (lane == i) ? x[i] : g;
+    return o;
+}
+
+template <int N, bool F32>
+__device__ __forceinline__ AveragedResult averaged_iteration(const double (&row)[N], double v, double alpha, double stop2, int max_iter,
+                                                             double* s_A, double& g) {
+    if constexpr (N <= 4) return averaged_iteration_wide<N, F32>(row, v, alpha, stop2, max_iter, s_A, g);
+    AveragedResult o = {0, 0, 0, 0, alpha, 0.0};
+    const int lane = threadIdx.x & 63;
+    double M[N], b = 0.0, x = v, prev = __builtin_inf();
     int attempt = 0, grow = 0;
-    double prev = __builtin_inf();
     bool start = true;
     for (;;) {
         if (start) {
             start = false;
+            x = v;
+            b = o.alpha * v;
 #pragma unroll
-            for (int i = 0; i < NV; ++i) {
-                x[i] = v0[i];
-                b[i] = o.alpha * v0[i];
-#pragma unroll
-                for (int c = 0; c < N; ++c) M[i][c] = o.alpha * J[i][c] + ((ALL ? i : lane) == c ? 1.0 - o.alpha : 0.0);
-            }
+            for (int c = 0; c < N; ++c) M[c] = o.alpha * row[c] + (lane == c ? 1.0 - o.alpha : 0.0);
         }
-        double xn[NV], d2 = 0.0;
-        if constexpr (ALL) {
-#pragma unroll
-            for (int i = 0; i < N; ++i) {
-                xn[i] = b[i];
-#pragma unroll
-                for (int c = 0; c < N; ++c) xn[i] = fma(M[i][c], x[c], xn[i]);
-            }
-#pragma unroll
-            for (int i = 0; i < N; ++i) {
-                const double df = xn[i] - x[i];
-                d2 = fma(df, df, d2);
-            }
-        } else {
-            xn[0] = b[0] + pair_apply<N>(M[0], x[0]);
-            const double df = lane < N ? xn[0] - x[0] : 0.0;
-            d2 = first_lanes_sum_d_dpp<N>(df * df);
-            d2 = lane_value_d(d2, 0);
-        }
+        const double xn = b + pair_apply<N>(M, x);
+        const double df = lane < N ? xn - x : 0.0;
+        double d2 = lane_value_d(first_lanes_sum_d_dpp<N>(df * df), 0);
         if (F32) d2 = (double)(float)d2;
         o.iters += 1;
         attempt += 1;
         o.step2 = d2;
-        bool diverged = !(d2 <= 1.7e308);
-        if (!diverged) {
-            if (d2 <= stop2) {
-                o.converged = 1;
-#pragma unroll
-                for (int i = 0; i < NV; ++i) x[i] = xn[i];
-                break;
-            }
+        const bool finite = d2 <= 1.7e308;
+        bool diverged = !finite;
+        if (finite && d2 <= stop2) {
+            o.converged = 1;
+            x = xn;
+            break;
+        }
+        if (finite) {
             grow = (d2 > prev) ? grow + 1 : 0;
             prev = d2;
             diverged = grow >= 5;
@@ -179,21 +257,14 @@ __device__ __forceinline__ AveragedResult averaged_iteration(const double (&row)
             start = true;
             continue;
         }
-#pragma unroll
-        for (int i = 0; i < NV; ++i) x[i] = xn[i];
+        x = xn;
         if (diverged) {
-            if (!(d2 <= 1.7e308)) o.bad = 1;  // every damping factor tried ended in a non-finite step
+            if (!finite) o.bad = 1;  // every damping factor tried ended in a non-finite step
             break;
         }
         if (attempt >= max_iter) break;
     }
-    if constexpr (ALL) {
-        g = x[0];
-#pragma unroll
-        for (int i = 1; i < N; ++i) g = (lane == i) ? x[i] : g;
-    } else {
-        g = x[0];
-    }
+    g = x;
     return o;
 }
 

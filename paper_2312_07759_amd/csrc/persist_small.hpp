@@ -153,15 +153,6 @@ struct XShared {
     double totd[NACC];               // grid totals
 };
 
-// Between LDS accesses of ONE wavefront where a lane reads what another lane wrote: the hardware runs a wavefront's
-// LDS instructions in order, but the compiler reasons per thread (it may forward a thread's own earlier load past
-// another lane's store, or move accesses); this keeps its memory operations in program order.  No instruction issued
-// beyond a wait for the outstanding LDS operations.
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 // Index of the accelerator die this wavefront runs on.
 __device__ __forceinline__ unsigned int die_id() {
     unsigned int v;
@@ -1529,7 +1520,7 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
     constexpr int NXS = (HAS_DENSE ? NBJ : KD) > NBP ? (HAS_DENSE ? NBJ : KD) : NBP;
     extern __shared__ float s_tile[];
     __shared__ XShared<NXS, RAG> xs;
-    __shared__ double s_Fd[HAS_PAIRS ? KD : 1];
+    __shared__ double s_Fd[HAS_PAIRS ? KD : 1], s_A[HAS_PAIRS && KD <= 4 ? KD * KD : 1];
     __shared__ double s_v[KD], s_g[KD], s_rn[K];  // a reducer's own slice is the live one; s_rn = 1/(tau n)
     __shared__ float s_Cf[KD], s_Hs[KD], s_Hv[KD], s_Ff[KD];
     // product form of the (dF/dC)^T pass: its per-codeword operands (c_j - mu, -s^2 |c_j - mu|^2, mu, h_j . (F*_j - mu) / tau),
@@ -1835,7 +1826,7 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
                     }
                     r_g = hn;
                 } else {
-                    const AveragedResult o = averaged_iteration<KD, true>(row, r_v, pa.alpha, tol * tol * vnorm2, max_iter, r_g);
+                    const AveragedResult o = averaged_iteration<KD, true>(row, r_v, pa.alpha, tol * tol * vnorm2, max_iter, s_A, r_g);
                     if (tid < KD) s_g[tid] = r_g;
                     if (tid == 0) {
                         s_iters = o.iters;

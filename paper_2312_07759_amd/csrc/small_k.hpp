@@ -595,7 +595,7 @@ struct SmallItem {
 template <int K, int D, int DIST>
 __device__ __forceinline__ void grid_tail_pairs(const Args& a, unsigned int seq) {
     constexpr int KD = K * D, NACC = pair_sums(K, D, DIST);
-    __shared__ double s_tot[NACC], s_F[KD], s_rn[K];
+    __shared__ double s_tot[NACC], s_F[KD], s_rn[K], s_A[KD <= 4 ? KD * KD : 1];
     __shared__ float s_c[KD];
     if (!grid_totals<NACC>(a, seq, s_tot)) return;
     const int tid = threadIdx.x;
@@ -614,7 +614,7 @@ __device__ __forceinline__ void grid_tail_pairs(const Args& a, unsigned int seq)
     const bool finite = v2 <= 1.7e308;
     AveragedResult o = {0, 0, 0, 0, c->b_alpha, 0.0};
     if (finite)
-        o = averaged_iteration<KD, false>(row, v, c->b_alpha, c->b_tol * c->b_tol * v2, c->b_max_iter, g);
+        o = averaged_iteration<KD, false>(row, v, c->b_alpha, c->b_tol * c->b_tol * v2, c->b_max_iter, s_A, g);
     if (tid < KD) {
         a.vd[tid] = v;
         a.gd[tid] = g;

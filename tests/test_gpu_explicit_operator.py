@@ -93,6 +93,27 @@ def test_hard_rows_empty_clusters_and_distant_layers(ctx, k, d):
         assert rel(g, ref["g"]) < 1e-3 and rel(b["dW"].cpu().numpy(), ref["dW"]) < 1e-3
 
 
+@pytest.mark.parametrize("k,d", [(2, 1), (2, 2), (4, 1), (8, 1)])
+def test_step_counts_around_the_blocks_of_64(ctx, k, d):
+    """Up to four unknowns 64 steps are taken at once: the iterate and the count at the ends of the blocks, with a damping that
+    keeps the steps from vanishing, and the step at which a tolerance is met."""
+    W, C0, G = wl.random_problem(5_003, d, k, seed=k + d, std=0.7, spread=0.7)
+    W, C0, G = W.astype(np.float32), C0.astype(np.float32), G.astype(np.float32)
+    f = ctx.forward(dev(W), dev(C0), 0.1, 0.0, 60, wl.DIST_SQL2)
+    C = f["C"].cpu().numpy()
+    for n in (1, 63, 64, 65, 127, 128, 129, 300):
+        b = ctx.backward(dev(G), binding.BWD_IMPLICIT, tol=0.0, max_iter=n, alpha=0.02)
+        ref = orc.backward(W, C, 0.1, wl.DIST_SQL2, G, "implicit", tol=0.0, max_iter=n, alpha=0.02)
+        assert b["info"].iters == n and b["info"].alpha == np.float32(0.02)
+        assert rel(ctx.get_cotangents(k, d)[1], ref["g"]) < 1e-4
+        assert abs(b["info"].residual - ref["residual"]) < 1e-3 * ref["residual"]
+    for tol in (1e-2, 1e-3, 1e-4):
+        b = ctx.backward(dev(G), binding.BWD_IMPLICIT, tol=tol, max_iter=5_000, alpha=0.02)
+        ref = orc.backward(W, C, 0.1, wl.DIST_SQL2, G, "implicit", tol=tol, max_iter=5_000, alpha=0.02)
+        assert b["info"].converged and ref["converged"] and abs(b["info"].iters - ref["iters"]) <= 1
+        assert rel(ctx.get_cotangents(k, d)[1], ref["g"]) < 1e-4
+
+
 @pytest.mark.parametrize("k,seed", [(4, 1), (8, 0)])
 def test_divergence_restarts_with_half_the_step(ctx, k, seed):
     """An eigenvalue of dF/dC above 3 (a codebook far from its fixed point, plain norm): no damping converges; the steps of every
