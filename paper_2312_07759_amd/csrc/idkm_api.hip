@@ -437,7 +437,7 @@ bool plan_small(idkm_ctx* ctx, bool bwd, PersistPlan* pp, const void* dwq, int m
     pp->fn = fs.one;
     pp->fn_batch = fs.batch;
     if (!pp->fn) return false;
-    pp->threads = PT;
+    pp->threads = ctx->sink ? PT : bwd ? bwd_threads(K, d) : fwd_threads(K, d);
     pp->lane = false;
     const int64_t chunk = (int64_t)ctx->min_vec_per_thread * PT;
     int64_t g = (m + chunk - 1) / chunk;  // a few vectors per thread before adding workgroups
@@ -481,12 +481,16 @@ bool plan_small(idkm_ctx* ctx, bool bwd, PersistPlan* pp, const void* dwq, int m
         const PersistFns fg = persist_kernel_global(k, d, ctx->dist, bwd);
         const bool aligned = (reinterpret_cast<uintptr_t>(ctx->W) & 15u) == 0 &&
                              (!bwd || (dwq && (reinterpret_cast<uintptr_t>(dwq) & 15u) == 0));
-        // Measured on a 16.8 M-weight layer this form is within 5 % of the stream path (forward 28.3 against 29.9 us
-        // per evaluation, (dF/dC)^T pass 41.3 against 39.7): both are bound by the same arithmetic, so the default
-        // keeps the stream path and this one serves callers that ask for the persistent path (one launch per solve).
-        if (!fg.one || ctx->sink || !aligned || ctx->path != IDKM_PATH_PERSISTENT) return false;
+        // Forward solves take it under IDKM_PATH_AUTO too: an evaluation costs one exchange instead of a launch and a last
+        // workgroup that adds a thousand workgroups' sums (stream path against this, us per evaluation: 16.8 M scalar weights k = 2
+        // 19.7 / 12.8, k = 4 25.6 / 16.8, plain norm 26.9 / 22.6, k = 16 76.9 / 59.8; 60 M k = 4 68.1 / 48.7; 4 M 4-vectors k = 4 23.8 /
+        // 15.6, k = 16 59.8 / 37.7).  Backwards, two passes over the layer whatever the codebook, are within 5 % of each other
+        // up to k = 4 and up to 20 % slower here beyond (k = 8 and 16, 133 / 148 and 223 / 253 for a Jacobian-free call): the
+        // stream path unless the caller asks for this one.
+        if (!fg.one || ctx->sink || !aligned || (bwd && ctx->path != IDKM_PATH_PERSISTENT)) return false;
         pp->fn = fg.one;
         pp->fn_batch = nullptr;
+        pp->threads = global_threads(k, d, bwd);
         pp->lds = 0;
     }
     return true;

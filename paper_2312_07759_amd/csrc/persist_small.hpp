@@ -37,7 +37,16 @@
 
 namespace idkm {
 
-constexpr int PT = 256;      // threads per workgroup of the persistent kernels; also the largest grid
+constexpr int PT = 256;      // threads per workgroup of the persistent kernels (batched launches and layers read from memory); also the
+                             // largest grid
+// Threads of a workgroup that has its compute unit to itself: two wavefronts per SIMD.  One wavefront issues a multiply, an
+// addition or a multiply-add (operands in vector registers) every 4.9 cycles, two or more together one every 2.5 (an operand in a scalar
+// register, min / max / med3 and DPP forms 4.4 either way, an exponential or reciprocal 8.3).
+constexpr int PT2 = 512;
+__host__ __device__ constexpr int fwd_threads(int K, int D) { return PT2; }
+__host__ __device__ constexpr int bwd_threads(int K, int D) { return K * D <= 16 ? PT2 : PT; }
+// (layers read from memory)
+__host__ __device__ constexpr int global_threads(int K, int D, bool bwd) { return K * D <= (bwd ? 8 : 16) ? PT2 : PT; }
 constexpr int XLINE = 128;   // words reserved per workgroup in buf1 (K (D+1) <= 80, padded to a power of two)
 constexpr int XBCAST = 128;  // words reserved in buf2
 constexpr int DIES = 8;      // accelerator dies of the device (each with its own L2); workgroup b runs on die b mod 8
@@ -137,12 +146,13 @@ __device__ __forceinline__ void raise_abort(const PArgs& pa) {
 // solve the workgroups' sums as well -- and under the plain norm at k = 5 the gradient was 2.1e-6 from the 64-bit one with
 // float32 totals, 1.2e-6 in those kernels, 0.7e-6 with float64 ones.
 // The others keep float32 words: an evaluation at k = 4, d = 1 takes 1.3 % longer with wide ones.
-template <int NACC, bool WIDE_ = false>
+template <int NACC, bool WIDE_ = false, int NT_ = PT>
 struct XShared {
     static constexpr bool WIDE = WIDE_;
+    static constexpr int NT = NT_, WAVES = NT_ / 64;  // threads and wavefronts of the workgroup
     typedef typename std::conditional<WIDE_, double, float>::type total_t;
-    float rpart[pow2_at_least(NACC)][PT / 64];  // partial sums of every wavefront, [accumulator][wavefront]
-    double red2[PT];                 // reducer: per-thread sums (thread t: word t mod WPR, workgroups t/WPR + k PT/WPR)
+    float rpart[pow2_at_least(NACC)][WAVES];  // partial sums of every wavefront, [accumulator][wavefront]
+    double red2[NT];                 // reducer: per-thread sums (thread t: word t mod WPR, workgroups t/WPR + k PT/WPR)
     double tot[8];                   // reducer: totals of its slice
     unsigned int bc[XBCAST];         // payloads of the broadcast words
     total_t own[XLINE];              // this workgroup's own partial sums (read back directly by a team of one)
@@ -258,9 +268,14 @@ __device__ __forceinline__ void publish_partials(const PArgs& pa, unsigned int s
     __syncthreads();
     IDKM_SUB(2);
     if (tid < NACC) {
-        // the four wavefronts in float64, a fixed order
-        const double s = ((double)xs.rpart[tid][0] + (double)xs.rpart[tid][1]) +
-                         ((double)xs.rpart[tid][2] + (double)xs.rpart[tid][3]);
+        // the wavefronts in float64, a fixed order
+        double s = 0.0;
+#pragma unroll
+        for (int w = 0; w < XS::WAVES; w += 4) {
+            const double q = ((double)xs.rpart[tid][w] + (double)xs.rpart[tid][w + 1]) +
+                             ((double)xs.rpart[tid][w + 2] + (double)xs.rpart[tid][w + 3]);
+            s = w == 0 ? q : s + q;
+        }
         xs.own[tid] = (typename XS::total_t)s;
         // a workgroup's words lie together: one store transaction per workgroup and pass
         if constexpr (XS::WIDE) {  // (a leader reads its own sums from xs.own, a team of one too)
@@ -462,7 +477,7 @@ template <int NACC, class XS>
 __device__ __forceinline__ bool tree_die_totals(const PArgs& pa, unsigned int seq, XS& xs) {
     using Word = SumWords<XS::WIDE>;
     constexpr int LINE = xline_of(NACC) * Word::N;
-    constexpr int PARTS = PT / NACC;                 // member groups
+    constexpr int PARTS = XS::NT / NACC;             // member groups
     constexpr int MPT = (32 + PARTS - 1) / PARTS;    // members per thread
     static_assert(PARTS >= 1, "one thread per accumulator at least");
     const int tid = threadIdx.x, x = pa.wg, q = tid % NACC, part = tid / NACC;
@@ -527,14 +542,14 @@ template <int NACC, class XS>
 __device__ __forceinline__ bool tree_grid_totals(const PArgs& pa, unsigned int seq, XS& xs) {
     using Word = SumWords<XS::WIDE>;
     constexpr int LINE = xline_of(NACC) * Word::N;
-    constexpr int NLD = (DIES * NACC + PT - 1) / PT;
+    constexpr int NT = XS::NT, NLD = (DIES * NACC + NT - 1) / NT;
     const int tid = threadIdx.x;
     const unsigned long long* base = pa.buf3 + (size_t)(seq & 1u) * DIES * LINE;
     Word w[NLD];
     bool valid[NLD];
 #pragma unroll
     for (int u = 0; u < NLD; ++u) {
-        const int f = tid + u * PT, x = f / NACC;
+        const int f = tid + u * NT, x = f / NACC;
         valid[u] = f < DIES * NACC && x != pa.wg;  // a leader has left its own die's totals in xs.stage2 already
     }
     bool aborted = false;
@@ -542,7 +557,7 @@ __device__ __forceinline__ bool tree_grid_totals(const PArgs& pa, unsigned int s
     for (;;) {
 #pragma unroll
         for (int u = 0; u < NLD; ++u) {
-            const int f = tid + u * PT, x = f / NACC, q = f - x * NACC;
+            const int f = tid + u * NT, x = f / NACC, q = f - x * NACC;
             if (valid[u])
                 w[u].load(base + (size_t)x * LINE + q, xline_of(NACC));
             else
@@ -561,7 +576,7 @@ __device__ __forceinline__ bool tree_grid_totals(const PArgs& pa, unsigned int s
     }
 #pragma unroll
     for (int u = 0; u < NLD; ++u)
-        if (valid[u]) xs.stage2[tid + u * PT] = (typename XS::total_t)w[u].value();
+        if (valid[u]) xs.stage2[tid + u * NT] = (typename XS::total_t)w[u].value();
     if (aborted) {
         xs.abort = 1;
         raise_abort(pa);
@@ -607,7 +622,7 @@ __device__ __forceinline__ void publish_waves(const PArgs& pa, unsigned int seq,
     if (lane < 8) {
         xs.own[wave * 8 + lane] = tot;
         if (pa.wg >= DIES) {  // (a leader reads its own sums from xs.own)
-            unsigned long long* dst = &pa.buf1[((size_t)(seq & 1u) * PT + pa.wg) * 32 + wave * 8 + lane];
+            unsigned long long* dst = &pa.buf1[((size_t)(seq & 1u) * PT + pa.wg) * (XS::WAVES * 8) + wave * 8 + lane];
             if (xs.local)
                 st_word_die(dst, pack_f(seq, tot));
             else
@@ -616,15 +631,15 @@ __device__ __forceinline__ void publish_waves(const PArgs& pa, unsigned int seq,
     }
 }
 
-// hop 1, leader side: thread t adds the four wavefront words of slot t % 8 of member t / 8; the members of a
-// wavefront are added across lanes, the four wavefronts through LDS.  Publishes the die's line and keeps its
+// hop 1, leader side: thread t adds four wavefront words of slot t % 8 of member t / 8 % 32 (wavefronts 4 h .. 4 h + 3, h = t / 256);
+// the members of a wavefront are added across lanes, the leader's wavefronts through LDS.  Publishes the die's line and keeps its
 // totals in xs.stage2[die][slot].  Returns false if the wait was abandoned.
 template <class XS>
 __device__ __forceinline__ bool tree8_die_totals(const PArgs& pa, unsigned int seq, XS& xs) {
-    const int tid = threadIdx.x, x = pa.wg, p = tid & 7, mi = tid >> 3;
+    const int tid = threadIdx.x, x = pa.wg, p = tid & 7, mi = (tid >> 3) & 31, half = (tid >> 8) * 32;
     const int nmem = (pa.G - x + DIES - 1) / DIES;
     const bool valid = mi >= 1 && mi < nmem;
-    const unsigned long long* src = pa.buf1 + ((size_t)(seq & 1u) * PT + x + (size_t)mi * DIES) * 32 + p;
+    const unsigned long long* src = pa.buf1 + ((size_t)(seq & 1u) * PT + x + (size_t)mi * DIES) * (XS::WAVES * 8) + half + p;
     unsigned long long w[4];
     bool aborted = false;
     if (valid) aborted = !poll_words<4>(pa, src, 8, seq, w);
@@ -634,7 +649,7 @@ __device__ __forceinline__ bool tree8_die_totals(const PArgs& pa, unsigned int s
         s = ((double)__uint_as_float((unsigned int)w[0]) + (double)__uint_as_float((unsigned int)w[1])) +
             ((double)__uint_as_float((unsigned int)w[2]) + (double)__uint_as_float((unsigned int)w[3]));
     else if (mi == 0)
-        s = ((double)xs.own[p] + (double)xs.own[8 + p]) + ((double)xs.own[16 + p] + (double)xs.own[24 + p]);
+        s = ((double)xs.own[half + p] + (double)xs.own[half + 8 + p]) + ((double)xs.own[half + 16 + p] + (double)xs.own[half + 24 + p]);
     s = sum_over_lane_bits_3_to_5(s);  // the eight members of this wavefront
     if ((tid & 63) < 8) xs.red2[(tid >> 6) * 8 + p] = s;
     if (aborted) {
@@ -643,15 +658,24 @@ __device__ __forceinline__ bool tree8_die_totals(const PArgs& pa, unsigned int s
     }
     __syncthreads();
     if (xs.abort) return false;
+    auto die_total = [&](int q) {
+        double t = 0.0;
+#pragma unroll
+        for (int v = 0; v < XS::WAVES; v += 4) {
+            const double f = (xs.red2[v * 8 + q] + xs.red2[v * 8 + 8 + q]) + (xs.red2[v * 8 + 16 + q] + xs.red2[v * 8 + 24 + q]);
+            t = v == 0 ? f : t + f;
+        }
+        return t;
+    };
     if constexpr (XS::WIDE) {
         if (tid < 16) {  // (lanes 8 .. 15 store the upper halves)
-            const double tot = (xs.red2[p] + xs.red2[8 + p]) + (xs.red2[16 + p] + xs.red2[24 + p]);
+            const double tot = die_total(p);
             if (tid < 8) xs.stage2[x * 8 + tid] = tot;
             st_word(&pa.buf3[((size_t)(seq & 1u) * DIES + x) * 32 + tid],
                     pack_u(seq, (unsigned int)(tid < 8 ? __double2loint(tot) : __double2hiint(tot))));
         }
     } else if (tid < 8) {
-        const float tot = (float)((xs.red2[tid] + xs.red2[8 + tid]) + (xs.red2[16 + tid] + xs.red2[24 + tid]));
+        const float tot = (float)die_total(tid);
         xs.stage2[x * 8 + tid] = tot;
         st_word(&pa.buf3[((size_t)(seq & 1u) * DIES + x) * 32 + tid], pack_f(seq, tot));
     }
@@ -724,15 +748,23 @@ __device__ __forceinline__ bool tree_totals(const PArgs& pa, unsigned int seq, X
 
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
+// Vectors of a lane that the ratio form (see RatioForm) takes at a time; tiles with fewer stay with the general form.  Per evaluation
+// with two wavefronts per SIMD, general form / 6 / 9 / 18 at a time, us: 2.4 M weights 4.50 / 4.41 / 4.40 / 4.43, 8 M 9.45 / 8.45 / 8.62 /
+// 8.94, 1 M (8 vectors a lane) 3.59 / 3.34 / 3.65 / 3.76.  Not in batched launches: workgroups that share their SIMDs fill each
+// other's gaps, and the registers it takes cost more than its shorter code saves (21 tensors of ResNet18, k = 4, two at a time:
+// 1061 -> 1140 us).
+constexpr int RATIO_BLOCK = 6;
+
 // One pass over the workgroup's LDS tile.
 // SHARED: the workgroup shares its SIMDs with other teams' workgroups (batched launches); the hardware then
 // interleaves wavefronts, and short groups keep the registers low enough for four or five workgroups per compute unit.
 // s_tab: the caller's LDS table of the product forms' per-codeword operands (fwd_dot_tables), or null: then every lane
 // forms them itself in prepare().
-template <int K, int D, int DIST, int PASS, bool SHARED, bool RAG>
+template <int K, int D, int DIST, int PASS, bool SHARED, bool RAG, int NT>
 __device__ __forceinline__ void tile_pass(const Args& a, const float* s_w, const float* s_g, int64_t base, int cnt,
                                           const float* s_Cf, const float* s_Hs, const float* s_Ff,
-                                          float (&acc)[SmallItem<K, D, DIST, PASS, RAG>::NREG], const float* s_tab = nullptr) {
+                                          float (&acc)[SmallItem<K, D, DIST, PASS, RAG>::NREG], const float* s_tab = nullptr,
+                                          const int* s_solid = nullptr) {
     using Item = SmallItem<K, D, DIST, PASS, RAG>;
     float c[K][D], hs[K][D], ff[K][D + 1];
 #pragma unroll
@@ -776,21 +808,15 @@ __device__ __forceinline__ void tile_pass(const Args& a, const float* s_w, const
     }
 #pragma unroll
     for (int q = 0; q < Item::NREG; ++q) acc[q] = 0.f;
-    // one wavefront per SIMD: the latencies of a vector's chain (LDS load, exponentials, reciprocal) are hidden by
-    // other vectors of the same lane, so vectors are taken in groups whose bodies the scheduler interleaves: in the
-    // forward passes groups of UNR while they last, then groups of 4, then single vectors
+    // two wavefronts per SIMD (one with NT = 256): the latencies of a vector's chain (LDS load, exponentials, reciprocal) are hidden
+    // by other vectors of the same lane too, so vectors are taken in groups whose bodies the scheduler interleaves: in the forward
+    // passes groups of UNR while they last, then single vectors (2.4 M weights, k = 4, general form: groups of 4 / 9 / 18
+    // 4.50 / 4.54 / 4.53 us per evaluation; with one wavefront per SIMD 18 was best); in the backward passes at k <= 4, 4 / 6 / 9 / 12 vectors
+    // gave 6.53 / 6.34 / 6.30 / 6.24 us per (dF/dC)^T pass with one wavefront
     constexpr bool FWD_LIKE = (PASS == PASS_FWD || PASS == PASS_FIN);
-    // (for k = 8 and 16 the group size makes no measurable difference: 2 to 16 vectors are within 2 % of each other;
-    // in the backward passes at k <= 4, 4 / 6 / 9 / 12 vectors give 6.53 / 6.34 / 6.30 / 6.24 us per pass at C3; in the forward
-    // loop 9 / 12 / 18 / 36 give 4.79 / 4.79 / 4.71 / 4.65 us per evaluation)
-#ifndef IDKM_FWD_UNR
-#define IDKM_FWD_UNR 18
-#endif
-#ifndef IDKM_BWD_UNR
-#define IDKM_BWD_UNR 12
-#endif
     constexpr int UNR = SHARED ? (K <= 4 ? 4 : 2)
-                               : (FWD_LIKE ? (K <= 4 ? IDKM_FWD_UNR : (K == 8 ? 8 : 4)) : (K <= 4 ? IDKM_BWD_UNR : (K == 8 ? 3 : 2)));
+                               : FWD_LIKE ? (K * D >= 64 && PASS == PASS_FIN ? 1 : K * D >= 32 ? 2 : 4)
+                                          : (K <= 4 ? 12 : (K == 8 ? 3 : 2));
     auto one = [&](int it) {
         float w[D], g[D];
 #pragma unroll
@@ -800,47 +826,53 @@ __device__ __forceinline__ void tile_pass(const Args& a, const float* s_w, const
         }
         Item::run(a, base + it, w, g, c, hs, ff, acc);
     };
-    if constexpr (FWD_LIKE) {
+    auto sweep_forward = [&](auto one) {
         int it = threadIdx.x;
-        if constexpr (UNR >= 18) {
-            // a tile of 2 UNR or more vectors per lane: one straight block of 2 UNR bodies first (C3: the whole tile)
-            for (; it + (2 * UNR - 1) * PT < cnt; it += 2 * UNR * PT) {
+        for (; it + (UNR - 1) * NT < cnt; it += UNR * NT) {
 #pragma unroll
-                for (int u = 0; u < 2 * UNR; ++u) one(it + u * PT);
-            }
+            for (int u = 0; u < UNR; ++u) one(it + u * NT);
         }
-        for (; it + (UNR - 1) * PT < cnt; it += UNR * PT) {
+        for (; it < cnt; it += NT) one(it);
+    };
+    if constexpr (Item::RATIO && !SHARED) {
+        RatioForm<K> rf;
+        constexpr int U = RATIO_BLOCK;
+        rf.ok = false;
+        if (cnt >= U * NT) rf.prepare(c, a.nscale, RAG ? a.k : K, *s_solid != 0);
+        if (rf.ok) {
+            const float* src = s_w + threadIdx.x;
+            const int nb = cnt / (U * NT);
+            rf.template sweep<U, RAG>(nb, [&](int b, float(&w)[U]) {
 #pragma unroll
-            for (int u = 0; u < UNR; ++u) one(it + u * PT);
+                for (int u = 0; u < U; ++u) w[u] = src[(b * U + u) * NT];
+            }, acc);
+            for (int i = nb * U * NT; i + (int)threadIdx.x < cnt; i += NT) rf.template one<RAG>(src[i], acc);
+            return;
         }
-        if (UNR > 4) {
-            for (; it + 3 * PT < cnt; it += 4 * PT) {
-#pragma unroll
-                for (int u = 0; u < 4; ++u) one(it + u * PT);
-            }
-        }
-        for (; it < cnt; it += PT) one(it);
+    }
+    if constexpr (FWD_LIKE) {
+        sweep_forward(one);
     } else if constexpr (PASS == PASS_B2 && K <= 4 && D == 1 && !SHARED) {
         // the pass an implicit solve repeats, scalar weights: straight blocks of 36 vectors per lane while they last (C3:
         // the whole tile), then of UNR, of 4, and single vectors (6.29 -> 6.06 us per pass at C3 against blocks of 12)
         int it = threadIdx.x;
-        for (; it + 35 * PT < cnt; it += 36 * PT) {
+        for (; it + 35 * NT < cnt; it += 36 * NT) {
 #pragma unroll
-            for (int u = 0; u < 36; ++u) one(it + u * PT);
+            for (int u = 0; u < 36; ++u) one(it + u * NT);
         }
-        for (; it + (UNR - 1) * PT < cnt; it += UNR * PT) {
+        for (; it + (UNR - 1) * NT < cnt; it += UNR * NT) {
 #pragma unroll
-            for (int u = 0; u < UNR; ++u) one(it + u * PT);
+            for (int u = 0; u < UNR; ++u) one(it + u * NT);
         }
-        for (; it + 3 * PT < cnt; it += 4 * PT) {
+        for (; it + 3 * NT < cnt; it += 4 * NT) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) one(it + u * PT);
+            for (int u = 0; u < 4; ++u) one(it + u * NT);
         }
-        for (; it < cnt; it += PT) one(it);
+        for (; it < cnt; it += NT) one(it);
     } else {
         // the backward passes carry more state per vector; a plainly unrolled loop schedules them better (measured)
 #pragma unroll UNR
-        for (int it = threadIdx.x; it < cnt; it += PT) one(it);
+        for (int it = threadIdx.x; it < cnt; it += NT) one(it);
     }
     Item::finish(a, c, acc);
 }
@@ -851,10 +883,10 @@ __device__ __forceinline__ void tile_pass(const Args& a, const float* s_w, const
 // turn (block t G + wg in round t), so that at any moment the team reads one contiguous window of memory: with a
 // contiguous share per workgroup and a power-of-two layer, all workgroups would hit the same memory channel.
 // gw, gg: the whole tensors, 16-byte aligned.
-template <int K, int D, int DIST, int PASS>
+template <int NT, int K, int D, int DIST, int PASS>
 __device__ __forceinline__ void tile_pass_global(const Args& a, const float* gw, const float* gg, int wg, int G,
                                                  const float* s_Cf, const float* s_Hs, const float* s_Ff,
-                                                 float (&acc)[SmallItem<K, D, DIST, PASS>::NREG]) {
+                                                 float (&acc)[SmallItem<K, D, DIST, PASS>::NREG], const int* s_solid) {
     using Item = SmallItem<K, D, DIST, PASS>;
     float c[K][D], hs[K][D], ff[K][D + 1];
 #pragma unroll
@@ -885,10 +917,38 @@ __device__ __forceinline__ void tile_pass_global(const Args& a, const float* gw,
             Item::run(a, gi * VPL + v, w, g, c, hs, ff, acc);
         }
     };
+    if constexpr (Item::RATIO) {
+        RatioForm<K> rf;
+        rf.prepare(c, a.nscale, K, *s_solid != 0);
+        if (rf.ok) {
+            constexpr int L = 4;  // 16-byte loads of a block
+            const int64_t step = (int64_t)G * NT, at = (int64_t)wg * NT + threadIdx.x;
+            const int nb = (int)(ngroups / (step * L));
+            if (nb > 0)
+                rf.template sweep<4 * L, false>(nb, [&](int b, float(&w)[4 * L]) {
+#pragma unroll
+                    for (int u = 0; u < L; ++u) {
+                        const f32x4_t v = w4[((int64_t)b * L + u) * step + at];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) w[4 * u + e] = v[e];
+                    }
+                }, acc);
+            for (int64_t gi = nb * L * step + at; gi < ngroups; gi += step) {
+                const f32x4_t v = w4[gi];
+                rf.template sweep<4, false>(1, [&](int, float(&w)[4]) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) w[e] = v[e];
+                }, acc);
+            }
+            if (wg == G - 1)
+                for (int64_t it = ngroups * 4 + threadIdx.x; it < a.m; it += NT) rf.template one<false>(gw[it], acc);
+            return;
+        }
+    }
     const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
     f32x4_t cw[NLD], cg[NLD], nw[NLD], ng[NLD];
-    const int64_t step = (int64_t)G * PT;           // groups per round of the team
-    int64_t gi = (int64_t)wg * PT + threadIdx.x;    // this lane's group on its first turn
+    const int64_t step = (int64_t)G * NT;           // groups per round of the team
+    int64_t gi = (int64_t)wg * NT + threadIdx.x;    // this lane's group on its first turn
 #pragma unroll
     for (int u = 0; u < NLD; ++u) {
         const int64_t i = gi + u * step;
@@ -916,7 +976,7 @@ __device__ __forceinline__ void tile_pass_global(const Args& a, const float* gw,
     }
     // the vectors behind the last whole 16-byte group of the layer (fewer than VPL) go to the last workgroup
     if (wg == G - 1) {
-        for (int64_t it = ngroups * VPL + threadIdx.x; it < a.m; it += PT) {
+        for (int64_t it = ngroups * VPL + threadIdx.x; it < a.m; it += NT) {
             float w[D], g[D];
 #pragma unroll
             for (int r = 0; r < D; ++r) {
@@ -931,15 +991,15 @@ __device__ __forceinline__ void tile_pass_global(const Args& a, const float* gw,
 
 // A pass over the workgroup's share of the layer: its LDS tile (w, g: the tile; base, cnt: its place in the layer) or,
 // GLOBALW, its blocks of the tensors in memory (w, g: the whole tensors).
-template <int K, int D, int DIST, int PASS, bool SHARED, bool GLOBALW, bool RAG>
+template <int NT, int K, int D, int DIST, int PASS, bool SHARED, bool GLOBALW, bool RAG>
 __device__ __forceinline__ void any_tile_pass(const Args& a, const PArgs& pa, const float* w, const float* g,
                                               int64_t base, int cnt, const float* s_Cf, const float* s_Hs,
                                               const float* s_Ff, float (&acc)[SmallItem<K, D, DIST, PASS, RAG>::NREG],
-                                              const float* s_tab = nullptr) {
+                                              const float* s_tab = nullptr, const int* s_solid = nullptr) {
     if constexpr (GLOBALW)
-        tile_pass_global<K, D, DIST, PASS>(a, w, g, pa.wg, pa.G, s_Cf, s_Hs, s_Ff, acc);
+        tile_pass_global<NT, K, D, DIST, PASS>(a, w, g, pa.wg, pa.G, s_Cf, s_Hs, s_Ff, acc, s_solid);
     else
-        tile_pass<K, D, DIST, PASS, SHARED, RAG>(a, w, g, base, cnt, s_Cf, s_Hs, s_Ff, acc, s_tab);
+        tile_pass<K, D, DIST, PASS, SHARED, RAG, NT>(a, w, g, base, cnt, s_Cf, s_Hs, s_Ff, acc, s_tab, s_solid);
 }
 
 // Codewords per reducer: as many as fit 8 words of (n_j, s_j) per workgroup.
@@ -991,7 +1051,7 @@ __device__ __forceinline__ void bwd_dot_hf(float hfm, float* tab) {
 // GLOBALW: the layer does not fit the chip's LDS; every pass reads the workgroup's share of W from memory.
 // RAG: a codebook of a.k codewords, K/2 < a.k < K, in the kernel for K (see live_weight).  Launched only as a team of one
 // or with the two-level exchange.
-template <int K, int D, int DIST, bool SHARED, bool GLOBALW = false, bool RAG = false>
+template <int NT, int K, int D, int DIST, bool SHARED, bool GLOBALW = false, bool RAG = false>
 __device__ __forceinline__ void persist_fwd_body(const Args& a, const PArgs& pa) {
     constexpr int KD = K * D;
     constexpr int ACCW = D + 1;
@@ -1000,12 +1060,13 @@ __device__ __forceinline__ void persist_fwd_body(const Args& a, const PArgs& pa)
     constexpr int R = K / KPR;                 // reducers
     constexpr int WPR = KPR * ACCW;            // words a reducer reads per workgroup
     constexpr int NB = KD;                     // broadcast words: the new codebook
-    static_assert(NACC <= XLINE && NB <= XBCAST && KD <= 64 && PT / 16 == 16, "shape does not fit the exchange layout");
+    static_assert(NACC <= XLINE && NB <= XBCAST && KD <= 64, "shape does not fit the exchange layout");
     extern __shared__ float s_tile[];
-    __shared__ XShared<NACC, RAG> xs;
+    __shared__ XShared<NACC, RAG, NT> xs;
     __shared__ double s_Cd[KD];  // float64 master copy (a reducer's own slice is the live one)
     __shared__ float s_Cf[KD];
     __shared__ int s_done, s_iters, s_conv, s_bad;
+    __shared__ int s_solid;  // every codeword had a mass worth the name in the last evaluation (see RatioForm)
     __shared__ double s_res;
     // product form of the loop's E-step: its per-codeword operands, kept up to date by wavefront 0
     // (worth it from k d = 32 on: below, what a lane saves at the start of its pass is less than wavefront 0 adds to the
@@ -1019,7 +1080,7 @@ __device__ __forceinline__ void persist_fwd_body(const Args& a, const PArgs& pa)
     if (base < a.m) cnt = (a.m - base < pa.per) ? (int)(a.m - base) : pa.per;
     tree_announce(pa);
     if (!GLOBALW)
-        load_tile<PT>(s_tile, a.W + base * D, cnt * D);
+        load_tile<NT>(s_tile, a.W + base * D, cnt * D);
     const float* s_w = GLOBALW ? a.W : s_tile;
     const int k = RAG ? a.k : K, kd = k * D;                              // codewords that exist
     const int src = (RAG && tid >= kd && tid < KD) ? tid % D : tid;       // (the others follow codeword 0)
@@ -1034,6 +1095,7 @@ __device__ __forceinline__ void persist_fwd_body(const Args& a, const PArgs& pa)
         s_iters = 0;
         s_conv = 0;
         s_bad = 0;
+        s_solid = 0;
         s_res = 0.0;
     }
     if constexpr (DOT) {
@@ -1056,6 +1118,8 @@ __device__ __forceinline__ void persist_fwd_body(const Args& a, const PArgs& pa)
         r_cf = pa.C0[src];
         r_cd = (double)r_cf;
     }
+    const double least_mass = solid_mass(a.m);
+    const bool ratio_tile = GLOBALW || pa.per >= RATIO_BLOCK * NT;  // (a smaller tile never takes that form)
     // n, sv: mass of this lane's codeword and the sum of its component (lanes < k d; all 64 lanes of wavefront 0 call)
     auto update_vals = [&](double n, double sv) {
         double df2 = 0.0;
@@ -1071,6 +1135,12 @@ __device__ __forceinline__ void persist_fwd_body(const Args& a, const PArgs& pa)
             s_Cf[tid] = cn;
         }
         const double r2 = first_lanes_sum_d_dpp<KD>(df2);
+        if constexpr (SmallItem<K, D, DIST, PASS_FWD, RAG>::RATIO && !SHARED) {
+            if (ratio_tile) {
+                const bool solid = __builtin_amdgcn_ballot_w64(tid < KD && !(n >= least_mass)) == 0ull;
+                if (tid == 0) s_solid = solid ? 1 : 0;
+            }
+        }
         r_iters += 1;  // (wavefront 0 counts in a register: nothing on this path waits for an LDS read of the state)
         if (tid == 0) {
             s_iters = r_iters;
@@ -1095,7 +1165,7 @@ __device__ __forceinline__ void persist_fwd_body(const Args& a, const PArgs& pa)
     float acc[NACC];
     while (!s_done) {
         IDKM_STAMP(0);
-        any_tile_pass<K, D, DIST, PASS_FWD, SHARED, GLOBALW, RAG>(a, pa, s_w, nullptr, base, cnt, s_Cf, nullptr, nullptr, acc, DOT ? s_tab : nullptr);
+        any_tile_pass<NT, K, D, DIST, PASS_FWD, SHARED, GLOBALW, RAG>(a, pa, s_w, nullptr, base, cnt, s_Cf, nullptr, nullptr, acc, DOT ? s_tab : nullptr, &s_solid);
         IDKM_STAMP(1);
         ++seq;
         publish_partials<NACC>(pa, seq, acc, xs);
@@ -1199,7 +1269,7 @@ __device__ __forceinline__ void persist_fwd_body(const Args& a, const PArgs& pa)
     }
 
     // evaluation at C*: outputs, and n*, F* for the backward
-    any_tile_pass<K, D, DIST, PASS_FIN, SHARED, GLOBALW, RAG>(a, pa, s_w, nullptr, base, cnt, s_Cf, nullptr, nullptr, acc);
+    any_tile_pass<NT, K, D, DIST, PASS_FIN, SHARED, GLOBALW, RAG>(a, pa, s_w, nullptr, base, cnt, s_Cf, nullptr, nullptr, acc);
     ++seq;
     publish_partials<NACC>(pa, seq, acc, xs);
     if (pa.tree) {
@@ -1502,7 +1572,7 @@ __device__ __forceinline__ int gmres_step(const GmView<N>& gm, U u, const double
 // Backward (Alg. 2 per-layer steps): v, the averaged fixed-point iteration of
 // Sec. 4.2 for g (skipped for JFB), and dW, in one launch.  RAG: as in the forward; the components of v, g and h that
 // belong to no codeword are zero throughout.
-template <int K, int D, int DIST, bool SHARED, bool GLOBALW = false, bool RAG = false>
+template <int NT, int K, int D, int DIST, bool SHARED, bool GLOBALW = false, bool RAG = false>
 __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa) {
     constexpr int KD = K * D;
     constexpr int KPR = (8 / D) > K ? K : (8 / D);  // codewords per reducer: 8 words of D components
@@ -1519,7 +1589,7 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
     constexpr int NBP = HAS_PAIRS ? pair_sums(K, D, DIST) : 1;
     constexpr int NXS = (HAS_DENSE ? NBJ : KD) > NBP ? (HAS_DENSE ? NBJ : KD) : NBP;
     extern __shared__ float s_tile[];
-    __shared__ XShared<NXS, RAG> xs;
+    __shared__ XShared<NXS, RAG, NT> xs;
     __shared__ double s_Fd[HAS_PAIRS ? KD : 1], s_A[HAS_PAIRS && KD <= 4 ? KD * KD : 1];
     __shared__ double s_v[KD], s_g[KD], s_rn[K];  // a reducer's own slice is the live one; s_rn = 1/(tau n)
     __shared__ float s_Cf[KD], s_Hs[KD], s_Hv[KD], s_Ff[KD];
@@ -1550,8 +1620,8 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
     const float* s_gt = GLOBALW ? a.G : (SHARED ? a.G + base * D : s_tile + (size_t)pa.per * D);
     tree_announce(pa);
     if (!GLOBALW) {
-        load_tile<PT>(s_tile, a.W + base * D, cnt * D);
-        if (!SHARED) load_tile<PT>(s_tile + (size_t)pa.per * D, a.G + base * D, cnt * D);
+        load_tile<NT>(s_tile, a.W + base * D, cnt * D);
+        if (!SHARED) load_tile<NT>(s_tile + (size_t)pa.per * D, a.G + base * D, cnt * D);
     }
     if (tid < KD) {
         s_Cf[tid] = a.Cf[src];
@@ -1608,7 +1678,7 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
             // one pass accumulates v and the sums T, U of dF/dC* (layout as in the stream path's tail_bj); workgroup 0
             // adds them over the team, solves (I - dF/dC*)^T g = v by Gauss-Jordan elimination and broadcasts h/tau
             float accj[NBJ];
-            any_tile_pass<K, D, DIST, PASS_BJ, SHARED, GLOBALW, RAG>(a, pa, s_w, s_gt, base, cnt, s_Cf, s_Hs, s_Ff, accj);
+            any_tile_pass<NT, K, D, DIST, PASS_BJ, SHARED, GLOBALW, RAG>(a, pa, s_w, s_gt, base, cnt, s_Cf, s_Hs, s_Ff, accj);
             ++seq;
             publish_partials<NBJ>(pa, seq, accj, xs);
             if (wg == 0) {
@@ -1681,7 +1751,7 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
     if constexpr (HAS_PAIRS) {
         if (pairs) {
             float accp[NBP];
-            any_tile_pass<K, D, DIST, PASS_BP, SHARED, GLOBALW, RAG>(a, pa, s_w, s_gt, base, cnt, s_Cf, s_Hs, s_Ff, accp);
+            any_tile_pass<NT, K, D, DIST, PASS_BP, SHARED, GLOBALW, RAG>(a, pa, s_w, s_gt, base, cnt, s_Cf, s_Hs, s_Ff, accp);
             ++seq;
             publish_partials<NBP>(pa, seq, accp, xs);
             if (tree) {
@@ -1709,7 +1779,7 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
     }
     if (!dense_done && !pairs) {
     // B1: v = dL/dC* with W fixed; the solve starts at g = v
-    any_tile_pass<K, D, DIST, PASS_B1, SHARED, GLOBALW, RAG>(a, pa, s_w, s_gt, base, cnt, s_Cf, s_Hs, s_Ff, acc);
+    any_tile_pass<NT, K, D, DIST, PASS_B1, SHARED, GLOBALW, RAG>(a, pa, s_w, s_gt, base, cnt, s_Cf, s_Hs, s_Ff, acc);
     ++seq;
     publish_partials<KD>(pa, seq, acc, xs);
     if (tree) {
@@ -1845,7 +1915,7 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
     }
     while (!s_done) {
         IDKM_STAMP(0);
-        any_tile_pass<K, D, DIST, PASS_B2, SHARED, GLOBALW, RAG>(a, pa, s_w, s_gt, base, cnt, s_Cf, s_Hs, s_Ff, accr, BTAB ? s_tabB : nullptr);
+        any_tile_pass<NT, K, D, DIST, PASS_B2, SHARED, GLOBALW, RAG>(a, pa, s_w, s_gt, base, cnt, s_Cf, s_Hs, s_Ff, accr, BTAB ? s_tabB : nullptr);
         IDKM_STAMP(1);
         ++seq;
         publish_partials<KD>(pa, seq, acc, xs);
@@ -2049,7 +2119,7 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
     }
 
     // B3: dW = direct + (dF/dW)^T g
-    any_tile_pass<K, D, DIST, PASS_B3, SHARED, GLOBALW, RAG>(a, pa, s_w, s_gt, base, cnt, s_Cf, s_Hs, s_Ff, reinterpret_cast<float(&)[1]>(acc[0]));
+    any_tile_pass<NT, K, D, DIST, PASS_B3, SHARED, GLOBALW, RAG>(a, pa, s_w, s_gt, base, cnt, s_Cf, s_Hs, s_Ff, reinterpret_cast<float(&)[1]>(acc[0]));
     if (dense_done || tree || pairs) {
         if (wg == 0 && tid < kd) {
             a.gd[tid] = s_g[tid];
@@ -2080,34 +2150,34 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
 
 // One team per launch: the grid is the team.
 template <int K, int D, int DIST, bool RAG = false>
-__global__ __launch_bounds__(PT) void persist_fwd(const Args a, const PArgs pa_in) {
+__global__ __launch_bounds__(fwd_threads(K, D)) void persist_fwd(const Args a, const PArgs pa_in) {
     PArgs pa = pa_in;
     pa.wg = blockIdx.x;
     pa.G = gridDim.x;
-    persist_fwd_body<K, D, DIST, false, false, RAG>(a, pa);
+    persist_fwd_body<fwd_threads(K, D), K, D, DIST, false, false, RAG>(a, pa);
 }
 template <int K, int D, int DIST, bool RAG = false>
-__global__ __launch_bounds__(PT) void persist_bwd(const Args a, const PArgs pa_in) {
+__global__ __launch_bounds__(bwd_threads(K, D)) void persist_bwd(const Args a, const PArgs pa_in) {
     PArgs pa = pa_in;
     pa.wg = blockIdx.x;
     pa.G = gridDim.x;
-    persist_bwd_body<K, D, DIST, false, false, RAG>(a, pa);
+    persist_bwd_body<bwd_threads(K, D), K, D, DIST, false, false, RAG>(a, pa);
 }
 
 // The same for a layer larger than the chip's LDS (W is read from memory in every pass; no dynamic LDS).
 template <int K, int D, int DIST>
-__global__ __launch_bounds__(PT) void persist_fwd_global(const Args a, const PArgs pa_in) {
+__global__ __launch_bounds__(global_threads(K, D, false)) void persist_fwd_global(const Args a, const PArgs pa_in) {
     PArgs pa = pa_in;
     pa.wg = blockIdx.x;
     pa.G = gridDim.x;
-    persist_fwd_body<K, D, DIST, false, true>(a, pa);
+    persist_fwd_body<global_threads(K, D, false), K, D, DIST, false, true>(a, pa);
 }
 template <int K, int D, int DIST>
-__global__ __launch_bounds__(PT) void persist_bwd_global(const Args a, const PArgs pa_in) {
+__global__ __launch_bounds__(global_threads(K, D, true)) void persist_bwd_global(const Args a, const PArgs pa_in) {
     PArgs pa = pa_in;
     pa.wg = blockIdx.x;
     pa.G = gridDim.x;
-    persist_bwd_body<K, D, DIST, false, true>(a, pa);
+    persist_bwd_body<global_threads(K, D, true), K, D, DIST, false, true>(a, pa);
 }
 
 // Several independent problems of one shape (the layers of Alg. 2's loops) in one launch: item_of_wg maps a
@@ -2119,7 +2189,7 @@ __global__ __launch_bounds__(PT) void persist_fwd_batch(const BatchItem* items, 
     PArgs pa = it.p;
     pa.wg = (int)blockIdx.x - it.wg_begin;
     pa.G = it.wg_count;
-    persist_fwd_body<K, D, DIST, true, false, RAG>(a, pa);
+    persist_fwd_body<PT, K, D, DIST, true, false, RAG>(a, pa);
 }
 template <int K, int D, int DIST, bool RAG = false>
 __global__ __launch_bounds__(PT) void persist_bwd_batch(const BatchItem* items, const unsigned short* item_of_wg) {
@@ -2128,7 +2198,7 @@ __global__ __launch_bounds__(PT) void persist_bwd_batch(const BatchItem* items, 
     PArgs pa = it.p;
     pa.wg = (int)blockIdx.x - it.wg_begin;
     pa.G = it.wg_count;
-    persist_bwd_body<K, D, DIST, true, false, RAG>(a, pa);
+    persist_bwd_body<PT, K, D, DIST, true, false, RAG>(a, pa);
 }
 
 }  // namespace idkm

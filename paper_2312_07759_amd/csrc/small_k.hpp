@@ -137,6 +137,126 @@ __device__ __forceinline__ float delta_small(const float (&df)[K][D], const floa
     return df[j][r] * ri[j];  // plain norm, D > 1: unit vector; squared energy, D == 1: df is scaled, ri = 2/s
 }
 
+// Forward loop, scalar weights under two to four codewords in ascending order, squared energy: the row's weights from the ratios
+// of neighbours, p_{j+1} / p_j = exp2(y_j) with y_j = 2 s^2 (c_{j+1} - c_j) (w - (c_j + c_{j+1})/2), s^2 = log2(e)/tau, relative to one inner
+// codeword r (p_r = 1): the square of w drops out, codeword r costs neither an exponent nor an exponential, and there is no
+// row minimum to form and subtract -- 28 issue slots a vector at k = 4 instead of 37.  Where two codewords compete y is small and so is its
+// error (in the general form below the errors of two squares of 5 to 10 meet).
+// w is clamped to [lo, hi], where no weight exceeds 2^TOP.  Beyond, the weights of a row stay what they are at the end of the
+// interval: right to 2^-GAP where the outermost codeword outweighs every other by 2^GAP there already, since the true
+// ratio only grows.  At the lower end, and with three codewords or fewer at both, that is the ratio to r itself, 2^TOP; at the
+// upper one of four prepare() looks (rows harder than about the spacing keep the general form).  `solid`: the caller says that every
+// codeword had a mass of at least m / 1024 in the evaluation before; what the clamp leaves out is then below 2^-24 of any sum.
+// A NaN or an infinity still reaches every sum of w.  The order, like everything here, is the same in all lanes.
+__device__ __forceinline__ double solid_mass(int64_t m) { return (double)m * (1.0 / 1024.0); }
+template <int K>
+struct RatioForm {
+    static constexpr int R = K == 4 ? 1 : 0;
+    static constexpr float TOP = 120.f, GAP = 34.f;
+    float A[K - 1], mid[K - 1], B[K - 1], lo, hi;  // y_j = A_j (w - mid_j) + B_j: B carries what rounding took from the midpoint
+    bool ok;
+    __device__ __forceinline__ void prepare(const float (&c)[K][1], float nscale, int k, bool solid) {
+        bool good = solid;
+        const float two_s2 = -2.f * nscale;
+#pragma unroll
+        for (int j = 0; j + 1 < K; ++j) {
+            const bool live = K < 4 || j + 1 < k;  // (three codewords in the kernel for four: the last ratio is not used)
+            const float c0 = c[j][0], c1 = c[j + 1][0];
+            const float t = c0 + c1, c1t = t - c0, rest = (c0 - (t - c1t)) + (c1 - c1t);  // t + rest = c0 + c1 exactly
+            const float slope = two_s2 * (c1 - c0);
+            good = good && (!live || (slope > 1e-30f && slope < 1e30f));
+            A[j] = j < R ? -slope : slope;  // (below r the ratio is taken the other way round)
+            mid[j] = 0.5f * t;
+            B[j] = -0.5f * rest * A[j];
+        }
+        if constexpr (K == 2) {
+            lo = -3.4e38f;
+            hi = fmaf(TOP, fast_rcp(A[0]), mid[0]);
+        } else {
+            lo = fmaf(TOP, fast_rcp(A[0]), mid[0]);
+            if (k == 3) {
+                hi = fmaf(TOP, fast_rcp(A[1]), mid[1]);
+            } else {
+                hi = fmaf(A[1], mid[1], fmaf(A[2], mid[2], TOP)) * fast_rcp(A[1] + A[2]);
+                good = good && (hi - mid[2]) * A[2] >= GAP;
+            }
+        }
+        good = good && fabsf(hi) < 1e30f && (K == 2 || fabsf(lo) < 1e30f);
+        ok = __builtin_amdgcn_ballot_w64(good) == ~0ull;
+    }
+
+    template <bool K3>
+    __device__ __forceinline__ void one(float w, float (&acc)[2 * K]) const {
+        sweep<1, K3>(1, [&](int, float(&x)[1]) { x[0] = w; }, acc);
+    }
+    // nb blocks of U vectors; load(i, w): block i.  Each operation is issued for all U vectors before the next one, so that a
+    // result is not used before U other instructions and exponentials stand together (left to itself the scheduler takes one vector
+    // after the other, which gains nothing over the general form); the loads of the next block are in flight meanwhile.
+    template <int U, bool K3, class LOAD>
+    __device__ __forceinline__ void sweep(int nb, LOAD load, float (&acc)[2 * K]) const {
+        float w[U], nw[U];
+        load(0, w);
+        for (int i = 0; i < nb; ++i) {
+            load(i + 1 < nb ? i + 1 : i, nw);
+            if (U > 1) __builtin_amdgcn_sched_barrier(0);
+            float x[U], p[K - 1][U], S[U];
+#define IDKM_ALL _Pragma("unroll") for (int u = 0; u < U; ++u)
+#define IDKM_NEXT if (U > 1) __builtin_amdgcn_sched_barrier(0);
+            IDKM_ALL x[u] = __builtin_amdgcn_fmed3f(w[u], lo, hi);
+            IDKM_NEXT
+#pragma unroll
+            for (int j = 0; j < K - 1; ++j) {
+                if (K3 && j == 2) continue;
+                IDKM_ALL p[j][u] = x[u] - mid[j];
+                IDKM_NEXT
+            }
+#pragma unroll
+            for (int j = 0; j < K - 1; ++j) {
+                if (K3 && j == 2) continue;
+                IDKM_ALL p[j][u] = fmaf(p[j][u], A[j], B[j]);
+                IDKM_NEXT
+            }
+#pragma unroll
+            for (int j = 0; j < K - 1; ++j) {
+                if (K3 && j == 2) continue;
+                IDKM_ALL p[j][u] = fast_exp2(p[j][u]);
+                IDKM_NEXT
+            }
+            IDKM_ALL S[u] = 1.f + p[0][u];
+            IDKM_NEXT
+            if constexpr (K == 4) {
+                IDKM_ALL S[u] += p[1][u];
+                IDKM_NEXT
+                if (!K3) {
+                    IDKM_ALL p[2][u] *= p[1][u];
+                    IDKM_NEXT
+                    IDKM_ALL S[u] += p[2][u];
+                    IDKM_NEXT
+                }
+            }
+            IDKM_ALL S[u] = fast_rcp(S[u]);
+            IDKM_NEXT
+            IDKM_ALL x[u] = S[u] * w[u];
+            IDKM_NEXT
+            IDKM_ALL {
+                acc[2 * R] += S[u];
+                acc[2 * R + 1] += x[u];
+#pragma unroll
+                for (int j = 0; j < K - 1; ++j) {
+                    const int q = 2 * (j < R ? j : j + 1);
+                    if (K3 && j == 2) continue;
+                    acc[q] = fmaf(p[j][u], S[u], acc[q]);
+                    acc[q + 1] = fmaf(p[j][u], x[u], acc[q + 1]);
+                }
+                IDKM_NEXT
+            }
+            IDKM_ALL w[u] = nw[u];
+#undef IDKM_ALL
+#undef IDKM_NEXT
+        }
+    }
+};
+
 // Everything one pass does for one weight vector i: E-step, then the pass's own
 // accumulation or per-vector output.  acc has K*(D+1) entries for the forward
 // passes ((n_j, s_j) interleaved), K*D for B1/B2, and is unused for B3.
@@ -185,6 +305,9 @@ struct SmallItem {
     // s^2 |c - mu| |w - mu|, i.e. of the exponents themselves; the closest-codeword key of the last pass is not formed
     // this way.
     static constexpr bool FWD_DOT = (PASS == PASS_FWD && DIST == DIST_SQL2 && D >= 2 && K >= D && !RAG);
+
+    // Forward loop by ratios of neighbouring codewords (see RatioForm).
+    static constexpr bool RATIO = (PASS == PASS_FWD && DIST == DIST_SQL2 && D == 1 && K <= 4);
 
     // Called once per pass by every caller of run(), after it has loaded the tables into registers.
     static __device__ __forceinline__ void prepare(const Args& a, float (&c)[K][D], float (&hs)[K][D], float (&ff)[K][D + 1]) {

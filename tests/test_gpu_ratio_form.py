@@ -1,0 +1,95 @@
+"""Forward loop of two to four ascending codewords (scalar weights, squared energy): the row's weights come from ratios of neighbouring
+codewords, with far weights clamped; other orders, hard rows and nearly empty clusters keep the general form.  Tiles in LDS around the block
+sizes of that form, and layers read from memory."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import idkm_oracle as orc
+from paper_2312_07759_amd import binding
+from paper_2312_07759_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+# after a few evaluations: each rounds the codebook to float32 (6e-8) and sums float32 weights good to 3e-6 where they matter
+# with random signs; 2e-6 of the codebook's spread
+TOL = 2e-6
+
+
+def dev(x):
+    return torch.as_tensor(np.ascontiguousarray(x), dtype=torch.float32).cuda()
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = binding.Context(0)
+    yield c
+    c.close()
+
+
+def _case(k, m, soft, order, shift, outliers):
+    rng = np.random.default_rng(k * 1000 + m)
+    W = rng.standard_normal((m, 1)) * 0.1
+    if outliers:
+        W[::101] *= 20.0                     # far beyond the clamp
+    C0 = np.quantile(W, (np.arange(k) + 0.5) / k).reshape(k, 1)
+    if order == "down":
+        C0 = C0[::-1]
+    if order == "mixed":
+        C0 = np.roll(C0, 1, axis=0)
+    return (W + shift).astype(np.float32), (C0 + shift).astype(np.float32), soft * (0.1 / k) ** 2
+
+
+# 512 threads take 6 vectors at a time: tiles of 6 x 512 and one less or more, one workgroup and teams
+@pytest.mark.parametrize("k", [2, 3, 4])
+@pytest.mark.parametrize("m", [3_071, 3_072, 3_073, 4_096, 24_577, 800_003, 2_000_001])
+@pytest.mark.parametrize("soft,order,shift,outliers", [(2.0, "up", 0.0, False), (2.0, "up", 0.7, True), (0.6, "up", 0.0, True),
+                                                       (0.01, "up", 0.0, False), (2.0, "down", 0.0, True), (2.0, "mixed", 0.0, False)])
+def test_against_the_oracle(ctx, k, m, soft, order, shift, outliers):
+    W, C0, tau = _case(k, m, soft, order, shift, outliers)
+    ref = orc.soft_kmeans(W, C0, tau, 0.0, 5, wl.DIST_SQL2)
+    f = ctx.forward(dev(W), dev(C0), tau, 0.0, 5, wl.DIST_SQL2)
+    assert f["info"].iters == 5 and f["info"].path == binding.PATH_PERSISTENT
+    C = f["C"].cpu().numpy()
+    spread = np.ptp(ref["C"]) + 2e-2 * abs(shift)     # (a float32 codebook at the shift carries its rounding)
+    assert np.max(np.abs(C - ref["C"])) < TOL * spread, np.max(np.abs(C - ref["C"])) / spread
+
+
+@pytest.mark.parametrize("k", [2, 4])
+@pytest.mark.parametrize("m", [1_000, 16_385, 70_003, 600_001])
+def test_layers_read_from_memory(k, m):
+    """A tile limit of zero sends every layer to the kernel that reads W in each pass; the default takes it for forward solves."""
+    ctx = binding.Context(0)
+    try:
+        ctx.set_tile_limit(0)
+        W, C0, tau = _case(k, m, 2.0, "up", 0.0, True)
+        ref = orc.soft_kmeans(W, C0, tau, 0.0, 5, wl.DIST_SQL2)
+        Wd, G = dev(W), dev(np.random.default_rng(1).standard_normal(W.shape))
+        f = ctx.forward(Wd, dev(C0), tau, 0.0, 5, wl.DIST_SQL2)
+        assert f["info"].path == binding.PATH_PERSISTENT
+        C = f["C"].cpu().numpy()
+        assert np.max(np.abs(C - ref["C"])) < TOL * np.ptp(ref["C"])
+        b = ctx.backward(G, binding.BWD_IMPLICIT, tol=0.0, max_iter=4)      # (backwards stay on the stream path)
+        assert b["info"].path == binding.PATH_STREAM
+        rb = orc.backward(W, C, tau, wl.DIST_SQL2, G.cpu().numpy(), "implicit", tol=0.0, max_iter=4)
+        assert np.linalg.norm(b["dW"].cpu().numpy() - rb["dW"]) < 1e-4 * np.linalg.norm(rb["dW"])
+        # a wait that expires is answered by the stream path
+        ctx.set_spin_limit(0)
+        f = ctx.forward(Wd, dev(C0), tau, 0.0, 5, wl.DIST_SQL2)
+        assert np.max(np.abs(f["C"].cpu().numpy() - ref["C"])) < TOL * np.ptp(ref["C"])
+    finally:
+        ctx.close()
+
+
+def test_non_finite_weights_are_still_refused(ctx):
+    W, C0, tau = _case(4, 6_000, 2.0, "up", 0.0, False)
+    for bad in (np.nan, np.inf, -np.inf):
+        V = W.copy()
+        V[5_000] = bad
+        with pytest.raises(binding.IdkmError):
+            ctx.forward(dev(V), dev(C0), tau, 0.0, 5, wl.DIST_SQL2)
+    # a codeword no weight is near keeps its place
+    C1 = C0.copy()
+    C1[3] = 50.0
+    f = ctx.forward(dev(W), dev(C1), tau, 0.0, 5, wl.DIST_SQL2)
+    assert f["info"].empty_clusters == 1 and f["C"][3].item() == 50.0
