@@ -441,12 +441,15 @@ bool plan_small(idkm_ctx* ctx, bool bwd, PersistPlan* pp, const void* dwq, int m
     pp->lane = false;
     const int64_t chunk = (int64_t)ctx->min_vec_per_thread * PT;
     int64_t g = (m + chunk - 1) / chunk;  // a few vectors per thread before adding workgroups
-    // Up to 16 vectors per thread one workgroup alone needs no exchange through memory (2.0 to 5.5 us a pass in a team of
-    // eight whatever m is), but walks through all vectors itself.  Where the lines lie (us per evaluation, one workgroup
-    // against eight; m = 1024 / 1800 / 4096, plain norm): k = 4, d = 1 1.1 / 1.6 / 1.9 against 2.2; k = 8, d = 1 1.4 / 2.7 /
-    // 2.8 against 2.5; k = 16, d = 1 2.0 / 3.7 / 4.8 against 2.8; k = 8, d = 4 2.6 / 6.2 / 6.6 against 3.4; k = 16, d = 4
-    // 4.4 / 8.7 / 11.8 against 4.5.  (dF/dC)^T passes: k = 4, d = 1 1.6 / 2.4 / 2.9 against 2.5; k = 16, d = 1 2.9 / 4.8 /
-    // 7.2 against 3.2; k = 16, d = 4 6.9 / 12.0 / 19.1 against 5.8.  Batched launches hide the exchange behind other layers
+    // Up to 16 vectors for each of PT threads one workgroup alone needs no exchange through memory (2.6 to 4.8 us a pass in a team of
+    // eight whatever m is), but walks through all vectors itself.  Where the lines lie (us per evaluation, one workgroup against
+    // eight; m = 1024 / 1500 / 2048 / 3072 / 4096, plain norm): k = 4, d = 1 0.95 / 1.0 / 1.3 / 1.4 / 1.7 against 2.3; k = 8, d = 1 1.4 / 1.6 /
+    // 1.8 / 2.3 / 2.6 against 2.6; k = 16, d = 1 2.1 / 2.4 / 2.9 / 3.7 / 4.5 against 2.9 to 3.1; k = 8, d = 2 2.0 / 2.4 / 2.9 / 3.7 / 4.6 against
+    // 2.9 to 3.1 (squared energy 1.7 / 2.0 / 2.3 / 2.8 / 3.3); k = 4, d = 4 1.7 / 2.0 / 2.3 / 2.9 / 3.4 against 3.0; k = 8, d = 4 2.5 / 2.9 / 3.6 /
+    // 4.8 / 5.8 against 3.2 to 3.4; k = 16, d = 2 3.3 / 4.1 / 5.0 / 6.7 / 8.5 against 3.6 to 4.0; k = 16, d = 4 4.3 / 5.4 / 6.5 / 8.6 / 11.0 against
+    // 4.4 to 4.8.  Jacobian-free backward, whole launch: k = 4, d = 1 8.1 / 8.6 / 8.7 / 10.1 / 11.0 against 8.6; k = 8, d = 1 8.8 / 10.9 /
+    // 10.4 / 12.6 / 14.3 against 8.6; k = 16, d = 1 11.5 / 12.9 / 15.4 / 18.9 / 22.5 against 9.6 to 10.3; k = 16, d = 4 23 / 30 / 33 / 43 / 53 against 12.6 to 15.6.
+    // Batched launches hide the exchange behind other layers
     // and keep one workgroup, as do the modes that are solved in one place, and calls whose result nobody may wait for
     // (idkm_forward_noalloc).  One workgroup waits for nobody: a team that gave up a wait is solved again by one (`alone`).
     if (m <= (int64_t)16 * PT) {
@@ -454,11 +457,11 @@ bool plan_small(idkm_ctx* ctx, bool bwd, PersistPlan* pp, const void* dwq, int m
         const int kd = K * d;
         int from = 99;  // vectors per thread from which the team of eight is faster
         if (bwd)
-            from = kd >= 64 ? 4 : kd >= 16 ? 5 : (kd >= 8 && K > 2) ? 8 : kd >= 4 ? 12 : 99;
+            from = kd >= 16 ? 4 : (kd >= 8 && K > 2) ? 6 : kd >= 4 ? 10 : 99;
         else if (K >= 8)
-            from = kd >= 32 ? 5 : kd >= 16 ? 6 : 8;
+            from = kd >= 64 ? 5 : kd >= 32 ? (K == 16 ? 6 : 8) : kd >= 16 ? (K == 16 ? 8 : 12) : 99;
         else if (kd >= 16)
-            from = 12;
+            from = 14;
         const bool one = alone || ctx->sink || ctx->res_on_device || !ctx->tree_exchange || mode == IDKM_BWD_DENSE || mode == IDKM_BWD_GMRES;
         g = (!one && v >= from) ? DIES : 1;
         pp->small_team = g > 1;
