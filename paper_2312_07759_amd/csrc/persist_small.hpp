@@ -599,7 +599,7 @@ __device__ __forceinline__ bool tree_grid_totals(const PArgs& pa, unsigned int s
 // The shapes whose passes leave at most 8 sums per workgroup (k = 2 and k = 4 with scalar weights in the forward loop, k d <= 8
 // in the backward passes) take the two-level exchange without a detour through LDS on the sending side: every
 // WAVEFRONT reduces its lanes' sums to one value each (the halving network inside rows of 16 lanes, then two row
-// swaps) and stores its own 8 words; the leader adds 4 wavefronts x up to 32 workgroups, again across lanes, and hop
+// swaps) and stores its own 8 words; the leader adds the 4 or 8 wavefronts of up to 32 workgroups, again across lanes, and hop
 // 2 runs inside wavefront 0 of every workgroup.  Slot p of a line holds accumulator slot_acc(p) (the order in which
 // the halving network leaves them in the lanes); unused slots carry zeros.
 __host__ __device__ constexpr int slot_acc(int p) { return (p & 1) * 4 + ((p >> 1) & 1) * 2 + ((p >> 2) & 1); }
@@ -832,6 +832,14 @@ __device__ __forceinline__ void tile_pass(const Args& a, const float* s_w, const
 #pragma unroll
             for (int u = 0; u < UNR; ++u) one(it + u * NT);
         }
+        if constexpr (UNR >= 4) {
+            // (two left over side by side, not one after the other)
+            if (it + NT < cnt) {
+                one(it);
+                one(it + NT);
+                it += 2 * NT;
+            }
+        }
         for (; it < cnt; it += NT) one(it);
     };
     if constexpr (Item::RATIO && !SHARED) {
@@ -852,23 +860,6 @@ __device__ __forceinline__ void tile_pass(const Args& a, const float* s_w, const
     }
     if constexpr (FWD_LIKE) {
         sweep_forward(one);
-    } else if constexpr (PASS == PASS_B2 && K <= 4 && D == 1 && !SHARED) {
-        // the pass an implicit solve repeats, scalar weights: straight blocks of 36 vectors per lane while they last (C3:
-        // the whole tile), then of UNR, of 4, and single vectors (6.29 -> 6.06 us per pass at C3 against blocks of 12)
-        int it = threadIdx.x;
-        for (; it + 35 * NT < cnt; it += 36 * NT) {
-#pragma unroll
-            for (int u = 0; u < 36; ++u) one(it + u * NT);
-        }
-        for (; it + (UNR - 1) * NT < cnt; it += UNR * NT) {
-#pragma unroll
-            for (int u = 0; u < UNR; ++u) one(it + u * NT);
-        }
-        for (; it + 3 * NT < cnt; it += 4 * NT) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) one(it + u * NT);
-        }
-        for (; it < cnt; it += NT) one(it);
     } else {
         // the backward passes carry more state per vector; a plainly unrolled loop schedules them better (measured)
 #pragma unroll UNR
