@@ -159,6 +159,9 @@ idkm_status idkm_forward(idkm_ctx* ctx, const float* W, int64_t m, int32_t d, co
  *       g <- alpha (v + (dF/dC*)^T g) + (1-alpha) g,  g_0 = v,
  *   stopped when ||g+ - g||_F <= tol ||v||_F or after max_iter passes; a non-finite step or a step norm
  *   that grows on 5 consecutive passes restarts from g = v with alpha halved (at most 6 times).
+ *   Small codebooks (k <= 8 with d = 1, k <= 4 with d = 2 and, squared energy, 4, k = 2) form (dF/dC*)^T once, as a k d x k d
+ *   matrix in the pass that computes v, and take the steps of this iteration and of IDKM_BWD_GMRES on it in float64:
+ *   two passes over W in total; info.iters still counts the steps.
  *   IDKM_BWD_JFB sets g = v (no pass).  IDKM_BWD_DENSE forms dF/dC* explicitly (the k x k matrix of Sec. 4.2,
  *   k d x k d in general) in the same pass that computes v and solves (I - dF/dC*)^T g = v by Gaussian
  *   elimination in float64: two passes over W in total, tol / max_iter / alpha are ignored, info.iters = 0 and
