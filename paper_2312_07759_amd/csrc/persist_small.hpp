@@ -869,8 +869,8 @@ __device__ __forceinline__ void tile_pass(const Args& a, const float* s_w, const
 }
 
 // The same pass for a layer that does not fit the chip's LDS: W (and dL/dWq) are read from memory in every pass, 16
-// bytes per lane and load, with the loads of the next batch in flight while the current one is worked on (one
-// wavefront per SIMD has nothing else to hide their latency with).  The workgroups of the team take 4 KB blocks in
+// bytes per lane and load, with the loads of the next batch in flight while the current one is worked on (one or two
+// wavefronts per SIMD have little else to hide their latency with).  The workgroups of the team take blocks of 16 bytes a thread in
 // turn (block t G + wg in round t), so that at any moment the team reads one contiguous window of memory: with a
 // contiguous share per workgroup and a power-of-two layer, all workgroups would hit the same memory channel.
 // gw, gg: the whole tensors, 16-byte aligned.
