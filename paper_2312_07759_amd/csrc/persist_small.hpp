@@ -1829,9 +1829,11 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
     }
     __syncthreads();
     {
-        if (mode == BWD_GMRES && !s_done) {
+        // (the branches around the barriers here and below must not ask for s_done, which wavefront 0 may already have set while
+        // another wavefront has yet to read it: that one would pass a barrier less and start the last pass on half-written h)
+        if (mode == BWD_GMRES) {
             // from g = 0: the first residual is v itself, the first basis vector v / ||v||  (every workgroup holds v)
-            if (tid < 64) {
+            if (tid < 64 && !s_done) {
                 double v2 = 0.0;
                 if (tid < KD) v2 = s_v[tid] * s_v[tid];
                 v2 = first_lanes_sum_d_dpp<KD>(v2);
@@ -1874,8 +1876,8 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
         r_rn = s_rn[tid / D];
     }
     if constexpr (HAS_PAIRS) {
-        if (pairs && !s_done) {
-            if (tid < 64) {
+        if (pairs) {
+            if (tid < 64 && !s_done) {
                 if (mode == BWD_GMRES) {
                     const double vn = fast_sqrt_d(vnorm2);
                     wave_lds_sync();
@@ -1899,12 +1901,11 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
                     }
                 }
                 if (tid < KD) set_h((float)(r_g * r_rn));
-                if (tid == 0) s_done = 1;
             }
             __syncthreads();
         }
     }
-    while (!s_done) {
+    while (!pairs && !s_done) {
         IDKM_STAMP(0);
         any_tile_pass<NT, K, D, DIST, PASS_B2, SHARED, GLOBALW, RAG>(a, pa, s_w, s_gt, base, cnt, s_Cf, s_Hs, s_Ff, accr, BTAB ? s_tabB : nullptr);
         IDKM_STAMP(1);

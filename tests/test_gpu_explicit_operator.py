@@ -129,3 +129,27 @@ def test_divergence_restarts_with_half_the_step(ctx, k, seed):
     ref = orc.backward(W, C, tau, wl.DIST_L2, G, "implicit", tol=1e-6, max_iter=400)
     assert not b["info"].converged and b["info"].alpha == ref["alpha"] == 1.0 / 64 and b["info"].iters == ref["iters"]
     assert rel(ctx.get_cotangents(k, 1)[1], ref["g"]) < 1e-3 and rel(b["dW"].cpu().numpy(), ref["dW"]) < 1e-3
+
+
+@pytest.mark.parametrize("k,d,mode,n", [(2, 1, "implicit", 1), (4, 1, "implicit", 1), (2, 1, "gmres", 3), (8, 1, "implicit", 3)])
+def test_every_wavefront_waits_for_the_solve(k, d, mode, n):
+    """A solve of one to three steps is over before a workgroup's other wavefronts have looked whether there is one: they have to
+    wait for its h all the same.  Many workgroups on a compute unit (batched launches), the same rows call after call."""
+    mode = binding.BWD_IMPLICIT if mode == "implicit" else binding.BWD_GMRES
+    sizes = [300 + 97 * i for i in range(64)]
+    layers = [tuple(x.astype(np.float32) for x in wl.random_problem(m, d, k, seed=m, std=0.7, spread=0.7)) for m in sizes]
+    layers[5][2][:] = 0.0                    # v = 0: there is nothing to solve
+    b = binding.Batch(len(sizes))
+    try:
+        f = b.forward([(dev(W), dev(C0)) for W, C0, _ in layers], 0.15, 0.0, 3, wl.DIST_SQL2)
+        G = [dev(g) for _, _, g in layers]
+        first = [x["dW"].clone() for x in b.backward(G, mode, tol=1e-30, max_iter=n)]
+        for (W, _, g), fw, dW in zip(layers, f, first):
+            if mode == binding.BWD_IMPLICIT:
+                ref = orc.backward(W, fw["C"].cpu().numpy(), 0.15, wl.DIST_SQL2, g, "implicit", tol=0.0, max_iter=n)["dW"]
+                assert rel(dW.cpu().numpy(), ref) < 1e-4
+        assert not first[5].any()
+        for _ in range(20):
+            assert all(torch.equal(x["dW"], y) for x, y in zip(b.backward(G, mode, tol=1e-30, max_iter=n), first))
+    finally:
+        b.close()
