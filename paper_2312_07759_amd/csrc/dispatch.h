@@ -30,8 +30,12 @@ struct PersistFns {
     PersistBatchFn batch = nullptr;
     bool matrix = false;  // matrix-core kernel: tile padded by 16 vectors plus one float per vector, `threads` per workgroup
     int threads = 0;
+    // backward: the kernels that form the operator as a matrix and solve on it (empty where its sums do not fit an exchange line)
+    PersistFn pairs = nullptr;
+    PersistBatchFn pairs_batch = nullptr;
 };
-// Persistent forward / backward solve for the lane<->vector family; empty if K (D+1) > 32.
+// Persistent forward / backward solve for the lane<->vector family, energy variants 0 and 1; empty for other shapes than
+// K in {2,4,8,16}, D in {1,2,4}.
 PersistFns persist_kernel_0(int K, int D, bool bwd);
 PersistFns persist_kernel_1(int K, int D, bool bwd);
 // The same for a codebook of K/2 < k < K codewords in the kernels for K codewords (K in {4,8,16}); teams of one, or

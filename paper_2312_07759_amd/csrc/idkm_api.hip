@@ -207,8 +207,10 @@ idkm_status fail(idkm_ctx* ctx, idkm_status s, const std::string& msg) {
 #define HIP_TRY(ctx, expr)                                                                         \
     do {                                                                                           \
         hipError_t e_ = (expr);                                                                    \
-        if (e_ != hipSuccess)                                                                      \
+        if (e_ != hipSuccess) {                                                                    \
+            (void)hipGetLastError(); /* or the next launch's check would find it again */          \
             return fail(ctx, IDKM_ERR_DEVICE, std::string(#expr) + ": " + hipGetErrorString(e_)); \
+        }                                                                                          \
     } while (0)
 
 // Distance between two 32-bit words (not of one array), in words.
@@ -304,8 +306,10 @@ idkm_status ensure_partials(idkm_ctx* ctx, size_t need) {
         ctx->partials = nullptr;
         ctx->partials_cap = 0;
     }
-    if (hipMalloc(&ctx->partials, need * sizeof(double)) != hipSuccess)
+    if (hipMalloc(&ctx->partials, need * sizeof(double)) != hipSuccess) {
+        (void)hipGetLastError();
         return fail(ctx, IDKM_ERR_ALLOC, "hipMalloc of the partial-sum buffer failed");
+    }
     // stamped words: sequence number 0 is never used, so a cleared buffer holds no valid word
     HIP_TRY(ctx, hipMemset(ctx->partials, 0, need * sizeof(double)));
     ctx->partials_cap = need;
@@ -419,8 +423,19 @@ struct LaneBuf {
     size_t words() const { return buf1() + 2 * buf3 + PT; }
 };
 
+// Bytes of static LDS of a kernel (all of a compute unit's if the runtime does not say).
+size_t static_lds_of(idkm_ctx* ctx, const void* fn) {
+    size_t& fixed = ctx->static_lds[fn];
+    if (fixed == 0) {
+        hipFuncAttributes at;
+        fixed = (hipFuncGetAttributes(&at, fn) == hipSuccess) ? at.sharedSizeBytes : LDS_PER_CU;
+        (void)hipGetLastError();
+    }
+    return fixed;
+}
+
 // The lane<->vector family's part of plan_persistent.
-bool plan_small(idkm_ctx* ctx, bool bwd, PersistPlan* pp, const void* dwq, int mode, bool alone) {
+bool plan_small(idkm_ctx* ctx, bool bwd, PersistPlan* pp, const void* dwq, int mode, int max_iter, bool alone) {
     const int k = ctx->k, d = ctx->d;
     const int64_t m = ctx->m;
     // A codebook whose size is not a power of two runs in the kernels for the next one, the surplus codewords' weights held
@@ -477,8 +492,21 @@ bool plan_small(idkm_ctx* ctx, bool bwd, PersistPlan* pp, const void* dwq, int m
     pp->grid = (int)((m + per - 1) / per);
     pp->per = (int)per;
     pp->lds = ctx->sink ? (size_t)per * d * sizeof(float) : lds;  // (a batched backward keeps dL/dWq in memory)
-    if (ragged && (lds > ctx->tile_limit || (pp->grid > 1 && pp->grid < TREE_MIN_G))) return false;
-    if (lds > ctx->tile_limit) {
+    // The operator as a matrix: for the modes that solve a system, where every workgroup receives the totals and where it pays.
+    const bool matrix = bwd && (mode == IDKM_BWD_IMPLICIT || mode == IDKM_BWD_GMRES) && pair_shape(K, d, ctx->dist) &&
+                        pair_solve_pays(K, d, max_iter) && (pp->grid == 1 || (ctx->tree_exchange && pp->grid >= TREE_MIN_G));
+    if (matrix && lds <= ctx->tile_limit) {
+        // (its kernel has more static LDS than the one that runs pass by pass, up to 10 KB with many sums; where the tile, and the
+        // state of a Krylov solve behind it, no longer fit beside it, the passes serve the call)
+        const size_t state = mode == IDKM_BWD_GMRES ? 16 + gm_state_bytes(K * d, gm_basis_length(ctx->gmres_basis, k * d)) : 0;
+        if (pp->lds + state + static_lds_of(ctx, (const void*)fs.pairs) <= LDS_PER_CU) {
+            pp->fn = fs.pairs;
+            pp->fn_batch = fs.pairs_batch;
+        }
+    }
+    const bool fits = lds <= ctx->tile_limit && pp->lds + static_lds_of(ctx, (const void*)pp->fn) <= LDS_PER_CU;
+    if (ragged && (!fits || (pp->grid > 1 && pp->grid < TREE_MIN_G))) return false;
+    if (!fits) {
         // the layer does not fit on chip: the same solve with W (and dL/dWq) read from memory in every pass.  Not
         // inside a batched launch (such a layer fills the device on its own), and only from 16-byte aligned tensors.
         const PersistFns fg = persist_kernel_global(k, d, ctx->dist, bwd);
@@ -491,7 +519,7 @@ bool plan_small(idkm_ctx* ctx, bool bwd, PersistPlan* pp, const void* dwq, int m
         // up to k = 4 and up to 20 % slower here beyond (k = 8 and 16, 133 / 148 and 223 / 253 for a Jacobian-free call): the
         // stream path unless the caller asks for this one.
         if (!fg.one || ctx->sink || !aligned || (bwd && ctx->path != IDKM_PATH_PERSISTENT)) return false;
-        pp->fn = fg.one;
+        pp->fn = matrix ? fg.pairs : fg.one;
         pp->fn_batch = nullptr;
         pp->threads = global_threads(k, d, bwd);
         pp->lds = 0;
@@ -503,14 +531,14 @@ bool plan_small(idkm_ctx* ctx, bool bwd, PersistPlan* pp, const void* dwq, int m
 // matrix_ok: the matrix-core kernels may serve the call (every pass of both energies has a matrix-core form).
 // dwq: the backward's upstream gradient (a layer too large for LDS is streamed from memory with 16-byte loads, which
 // W and dL/dWq must allow).
-// mode: the backward's (BWD_JFB where there is none).  alone: small layers in one workgroup.
+// mode, max_iter: the backward's (BWD_JFB where there is none).  alone: small layers in one workgroup.
 bool plan_persistent(idkm_ctx* ctx, bool bwd, PersistPlan* pp, bool matrix_ok = true, const void* dwq = nullptr, int mode = IDKM_BWD_JFB,
-                     bool alone = false) {
+                     int max_iter = 1, bool alone = false) {
     pp->small_team = false;
     if (!ctx->coop || ctx->num_cu < 1) return false;
     const int k = ctx->k, d = ctx->d;
     const int64_t m = ctx->m;
-    if (plan_small(ctx, bwd, pp, dwq, mode, alone)) return true;
+    if (plan_small(ctx, bwd, pp, dwq, mode, max_iter, alone)) return true;
     pp->small_team = false;
     if (!(k >= 2 && k <= 16 && pow2(k) && d <= 4)) {
         // lane<->codeword family
@@ -548,13 +576,7 @@ bool plan_persistent(idkm_ctx* ctx, bool bwd, PersistPlan* pp, bool matrix_ok = 
             // tile padded by 16 vectors, then one float per vector (dL/dWq is not kept); these kernels hold more
             // static LDS than the vector-ALU ones.  A tile too large for what is left goes to the vector-ALU kernel.
             const size_t lds_m = (size_t)(per + 16) * (d + 1) * sizeof(float);
-            size_t& fixed = ctx->static_lds[(const void*)fl.one];
-            if (fixed == 0) {
-                hipFuncAttributes at;
-                fixed = (hipFuncGetAttributes(&at, (const void*)fl.one) == hipSuccess) ? at.sharedSizeBytes : LDS_PER_CU;
-                (void)hipGetLastError();
-            }
-            if (fixed + lds_m <= LDS_PER_CU) {
+            if (static_lds_of(ctx, (const void*)fl.one) + lds_m <= LDS_PER_CU) {
                 pp->fn = fl.one;
                 pp->fn_batch = fl.batch;
                 pp->grid = (int)((m + per - 1) / per);
@@ -571,13 +593,7 @@ bool plan_persistent(idkm_ctx* ctx, bool bwd, PersistPlan* pp, bool matrix_ok = 
         if (!pp->fn) return false;
         size_t most = LANE_TILE_MAX;
         if (row8) {
-            size_t& fixed = ctx->static_lds[(const void*)pp->fn];
-            if (fixed == 0) {
-                hipFuncAttributes at;
-                fixed = (hipFuncGetAttributes(&at, (const void*)pp->fn) == hipSuccess) ? at.sharedSizeBytes : LDS_PER_CU;
-                (void)hipGetLastError();
-            }
-            most = std::min(most, LDS_PER_CU - std::min(fixed, LDS_PER_CU));
+            most = std::min(most, LDS_PER_CU - std::min(static_lds_of(ctx, (const void*)pp->fn), LDS_PER_CU));
         }
         if (lds > most) return false;
         pp->grid = (int)((m + per - 1) / per);
@@ -1022,7 +1038,7 @@ idkm_status idkm_forward(idkm_ctx* ctx, const float* W, int64_t m, int32_t d, co
                 if (ctx->defer_wait) return IDKM_OK;
                 st = finish_persistent(ctx, info);
             }
-            again = st == IDKM_ERR_DEVICE && pp.small_team && plan_persistent(ctx, false, &pp, true, nullptr, IDKM_BWD_JFB, true);
+            again = st == IDKM_ERR_DEVICE && pp.small_team && plan_persistent(ctx, false, &pp, true, nullptr, IDKM_BWD_JFB, 1, true);
             if (again) ctx->err.clear();
         }
         // Under IDKM_PATH_AUTO a persistent attempt that could not run to its end -- the grid was not co-resident
@@ -1166,7 +1182,7 @@ idkm_status idkm_backward(idkm_ctx* ctx, const float* dWq, idkm_bwd_mode mode, f
     }
 
     PersistPlan pp;
-    bool persistent = ctx->path != IDKM_PATH_STREAM && plan_persistent(ctx, true, &pp, true, dWq, (int)mode);
+    bool persistent = ctx->path != IDKM_PATH_STREAM && plan_persistent(ctx, true, &pp, true, dWq, (int)mode, (int)max_iter);
     // The minimal-residual solve keeps O(k d R) state.  Inside the persistent kernel every workgroup holds all of it
     // (in LDS, behind its tiles), which takes a team where every workgroup receives the grid totals (one workgroup, or
     // the two-level exchange of a full-device team), k d <= 64 and room for the state beside the tiles; everything
@@ -1177,16 +1193,10 @@ idkm_status idkm_backward(idkm_ctx* ctx, const float* dWq, idkm_bwd_mode mode, f
         persistent = !pp.lane && kd <= 64 && (pow2(ctx->k) || ctx->path == IDKM_PATH_AUTO) &&
                      (pp.grid == 1 || (ctx->tree_exchange && !ctx->sink && pp.grid >= TREE_MIN_G));
         if (persistent) {
-            size_t& fixed = ctx->static_lds[(const void*)pp.fn];
-            if (fixed == 0) {
-                hipFuncAttributes at;
-                fixed = (hipFuncGetAttributes(&at, (const void*)pp.fn) == hipSuccess) ? at.sharedSizeBytes : LDS_PER_CU;
-                (void)hipGetLastError();
-            }
             gm_off = (unsigned int)((pp.lds + 15) / 16 * 16);
             // (the kernel's rows are as long as its padded codebook; the basis has one vector per unknown at most)
             const size_t lds = gm_off + gm_state_bytes(pow2_at_least(ctx->k) * ctx->d, gm_basis_length(ctx->gmres_basis, kd));
-            if (fixed + lds <= LDS_PER_CU)
+            if (static_lds_of(ctx, (const void*)pp.fn) + lds <= LDS_PER_CU)
                 pp.lds = lds;
             else
                 persistent = false;
@@ -1215,7 +1225,7 @@ idkm_status idkm_backward(idkm_ctx* ctx, const float* dWq, idkm_bwd_mode mode, f
                     if (ctx->defer_wait) return IDKM_OK;
                     st = finish_persistent(ctx, info);
                 }
-                again = st == IDKM_ERR_DEVICE && pp.small_team && plan_persistent(ctx, true, &pp, true, dWq, (int)mode, true);
+                again = st == IDKM_ERR_DEVICE && pp.small_team && plan_persistent(ctx, true, &pp, true, dWq, (int)mode, (int)max_iter, true);
                 if (again) ctx->err.clear();
             }
             if (st != IDKM_ERR_DEVICE || ctx->path != IDKM_PATH_AUTO) return st;

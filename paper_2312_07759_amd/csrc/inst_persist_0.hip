@@ -6,8 +6,13 @@ namespace idkm {
 
 template <int K, int D>
 static PersistFns pick(bool bwd) {
-    return bwd ? PersistFns{persist_bwd<K, D, 0>, persist_bwd_batch<K, D, 0>}
-               : PersistFns{persist_fwd<K, D, 0>, persist_fwd_batch<K, D, 0>};
+    if (!bwd) return PersistFns{persist_fwd<K, D, 0>, persist_fwd_batch<K, D, 0>};
+    PersistFns f{persist_bwd<K, D, 0>, persist_bwd_batch<K, D, 0>};
+    if constexpr (pair_shape(K, D, 0)) {
+        f.pairs = persist_bwd<K, D, 0, false, true>;
+        f.pairs_batch = persist_bwd_batch<K, D, 0, false, true>;
+    }
+    return f;
 }
 
 // Offered for every shape of the lane<->vector family: K (D+1) <= 80 sums per workgroup.

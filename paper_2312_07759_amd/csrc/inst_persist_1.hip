@@ -6,8 +6,13 @@ namespace idkm {
 
 template <int K, int D>
 static PersistFns pick(bool bwd) {
-    return bwd ? PersistFns{persist_bwd<K, D, 1>, persist_bwd_batch<K, D, 1>}
-               : PersistFns{persist_fwd<K, D, 1>, persist_fwd_batch<K, D, 1>};
+    if (!bwd) return PersistFns{persist_fwd<K, D, 1>, persist_fwd_batch<K, D, 1>};
+    PersistFns f{persist_bwd<K, D, 1>, persist_bwd_batch<K, D, 1>};
+    if constexpr (pair_shape(K, D, 1)) {
+        f.pairs = persist_bwd<K, D, 1, false, true>;
+        f.pairs_batch = persist_bwd_batch<K, D, 1, false, true>;
+    }
+    return f;
 }
 
 // Offered for every shape of the lane<->vector family: K (D+1) <= 80 sums per workgroup.

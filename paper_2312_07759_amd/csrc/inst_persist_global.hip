@@ -4,11 +4,16 @@
 
 namespace idkm {
 
+template <int K, int D, int DIST>
+static PersistFns pick_dist(bool bwd) {
+    if (!bwd) return PersistFns{persist_fwd_global<K, D, DIST>, nullptr};
+    PersistFns f{persist_bwd_global<K, D, DIST>, nullptr};
+    if constexpr (pair_shape(K, D, DIST)) f.pairs = persist_bwd_global<K, D, DIST, true>;
+    return f;
+}
 template <int K, int D>
 static PersistFns pick(int dist, bool bwd) {
-    if (dist == DIST_L2)
-        return bwd ? PersistFns{persist_bwd_global<K, D, DIST_L2>, nullptr} : PersistFns{persist_fwd_global<K, D, DIST_L2>, nullptr};
-    return bwd ? PersistFns{persist_bwd_global<K, D, DIST_SQL2>, nullptr} : PersistFns{persist_fwd_global<K, D, DIST_SQL2>, nullptr};
+    return dist == DIST_L2 ? pick_dist<K, D, DIST_L2>(bwd) : pick_dist<K, D, DIST_SQL2>(bwd);
 }
 
 PersistFns persist_kernel_global(int K, int D, int dist, bool bwd) {

@@ -6,8 +6,13 @@ namespace idkm {
 
 template <int K, int D>
 static PersistFns pick(bool bwd) {
-    return bwd ? PersistFns{persist_bwd<K, D, 0, true>, persist_bwd_batch<K, D, 0, true>}
-               : PersistFns{persist_fwd<K, D, 0, true>, persist_fwd_batch<K, D, 0, true>};
+    if (!bwd) return PersistFns{persist_fwd<K, D, 0, true>, persist_fwd_batch<K, D, 0, true>};
+    PersistFns f{persist_bwd<K, D, 0, true>, persist_bwd_batch<K, D, 0, true>};
+    if constexpr (pair_shape(K, D, 0)) {
+        f.pairs = persist_bwd<K, D, 0, true, true>;
+        f.pairs_batch = persist_bwd_batch<K, D, 0, true, true>;
+    }
+    return f;
 }
 
 PersistFns persist_kernel_ragged_0(int K, int D, bool bwd) {

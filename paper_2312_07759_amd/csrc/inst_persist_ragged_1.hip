@@ -6,8 +6,13 @@ namespace idkm {
 
 template <int K, int D>
 static PersistFns pick(bool bwd) {
-    return bwd ? PersistFns{persist_bwd<K, D, 1, true>, persist_bwd_batch<K, D, 1, true>}
-               : PersistFns{persist_fwd<K, D, 1, true>, persist_fwd_batch<K, D, 1, true>};
+    if (!bwd) return PersistFns{persist_fwd<K, D, 1, true>, persist_fwd_batch<K, D, 1, true>};
+    PersistFns f{persist_bwd<K, D, 1, true>, persist_bwd_batch<K, D, 1, true>};
+    if constexpr (pair_shape(K, D, 1)) {
+        f.pairs = persist_bwd<K, D, 1, true, true>;
+        f.pairs_batch = persist_bwd_batch<K, D, 1, true, true>;
+    }
+    return f;
 }
 
 PersistFns persist_kernel_ragged_1(int K, int D, bool bwd) {

@@ -146,16 +146,19 @@ __device__ __forceinline__ void raise_abort(const PArgs& pa) {
 // solve the workgroups' sums as well -- and under the plain norm at k = 5 the gradient was 2.1e-6 from the 64-bit one with
 // float32 totals, 1.2e-6 in those kernels, 0.7e-6 with float64 ones.
 // The others keep float32 words: an evaluation at k = 4, d = 1 takes 1.3 % longer with wide ones.
-template <int NACC, bool WIDE_ = false, int NT_ = PT>
+// NACC: sums of the kernel's widest pass; TREE: of the widest one that takes the two-level exchange.  Nothing here is larger than its
+// users need: the tiles get what is left of the compute unit's 160 KB.
+template <int NACC, bool WIDE_ = false, int NT_ = PT, int TREE = NACC>
 struct XShared {
     static constexpr bool WIDE = WIDE_;
     static constexpr int NT = NT_, WAVES = NT_ / 64;  // threads and wavefronts of the workgroup
+    static constexpr int RED = TREE <= 8 ? PT : (NT_ / TREE < 32 ? NT_ / TREE : 32) * TREE > PT ? (NT_ / TREE < 32 ? NT_ / TREE : 32) * TREE : PT;
     typedef typename std::conditional<WIDE_, double, float>::type total_t;
     float rpart[pow2_at_least(NACC)][WAVES];  // partial sums of every wavefront, [accumulator][wavefront]
-    double red2[NT];                 // reducer: per-thread sums (thread t: word t mod WPR, workgroups t/WPR + k PT/WPR)
+    double red2[RED];                // reducer: per-thread sums (thread t < PT: word t mod WPR, workgroups t/WPR + k PT/WPR)
     double tot[8];                   // reducer: totals of its slice
-    unsigned int bc[XBCAST];         // payloads of the broadcast words
-    total_t own[XLINE];              // this workgroup's own partial sums (read back directly by a team of one)
+    unsigned int bc[2 * NACC < XBCAST ? 2 * NACC : XBCAST];  // payloads of the broadcast words (k d and one per reducer)
+    total_t own[NACC < WAVES * 8 ? WAVES * 8 : NACC];  // this workgroup's own partial sums (read back directly by a team of one)
     int abort;
     // two-level exchange
     int local;                       // this workgroup runs on its leader's die: its partial sums need only reach the L2
@@ -387,7 +390,7 @@ __device__ __forceinline__ bool reduce_slice(const PArgs& pa, unsigned int seq, 
         }
     }
     IDKM_SUB(5);
-    xs.red2[tid] = s;
+    if (tid < PT) xs.red2[tid] = s;  // (g0 < GPT: no thread beyond has words)
     if (aborted) {
         xs.abort = 1;
         raise_abort(pa);
@@ -477,9 +480,9 @@ template <int NACC, class XS>
 __device__ __forceinline__ bool tree_die_totals(const PArgs& pa, unsigned int seq, XS& xs) {
     using Word = SumWords<XS::WIDE>;
     constexpr int LINE = xline_of(NACC) * Word::N;
-    constexpr int PARTS = XS::NT / NACC;             // member groups
-    constexpr int MPT = (32 + PARTS - 1) / PARTS;    // members per thread
-    static_assert(PARTS >= 1, "one thread per accumulator at least");
+    constexpr int PARTS = XS::NT / NACC < 32 ? XS::NT / NACC : 32;  // member groups
+    constexpr int MPT = (32 + PARTS - 1) / PARTS;                   // members per thread
+    static_assert(PARTS >= 1 && PARTS * NACC <= XS::RED, "one thread per accumulator at least");
     const int tid = threadIdx.x, x = pa.wg, q = tid % NACC, part = tid / NACC;
     const bool live = part < PARTS;
     const int nmem = (pa.G - x + DIES - 1) / DIES;  // members of this die, the leader included; <= 32
@@ -1563,7 +1566,11 @@ __device__ __forceinline__ int gmres_step(const GmView<N>& gm, U u, const double
 // Backward (Alg. 2 per-layer steps): v, the averaged fixed-point iteration of
 // Sec. 4.2 for g (skipped for JFB), and dW, in one launch.  RAG: as in the forward; the components of v, g and h that
 // belong to no codeword are zero throughout.
-template <int NT, int K, int D, int DIST, bool SHARED, bool GLOBALW = false, bool RAG = false>
+// PAIRS: the operator is formed once, as a matrix (pairs.hpp), and the solve runs on it: BWD_IMPLICIT and BWD_GMRES of the
+// codebooks pair_shape() admits, a team of one or with the two-level exchange.  A kernel of its own: its 22 to 120 sums take registers
+// and LDS that the other modes' kernel would carry for nothing (in one kernel k = 8, plain norm, batched, 153 -> 254 registers, three workgroups
+// of a compute unit -> two).
+template <int NT, int K, int D, int DIST, bool SHARED, bool GLOBALW = false, bool RAG = false, bool PAIRS = false>
 __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa) {
     constexpr int KD = K * D;
     constexpr int KPR = (8 / D) > K ? K : (8 / D);  // codewords per reducer: 8 words of D components
@@ -1574,14 +1581,13 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
     // explicit-Jacobian mode (Eq. "grad", "inv" taken literally): offered when its K D (K D + D + 1) sums fit one
     // exchange line
     constexpr int NBJ = KD * KD + KD * D + KD;
-    constexpr bool HAS_DENSE = NBJ <= XDENSE && !RAG;
-    // the averaged iteration and the Krylov solve on the explicit operator (see pairs.hpp)
-    constexpr bool HAS_PAIRS = pair_shape(K, D, DIST);
-    constexpr int NBP = HAS_PAIRS ? pair_sums(K, D, DIST) : 1;
-    constexpr int NXS = (HAS_DENSE ? NBJ : KD) > NBP ? (HAS_DENSE ? NBJ : KD) : NBP;
+    constexpr bool HAS_DENSE = NBJ <= XDENSE && !RAG && !PAIRS;
+    static_assert(!PAIRS || pair_shape(K, D, DIST), "the sums of the pass do not fit an exchange line");
+    constexpr int NBP = PAIRS ? pair_sums(K, D, DIST) : 1;
+    constexpr int NXS = PAIRS ? NBP : HAS_DENSE ? NBJ : KD;
     extern __shared__ float s_tile[];
-    __shared__ XShared<NXS, RAG, NT> xs;
-    __shared__ double s_Fd[HAS_PAIRS ? KD : 1], s_A[HAS_PAIRS && KD <= 4 ? KD * KD : 1];
+    __shared__ XShared<NXS, RAG, NT, PAIRS ? NBP : KD> xs;
+    __shared__ double s_Fd[PAIRS ? KD : 1], s_A[PAIRS && KD <= 4 ? KD * KD : 1];
     __shared__ double s_v[KD], s_g[KD], s_rn[K];  // a reducer's own slice is the live one; s_rn = 1/(tau n)
     __shared__ float s_Cf[KD], s_Hs[KD], s_Hv[KD], s_Ff[KD];
     // product form of the (dF/dC)^T pass: its per-codeword operands (c_j - mu, -s^2 |c_j - mu|^2, mu, h_j . (F*_j - mu) / tau),
@@ -1617,7 +1623,7 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
     if (tid < KD) {
         s_Cf[tid] = a.Cf[src];
         s_Ff[tid] = a.Ff[src];
-        if (HAS_PAIRS) s_Fd[tid] = a.Fd[src];
+        if (PAIRS) s_Fd[tid] = a.Fd[src];
         s_Hs[tid] = 0.f;
         s_Hv[tid] = 0.f;
     }
@@ -1735,12 +1741,9 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
             dense_done = true;
         }
     }
-    // (every workgroup has to receive the totals)
-    const bool pairs = HAS_PAIRS && (mode == BWD_IMPLICIT || mode == BWD_GMRES) && (tree || pa.G == 1) &&
-                       pair_solve_pays(K, D, max_iter);
-    double row[HAS_PAIRS ? KD : 1];  // lane j d + r of wavefront 0: its row of (dF/dC)^T
-    if constexpr (HAS_PAIRS) {
-        if (pairs) {
+    double row[PAIRS ? KD : 1];  // lane j d + r of wavefront 0: its row of (dF/dC)^T
+    if constexpr (PAIRS) {
+        {
             float accp[NBP];
             any_tile_pass<NT, K, D, DIST, PASS_BP, SHARED, GLOBALW, RAG>(a, pa, s_w, s_gt, base, cnt, s_Cf, s_Hs, s_Ff, accp);
             ++seq;
@@ -1768,7 +1771,8 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
             __syncthreads();
         }
     }
-    if (!dense_done && !pairs) {
+    if constexpr (!PAIRS)
+    if (!dense_done) {
     // B1: v = dL/dC* with W fixed; the solve starts at g = v
     any_tile_pass<NT, K, D, DIST, PASS_B1, SHARED, GLOBALW, RAG>(a, pa, s_w, s_gt, base, cnt, s_Cf, s_Hs, s_Ff, acc);
     ++seq;
@@ -1813,7 +1817,8 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
     }
     }
     }
-    if (!(tree && !dense_done) && !pairs && !gather_bcast<KD, WPR, KD>(pa, seq, NB, !dense_done, xs)) return;
+    if constexpr (!PAIRS)
+        if (!(tree && !dense_done) && !gather_bcast<KD, WPR, KD>(pa, seq, NB, !dense_done, xs)) return;
     if (tid < KD) {
         set_h(__uint_as_float(xs.bc[tid]));
         s_Hv[tid] = __uint_as_float(xs.bc[tid]);
@@ -1875,8 +1880,8 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
         r_v = s_v[tid];
         r_rn = s_rn[tid / D];
     }
-    if constexpr (HAS_PAIRS) {
-        if (pairs) {
+    if constexpr (PAIRS) {
+        {
             if (tid < 64 && !s_done) {
                 if (mode == BWD_GMRES) {
                     const double vn = fast_sqrt_d(vnorm2);
@@ -1905,7 +1910,8 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
             __syncthreads();
         }
     }
-    while (!pairs && !s_done) {
+    if constexpr (!PAIRS)
+    while (!s_done) {
         IDKM_STAMP(0);
         any_tile_pass<NT, K, D, DIST, PASS_B2, SHARED, GLOBALW, RAG>(a, pa, s_w, s_gt, base, cnt, s_Cf, s_Hs, s_Ff, accr, BTAB ? s_tabB : nullptr);
         IDKM_STAMP(1);
@@ -2112,7 +2118,7 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
 
     // B3: dW = direct + (dF/dW)^T g
     any_tile_pass<NT, K, D, DIST, PASS_B3, SHARED, GLOBALW, RAG>(a, pa, s_w, s_gt, base, cnt, s_Cf, s_Hs, s_Ff, reinterpret_cast<float(&)[1]>(acc[0]));
-    if (dense_done || tree || pairs) {
+    if (dense_done || tree || PAIRS) {
         if (wg == 0 && tid < kd) {
             a.gd[tid] = s_g[tid];
             a.vd[tid] = s_v[tid];
@@ -2148,12 +2154,12 @@ __global__ __launch_bounds__(fwd_threads(K, D)) void persist_fwd(const Args a, c
     pa.G = gridDim.x;
     persist_fwd_body<fwd_threads(K, D), K, D, DIST, false, false, RAG>(a, pa);
 }
-template <int K, int D, int DIST, bool RAG = false>
+template <int K, int D, int DIST, bool RAG = false, bool PAIRS = false>
 __global__ __launch_bounds__(bwd_threads(K, D)) void persist_bwd(const Args a, const PArgs pa_in) {
     PArgs pa = pa_in;
     pa.wg = blockIdx.x;
     pa.G = gridDim.x;
-    persist_bwd_body<bwd_threads(K, D), K, D, DIST, false, false, RAG>(a, pa);
+    persist_bwd_body<bwd_threads(K, D), K, D, DIST, false, false, RAG, PAIRS>(a, pa);
 }
 
 // The same for a layer larger than the chip's LDS (W is read from memory in every pass; no dynamic LDS).
@@ -2164,12 +2170,12 @@ __global__ __launch_bounds__(global_threads(K, D, false)) void persist_fwd_globa
     pa.G = gridDim.x;
     persist_fwd_body<global_threads(K, D, false), K, D, DIST, false, true>(a, pa);
 }
-template <int K, int D, int DIST>
+template <int K, int D, int DIST, bool PAIRS = false>
 __global__ __launch_bounds__(global_threads(K, D, true)) void persist_bwd_global(const Args a, const PArgs pa_in) {
     PArgs pa = pa_in;
     pa.wg = blockIdx.x;
     pa.G = gridDim.x;
-    persist_bwd_body<global_threads(K, D, true), K, D, DIST, false, true>(a, pa);
+    persist_bwd_body<global_threads(K, D, true), K, D, DIST, false, true, false, PAIRS>(a, pa);
 }
 
 // Several independent problems of one shape (the layers of Alg. 2's loops) in one launch: item_of_wg maps a
@@ -2183,14 +2189,14 @@ __global__ __launch_bounds__(PT) void persist_fwd_batch(const BatchItem* items, 
     pa.G = it.wg_count;
     persist_fwd_body<PT, K, D, DIST, true, false, RAG>(a, pa);
 }
-template <int K, int D, int DIST, bool RAG = false>
+template <int K, int D, int DIST, bool RAG = false, bool PAIRS = false>
 __global__ __launch_bounds__(PT) void persist_bwd_batch(const BatchItem* items, const unsigned short* item_of_wg) {
     const BatchItem& it = items[item_of_wg[blockIdx.x]];
     const Args a = it.a;
     PArgs pa = it.p;
     pa.wg = (int)blockIdx.x - it.wg_begin;
     pa.G = it.wg_count;
-    persist_bwd_body<PT, K, D, DIST, true, false, RAG>(a, pa);
+    persist_bwd_body<PT, K, D, DIST, true, false, RAG, PAIRS>(a, pa);
 }
 
 }  // namespace idkm
