@@ -2180,8 +2180,21 @@ __global__ __launch_bounds__(global_threads(K, D, true)) void persist_bwd_global
 
 // Several independent problems of one shape (the layers of Alg. 2's loops) in one launch: item_of_wg maps a
 // workgroup to its problem; every team runs its own solve and leaves when that solve is over.
+// How many workgroups of 256 threads, one wavefront per SIMD each, a compute unit holds is 512 registers over those of the kernel,
+// and one register beyond a line can cost a launch of its own, a whole solve in series: the 21 tensors of ResNet18 at k = 4 took launches of
+// 1024 / 1280 / 826 workgroups with 96 registers (five workgroups, 574 us) and 1024 / 1024 / 944 / 138 with 97 (four, 662 us).  So the
+// lines are part of the kernels.  All but two compile below theirs by themselves: k = 5 to 7, d = 1, with the operator, take 170 and 173
+// registers if left alone and spill 6 and 11 under the line of 168, which gives the 21 tensors two launches fewer (implicit backward 402 -> 357
+// and 372 -> 333 us).  k = 8, d = 1 with the operator and the plain norm keeps two workgroups (120 sums, 254 registers).
+__host__ __device__ constexpr int fwd_batch_groups(int K, int D) {
+    return K <= 4 && D == 1 ? 5 : K * D <= 8 ? 4 : K * D <= 16 ? 3 : K <= 8 || D <= 2 ? 2 : 1;
+}
+__host__ __device__ constexpr int bwd_batch_groups(int K, int D, int dist, bool rag, bool pairs) {
+    return K * D <= 4 ? 4 : K * D <= 8 ? (K == 8 && pairs && !rag && dist == DIST_L2 ? 2 : 3)
+           : K * D <= 16 ? (D == 4 && dist == DIST_SQL2 && (rag || pairs) ? 3 : 2) : 1;
+}
 template <int K, int D, int DIST, bool RAG = false>
-__global__ __launch_bounds__(PT) void persist_fwd_batch(const BatchItem* items, const unsigned short* item_of_wg) {
+__global__ __launch_bounds__(PT, fwd_batch_groups(K, D)) void persist_fwd_batch(const BatchItem* items, const unsigned short* item_of_wg) {
     const BatchItem& it = items[item_of_wg[blockIdx.x]];
     const Args a = it.a;
     PArgs pa = it.p;
@@ -2190,7 +2203,7 @@ __global__ __launch_bounds__(PT) void persist_fwd_batch(const BatchItem* items, 
     persist_fwd_body<PT, K, D, DIST, true, false, RAG>(a, pa);
 }
 template <int K, int D, int DIST, bool RAG = false, bool PAIRS = false>
-__global__ __launch_bounds__(PT) void persist_bwd_batch(const BatchItem* items, const unsigned short* item_of_wg) {
+__global__ __launch_bounds__(PT, bwd_batch_groups(K, D, DIST, RAG, PAIRS)) void persist_bwd_batch(const BatchItem* items, const unsigned short* item_of_wg) {
     const BatchItem& it = items[item_of_wg[blockIdx.x]];
     const Args a = it.a;
     PArgs pa = it.p;

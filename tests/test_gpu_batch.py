@@ -168,3 +168,33 @@ def test_batch_argument_errors():
     assert lib.idkm_batch_context(b._h, 2) is None
     assert lib.idkm_batch_context(b._h, 1) is not None
     b.close()
+
+
+# (k, d, dist, workgroups of a forward launch that share a compute unit, of a Jacobian-free backward, of an implicit one)
+SHARE = [(2, 1, "sql2", 5, 4, 4), (4, 1, "sql2", 5, 4, 4), (4, 1, "l2", 5, 4, 4), (3, 1, "sql2", 5, 4, 4), (8, 1, "sql2", 4, 3, 3),
+         (8, 1, "l2", 4, 3, 2), (7, 1, "l2", 4, 3, 3), (4, 2, "l2", 4, 3, 3), (2, 4, "sql2", 4, 3, 3), (16, 1, "sql2", 3, 2, 2), (4, 4, "sql2", 3, 2, 2)]
+
+
+@pytest.mark.parametrize("k,d,dist,fwd,jfb,implicit", SHARE)
+def test_layers_that_share_the_compute_units_take_one_launch(k, d, dist, fwd, jfb, implicit):
+    """One register more than a line allows is a workgroup less on every compute unit, and a launch more for the batch: layers of
+    256 workgroups each, as many as the device holds."""
+    m = 300_001
+    D = wl.DIST_L2 if dist == "l2" else wl.DIST_SQL2
+    gen = torch.Generator(device="cuda").manual_seed(k + d)
+    layers, G = [], []
+    for _ in range(max(fwd, jfb, implicit)):
+        W = torch.randn((m, d), generator=gen, device="cuda") * 0.1
+        layers.append((W, W[:k].clone() + 0.01 * torch.randn((k, d), generator=gen, device="cuda")))
+        G.append(torch.randn((m, d), generator=gen, device="cuda"))
+    tau = 0.1 / k * (1.0 if dist == "l2" else 0.1)
+    b = binding.Batch(len(layers))
+    try:
+        out = b.forward(layers[:fwd], tau, 0.0, 3, D)
+        assert b.launches() == 1 and all(o["info"].path == binding.PATH_PERSISTENT for o in out)
+        b.forward(layers, tau, 0.0, 3, D)
+        for mode, n in ((binding.BWD_JFB, jfb), (binding.BWD_IMPLICIT, implicit)):
+            out = b.backward(G[:n], mode, tol=1e-6, max_iter=5)
+            assert b.launches() == 1 and all(o["info"].path == binding.PATH_PERSISTENT for o in out)
+    finally:
+        b.close()
