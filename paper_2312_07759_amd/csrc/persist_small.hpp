@@ -2186,15 +2186,15 @@ __global__ __launch_bounds__(global_threads(K, D, true)) void persist_bwd_global
 // lines are part of the kernels.  All but two compile below theirs by themselves: k = 5 to 7, d = 1, with the operator, take 170 and 173
 // registers if left alone and spill 6 and 11 under the line of 168, which gives the 21 tensors two launches fewer (implicit backward 402 -> 357
 // and 372 -> 333 us).  k = 8, d = 1 with the operator and the plain norm keeps two workgroups (120 sums, 254 registers).
-__host__ __device__ constexpr int fwd_batch_groups(int K, int D) {
-    return K <= 4 && D == 1 ? 5 : K * D <= 8 ? 4 : K * D <= 16 ? 3 : K <= 8 || D <= 2 ? 2 : 1;
+__host__ __device__ constexpr int fwd_batch_groups(int K, int D, int dist, bool rag) {
+    return K <= 4 && D == 1 ? 5 : K * D <= 8 ? 4 : K * D <= 16 ? (K == 8 && (dist == DIST_L2 || rag) ? 4 : 3) : K * D <= 32 ? 2 : 1;
 }
 __host__ __device__ constexpr int bwd_batch_groups(int K, int D, int dist, bool rag, bool pairs) {
     return K * D <= 4 ? 4 : K * D <= 8 ? (K == 8 && pairs && !rag && dist == DIST_L2 ? 2 : 3)
-           : K * D <= 16 ? (D == 4 && dist == DIST_SQL2 && (rag || pairs) ? 3 : 2) : 1;
+           : K * D <= 16 ? (D == 4 && dist == DIST_SQL2 && (rag || pairs) ? 3 : 2) : K * D <= 32 && !rag ? 2 : 1;
 }
 template <int K, int D, int DIST, bool RAG = false>
-__global__ __launch_bounds__(PT, fwd_batch_groups(K, D)) void persist_fwd_batch(const BatchItem* items, const unsigned short* item_of_wg) {
+__global__ __launch_bounds__(PT, fwd_batch_groups(K, D, DIST, RAG)) void persist_fwd_batch(const BatchItem* items, const unsigned short* item_of_wg) {
     const BatchItem& it = items[item_of_wg[blockIdx.x]];
     const Args a = it.a;
     PArgs pa = it.p;

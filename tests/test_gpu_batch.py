@@ -172,7 +172,8 @@ def test_batch_argument_errors():
 
 # (k, d, dist, workgroups of a forward launch that share a compute unit, of a Jacobian-free backward, of an implicit one)
 SHARE = [(2, 1, "sql2", 5, 4, 4), (4, 1, "sql2", 5, 4, 4), (4, 1, "l2", 5, 4, 4), (3, 1, "sql2", 5, 4, 4), (8, 1, "sql2", 4, 3, 3),
-         (8, 1, "l2", 4, 3, 2), (7, 1, "l2", 4, 3, 3), (4, 2, "l2", 4, 3, 3), (2, 4, "sql2", 4, 3, 3), (16, 1, "sql2", 3, 2, 2), (4, 4, "sql2", 3, 2, 2)]
+         (8, 1, "l2", 4, 3, 2), (7, 1, "l2", 4, 3, 3), (4, 2, "l2", 4, 3, 3), (2, 4, "sql2", 4, 3, 3), (16, 1, "sql2", 3, 2, 2), (4, 4, "sql2", 3, 2, 2),
+         (8, 2, "l2", 4, 2, 2), (8, 2, "sql2", 3, 2, 2), (6, 2, "sql2", 4, 2, 2), (16, 2, "l2", 2, 2, 2), (8, 4, "sql2", 2, 2, 2)]
 
 
 @pytest.mark.parametrize("k,d,dist,fwd,jfb,implicit", SHARE)
