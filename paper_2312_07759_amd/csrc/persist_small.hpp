@@ -158,12 +158,12 @@ struct XShared {
     double red2[RED];                // reducer: per-thread sums (thread t < PT: word t mod WPR, workgroups t/WPR + k PT/WPR)
     double tot[8];                   // reducer: totals of its slice
     unsigned int bc[2 * NACC < XBCAST ? 2 * NACC : XBCAST];  // payloads of the broadcast words (k d and one per reducer)
-    total_t own[NACC < WAVES * 8 ? WAVES * 8 : NACC];  // this workgroup's own partial sums (read back directly by a team of one)
+    total_t own[NACC < WAVES * 8 ? WAVES * 8 : NACC];  // this workgroup's own partial sums (a leader reads them back)
     int abort;
     // two-level exchange
     int local;                       // this workgroup runs on its leader's die: its partial sums need only reach the L2
     total_t stage2[DIES * (NACC <= 8 ? 8 : NACC)];  // totals of the dies, [die][slot]
-    double totd[NACC];               // grid totals
+    double totd[NACC];               // grid totals (a team of one: its own)
 };
 
 // Index of the accelerator die this wavefront runs on.
@@ -232,13 +232,33 @@ constexpr int pow2_at_most(int n) {
     while (2 * p <= n) p *= 2;
     return p;
 }
+// A team of one has 8 wavefronts where a small team has 32 or 64, and their rounding counts: from 16 sums on, where layers of up to 4096
+// vectors may run in either (see plan_small), it adds the four rows of a wavefront in float64, and what float32 leaves of the sum lies
+// beside it (in stage2, which serves nobody else there).  1,800 weights, k = 8, plain norm, 31 evaluations: error of the codebook against 64 bits, geometric
+// mean of 300 seeds, 4.9e-8 in a team of eight, 5.3e-8 in one workgroup without this and 4.6e-8 with it (7.3e-8 with totals of float32);
+// launch 58.4, 52.9 and 55.8 us.
+constexpr bool alone_in_doubles(int nacc) { return nacc >= 16; }
 template <int NACC, int OFF, class XS>
-__device__ __forceinline__ void publish_rows(const float (&acc)[NACC], XS& xs, int lane, int wave) {
+__device__ __forceinline__ void publish_rows(const float (&acc)[NACC], XS& xs, int lane, int wave, bool alone) {
     constexpr int NP = pow2_at_most(NACC - OFF);
     float v[NP];
 #pragma unroll
     for (int q = 0; q < NP; ++q) v[q] = (OFF + q < NACC) ? acc[OFF + q] : 0.f;
     row_sums<NP>(v, lane);
+    if (alone_in_doubles(NACC) && alone) {
+        static_assert(XS::WAVES <= DIES, "stage2 has a place for every wavefront");
+#pragma unroll
+        for (int i = 0; i < row_sum_live(NP); ++i) {
+            const double t = cross_row_sum_d((double)v[i]);
+            const int q = OFF + row_sum_index<NP>(lane & 15, i);
+            if (lane < 16 && row_sum_owner<NP>(lane) && q < NACC) {
+                xs.rpart[q][wave] = (float)t;
+                xs.stage2[q * XS::WAVES + wave] = (typename XS::total_t)(t - (double)(float)t);
+            }
+        }
+        if constexpr (OFF + NP < NACC) publish_rows<NACC, OFF + NP>(acc, xs, lane, wave, alone);
+        return;
+    }
     // the four rows of the wavefront in registers (two row swaps per value), so that LDS only sees one value per
     // wavefront and accumulator
 #pragma unroll
@@ -250,7 +270,7 @@ __device__ __forceinline__ void publish_rows(const float (&acc)[NACC], XS& xs, i
             if (q < NACC) xs.rpart[q][wave] = v[i];
         }
     }
-    if constexpr (OFF + NP < NACC) publish_rows<NACC, OFF + NP>(acc, xs, lane, wave);
+    if constexpr (OFF + NP < NACC) publish_rows<NACC, OFF + NP>(acc, xs, lane, wave, false);
 }
 
 // hop 1, sender side: workgroup partial of every accumulator into this workgroup's line.
@@ -266,7 +286,7 @@ __device__ __forceinline__ void publish_partials(const PArgs& pa, unsigned int s
         }
     }
     IDKM_SUB(0);
-    publish_rows<NACC, 0>(acc, xs, lane, tid >> 6);
+    publish_rows<NACC, 0>(acc, xs, lane, tid >> 6, pa.G == 1);
     IDKM_SUB(1);
     __syncthreads();
     IDKM_SUB(2);
@@ -279,9 +299,17 @@ __device__ __forceinline__ void publish_partials(const PArgs& pa, unsigned int s
                              ((double)xs.rpart[tid][w + 2] + (double)xs.rpart[tid][w + 3]);
             s = w == 0 ? q : s + q;
         }
+        if (pa.G == 1) {  // nobody waits for a word of it: the totals stay float64
+            if constexpr (alone_in_doubles(NACC)) {
+#pragma unroll
+                for (int w = 0; w < XS::WAVES; ++w) s += (double)xs.stage2[tid * XS::WAVES + w];
+            }
+            xs.totd[tid] = s;
+            return;
+        }
         xs.own[tid] = (typename XS::total_t)s;
         // a workgroup's words lie together: one store transaction per workgroup and pass
-        if constexpr (XS::WIDE) {  // (a leader reads its own sums from xs.own, a team of one too)
+        if constexpr (XS::WIDE) {  // (a leader reads its own sums from xs.own)
             if (pa.tree && pa.wg >= DIES)
                 st_sum<true>(&pa.buf1[((size_t)(seq & 1u) * PT + pa.wg) * xline_of(NACC) * 2 + tid], xline_of(NACC), seq, s, xs.local != 0);
             return;
@@ -363,7 +391,7 @@ __device__ __forceinline__ bool reduce_slice(const PArgs& pa, unsigned int seq, 
     if (G == 1) {
         // a team of one has nobody to wait for: its partial sums are the totals
         __syncthreads();
-        if (tid < WPR) s = (double)xs.own[first + tid];
+        if (tid < WPR) s = xs.totd[first + tid];
     } else if (g0 < GPT && g0 < G) {
         constexpr int LINE = xline_of(NACC);
         const unsigned long long* src = pa.buf1 + ((size_t)(seq & 1u) * PT + g0) * LINE + first + q;
@@ -1165,10 +1193,9 @@ __device__ __forceinline__ void persist_fwd_body(const Args& a, const PArgs& pa)
         publish_partials<NACC>(pa, seq, acc, xs);
         IDKM_STAMP(2);
         if (pa.G == 1) {
-            // a team of one has no exchange: its partial sums (xs.own, the float32 words it would have published)
-            // are the totals, and the whole codebook is updated here
+            // a team of one has no exchange: publish_partials leaves the totals, and the whole codebook is updated here
             __syncthreads();
-            if (tid < 64) update_all([&](int i) { return (double)xs.own[i]; });
+            if (tid < 64) update_all([&](int i) { return xs.totd[i]; });
         } else if (pa.tree) {
             if constexpr (NACC <= WAVE_WORDS_MAX) {
                 // hop 2 and the update stay inside wavefront 0: no barrier between them
@@ -1752,8 +1779,6 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
                 if (!tree_totals<NBP>(pa, seq, xs)) return;
             } else {
                 __syncthreads();
-                if (tid < NBP) xs.totd[tid] = (double)xs.own[tid];
-                __syncthreads();
             }
             if (tid < 64) {
                 pair_row<K, D, DIST>([&](int i) { return xs.totd[i]; }, s_Cf, s_Fd, s_rn, a.escale, row);
@@ -1930,12 +1955,8 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
                     double hn;
                     const double vn = fast_sqrt_d(s_vnorm);
                     int over;
-                    if (tree)
-                        over = gmres_step<KD>(gm, [&](int i) { return xs.totd[i]; }, s_v, s_g, tol, vn, max_iter, s_iters,
-                                              s_conv, s_bad, s_res, hn);
-                    else
-                        over = gmres_step<KD>(gm, [&](int i) { return (double)xs.own[i]; }, s_v, s_g, tol, vn, max_iter,
-                                              s_iters, s_conv, s_bad, s_res, hn);
+                    over = gmres_step<KD>(gm, [&](int i) { return xs.totd[i]; }, s_v, s_g, tol, vn, max_iter, s_iters,
+                                          s_conv, s_bad, s_res, hn);
                     if (tid < KD) set_h((float)(hn * s_rn[tid / D]));
                     if (tid == 0 && over) s_done = 1;
                 }
@@ -1944,8 +1965,8 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
             }
         }
         if (pa.G == 1 || tree) {
-            // a team of one has no exchange: its partial sums (xs.own) are the totals; with the two-level exchange
-            // every workgroup receives the totals (xs.totd).  Either way the whole of g is updated here
+            // a team of one has no exchange, with the two-level one every workgroup receives the totals: either way they are
+            // in xs.totd and the whole of g is updated here
             bool wave0_abort = false;
             double u_reg = 0.0;   // (total of this lane's component where hop 2 leaves the totals in registers)
             bool in_regs = false;
@@ -1969,7 +1990,7 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
             if (tid < 64 && !wave0_abort) {
                 double d2 = 0.0, gn = 0.0;
                 if (tid < KD) {
-                    const double u = in_regs ? u_reg : (tree ? xs.totd[tid] : (double)xs.own[tid]);
+                    const double u = in_regs ? u_reg : xs.totd[tid];
                     gn = r_alpha * (r_v + u) + (1.0 - r_alpha) * r_g;
                     const double df = gn - r_g;
                     d2 = df * df;
