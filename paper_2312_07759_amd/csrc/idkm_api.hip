@@ -789,6 +789,10 @@ idkm_status validate_problem(idkm_ctx* ctx, const float* W, int64_t m, int d, co
     return IDKM_OK;
 }
 
+// Most vectors a thread of PASS_BP adds up in float32, as in the pass that forms the explicit Jacobian (runs of 32 give the same errors of v and g at
+// 16.8 and 60 M weights, k = 2, 4, 8; twice the workgroups whose sums the last one adds cost 3 us at k = 4 and 23 at k = 8).
+constexpr int64_t PAIR_RUN = 64;
+
 // Runs `pass` repeatedly in growing chunks until the device-side flag says the solve is over.
 template <class DoneFn>
 idkm_status run_until_done(idkm_ctx* ctx, const Geometry& g, int pass, Args& a, hipStream_t s, int64_t budget,
@@ -1241,7 +1245,7 @@ idkm_status idkm_backward(idkm_ctx* ctx, const float* dWq, idkm_bwd_mode mode, f
         // v and the operator in one pass, whose last workgroup runs the whole iteration (about four workgroups per compute unit:
         // it adds the sums of all of them)
         Geometry gp = g;
-        gp.vec_per_wg = (int64_t)WG * std::max<int64_t>(1, (ctx->m + (int64_t)WG * 1024 - 1) / ((int64_t)WG * 1024));
+        gp.vec_per_wg = (int64_t)WG * std::min<int64_t>(PAIR_RUN, std::max<int64_t>(1, (ctx->m + (int64_t)WG * 1024 - 1) / ((int64_t)WG * 1024)));
         gp.nwg = (int)((ctx->m + gp.vec_per_wg - 1) / gp.vec_per_wg);
         st = ensure_partials(ctx, (size_t)gp.nwg * (size_t)pair_sums(ctx->k, ctx->d, ctx->dist));
         if (st != IDKM_OK) return st;

@@ -148,9 +148,10 @@ __device__ __forceinline__ void raise_abort(const PArgs& pa) {
 // The others keep float32 words: an evaluation at k = 4, d = 1 takes 1.3 % longer with wide ones.
 // NACC: sums of the kernel's widest pass; TREE: of the widest one that takes the two-level exchange.  Nothing here is larger than its
 // users need: the tiles get what is left of the compute unit's 160 KB.
-template <int NACC, bool WIDE_ = false, int NT_ = PT, int TREE = NACC>
+// RUNS: the layer is read from memory, a lane's share has no bound, and what it has added up goes to `run` now and then (see RUN_MAX).
+template <int NACC, bool WIDE_ = false, int NT_ = PT, int TREE = NACC, bool RUNS_ = false>
 struct XShared {
-    static constexpr bool WIDE = WIDE_;
+    static constexpr bool WIDE = WIDE_, RUNS = RUNS_;
     static constexpr int NT = NT_, WAVES = NT_ / 64;  // threads and wavefronts of the workgroup
     static constexpr int RED = TREE <= 8 ? PT : (NT_ / TREE < 32 ? NT_ / TREE : 32) * TREE > PT ? (NT_ / TREE < 32 ? NT_ / TREE : 32) * TREE : PT;
     typedef typename std::conditional<WIDE_, double, float>::type total_t;
@@ -164,6 +165,7 @@ struct XShared {
     int local;                       // this workgroup runs on its leader's die: its partial sums need only reach the L2
     total_t stage2[DIES * (NACC <= 8 ? 8 : NACC)];  // totals of the dies, [die][slot]
     double totd[NACC];               // grid totals (a team of one: its own)
+    double run[RUNS_ ? NACC : 1][RUNS_ ? WAVES : 1];  // [accumulator][wavefront], zero between passes
 };
 
 // Index of the accelerator die this wavefront runs on.
@@ -273,6 +275,44 @@ __device__ __forceinline__ void publish_rows(const float (&acc)[NACC], XS& xs, i
     if constexpr (OFF + NP < NACC) publish_rows<NACC, OFF + NP>(acc, xs, lane, wave, false);
 }
 
+// Most vectors whose float32 sums a lane of a layer read from memory keeps before they are added up over the wavefront and move to
+// float64, the stream path's run.  A sum that only grows swallows ever larger terms, so the error grows with the run (codebook after five
+// evaluations and Jacobian-free gradient against 64 bits, 60 M weights, stream path / one run of 458 / runs of 32: k = 8, plain norm 3.9e-8 /
+// 3.0e-7 / 4.1e-8 and 2.2e-6 / 6.3e-6 / 2.1e-6, k = 4 3.5e-8 / 7.8e-8 / 3.3e-8).  Us per evaluation, one run / runs of 32: 16.8 M weights k = 4
+// 18.2 / 18.6, k = 8 36.1 / 38.4, k = 16, plain norm 61.8 / 65.7; 4 M 4-vectors k = 4 16.2 / 17.7, k = 16 39.7 / 44.4; 60 M k = 4 52.9 / 55.3.
+constexpr int RUN_MAX = 32;
+template <int NACC, int OFF, int N, class XS>
+__device__ __forceinline__ void move_run(float (&acc)[N], XS& xs, int lane, int wave) {
+    constexpr int NP = pow2_at_most(NACC - OFF);
+    float v[NP];
+#pragma unroll
+    for (int q = 0; q < NP; ++q) v[q] = (OFF + q < NACC) ? acc[OFF + q] : 0.f;
+    row_sums<NP>(v, lane);
+#pragma unroll
+    for (int i = 0; i < row_sum_live(NP); ++i) v[i] = cross_row_sum(v[i]);
+    if (lane < 16 && row_sum_owner<NP>(lane)) {
+#pragma unroll
+        for (int i = 0; i < row_sum_live(NP); ++i) {
+            const int q = OFF + row_sum_index<NP>(lane, i);
+            if (q < NACC) xs.run[q][wave] += (double)v[i];
+        }
+    }
+    if constexpr (OFF + NP < NACC) move_run<NACC, OFF + NP>(acc, xs, lane, wave);
+}
+template <class XS>
+__device__ __forceinline__ void clear_runs(XS& xs) {
+    if constexpr (XS::RUNS)
+        for (int i = threadIdx.x; i < (int)(sizeof(xs.run) / sizeof(double)); i += XS::NT) (&xs.run[0][0])[i] = 0.0;
+}
+// (all lanes of a wavefront together)
+template <int NACC, int N, class XS>
+__device__ __forceinline__ void end_run(float (&acc)[N], XS& xs) {
+    wave_lds_sync();
+    move_run<NACC, 0>(acc, xs, threadIdx.x & 63, threadIdx.x >> 6);
+#pragma unroll
+    for (int q = 0; q < N; ++q) acc[q] = 0.f;
+}
+
 // hop 1, sender side: workgroup partial of every accumulator into this workgroup's line.
 template <int NACC, class XS>
 __device__ __forceinline__ void publish_waves(const PArgs& pa, unsigned int seq, const float (&acc)[NACC], XS& xs);
@@ -298,6 +338,13 @@ __device__ __forceinline__ void publish_partials(const PArgs& pa, unsigned int s
             const double q = ((double)xs.rpart[tid][w] + (double)xs.rpart[tid][w + 1]) +
                              ((double)xs.rpart[tid][w + 2] + (double)xs.rpart[tid][w + 3]);
             s = w == 0 ? q : s + q;
+        }
+        if constexpr (XS::RUNS) {
+#pragma unroll
+            for (int w = 0; w < XS::WAVES; ++w) {
+                s += xs.run[tid][w];
+                xs.run[tid][w] = 0.0;
+            }
         }
         if (pa.G == 1) {  // nobody waits for a word of it: the totals stay float64
             if constexpr (alone_in_doubles(NACC)) {
@@ -649,8 +696,16 @@ __device__ __forceinline__ void publish_waves(const PArgs& pa, unsigned int seq,
 #pragma unroll
     for (int q = 0; q < 8; ++q) v[q] = (q < NACC) ? acc[q] : 0.f;
     row_sums<8>(v, lane);  // lane l of a row: the row's total of accumulator slot_acc(l % 8)
-    const float tot = cross_row_sum(v[0]);
+    float tot = cross_row_sum(v[0]);
     if (lane < 8) {
+        if constexpr (XS::RUNS) {
+            wave_lds_sync();
+            const int q = slot_acc(lane);
+            if (q < NACC) {
+                tot = (float)((double)tot + xs.run[q][wave]);
+                xs.run[q][wave] = 0.0;
+            }
+        }
         xs.own[wave * 8 + lane] = tot;
         if (pa.wg >= DIES) {  // (a leader reads its own sums from xs.own)
             unsigned long long* dst = &pa.buf1[((size_t)(seq & 1u) * PT + pa.wg) * (XS::WAVES * 8) + wave * 8 + lane];
@@ -905,8 +960,8 @@ __device__ __forceinline__ void tile_pass(const Args& a, const float* s_w, const
 // turn (block t G + wg in round t), so that at any moment the team reads one contiguous window of memory: with a
 // contiguous share per workgroup and a power-of-two layer, all workgroups would hit the same memory channel.
 // gw, gg: the whole tensors, 16-byte aligned.
-template <int NT, int K, int D, int DIST, int PASS>
-__device__ __forceinline__ void tile_pass_global(const Args& a, const float* gw, const float* gg, int wg, int G,
+template <int NT, int K, int D, int DIST, int PASS, class XS>
+__device__ __forceinline__ void tile_pass_global(const Args& a, XS& xs, const float* gw, const float* gg, int wg, int G,
                                                  const float* s_Cf, const float* s_Hs, const float* s_Ff,
                                                  float (&acc)[SmallItem<K, D, DIST, PASS>::NREG], const int* s_solid) {
     using Item = SmallItem<K, D, DIST, PASS>;
@@ -946,6 +1001,7 @@ __device__ __forceinline__ void tile_pass_global(const Args& a, const float* gw,
             constexpr int L = 4;  // 16-byte loads of a block
             const int64_t step = (int64_t)G * NT, at = (int64_t)wg * NT + threadIdx.x;
             const int nb = (int)(ngroups / (step * L));
+            constexpr int BLOCKS = RUN_MAX / (4 * L);  // of a run
             if (nb > 0)
                 rf.template sweep<4 * L, false>(nb, [&](int b, float(&w)[4 * L]) {
 #pragma unroll
@@ -954,7 +1010,9 @@ __device__ __forceinline__ void tile_pass_global(const Args& a, const float* gw,
 #pragma unroll
                         for (int e = 0; e < 4; ++e) w[4 * u + e] = v[e];
                     }
-                }, acc);
+                }, acc, [&](int b) {
+                    if (b % BLOCKS == BLOCKS - 1) end_run<Item::NACC>(acc, xs);
+                });
             for (int64_t gi = nb * L * step + at; gi < ngroups; gi += step) {
                 const f32x4_t v = w4[gi];
                 rf.template sweep<4, false>(1, [&](int, float(&w)[4]) {
@@ -970,15 +1028,23 @@ __device__ __forceinline__ void tile_pass_global(const Args& a, const float* gw,
     const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
     f32x4_t cw[NLD], cg[NLD], nw[NLD], ng[NLD];
     const int64_t step = (int64_t)G * NT;           // groups per round of the team
-    int64_t gi = (int64_t)wg * NT + threadIdx.x;    // this lane's group on its first turn
+    const int64_t first = (int64_t)wg * NT;         // lane 0's group on its first turn
+    int64_t gi = first + threadIdx.x;               // this lane's
+    constexpr int ROUNDS = RUN_MAX / (NLD * VPL) > 1 ? RUN_MAX / (NLD * VPL) : 1;  // of a run
+    int round = 0;
 #pragma unroll
     for (int u = 0; u < NLD; ++u) {
         const int64_t i = gi + u * step;
         cw[u] = (i < ngroups) ? w4[i] : zero;
         cg[u] = (Item::USE_G && i < ngroups) ? g4[i] : zero;
     }
-    // the loop bound is the same for all lanes of the workgroup up to the last, partial block
-    for (; gi < ngroups; gi += NLD * step) {
+    // (the same number of rounds for all lanes: they end their runs together)
+    for (int64_t g0 = first; g0 < ngroups; g0 += NLD * step, gi += NLD * step) {
+        if (PASS != PASS_B3 && ++round > ROUNDS) {
+            round = 1;
+            Item::finish(a, c, acc);
+            end_run<Item::NACC>(acc, xs);
+        }
         const int64_t nx = gi + NLD * step;
 #pragma unroll
         for (int u = 0; u < NLD; ++u) {
@@ -1013,13 +1079,13 @@ __device__ __forceinline__ void tile_pass_global(const Args& a, const float* gw,
 
 // A pass over the workgroup's share of the layer: its LDS tile (w, g: the tile; base, cnt: its place in the layer) or,
 // GLOBALW, its blocks of the tensors in memory (w, g: the whole tensors).
-template <int NT, int K, int D, int DIST, int PASS, bool SHARED, bool GLOBALW, bool RAG>
-__device__ __forceinline__ void any_tile_pass(const Args& a, const PArgs& pa, const float* w, const float* g,
+template <int NT, int K, int D, int DIST, int PASS, bool SHARED, bool GLOBALW, bool RAG, class XS>
+__device__ __forceinline__ void any_tile_pass(const Args& a, const PArgs& pa, XS& xs, const float* w, const float* g,
                                               int64_t base, int cnt, const float* s_Cf, const float* s_Hs,
                                               const float* s_Ff, float (&acc)[SmallItem<K, D, DIST, PASS, RAG>::NREG],
                                               const float* s_tab = nullptr, const int* s_solid = nullptr) {
     if constexpr (GLOBALW)
-        tile_pass_global<NT, K, D, DIST, PASS>(a, w, g, pa.wg, pa.G, s_Cf, s_Hs, s_Ff, acc, s_solid);
+        tile_pass_global<NT, K, D, DIST, PASS>(a, xs, w, g, pa.wg, pa.G, s_Cf, s_Hs, s_Ff, acc, s_solid);
     else
         tile_pass<K, D, DIST, PASS, SHARED, RAG, NT>(a, w, g, base, cnt, s_Cf, s_Hs, s_Ff, acc, s_tab, s_solid);
 }
@@ -1084,7 +1150,7 @@ __device__ __forceinline__ void persist_fwd_body(const Args& a, const PArgs& pa)
     constexpr int NB = KD;                     // broadcast words: the new codebook
     static_assert(NACC <= XLINE && NB <= XBCAST && KD <= 64, "shape does not fit the exchange layout");
     extern __shared__ float s_tile[];
-    __shared__ XShared<NACC, RAG, NT> xs;
+    __shared__ XShared<NACC, RAG, NT, NACC, GLOBALW> xs;
     __shared__ double s_Cd[KD];  // float64 master copy (a reducer's own slice is the live one)
     __shared__ float s_Cf[KD];
     __shared__ int s_done, s_iters, s_conv, s_bad;
@@ -1101,6 +1167,7 @@ __device__ __forceinline__ void persist_fwd_body(const Args& a, const PArgs& pa)
     int cnt = 0;
     if (base < a.m) cnt = (a.m - base < pa.per) ? (int)(a.m - base) : pa.per;
     tree_announce(pa);
+    clear_runs(xs);
     if (!GLOBALW)
         load_tile<NT>(s_tile, a.W + base * D, cnt * D);
     const float* s_w = GLOBALW ? a.W : s_tile;
@@ -1187,7 +1254,7 @@ __device__ __forceinline__ void persist_fwd_body(const Args& a, const PArgs& pa)
     float acc[NACC];
     while (!s_done) {
         IDKM_STAMP(0);
-        any_tile_pass<NT, K, D, DIST, PASS_FWD, SHARED, GLOBALW, RAG>(a, pa, s_w, nullptr, base, cnt, s_Cf, nullptr, nullptr, acc, DOT ? s_tab : nullptr, &s_solid);
+        any_tile_pass<NT, K, D, DIST, PASS_FWD, SHARED, GLOBALW, RAG>(a, pa, xs, s_w, nullptr, base, cnt, s_Cf, nullptr, nullptr, acc, DOT ? s_tab : nullptr, &s_solid);
         IDKM_STAMP(1);
         ++seq;
         publish_partials<NACC>(pa, seq, acc, xs);
@@ -1290,7 +1357,7 @@ __device__ __forceinline__ void persist_fwd_body(const Args& a, const PArgs& pa)
     }
 
     // evaluation at C*: outputs, and n*, F* for the backward
-    any_tile_pass<NT, K, D, DIST, PASS_FIN, SHARED, GLOBALW, RAG>(a, pa, s_w, nullptr, base, cnt, s_Cf, nullptr, nullptr, acc);
+    any_tile_pass<NT, K, D, DIST, PASS_FIN, SHARED, GLOBALW, RAG>(a, pa, xs, s_w, nullptr, base, cnt, s_Cf, nullptr, nullptr, acc);
     ++seq;
     publish_partials<NACC>(pa, seq, acc, xs);
     if (pa.tree) {
@@ -1613,7 +1680,7 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
     constexpr int NBP = PAIRS ? pair_sums(K, D, DIST) : 1;
     constexpr int NXS = PAIRS ? NBP : HAS_DENSE ? NBJ : KD;
     extern __shared__ float s_tile[];
-    __shared__ XShared<NXS, RAG, NT, PAIRS ? NBP : KD> xs;
+    __shared__ XShared<NXS, RAG, NT, PAIRS ? NBP : KD, GLOBALW> xs;
     __shared__ double s_Fd[PAIRS ? KD : 1], s_A[PAIRS && KD <= 4 ? KD * KD : 1];
     __shared__ double s_v[KD], s_g[KD], s_rn[K];  // a reducer's own slice is the live one; s_rn = 1/(tau n)
     __shared__ float s_Cf[KD], s_Hs[KD], s_Hv[KD], s_Ff[KD];
@@ -1643,6 +1710,7 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
     // 30 evaluations and the averaged iteration: 4.07 -> 3.56 ms together with the order of the launches).
     const float* s_gt = GLOBALW ? a.G : (SHARED ? a.G + base * D : s_tile + (size_t)pa.per * D);
     tree_announce(pa);
+    clear_runs(xs);
     if (!GLOBALW) {
         load_tile<NT>(s_tile, a.W + base * D, cnt * D);
         if (!SHARED) load_tile<NT>(s_tile + (size_t)pa.per * D, a.G + base * D, cnt * D);
@@ -1702,7 +1770,7 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
             // one pass accumulates v and the sums T, U of dF/dC* (layout as in the stream path's tail_bj); workgroup 0
             // adds them over the team, solves (I - dF/dC*)^T g = v by Gauss-Jordan elimination and broadcasts h/tau
             float accj[NBJ];
-            any_tile_pass<NT, K, D, DIST, PASS_BJ, SHARED, GLOBALW, RAG>(a, pa, s_w, s_gt, base, cnt, s_Cf, s_Hs, s_Ff, accj);
+            any_tile_pass<NT, K, D, DIST, PASS_BJ, SHARED, GLOBALW, RAG>(a, pa, xs, s_w, s_gt, base, cnt, s_Cf, s_Hs, s_Ff, accj);
             ++seq;
             publish_partials<NBJ>(pa, seq, accj, xs);
             if (wg == 0) {
@@ -1772,7 +1840,7 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
     if constexpr (PAIRS) {
         {
             float accp[NBP];
-            any_tile_pass<NT, K, D, DIST, PASS_BP, SHARED, GLOBALW, RAG>(a, pa, s_w, s_gt, base, cnt, s_Cf, s_Hs, s_Ff, accp);
+            any_tile_pass<NT, K, D, DIST, PASS_BP, SHARED, GLOBALW, RAG>(a, pa, xs, s_w, s_gt, base, cnt, s_Cf, s_Hs, s_Ff, accp);
             ++seq;
             publish_partials<NBP>(pa, seq, accp, xs);
             if (tree) {
@@ -1799,7 +1867,7 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
     if constexpr (!PAIRS)
     if (!dense_done) {
     // B1: v = dL/dC* with W fixed; the solve starts at g = v
-    any_tile_pass<NT, K, D, DIST, PASS_B1, SHARED, GLOBALW, RAG>(a, pa, s_w, s_gt, base, cnt, s_Cf, s_Hs, s_Ff, acc);
+    any_tile_pass<NT, K, D, DIST, PASS_B1, SHARED, GLOBALW, RAG>(a, pa, xs, s_w, s_gt, base, cnt, s_Cf, s_Hs, s_Ff, acc);
     ++seq;
     publish_partials<KD>(pa, seq, acc, xs);
     if (tree) {
@@ -1938,7 +2006,7 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
     if constexpr (!PAIRS)
     while (!s_done) {
         IDKM_STAMP(0);
-        any_tile_pass<NT, K, D, DIST, PASS_B2, SHARED, GLOBALW, RAG>(a, pa, s_w, s_gt, base, cnt, s_Cf, s_Hs, s_Ff, accr, BTAB ? s_tabB : nullptr);
+        any_tile_pass<NT, K, D, DIST, PASS_B2, SHARED, GLOBALW, RAG>(a, pa, xs, s_w, s_gt, base, cnt, s_Cf, s_Hs, s_Ff, accr, BTAB ? s_tabB : nullptr);
         IDKM_STAMP(1);
         ++seq;
         publish_partials<KD>(pa, seq, acc, xs);
@@ -2138,7 +2206,7 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
     }
 
     // B3: dW = direct + (dF/dW)^T g
-    any_tile_pass<NT, K, D, DIST, PASS_B3, SHARED, GLOBALW, RAG>(a, pa, s_w, s_gt, base, cnt, s_Cf, s_Hs, s_Ff, reinterpret_cast<float(&)[1]>(acc[0]));
+    any_tile_pass<NT, K, D, DIST, PASS_B3, SHARED, GLOBALW, RAG>(a, pa, xs, s_w, s_gt, base, cnt, s_Cf, s_Hs, s_Ff, reinterpret_cast<float(&)[1]>(acc[0]));
     if (dense_done || tree || PAIRS) {
         if (wg == 0 && tid < kd) {
             a.gd[tid] = s_g[tid];

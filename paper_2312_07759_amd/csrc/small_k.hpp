@@ -192,8 +192,13 @@ struct RatioForm {
     // nb blocks of U vectors; load(i, w): block i.  Each operation is issued for all U vectors before the next one, so that a
     // result is not used before U other instructions and exponentials stand together (left to itself the scheduler takes one vector
     // after the other, which gains nothing over the general form); the loads of the next block are in flight meanwhile.
+    // then(i): after block i, if another one follows.
     template <int U, bool K3, class LOAD>
     __device__ __forceinline__ void sweep(int nb, LOAD load, float (&acc)[2 * K]) const {
+        sweep<U, K3>(nb, load, acc, [](int) {});
+    }
+    template <int U, bool K3, class LOAD, class THEN>
+    __device__ __forceinline__ void sweep(int nb, LOAD load, float (&acc)[2 * K], THEN then) const {
         float w[U], nw[U];
         load(0, w);
         for (int i = 0; i < nb; ++i) {
@@ -251,6 +256,7 @@ struct RatioForm {
                 IDKM_NEXT
             }
             IDKM_ALL w[u] = nw[u];
+            if (i + 1 < nb) then(i);
 #undef IDKM_ALL
 #undef IDKM_NEXT
         }
