@@ -56,7 +56,8 @@ def test_against_the_oracle(ctx, k, m, soft, order, shift, outliers):
 
 
 @pytest.mark.parametrize("k", [2, 4])
-@pytest.mark.parametrize("m", [1_000, 16_385, 70_003, 600_001])
+# (a block of the ratio form is 16 weights of each of 256 x 512 lanes: none, one, two and a rest)
+@pytest.mark.parametrize("m", [1_000, 16_385, 70_003, 600_001, 2_097_151, 2_097_152, 4_300_007])
 def test_layers_read_from_memory(k, m):
     """A tile limit of zero sends every layer to the kernel that reads W in each pass; the default takes it for forward solves."""
     ctx = binding.Context(0)
