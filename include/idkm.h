@@ -11,7 +11,8 @@
  *
  * Ownership: every tensor pointer is caller-owned device memory; the library never frees or
  * reallocates it.  A context owns only its scratch memory and O(k d) solver state.
- * Threading: one context must not be used from two host threads at once.
+ * Threading: one context must not be used from two host threads at once.  Different contexts and batches may be,
+ * each on a stream of its own: one-launch solves that do not fit the device together take turns.
  * Errors: functions return an idkm_status; on any error nothing the caller can rely on has been
  * written to the outputs.  Non-convergence and empty clusters are reported in idkm_info, not as
  * errors.  Nothing is printed and the process is never terminated.

@@ -2,6 +2,7 @@
 // scheduling of passes over W.  All arithmetic of the method runs in the kernels.
 #include <hip/hip_runtime.h>
 
+#include <chrono>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -12,6 +13,7 @@
 #include <new>
 #include <algorithm>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "../../include/idkm.h"
@@ -162,6 +164,7 @@ struct idkm_ctx {
     bool timing = false;
     bool timed = false;          // ev0 / ev1 bracket the last persistent launch
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
+    hipEvent_t ev_order = nullptr;  // see join_running (created on first use)
     unsigned long long* xbuf = nullptr;  // exchange words: buf1 [2][PT][XLINE], then buf2 [2][XBCAST]
     size_t xbuf_words = 0;
     unsigned int seq_base = 0;
@@ -606,6 +609,88 @@ bool plan_persistent(idkm_ctx* ctx, bool bwd, PersistPlan* pp, bool matrix_ok = 
     return false;
 }
 
+// Teams that calls of this process have on a device.  The workgroups of a team wait for one another, so all of them have to be resident:
+// what one launch asks for is checked against the device where it is planned, what several streams ask for together is added up
+// here.  Two teams that got half of their workgroups each would wait until the waits expire, 0.2 s, and be solved again on the stream path
+// (threads with a stream and a context each, 300 steps of solve and Jacobian-free gradient, s: 300,000 weights, k = 16, three threads 37, with this
+// list 0.13; 2.4 M, k = 4, three 0.50 / 0.105; 16.8 M, k = 4, three, 100 steps 0.75 / 0.15).  A call leaves the list before it returns: it is never
+// longer than there are calls in progress, and a stream in it belongs to one of them.  Not in it: idkm_forward_noalloc, whose launches
+// may be recorded into a graph, and teams of one, which wait for nobody.
+struct Team {
+    const void* owner;
+    hipStream_t stream;
+    double share;  // of the device
+    bool last;     // starts when all that stand before it in the list are over
+};
+struct DeviceTeams {
+    std::mutex mutex;
+    std::vector<Team> running;
+};
+constexpr int TEAM_DEVICES = 64;
+DeviceTeams g_teams[TEAM_DEVICES];
+
+DeviceTeams* teams_of(int device) { return device >= 0 && device < TEAM_DEVICES ? &g_teams[device] : nullptr; }
+
+// Share of a device that holds `capacity` workgroups of a kernel, the same number on each die (workgroup b goes to die b mod DIES).
+double device_share(int64_t grid, int64_t capacity) { return (double)((grid + DIES - 1) / DIES * DIES) / (double)std::max<int64_t>(capacity, 1); }
+
+// With the list locked, adds what is about to be enqueued on s to it.  Where there is no room beside the teams of other calls, waits for
+// some of them to return for about the time of a solve, and otherwise puts s behind them with events, so that no call depends on
+// another's thread (events alone: 0.18 instead of 0.13 s and 0.15 instead of 0.105 in the first two examples above).  A failure leaves the order to
+// chance, as with other processes on the device: the waits in the kernels are bounded.
+constexpr auto JOIN_WAIT = std::chrono::microseconds(300);
+void join_running(DeviceTeams& t, std::unique_lock<std::mutex>& lock, const void* owner, double share, hipStream_t s, hipEvent_t* ev) {
+    auto room = [&] {
+        double load = share;
+        for (const Team& r : t.running) load += r.share;
+        return load <= 1.0 + 1e-9;
+    };
+    bool full = !room();
+    if (full) {
+        const auto until = std::chrono::steady_clock::now() + JOIN_WAIT;
+        while (full && std::chrono::steady_clock::now() < until) {
+            lock.unlock();
+            std::this_thread::yield();
+            lock.lock();
+            full = !room();
+        }
+    }
+    if (full) {
+        size_t from = 0;  // the first whose end is not implied by a later one's
+        for (size_t i = 0; i < t.running.size(); ++i)
+            if (t.running[i].last) from = i;
+        if (!*ev && hipEventCreateWithFlags(ev, hipEventDisableTiming) != hipSuccess) *ev = nullptr;
+        for (size_t i = from; *ev && i < t.running.size(); ++i)
+            if (t.running[i].stream != s && hipEventRecord(*ev, t.running[i].stream) == hipSuccess) (void)hipStreamWaitEvent(s, *ev, 0);
+        (void)hipGetLastError();
+    }
+    t.running.push_back({owner, s, share, full});
+}
+
+void leave_device(int device, const void* owner) {
+    DeviceTeams* t = teams_of(device);
+    if (!t) return;
+    std::lock_guard<std::mutex> lock(t->mutex);
+    t->running.erase(std::remove_if(t->running.begin(), t->running.end(), [&](const Team& r) { return r.owner == owner; }), t->running.end());
+}
+
+idkm_status enqueue_persistent(idkm_ctx* ctx, const PersistPlan& pp, Args& a, PArgs& pa, hipStream_t s) {
+    if (ctx->timing) HIP_TRY(ctx, hipEventRecord(ctx->ev0, s));
+    if (ctx->coop_launch) {
+        void* args[] = {(void*)&a, (void*)&pa};
+        HIP_TRY(ctx, hipLaunchCooperativeKernel((const void*)pp.fn, dim3(pp.grid), dim3(pp.threads), args, pp.lds, s));
+    } else {
+        // plain launch: the grid fits the device, every wait in the kernel is bounded
+        hipLaunchKernelGGL(pp.fn, dim3(pp.grid), dim3(pp.threads), pp.lds, s, a, pa);
+        HIP_TRY(ctx, hipGetLastError());
+    }
+    if (ctx->timing) {
+        HIP_TRY(ctx, hipEventRecord(ctx->ev1, s));
+        ctx->timed = true;
+    }
+    return IDKM_OK;
+}
+
 idkm_status launch_persistent(idkm_ctx* ctx, const PersistPlan& pp, Args& a, PArgs pa, unsigned int exchanges,
                               hipStream_t s) {
     if (pp.grid > PT || ctx->xbuf_words < XBUF_WORDS) return fail(ctx, IDKM_ERR_DEVICE, "exchange buffer too small");
@@ -700,18 +785,18 @@ idkm_status launch_persistent(idkm_ctx* ctx, const PersistPlan& pp, Args& a, PAr
     }
     if ((int64_t)checked.second * ctx->num_cu < pp.grid)
         return fail(ctx, IDKM_ERR_DEVICE, "persistent grid would not be co-resident");
-    if (ctx->timing) HIP_TRY(ctx, hipEventRecord(ctx->ev0, s));
-    if (ctx->coop_launch) {
-        void* args[] = {(void*)&a, (void*)&pa};
-        HIP_TRY(ctx, hipLaunchCooperativeKernel((const void*)pp.fn, dim3(pp.grid), dim3(pp.threads), args, pp.lds, s));
-    } else {
-        // plain launch: the grid fits the device (checked above), every wait in the kernel is bounded
-        hipLaunchKernelGGL(pp.fn, dim3(pp.grid), dim3(pp.threads), pp.lds, s, a, pa);
-        HIP_TRY(ctx, hipGetLastError());
+    // (one workgroup waits for nobody)
+    DeviceTeams* teams = pp.grid > 1 && !ctx->res_on_device ? teams_of(ctx->device) : nullptr;
+    std::unique_lock<std::mutex> lock;
+    if (teams) {
+        const double share = device_share(pp.grid, (int64_t)checked.second * ctx->num_cu);
+        lock = std::unique_lock<std::mutex>(teams->mutex);
+        join_running(*teams, lock, ctx, share, s, &ctx->ev_order);
     }
-    if (ctx->timing) {
-        HIP_TRY(ctx, hipEventRecord(ctx->ev1, s));
-        ctx->timed = true;
+    const idkm_status st = enqueue_persistent(ctx, pp, a, pa, s);
+    if (st != IDKM_OK) {
+        if (teams) teams->running.pop_back();
+        return st;
     }
     ctx->pending_id = ctx->seq_base + 1u;
     ctx->pending_stream = s;
@@ -727,7 +812,9 @@ idkm_status finish_persistent(idkm_ctx* ctx, idkm_info* info) {
     ctx->pending_kind = 0;
     if (ctx->res_on_device)
         HIP_TRY(ctx, hipMemcpyAsync(&ctx->res_copy, ctx->h_res, sizeof(PResult), hipMemcpyDeviceToHost, ctx->pending_stream));
-    HIP_TRY(ctx, hipStreamSynchronize(ctx->pending_stream));
+    const hipError_t waited = hipStreamSynchronize(ctx->pending_stream);
+    leave_device(ctx->device, ctx);
+    HIP_TRY(ctx, waited);
     const PResult& c = ctx->res_on_device ? ctx->res_copy : *ctx->h_res;
     if (c.done != ctx->pending_id || c.aborted == ctx->pending_id) return fail(ctx, IDKM_ERR_DEVICE, "a grid-wide wait hit its limit");
     if (kind == 1) {
@@ -911,6 +998,8 @@ idkm_status idkm_destroy(idkm_ctx* c) {
     void* dev[] = {c->ctrl, c->Cd, c->Fd, c->gd, c->vd, c->ud, c->nd, c->Cf, c->Ff, c->Hs, c->stage, c->tot, c->partials, c->kry, c->tickets, c->xbuf, c->lane_xbuf, c->rag_xbuf, c->abort_word};
     for (void* p : dev)
         if (p) (void)hipFree(p);
+    leave_device(c->device, c);
+    if (c->ev_order) (void)hipEventDestroy(c->ev_order);
     if (c->ev0) (void)hipEventDestroy(c->ev0);
     if (c->ev1) (void)hipEventDestroy(c->ev1);
     if (c->h_ctrl) (void)hipHostFree(c->h_ctrl);
@@ -1453,6 +1542,7 @@ idkm_status batch_launch(idkm_batch* b, hipStream_t s) {
         size_t lds;
         int64_t grid;
         size_t item, map;  // where its tables begin
+        double share;      // of the device
     };
     std::vector<Part> parts;
     std::vector<char> taken(q.size(), 0);
@@ -1487,8 +1577,18 @@ idkm_status batch_launch(idkm_batch* b, hipStream_t s) {
                 taken[i] = 1;
             }
             if (total == 0) break;
-            parts.push_back({q[first].pp.fn_batch, threads, lds, total, item_begin, map_begin});
+            parts.push_back({q[first].pp.fn_batch, threads, lds, total, item_begin, map_begin,
+                             device_share(total, batch_capacity(b, fn, threads, lds))});
         }
+    }
+    // (the launches run one after the other: the largest decides what the call takes of the device)
+    DeviceTeams* teams = teams_of(b->device);
+    std::unique_lock<std::mutex> lock;
+    if (teams) {
+        double share = 0.0;
+        for (const Part& p : parts) share = std::max(share, p.share);
+        lock = std::unique_lock<std::mutex>(teams->mutex);
+        join_running(*teams, lock, b, share, s, &b->ctx[0]->ev_order);
     }
     // the tables of all launches travel in two copies in front of the first one (a pair of copies before every launch cost the
     // 21 tensors of ResNet18 eight round trips through the copy queue a call)
@@ -1505,8 +1605,14 @@ idkm_status batch_launch(idkm_batch* b, hipStream_t s) {
 }
 
 // Collects the deferred solves after batch_launch (or abandons them if the launch failed).
-idkm_status batch_collect(idkm_batch* b, idkm_status launched, int32_t n, idkm_info* infos, idkm_status* statuses) {
+idkm_status batch_collect(idkm_batch* b, idkm_status launched, int32_t n, idkm_info* infos, idkm_status* statuses, hipStream_t s) {
     idkm_status first = launched;
+    // (a call that fails half way has launches and copies of its tables on their way)
+    if (!b->deferred.empty()) {
+        (void)hipStreamSynchronize(s);
+        if (launched != IDKM_OK) (void)hipGetLastError();  // (what failed has been reported; the stream path starts without it)
+    }
+    leave_device(b->device, b);
     for (int i = 0; i < n; ++i) {
         idkm_ctx* c = b->ctx[i];
         if (statuses[i] == IDKM_OK && c->pending_kind) {
@@ -1601,7 +1707,7 @@ idkm_status idkm_batch_forward(idkm_batch* b, const idkm_fwd_desc* layers, int32
         c->sink = nullptr;
     }
     const idkm_status launched = batch_launch(b, (hipStream_t)hip_stream);
-    idkm_status first = batch_collect(b, launched, n, infos, statuses);
+    idkm_status first = batch_collect(b, launched, n, infos, statuses, (hipStream_t)hip_stream);
     if (first != IDKM_OK) {
         // layers whose persistent solve could not run to its end are solved again, one by one, on the stream path
         // (contexts left at IDKM_PATH_AUTO only)
@@ -1643,7 +1749,7 @@ idkm_status idkm_batch_backward(idkm_batch* b, const idkm_bwd_desc* layers, int3
         c->sink = nullptr;
     }
     const idkm_status launched = batch_launch(b, (hipStream_t)hip_stream);
-    idkm_status first = batch_collect(b, launched, n, infos, statuses);
+    idkm_status first = batch_collect(b, launched, n, infos, statuses, (hipStream_t)hip_stream);
     if (first != IDKM_OK) {
         first = IDKM_OK;  // as in idkm_batch_forward
         for (int i = 0; i < n; ++i) {
