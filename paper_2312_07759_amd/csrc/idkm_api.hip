@@ -455,7 +455,7 @@ bool plan_small(idkm_ctx* ctx, bool bwd, PersistPlan* pp, const void* dwq, int m
     pp->fn = fs.one;
     pp->fn_batch = fs.batch;
     if (!pp->fn) return false;
-    pp->threads = ctx->sink ? PT : bwd ? bwd_threads(K, d) : fwd_threads(K, d);
+    pp->threads = ctx->sink ? PT : bwd ? bwd_threads(K, d) : fwd_threads();
     pp->lane = false;
     const int64_t chunk = (int64_t)ctx->min_vec_per_thread * PT;
     int64_t g = (m + chunk - 1) / chunk;  // a few vectors per thread before adding workgroups

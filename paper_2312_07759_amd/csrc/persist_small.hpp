@@ -43,8 +43,15 @@ constexpr int PT = 256;      // threads per workgroup of the persistent kernels 
 // addition or a multiply-add (operands in vector registers) every 4.9 cycles, two or more together one every 2.5 (an operand in a scalar
 // register, min / max / med3 and DPP forms 4.4 either way, an exponential or reciprocal 8.3).
 constexpr int PT2 = 512;
-__host__ __device__ constexpr int fwd_threads(int K, int D) { return PT2; }
+__host__ __device__ constexpr int fwd_threads() { return PT2; }
 __host__ __device__ constexpr int bwd_threads(int K, int D) { return K * D <= 16 ? PT2 : PT; }
+// Wavefronts per SIMD that the registers leave room for: with four (128 registers) two teams of the whole device fit beside each other.  Forward
+// kernels up to k d = 8 compile to that by themselves (k = 4, d = 1 127); where it has to be asked for it is, if it costs nothing (300,000 and 2.4 M weights
+// k = 4, plain norm, Jacobian-free 10.3 -> 10.0 and 19.9 -> 19.2 us, (2, 4) and (4, 2) 10.9 and 10.7 both).  Not: k = 8 (2 to 3 % slower), the kernels with the operator
+// (3 %), and a bound on the forward kernels, under which they are scheduled for it and take 2 to 9 % longer.
+__host__ __device__ constexpr int bwd_waves(int K, int D, bool pairs) {
+    return !pairs && ((K == 4 && D <= 2) || (K == 2 && D == 4)) ? 4 : bwd_threads(K, D) / 256;
+}
 // (layers read from memory)
 __host__ __device__ constexpr int global_threads(int K, int D, bool bwd) { return K * D <= (bwd ? 8 : 16) ? PT2 : PT; }
 constexpr int XLINE = 128;   // words reserved per workgroup in buf1 (K (D+1) <= 80, padded to a power of two)
@@ -2237,14 +2244,14 @@ __device__ __forceinline__ void persist_bwd_body(const Args& a, const PArgs& pa)
 
 // One team per launch: the grid is the team.
 template <int K, int D, int DIST, bool RAG = false>
-__global__ __launch_bounds__(fwd_threads(K, D)) void persist_fwd(const Args a, const PArgs pa_in) {
+__global__ __launch_bounds__(fwd_threads()) void persist_fwd(const Args a, const PArgs pa_in) {
     PArgs pa = pa_in;
     pa.wg = blockIdx.x;
     pa.G = gridDim.x;
-    persist_fwd_body<fwd_threads(K, D), K, D, DIST, false, false, RAG>(a, pa);
+    persist_fwd_body<fwd_threads(), K, D, DIST, false, false, RAG>(a, pa);
 }
 template <int K, int D, int DIST, bool RAG = false, bool PAIRS = false>
-__global__ __launch_bounds__(bwd_threads(K, D)) void persist_bwd(const Args a, const PArgs pa_in) {
+__global__ __launch_bounds__(bwd_threads(K, D), bwd_waves(K, D, PAIRS)) void persist_bwd(const Args a, const PArgs pa_in) {
     PArgs pa = pa_in;
     pa.wg = blockIdx.x;
     pa.G = gridDim.x;
