@@ -146,7 +146,10 @@ __device__ __forceinline__ float delta_small(const float (&df)[K][D], const floa
 // interval: right to 2^-GAP where the outermost codeword outweighs every other by 2^GAP there already, since the true
 // ratio only grows.  At the lower end, and with three codewords or fewer at both, that is the ratio to r itself, 2^TOP; at the
 // upper one of four prepare() looks (rows harder than about the spacing keep the general form).  `solid`: the caller says that every
-// codeword had a mass of at least m / 1024 in the evaluation before; what the clamp leaves out is then below 2^-24 of any sum.
+// codeword had a mass of at least m / 1024 in the evaluation before.  What a clamped row leaves codeword 2 of four is at most 2^-34, so its
+// mass n_2 is right to 2^-24; its sum s_2 carries 2^-34 of the clamped weights themselves, which moves it by about
+// 2^-34 (n_3 / n_2) (F_3 - c_2) at most, 2^-24 of the span of the new codebook.  (That span is what single weights many orders of magnitude out make of it:
+// such a weight drags codeword 3 along, which then has no mass and ends this form.)  Elsewhere the rest is 2^-120.
 // A NaN or an infinity still reaches every sum of w.  The order, like everything here, is the same in all lanes.
 __device__ __forceinline__ double solid_mass(int64_t m) { return (double)m * (1.0 / 1024.0); }
 template <int K>
