@@ -62,6 +62,14 @@ def operator_lane_ops_per_vector(k: int, d: int, dist: int):
     return kk * (kk - 1) // 2 * ops
 
 
+def forms_operator(k: int, d: int, dist: int, max_iter: int, path: int) -> bool:
+    """Whether the averaged iteration ran on that matrix: in one launch (path 2) with the two-level exchange, on the stream path (1)
+    for powers of two, and not for so few steps that passes are cheaper."""
+    if operator_lane_ops_per_vector(k, d, dist) is None or not ((k <= 4 and d == 1) or max_iter >= 3):
+        return False
+    return os.environ.get("IDKM_TREE", "1")[:1] != "0" if path == 2 else k & (k - 1) == 0
+
+
 def matrix_core_lane_cycles_per_vector(k: int, dist: int) -> int:
     """The same count for the shapes whose forward loop runs on the matrix cores (d = 4, 17 <= k <= 256, persistent
     path): per (vector, codeword) pair 8 float32 multiply-adds on the matrix cores (4 of the energy product, 4 of
@@ -253,7 +261,7 @@ def main() -> int:
     # in the pass for v and iterate on the matrix: there the whole launch, two passes over W, is what is priced.
     roofline_backward = None
     op_ops = operator_lane_ops_per_vector(cfg.k, cfg.d, dist)
-    if binfo.iters > 0 and op_ops is not None:
+    if binfo.iters > 0 and forms_operator(cfg.k, cfg.d, dist, args.bwd_max_iter, binfo.path):
         bops = 2 * bwd_lane_ops_per_vector(cfg.k, cfg.d, dist) + op_ops
         b_ms = kms.get("bwd") or bwd_ms
         roofline_backward = {

@@ -97,9 +97,10 @@ idkm_status idkm_set_matrix_cores(idkm_ctx* ctx, int32_t enable);
 /* Persistent path, 2 <= k <= 16, d <= 4: a workgroup keeps its share of W (and of dL/dWq in the backward) in LDS when it
  * is at most `bytes` (default and maximum 147456).  (A batched backward reads dL/dWq from memory, but the limit is compared
  * with both shares there too, so that a layer takes the same path alone and in a batch; k not a power of two: a larger layer
- * goes to the kernels that serve k > 16.)  A layer with larger shares (more than about 9.4 M weights) is
- * served by the stream path under IDKM_PATH_AUTO; under IDKM_PATH_PERSISTENT the same one-launch solve reads W and
- * dL/dWq from memory in every pass (needs both 16-byte aligned, else IDKM_ERR_UNSUPPORTED).  Smaller values of
+ * goes to the kernels that serve k > 16.)  A layer with larger shares (forward more than about 9.4 M
+ * weights, backward half of that), k a power of two: the same one-launch solve reads W and dL/dWq from memory in every pass, if they are 16-byte
+ * aligned, in the forward under IDKM_PATH_AUTO and IDKM_PATH_PERSISTENT, in the backward under the latter; otherwise the stream path under
+ * IDKM_PATH_AUTO and IDKM_ERR_UNSUPPORTED under IDKM_PATH_PERSISTENT.  Smaller values of
  * `bytes` send smaller layers that way (test support, comparisons). */
 idkm_status idkm_set_tile_limit(idkm_ctx* ctx, int64_t bytes);
 /* Bound of every device-side wait of the persistent kernels, in polls (default 2^20, about a second).  When a
@@ -162,7 +163,9 @@ idkm_status idkm_forward(idkm_ctx* ctx, const float* W, int64_t m, int32_t d, co
  *   that grows on 5 consecutive passes restarts from g = v with alpha halved (at most 6 times).
  *   Small codebooks (k <= 8 with d = 1, k <= 4 with d = 2 and, squared energy, 4, k = 2) form (dF/dC*)^T once, as a k d x k d
  *   matrix in the pass that computes v, and take the steps of this iteration and of IDKM_BWD_GMRES on it in float64:
- *   two passes over W in total; info.iters still counts the steps.
+ *   two passes over W in total; info.iters still counts the steps.  So it is in one launch (alone or in a batch; a team of one, or
+ *   the two-level exchange; not where the matrix kernel's scratch leaves no room for the largest tiles) and, for this iteration and k
+ *   a power of two, on the stream path -- unless max_iter is 1 or 2 and k > 4 or d > 1.  Everywhere else a step is a pass over W.
  *   IDKM_BWD_JFB sets g = v (no pass).  IDKM_BWD_DENSE forms dF/dC* explicitly (the k x k matrix of Sec. 4.2,
  *   k d x k d in general) in the same pass that computes v and solves (I - dF/dC*)^T g = v by Gaussian
  *   elimination in float64: two passes over W in total, tol / max_iter / alpha are ignored, info.iters = 0 and
@@ -170,10 +173,11 @@ idkm_status idkm_forward(idkm_ctx* ctx, const float* W, int64_t m, int32_t d, co
  *   (k = 2 with d <= 2, k = 4 with d = 1) and the tiles fit in LDS, the persistent kernel does all of it in one
  *   launch (info.path says which form ran), and batched calls share that launch between layers.
  *   IDKM_BWD_GMRES solves the same system from g = 0 by restarted GMRES (basis length min(k d, 64) unless idkm_set_gmres_basis changed it, float64
- *   orthogonalisation): every pass applies (dF/dC*)^T to one basis vector; when the estimated residual falls
- *   below tol ||v||_F (or the basis is full) the iterate is updated and one more pass measures the true residual
+ *   orthogonalisation): every step applies (dF/dC*)^T to one basis vector, by a pass over W or, small codebooks in one launch, by the
+ *   matrix above; when the estimated residual falls
+ *   below tol ||v||_F (or the basis is full) the iterate is updated and one more step measures the true residual
  *   ||v + (dF/dC*)^T g - g||_F, which is the step norm of the undamped iteration at g and is held to the same
- *   test <= tol ||v||_F; otherwise a new cycle starts from that residual.  info.iters counts all these passes
+ *   test <= tol ||v||_F; otherwise a new cycle starts from that residual.  info.iters counts all these steps
  *   (at most max_iter + 1), info.residual is the last true residual, alpha is ignored; two cycles in a row that
  *   leave more than 95 % of the residual end the solve with converged = 0.  With k d <= 64 the first cycle is exact up to
  *   rounding.  With k in {2,4,8,16} (under IDKM_PATH_AUTO every k in 2 .. 16), d <= 4, k d <= 64 and a layer whose tiles leave
