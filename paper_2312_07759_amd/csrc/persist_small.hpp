@@ -241,33 +241,13 @@ constexpr int pow2_at_most(int n) {
     while (2 * p <= n) p *= 2;
     return p;
 }
-// A team of one has 8 wavefronts where a small team has 32 or 64, and their rounding counts: from 16 sums on, where layers of up to 4096
-// vectors may run in either (see plan_small), it adds the four rows of a wavefront in float64, and what float32 leaves of the sum lies
-// beside it (in stage2, which serves nobody else there).  1,800 weights, k = 8, plain norm, 31 evaluations: error of the codebook against 64 bits, geometric
-// mean of 300 seeds, 4.9e-8 in a team of eight, 5.3e-8 in one workgroup without this and 4.6e-8 with it (7.3e-8 with totals of float32);
-// launch 58.4, 52.9 and 55.8 us.
-constexpr bool alone_in_doubles(int nacc) { return nacc >= 16; }
 template <int NACC, int OFF, class XS>
-__device__ __forceinline__ void publish_rows(const float (&acc)[NACC], XS& xs, int lane, int wave, bool alone) {
+__device__ __forceinline__ void publish_rows(const float (&acc)[NACC], XS& xs, int lane, int wave) {
     constexpr int NP = pow2_at_most(NACC - OFF);
     float v[NP];
 #pragma unroll
     for (int q = 0; q < NP; ++q) v[q] = (OFF + q < NACC) ? acc[OFF + q] : 0.f;
     row_sums<NP>(v, lane);
-    if (alone_in_doubles(NACC) && alone) {
-        static_assert(XS::WAVES <= DIES, "stage2 has a place for every wavefront");
-#pragma unroll
-        for (int i = 0; i < row_sum_live(NP); ++i) {
-            const double t = cross_row_sum_d((double)v[i]);
-            const int q = OFF + row_sum_index<NP>(lane & 15, i);
-            if (lane < 16 && row_sum_owner<NP>(lane) && q < NACC) {
-                xs.rpart[q][wave] = (float)t;
-                xs.stage2[q * XS::WAVES + wave] = (typename XS::total_t)(t - (double)(float)t);
-            }
-        }
-        if constexpr (OFF + NP < NACC) publish_rows<NACC, OFF + NP>(acc, xs, lane, wave, alone);
-        return;
-    }
     // the four rows of the wavefront in registers (two row swaps per value), so that LDS only sees one value per
     // wavefront and accumulator
 #pragma unroll
@@ -279,7 +259,7 @@ __device__ __forceinline__ void publish_rows(const float (&acc)[NACC], XS& xs, i
             if (q < NACC) xs.rpart[q][wave] = v[i];
         }
     }
-    if constexpr (OFF + NP < NACC) publish_rows<NACC, OFF + NP>(acc, xs, lane, wave, false);
+    if constexpr (OFF + NP < NACC) publish_rows<NACC, OFF + NP>(acc, xs, lane, wave);
 }
 
 // Most vectors whose float32 sums a lane of a layer read from memory keeps before they are added up over the wavefront and move to
@@ -320,6 +300,50 @@ __device__ __forceinline__ void end_run(float (&acc)[N], XS& xs) {
     for (int q = 0; q < N; ++q) acc[q] = 0.f;
 }
 
+// A team of one: nobody waits for a word of it, and its totals stay float64 (xs.totd).  It has 8 wavefronts where a small team has 32 or 64, and
+// their rounding counts: from 16 sums on, where layers of up to 4096 vectors may run in either (see plan_small), it adds the four rows of a
+// wavefront in float64 too (a function of its own: a branch inside publish_rows cost the other teams 1 to 2 %), and what float32 leaves of the sum lies beside it (in stage2, which serves nobody else there).  1,800 weights, k = 8, plain
+// norm, 31 evaluations: error of the codebook against 64 bits, geometric mean of 300 seeds, 4.9e-8 in a team of eight, 5.3e-8 in one workgroup
+// without this and 4.6e-8 with it (7.3e-8 with totals of float32); launch 58, 53 and 55 us.
+constexpr bool alone_in_doubles(int nacc) { return nacc >= 16; }
+template <int NACC, int OFF, class XS>
+__device__ __forceinline__ void alone_rows(const float (&acc)[NACC], XS& xs, int lane, int wave) {
+    static_assert(XS::WAVES <= DIES, "stage2 has a place for every wavefront");
+    constexpr int NP = pow2_at_most(NACC - OFF);
+    float v[NP];
+#pragma unroll
+    for (int q = 0; q < NP; ++q) v[q] = (OFF + q < NACC) ? acc[OFF + q] : 0.f;
+    row_sums<NP>(v, lane);
+#pragma unroll
+    for (int i = 0; i < row_sum_live(NP); ++i) {
+        const double t = cross_row_sum_d((double)v[i]);
+        const int q = OFF + row_sum_index<NP>(lane & 15, i);
+        if (lane < 16 && row_sum_owner<NP>(lane) && q < NACC) {
+            xs.rpart[q][wave] = (float)t;
+            xs.stage2[q * XS::WAVES + wave] = (typename XS::total_t)(t - (double)(float)t);
+        }
+    }
+    if constexpr (OFF + NP < NACC) alone_rows<NACC, OFF + NP>(acc, xs, lane, wave);
+}
+template <int NACC, class XS>
+__device__ __forceinline__ void publish_alone(const float (&acc)[NACC], XS& xs) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    alone_rows<NACC, 0>(acc, xs, lane, tid >> 6);
+    __syncthreads();
+    if (tid < NACC) {
+        double s = 0.0;
+#pragma unroll
+        for (int w = 0; w < XS::WAVES; ++w) {
+            s += (double)xs.rpart[tid][w] + (double)xs.stage2[tid * XS::WAVES + w];
+            if constexpr (XS::RUNS) {
+                s += xs.run[tid][w];
+                xs.run[tid][w] = 0.0;
+            }
+        }
+        xs.totd[tid] = s;
+    }
+}
+
 // hop 1, sender side: workgroup partial of every accumulator into this workgroup's line.
 template <int NACC, class XS>
 __device__ __forceinline__ void publish_waves(const PArgs& pa, unsigned int seq, const float (&acc)[NACC], XS& xs);
@@ -332,8 +356,14 @@ __device__ __forceinline__ void publish_partials(const PArgs& pa, unsigned int s
             return;
         }
     }
+    if constexpr (alone_in_doubles(NACC)) {
+        if (pa.G == 1) {
+            publish_alone<NACC>(acc, xs);
+            return;
+        }
+    }
     IDKM_SUB(0);
-    publish_rows<NACC, 0>(acc, xs, lane, tid >> 6, pa.G == 1);
+    publish_rows<NACC, 0>(acc, xs, lane, tid >> 6);
     IDKM_SUB(1);
     __syncthreads();
     IDKM_SUB(2);
@@ -353,11 +383,7 @@ __device__ __forceinline__ void publish_partials(const PArgs& pa, unsigned int s
                 xs.run[tid][w] = 0.0;
             }
         }
-        if (pa.G == 1) {  // nobody waits for a word of it: the totals stay float64
-            if constexpr (alone_in_doubles(NACC)) {
-#pragma unroll
-                for (int w = 0; w < XS::WAVES; ++w) s += (double)xs.stage2[tid * XS::WAVES + w];
-            }
+        if (!alone_in_doubles(NACC) && pa.G == 1) {
             xs.totd[tid] = s;
             return;
         }
