@@ -467,7 +467,7 @@ bool plan_small(idkm_ctx* ctx, bool bwd, PersistPlan* pp, const void* dwq, int m
     // 4.8 / 5.8 against 3.2 to 3.4; k = 16, d = 2 3.3 / 4.1 / 5.0 / 6.7 / 8.5 against 3.6 to 4.0; k = 16, d = 4 4.3 / 5.4 / 6.5 / 8.6 / 11.0 against
     // 4.4 to 4.8.  Jacobian-free backward, whole launch: k = 4, d = 1 8.1 / 8.6 / 8.7 / 10.1 / 11.0 against 8.6; k = 8, d = 1 8.8 / 10.9 /
     // 10.4 / 12.6 / 14.3 against 8.6; k = 16, d = 1 11.5 / 12.9 / 15.4 / 18.9 / 22.5 against 9.6 to 10.3; k = 16, d = 4 23 / 30 / 33 / 43 / 53 against 12.6 to 15.6.
-    // Batched launches hide the exchange behind other layers
+    // (The totals of one workgroup are float64, which adds 0.1 us from 16 sums on.)  Batched launches hide the exchange behind other layers
     // and keep one workgroup, as do the modes that are solved in one place, and calls whose result nobody may wait for
     // (idkm_forward_noalloc).  One workgroup waits for nobody: a team that gave up a wait is solved again by one (`alone`).
     if (m <= (int64_t)16 * PT) {
@@ -516,9 +516,9 @@ bool plan_small(idkm_ctx* ctx, bool bwd, PersistPlan* pp, const void* dwq, int m
         const bool aligned = (reinterpret_cast<uintptr_t>(ctx->W) & 15u) == 0 &&
                              (!bwd || (dwq && (reinterpret_cast<uintptr_t>(dwq) & 15u) == 0));
         // Forward solves take it under IDKM_PATH_AUTO too: an evaluation costs one exchange instead of a launch and a last
-        // workgroup that adds a thousand workgroups' sums (stream path against this, us per evaluation: 16.8 M scalar weights k = 2
-        // 19.7 / 12.8, k = 4 25.6 / 16.8, plain norm 26.9 / 22.6, k = 16 76.9 / 59.8; 60 M k = 4 68.1 / 48.7; 4 M 4-vectors k = 4 23.8 /
-        // 15.6, k = 16 59.8 / 37.7).  Backwards, two passes over the layer whatever the codebook, are within 5 % of each other
+        // workgroup that adds a thousand workgroups' sums (stream path against this, us per evaluation: 16.8 M scalar weights, plain norm k = 2
+        // 23.1 / 17.2, k = 16 79 / 66, squared energy k = 4 28.6 / 18.5, k = 8 45.6 / 38.4; 60 M k = 4 77 / 55; 4 M 4-vectors k = 4 25.8 /
+        // 17.7, k = 16 62 / 44).  Backwards, two passes over the layer whatever the codebook, are within 5 % of each other
         // up to k = 4 and up to 20 % slower here beyond (k = 8 and 16, 133 / 148 and 223 / 253 for a Jacobian-free call): the
         // stream path unless the caller asks for this one.
         if (!fg.one || ctx->sink || !aligned || (bwd && ctx->path != IDKM_PATH_PERSISTENT)) return false;
