@@ -103,7 +103,7 @@ idkm_status idkm_set_matrix_cores(idkm_ctx* ctx, int32_t enable);
  * IDKM_PATH_AUTO and IDKM_ERR_UNSUPPORTED under IDKM_PATH_PERSISTENT.  Smaller values of
  * `bytes` send smaller layers that way (test support, comparisons). */
 idkm_status idkm_set_tile_limit(idkm_ctx* ctx, int64_t bytes);
-/* Bound of every device-side wait of the persistent kernels, in polls (default 2^20, about a second).  When a
+/* Bound of every device-side wait of the persistent kernels, in polls (default 2^20, some tenths of a second).  When a
  * wait expires all workgroups leave the kernel.  Under IDKM_PATH_AUTO the call is then answered by the stream path
  * (a new launch from the host; idkm_info.path says IDKM_PATH_STREAM), and so is a call whose persistent grid would
  * not be resident at once; under an explicit IDKM_PATH_PERSISTENT the call returns IDKM_ERR_DEVICE.  (A layer of at most
